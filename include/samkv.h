@@ -301,8 +301,8 @@ int samkv_query_attn(const void* q_tok, int32_t n_q_tok, const void* k_c, const 
  * chunk (no partial results, no merge), which takes as long as the causal problem's longest row tile, so the query
  * attention hides inside the causal one.  The recompute outputs are bit-identical to samkv_recompute_attn's; the query
  * outputs follow the same definition as samkv_query_attn's but sum the keys in one chunk instead of several, so they
- * agree with it to rounding (both within the stated precision), not bit for bit.  float32: the two kernels one after
- * the other, bit-identical to the two calls.  Arguments as in the two calls; ws as for samkv_query_attn.  A caller
+ * agree with it to rounding (both within the stated precision), not bit for bit.  float32: one launch as well, with the
+ * query attention's key chunks as in samkv_query_attn, bit-identical to the two calls.  Arguments as in the two calls; ws as for samkv_query_attn.  A caller
  * that updates the cache between the two attentions (samkv_kv_update) uses the separate calls. */
 int samkv_recompute_query_attn(const void* q_rec, const void* q_tok, int32_t n_q_tok, const void* k_c, const void* v_c,
                                int32_t m_total, int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim, int32_t dtype,

@@ -16,111 +16,17 @@
 //                 power-of-two scale the final normalisation undoes.
 //   K/V tiles are double-buffered in LDS; the next tile's global loads are issued before the current
 //   tile's math and land in LDS after it, one barrier per tile.
-// f32 kernel (k_attn_f32): plain FMA arithmetic for float32 caches, 16 rows per workgroup.
+// Float32 caches: attn_f32.hip.
 // Keys can be cut into chunks (not causal only); k_attn_merge combines the per-chunk results with
 // their log-sum-exp.
 #include <math.h>
 
 #include <mutex>
 
-#include "common.hpp"
+#include "attn_common.hpp"
 
 namespace samkv {
 namespace {
-
-struct AttnArgs {
-  const void* q;
-  const void* k;
-  const void* v;           // half-precision copy of V (bf16 kernels)
-  const float* v_unscale;  // per KV head: undoes the copy's scale
-  float* out;
-  float* lse;
-  float* part_o;
-  float* part_lse;
-  int rows, m, batch_per_kv, n_batch, n_split, chunk;
-  int kv_groups;  // > 0: KV heads are walked in groups of 8 (one per XCD), see map_block
-  float scale;
-};
-
-// Exchange between lane l and lane l ^ 32 on the vector ALU (v_permlane32_swap; with both operands equal the first
-// result holds the lower half's values in both halves and the second the upper half's): no trip through LDS as a
-// 64-wide shuffle would take, which matters because the row maximum sits at the head of every step's dependence chain.
-__device__ __forceinline__ float max_across_halves(float v) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-__device__ __forceinline__ float sum_across_halves(float v) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-
-// Writes a wave's 32 x D block of normalised output rows.  In the accumulator layout a lane holds 4-float pieces of
-// ONE row (row = lane % 32), so a direct store instruction scatters 32-byte pieces over 32 rows; issuing the 4 D / 32
-// of them takes a few microseconds, which a short workgroup feels.  The block is therefore turned through LDS (the
-// wave's own `lds` area; rows of D * 4 + 16 bytes, the pad keeps the 16 lanes of a write phase on distinct banks)
-// and leaves as whole rows, 1 KB per instruction.  PARTS = 1 turns the 32 rows at once (area of 32 rows), PARTS = 2
-// in two passes of 16 rows (area of 16 rows).  Only this wave touches the area, and a wave's LDS operations execute
-// in order, so no workgroup barrier is needed.  dst points at the wave's first row; rows >= n_valid are not written.
-template <int D, int PARTS = 1>
-__device__ __forceinline__ void store_rows_via_lds(const f32x16 (&o)[D / 32], float inv, float* dst, int n_valid, char* lds,
-                                                   int lane) {
-  constexpr int RS = D * 4 + 16, LPR = D / 4, RPI = 64 / LPR, ROWS = 32 / PARTS;
-  const int rw = lane & 31, h = lane >> 5;
-#pragma unroll
-  for (int part = 0; part < PARTS; ++part) {
-    if (PARTS == 1 || rw / ROWS == part) {
-#pragma unroll
-      for (int dvb = 0; dvb < D / 32; ++dvb)
-#pragma unroll
-        for (int j4 = 0; j4 < 4; ++j4) {
-          f32x4 x;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) x[e] = o[dvb][4 * j4 + e] * inv;
-          *reinterpret_cast<f32x4*>(lds + (rw % ROWS) * RS + (dvb * 32 + 8 * j4 + 4 * h) * 4) = x;
-        }
-    }
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int i = 0; i < ROWS / RPI; ++i) {
-      const int lrow = i * RPI + lane / LPR, row = part * ROWS + lrow;
-      const f32x4 x = *reinterpret_cast<const f32x4*>(lds + lrow * RS + (lane % LPR) * 16);
-      if (row < n_valid) *reinterpret_cast<f32x4*>(dst + (size_t)row * D + (lane % LPR) * 4) = x;
-    }
-    __builtin_amdgcn_wave_barrier();
-  }
-}
-
-// (blockIdx.x, blockIdx.y) -> (KV head, batch, row tile).  Workgroups are handed out x-fastest and round-robin over
-// the 8 XCDs, each with its own L2.  The batches (query heads x row blocks) that read one KV head's K/V stream
-// should run on one XCD and close in time, and an XCD should not hold more streams at once than its L2 can serve.
-// So KV heads are taken in groups of 8, one head per XCD: x = 8 * member + XCD slot runs over the batches of the
-// group's heads, y = group * tiles + tile, and a group's row tiles (longest first when causal) are all handed out
-// before the next group starts.  With 8 KV heads there is one group and this is "KV head = x % 8, all row tiles in
-// longest-first order"; with many KV heads (several layers stacked as heads) an XCD still streams one head at a
-// time instead of dozens.  kv_groups == 0 (head count not a multiple of 8): plain x = batch, y = tile.
-// A workgroup's coordinates in the (batch, row tile, key chunk) grid of its problem: a plain launch takes them from
-// the hardware, the pair launch below hands out two problems' grids from one linear index
-// (x, y, z of grid_y rows): plain ints, so that nothing of it ever lives in memory.
-__device__ __forceinline__ void map_block(const AttnArgs& a, bool causal, int x, int y, int grid_y, int* kvh, int* batch,
-                                          int* tile) {
-  int ty;
-  if (a.kv_groups > 0) {
-    const int tiles = grid_y / a.kv_groups;
-    const int grp = y / tiles;
-    ty = y - grp * tiles;
-    *kvh = grp * 8 + (x & 7);
-    *batch = *kvh * a.batch_per_kv + (x >> 3);
-    *tile = causal ? tiles - 1 - ty : ty;
-  } else {
-    const int n_kv = a.n_batch / a.batch_per_kv;
-    *kvh = x % n_kv;
-    *batch = *kvh * a.batch_per_kv + x / n_kv;
-    *tile = causal ? grid_y - 1 - y : y;
-  }
-}
-
-constexpr float kLog2e = 1.4426950408889634f;
-constexpr float kLn2 = 0.6931471805599453f;
 
 // ------------------------------------------------------------------------------------------ bf16
 // NW waves = RG row groups (32 query rows each) x KG key groups.  With KG = 2 a step stages 128 keys and the two
@@ -433,9 +339,6 @@ __global__ __launch_bounds__(64 * NW, KG == 1 ? 2 : 1) void k_attn_bf16(AttnArgs
 // no merge): such a workgroup lasts as long as the causal problem's longest row tile, which is handed out right
 // behind it, so the query attention hides inside the causal one instead of waiting for it.  n_q_pad, the query
 // workgroups rounded up to a multiple of 8, keeps the causal workgroups on the XCD slots map_block assumes.
-struct PairGrid {
-  int n_q, n_q_pad, q_gx, q_gy, c_gx, c_gy;
-};
 template <int D, int NW, int KG>
 __global__ __launch_bounds__(64 * NW, KG == 1 ? 2 : 1) void k_attn_bf16_pair(AttnArgs ac, AttnArgs aq, PairGrid g) {
   const int bid = blockIdx.x;
@@ -767,114 +670,6 @@ __global__ __launch_bounds__(512, 2) void k_attn_bf16_dma_pair(AttnArgs ac, Attn
   }
 }
 
-// ------------------------------------------------------------------------------------------- f32
-template <int D, bool CAUSAL>
-__global__ __launch_bounds__(256) void k_attn_f32(AttnArgs a) {
-  constexpr int BK = 32, R = 4, RB = 16, KS = D + 1, NC = D / 64;
-  __shared__ float sK[BK * KS];
-  __shared__ float sV[BK * D];
-  __shared__ float sQ[RB * D];
-  __shared__ float sP[RB * BK];
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  const int kx = lane & 31, ch = lane >> 5;
-  int kvh, batch, qt;
-  map_block(a, CAUSAL, blockIdx.x, blockIdx.y, gridDim.y, &kvh, &batch, &qt);
-  const int q0 = qt * RB;
-  const int split = blockIdx.z;
-  const int kv_begin = CAUSAL ? 0 : split * a.chunk;
-  const int kv_end = CAUSAL ? min(a.m, q0 + RB) : min(a.m, kv_begin + a.chunk);
-  const int n_tiles = (kv_end - kv_begin + BK - 1) / BK;
-  const float* q = static_cast<const float*>(a.q);
-  const float* kbase = static_cast<const float*>(a.k) + (size_t)kvh * a.m * D;
-  const float* vbase = static_cast<const float*>(a.v) + (size_t)kvh * a.m * D;
-
-  for (int i = t; i < RB * D; i += 256) {
-    const int rc = min(q0 + i / D, a.rows - 1);
-    sQ[i] = q[((size_t)batch * a.rows + rc) * D + i % D];
-  }
-  float m_run[R], l_run[R], o[R][NC];
-#pragma unroll
-  for (int rr = 0; rr < R; ++rr) {
-    m_run[rr] = -INFINITY;
-    l_run[rr] = 0.f;
-#pragma unroll
-    for (int cc = 0; cc < NC; ++cc) o[rr][cc] = 0.f;
-  }
-
-  for (int tile = 0; tile < n_tiles; ++tile) {
-    const int k0 = kv_begin + tile * BK;
-    __syncthreads();
-    for (int i = t; i < BK * D; i += 256) {
-      const int row = i / D, c = i % D;
-      const size_t off = (size_t)min(k0 + row, a.m - 1) * D + c;
-      sK[row * KS + c] = kbase[off];
-      sV[row * D + c] = vbase[off];
-    }
-    __syncthreads();
-    float s[R];
-#pragma unroll
-    for (int rr = 0; rr < R; ++rr) s[rr] = 0.f;
-    for (int i = 0; i < D / 2; ++i) {
-      // the two half-waves walk the channels half a bank cycle apart
-      const int c = ch ? D / 2 + ((i + 32) % (D / 2)) : i;
-      const float kv = sK[kx * KS + c];
-#pragma unroll
-      for (int rr = 0; rr < R; ++rr) s[rr] = fmaf(sQ[(wave * R + rr) * D + c], kv, s[rr]);
-    }
-    const int key = k0 + kx;
-#pragma unroll
-    for (int rr = 0; rr < R; ++rr) {
-      const int row = q0 + wave * R + rr;
-      float x = s[rr] + __shfl_xor(s[rr], 32);
-      x = (key >= kv_end || (CAUSAL && key > row)) ? -INFINITY : x * a.scale;
-      float mx = x;
-#pragma unroll
-      for (int off = 16; off >= 1; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
-      const float m_new = fmaxf(m_run[rr], mx);
-      const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
-      const float p = expf(x - m_use);
-      float sum = p;
-#pragma unroll
-      for (int off = 16; off >= 1; off >>= 1) sum += __shfl_xor(sum, off);
-      const float alpha = expf(m_run[rr] - m_use);
-      l_run[rr] = l_run[rr] * alpha + sum;
-#pragma unroll
-      for (int cc = 0; cc < NC; ++cc) o[rr][cc] *= alpha;
-      m_run[rr] = m_new;
-      if (ch == 0) sP[(wave * R + rr) * BK + kx] = p;
-    }
-    __syncthreads();
-    for (int j = 0; j < BK; ++j) {
-#pragma unroll
-      for (int cc = 0; cc < NC; ++cc) {
-        const float vv = sV[j * D + lane + 64 * cc];
-#pragma unroll
-        for (int rr = 0; rr < R; ++rr) o[rr][cc] = fmaf(sP[(wave * R + rr) * BK + j], vv, o[rr][cc]);
-      }
-    }
-  }
-#pragma unroll
-  for (int rr = 0; rr < R; ++rr) {
-    const int row = q0 + wave * R + rr;
-    if (row >= a.rows) continue;
-    const size_t row_id = (size_t)batch * a.rows + row;
-    float* op;
-    float* lp;
-    if (a.n_split > 1) {
-      const size_t prow = (size_t)split * a.n_batch * a.rows + row_id;
-      op = a.part_o + prow * D;
-      lp = a.part_lse + prow;
-    } else {
-      op = a.out + row_id * D;
-      lp = a.lse + row_id;
-    }
-    const float inv = 1.f / l_run[rr];
-#pragma unroll
-    for (int cc = 0; cc < NC; ++cc) op[lane + 64 * cc] = o[rr][cc] * inv;
-    if (lane == 0) *lp = m_run[rr] + logf(l_run[rr]);
-  }
-}
-
 // out = sum_s w_s * part_o[s] with w_s = exp(lse_s - lse), lse = log sum_s exp(lse_s).  One thread per four
 // channels (16-byte loads), d/4 threads per row; chunks are visited in order, so the result is deterministic.
 __global__ __launch_bounds__(256) void k_attn_merge(AttnArgs a, int d) {
@@ -899,28 +694,6 @@ __global__ __launch_bounds__(256) void k_attn_merge(AttnArgs a, int d) {
   for (int e = 0; e < 4; ++e) acc[e] *= inv;
   *reinterpret_cast<f32x4*>(a.out + row * d + c4 * 4) = acc;
   if (c4 == 0) a.lse[row] = mx + logf(den);
-}
-
-AttnArgs make_args(const AttnLaunch& l) {
-  AttnArgs a;
-  a.q = l.q; a.k = l.k; a.v = l.v; a.v_unscale = l.v_unscale; a.out = l.out; a.lse = l.lse;
-  a.part_o = l.part_o; a.part_lse = l.part_lse;
-  a.rows = l.rows; a.m = l.m; a.batch_per_kv = l.batch_per_kv; a.n_batch = l.n_batch;
-  a.n_split = l.causal ? 1 : l.n_split;
-  a.chunk = l.chunk; a.scale = l.scale;
-  a.kv_groups = 0;
-  return a;
-}
-
-// Grid of an attention launch over `tiles` row tiles, and the matching kv_groups of the arguments.
-dim3 attn_grid(AttnArgs* a, int tiles) {
-  const int n_kv = a->n_batch / a->batch_per_kv;
-  if (n_kv % 8 == 0 && (long long)tiles * (n_kv / 8) <= 65535) {
-    a->kv_groups = n_kv / 8;
-    return dim3(8 * a->batch_per_kv, tiles * a->kv_groups, a->n_split);
-  }
-  a->kv_groups = 0;
-  return dim3(a->n_batch, tiles, a->n_split);
 }
 
 constexpr int kDmaLdsBytes = 6 * 64 * 256;
@@ -1025,17 +798,9 @@ hipError_t run_pair_d(const AttnLaunch& c, const AttnLaunch& q, hipStream_t s) {
   }
 }
 
-template <int D, bool CAUSAL>
-hipError_t run_f32(const AttnLaunch& l, hipStream_t s) {
-  AttnArgs a = make_args(l);
-  dim3 grid = attn_grid(&a, (l.rows + 15) / 16);
-  hipLaunchKernelGGL((k_attn_f32<D, CAUSAL>), grid, dim3(256), 0, s, a);
-  return hipGetLastError();
-}
-
 }  // namespace
 
-// Every bf16 attention kernel uses more dynamic LDS than the default limit allows; the limit belongs to the function
+// Nearly every attention kernel uses more dynamic LDS than the default limit allows; the limit belongs to the function
 // on a device, so it is raised for ALL variants the first time any attention call runs on that device.  After that
 // no attention call touches anything but the stream, whatever variant its shape selects (HIP graph capture).
 hipError_t attn_prepare_device() {
@@ -1060,7 +825,8 @@ hipError_t attn_prepare_device() {
       raise_lds_limit_pair<128, 8, 1>(),   raise_lds_limit_pair<128, 8, 2>(), raise_lds_limit_pair<128, 4, 1>(),
       raise_lds_limit_pair<64, 8, 1>(),    raise_lds_limit_pair<64, 8, 2>(),  raise_lds_limit_pair<64, 4, 1>(),
       hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attn_bf16_dma_pair),
-                          hipFuncAttributeMaxDynamicSharedMemorySize, kDmaLdsBytes)};
+                          hipFuncAttributeMaxDynamicSharedMemorySize, kDmaLdsBytes),
+      attn_f32_raise_limits()};
   for (hipError_t x : all)
     if (x != hipSuccess) return x;
   done[dev] = true;
@@ -1086,11 +852,6 @@ hipError_t launch_attn_bf16_pair(const AttnLaunch& causal, const AttnLaunch& que
   q.part_o = nullptr;
   q.part_lse = nullptr;
   return causal.d == 128 ? run_pair_d<128>(causal, q, s) : run_pair_d<64>(causal, q, s);
-}
-
-hipError_t launch_attn_f32(const AttnLaunch& l, hipStream_t s) {
-  if (l.d == 128) return l.causal ? run_f32<128, true>(l, s) : run_f32<128, false>(l, s);
-  return l.causal ? run_f32<64, true>(l, s) : run_f32<64, false>(l, s);
 }
 
 hipError_t launch_attn_merge(const AttnLaunch& l, hipStream_t s) {

@@ -133,6 +133,10 @@ bool attn_bf16_reads_v16(const AttnLaunch& a);
 // attention runs without key chunks whatever `query` says (its n_split, chunk and partial buffers are ignored).
 hipError_t launch_attn_bf16_pair(const AttnLaunch& causal, const AttnLaunch& query, hipStream_t s);
 hipError_t launch_attn_f32(const AttnLaunch& a, hipStream_t s);
+// Both float32 attentions in one launch (the query attention's key chunks as in its own launch; the merge, where there
+// is one, stays a launch of its own).
+hipError_t launch_attn_f32_pair(const AttnLaunch& causal, const AttnLaunch& query, hipStream_t s);
+hipError_t attn_f32_raise_limits();  // part of attn_prepare_device
 hipError_t launch_attn_merge(const AttnLaunch& a, hipStream_t s);
 
 // Half-precision copy of a bf16 V tensor [n_kv][m][d] for the attention kernels, one power-of-two scale per KV head.
@@ -140,7 +144,7 @@ hipError_t launch_attn_merge(const AttnLaunch& a, hipStream_t s);
 int v_prep_chunks(int n_kv, int m);
 hipError_t launch_v_prep(const void* v, int n_kv, int m, int d, void* v16, uint32_t* part, float* unscale, hipStream_t s);
 
-// Raises the dynamic-LDS limit of every bf16 attention kernel variant on the current device (once per device).
+// Raises the dynamic-LDS limit of every attention kernel variant that needs it on the current device (once per device).
 hipError_t attn_prepare_device();
 
 // Cache update after recomputation: rows of `cur` (old, updated in place) against rows of `fresh` (new).

@@ -113,8 +113,8 @@ ScoreWs score_ws(int n_ctx, int hq, int hkv, int d) {
 // Not-causal attention: cut the keys into chunks when the row tiles alone cannot fill the chip.
 struct SplitPlan { int n_split, chunk; size_t part_o, part_lse, bytes; };
 SplitPlan plan_splits(int dtype, int n_batch, int rows, int m, int d) {
-  const int bq = dtype == SAMKV_BF16 ? 32 * attn_bf16_waves(0, n_batch, rows) : 16;
-  const int bk = dtype == SAMKV_BF16 ? 64 : 32;
+  const int bq = dtype == SAMKV_BF16 ? 32 * attn_bf16_waves(0, n_batch, rows) : 32;
+  const int bk = dtype == SAMKV_BF16 ? 64 : 128;
   const long long base = (long long)((rows + bq - 1) / bq) * n_batch;
   const int key_tiles = (m + bk - 1) / bk;
   // aim at as many workgroups as are resident at once: one per compute unit for the eight-wave kernel (256 rows),
@@ -124,7 +124,7 @@ SplitPlan plan_splits(int dtype, int n_batch, int rows, int m, int d) {
   if (want > 64) want = 64;
   if (want < 1) want = 1;
   int tiles_per = (int)((key_tiles + want - 1) / want);
-  if (tiles_per < 4) tiles_per = 4;  // a chunk shorter than a few tiles costs more in the merge than it gains
+  if (tiles_per * bk < 256) tiles_per = 256 / bk;  // a shorter chunk costs more in the merge than it gains
   SplitPlan p;
   p.chunk = tiles_per * bk;
   p.n_split = (m + p.chunk - 1) / p.chunk;
@@ -811,8 +811,8 @@ int samkv_recompute_query_attn(const void* q_rec, const void* q_tok, int32_t n_q
   if (dtype == SAMKV_BF16) {
     if (e == hipSuccess) e = launch_attn_bf16_pair(rec, qry, s);
   } else {
-    if (e == hipSuccess) e = run_attn(rec, s);
-    if (e == hipSuccess) e = run_attn(qry, s);
+    if (e == hipSuccess) e = launch_attn_f32_pair(rec, qry, s);
+    if (e == hipSuccess && qry.n_split > 1) e = launch_attn_merge(qry, s);
   }
   return dev(e);
 }
