@@ -670,25 +670,75 @@ __global__ __launch_bounds__(512, 2) void k_attn_bf16_dma_pair(AttnArgs ac, Attn
   }
 }
 
-// out = sum_s w_s * part_o[s] with w_s = exp(lse_s - lse), lse = log sum_s exp(lse_s).  One thread per four
-// channels (16-byte loads), d/4 threads per row; chunks are visited in order, so the result is deterministic.
+// out = sum_s w_s * part_o[s] with w_s = exp(lse_s - lse), lse = log sum_s exp(lse_s).  d/4 threads per row, four
+// channels each; with many chunks, S groups of them share a row: group g takes the chunks g, g + S, ..., eight requested
+// at a time, and the groups meet in LDS.  Every order is fixed, so the result is deterministic.
+// One thread walking all chunks of its channels spends a memory round trip on each: 35 us for 64 rows x 64 chunks, 6 us
+// with S = 8.
+template <int S>
 __global__ __launch_bounds__(256) void k_attn_merge(AttnArgs a, int d) {
-  const int tpr = d / 4, rpb = 256 / tpr;
+  constexpr int U = 8;
+  __shared__ f32x4 s_acc[256];
+  __shared__ float s_mx[256], s_den[256];
+  const int tpr = d / 4, c4 = threadIdx.x % tpr;
+  const int slot = threadIdx.x / tpr, sg = slot % S;
   const size_t n_rows = (size_t)a.n_batch * a.rows;
-  const size_t row = (size_t)blockIdx.x * rpb + threadIdx.x / tpr;
-  const int c4 = threadIdx.x % tpr;
-  if (row >= n_rows) return;
-  float mx = -INFINITY;
-  for (int s = 0; s < a.n_split; ++s) mx = fmaxf(mx, a.part_lse[(size_t)s * n_rows + row]);
-  float den = 0.f;
+  const size_t row = (size_t)blockIdx.x * (256 / tpr / S) + slot / S;
+  const size_t row_c = row < n_rows ? row : n_rows - 1;
+  float mx = -INFINITY, den = 0.f;
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  for (int s = 0; s < a.n_split; ++s) {
-    const float w = expf(a.part_lse[(size_t)s * n_rows + row] - mx);
-    const f32x4 x = *reinterpret_cast<const f32x4*>(a.part_o + ((size_t)s * n_rows + row) * d + c4 * 4);
-    den += w;
+  for (int s0 = sg; s0 < a.n_split; s0 += S * U) {
+    float l[U];
+    f32x4 x[U];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) acc[e] = fmaf(w, x[e], acc[e]);
+    for (int u = 0; u < U; ++u) {
+      const size_t at = (size_t)min(s0 + u * S, a.n_split - 1) * n_rows + row_c;
+      l[u] = a.part_lse[at];
+      x[u] = *reinterpret_cast<const f32x4*>(a.part_o + at * d + c4 * 4);
+    }
+    float m_new = mx;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (s0 + u * S >= a.n_split) l[u] = -INFINITY;
+      m_new = fmaxf(m_new, l[u]);
+    }
+    const float w0 = expf(mx - m_new);
+    den *= w0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc[e] *= w0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const float w = expf(l[u] - m_new);
+      den += w;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[e] = fmaf(w, x[u][e], acc[e]);
+    }
+    mx = m_new;
   }
+  if constexpr (S > 1) {
+    s_acc[threadIdx.x] = acc;
+    s_mx[threadIdx.x] = mx;
+    s_den[threadIdx.x] = den;
+    __syncthreads();
+    if (sg > 0) return;
+    float m_all = mx;
+#pragma unroll
+    for (int g = 1; g < S; ++g) m_all = fmaxf(m_all, s_mx[threadIdx.x + g * tpr]);
+    const float w0 = expf(mx - m_all);
+    den *= w0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc[e] *= w0;
+#pragma unroll
+    for (int g = 1; g < S; ++g) {
+      const float w = expf(s_mx[threadIdx.x + g * tpr] - m_all);
+      const f32x4 x = s_acc[threadIdx.x + g * tpr];
+      den = fmaf(w, s_den[threadIdx.x + g * tpr], den);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[e] = fmaf(w, x[e], acc[e]);
+    }
+    mx = m_all;
+  }
+  if (row >= n_rows) return;
   const float inv = 1.f / den;
 #pragma unroll
   for (int e = 0; e < 4; ++e) acc[e] *= inv;
@@ -854,12 +904,16 @@ hipError_t launch_attn_bf16_pair(const AttnLaunch& causal, const AttnLaunch& que
   return causal.d == 128 ? run_pair_d<128>(causal, q, s) : run_pair_d<64>(causal, q, s);
 }
 
-hipError_t launch_attn_merge(const AttnLaunch& l, hipStream_t s) {
-  AttnArgs a = make_args(l);
-  const int rpb = 256 / (l.d / 4);
+template <int S>
+static hipError_t run_merge(const AttnLaunch& l, hipStream_t s) {
+  const int rpb = 256 / (l.d / 4) / S;
   const size_t n_rows = (size_t)l.n_batch * l.rows;
-  hipLaunchKernelGGL(k_attn_merge, dim3((unsigned)((n_rows + rpb - 1) / rpb)), dim3(256), 0, s, a, l.d);
+  hipLaunchKernelGGL(k_attn_merge<S>, dim3((unsigned)((n_rows + rpb - 1) / rpb)), dim3(256), 0, s, make_args(l), l.d);
   return hipGetLastError();
+}
+
+hipError_t launch_attn_merge(const AttnLaunch& l, hipStream_t s) {
+  return l.n_split <= 8 ? run_merge<1>(l, s) : run_merge<8>(l, s);  // one batch of requests per thread up to 64 chunks
 }
 
 }  // namespace samkv
