@@ -12,7 +12,7 @@ namespace {
 
 // GATHER: the workgroup also copies the row's kept K and V rows into the compacted cache (samkv_gather's job for
 // this document and KV head): the positions it has just written are read back after a workgroup-scope fence.
-template <bool BF16, int D, int E, int NT, bool GATHER>
+template <bool BF16, int D, int E, int NT, bool HIST, bool GATHER>
 __global__ __launch_bounds__(NT) void k_score_select(PtrTable kt, PtrTable vt, IntTable cu_len, IntTable cu_k, const float* qsrc,
                                                      int heads, int group, int total_len, int m_total, int n_ctx, int n_sink,
                                                      int n_local, float* scores, int32_t* idx, int32_t* cu_k_dev, char* k_c,
@@ -22,9 +22,8 @@ __global__ __launch_bounds__(NT) void k_score_select(PtrTable kt, PtrTable vt, I
   constexpr int ROWS_PER_WAVE = (64 / LPR) * 8 * 2;
   constexpr int NW = NT / 64;
   constexpr size_t ROW_BYTES = (size_t)D * (BF16 ? 2 : 4);
-  extern __shared__ float s_sc[];  // the row's scores
-  __shared__ uint32_t cnt[2][NW];
-  __shared__ uint64_t wsum[NW];
+  extern __shared__ __attribute__((aligned(16))) float s_sc[];  // the row's scores, then the selection's histograms
+  __shared__ uint2 wsum[NW];
   const int i = blockIdx.x, g = blockIdx.y, t = threadIdx.x, lane = t & 63, wave = t >> 6;
   if (cu_k_dev != nullptr && i == 0 && g == 0)
     for (int n = t; n <= n_ctx; n += NT) cu_k_dev[n] = cu_k.v[n];
@@ -44,12 +43,20 @@ __global__ __launch_bounds__(NT) void k_score_select(PtrTable kt, PtrTable vt, I
   }
 
   uint32_t key[E];
-  const int p0 = t * E;
 #pragma unroll
-  for (int e = 0; e < E; ++e) key[e] = (p0 + e < L) ? order_key(s_sc[p0 + e]) : 0u;
-  force_keys<E>(key, p0, L, n_sink, n_local);
+  for (int e = 0; e < E; ++e) {
+    const int p = key_position<E>(e);
+    key[e] = p < L ? order_key(s_sc[p]) : 0u;
+  }
+  force_keys<E>(key, L, n_sink, n_local);
   int32_t* ip = idx + (size_t)g * m_total + cu_k.v[i];
-  select_from_keys<E, NT>(key, p0, L, k, ip, cnt, wsum);
+  if constexpr (HIST) {
+    __syncthreads();  // every score has been read
+    write_kept<E, NT>(key, L, threshold_by_histogram<E, NT>(key, L, k, *reinterpret_cast<HistScratch<NT>*>(s_sc)), ip, wsum);
+  } else {
+    __shared__ uint32_t cnt[2][NW];
+    write_kept<E, NT>(key, L, threshold_by_bits<E, NT>(key, L, k, cnt), ip, wsum);
+  }
 
   if (GATHER) {
     __threadfence_block();
@@ -81,16 +88,17 @@ __global__ __launch_bounds__(NT) void k_score_select(PtrTable kt, PtrTable vt, I
   }
 }
 
-template <bool BF16, int D, int E, int NT>
+template <bool BF16, int D, int E, int NT, bool HIST>
 hipError_t run(const ScoreLaunch& a, const SelectLaunch& sl, const QuerySrc& q, const PtrTable& k, const IntTable& cu_len,
                const IntTable& cu_k, const GatherLaunch* ga, const PtrTable* v, hipStream_t s) {
-  const size_t lds = (size_t)E * NT * sizeof(float);
+  constexpr size_t row = (size_t)E * NT * sizeof(float), hist = HIST ? sizeof(HistScratch<NT>) : 0;
+  constexpr size_t lds = row > hist ? row : hist;
   if (ga != nullptr)
-    hipLaunchKernelGGL((k_score_select<BF16, D, E, NT, true>), dim3(a.n_ctx, a.hkv), dim3(NT), lds, s, k, *v, cu_len, cu_k, q.q,
+    hipLaunchKernelGGL((k_score_select<BF16, D, E, NT, HIST, true>), dim3(a.n_ctx, a.hkv), dim3(NT), lds, s, k, *v, cu_len, cu_k, q.q,
                        q.heads, q.group, a.total_len, sl.m_total, a.n_ctx, sl.n_sink, sl.n_local, a.scores, sl.idx,
                        sl.cu_k_dev, static_cast<char*>(ga->k_c), static_cast<char*>(ga->v_c));
   else
-    hipLaunchKernelGGL((k_score_select<BF16, D, E, NT, false>), dim3(a.n_ctx, a.hkv), dim3(NT), lds, s, k, k, cu_len, cu_k, q.q,
+    hipLaunchKernelGGL((k_score_select<BF16, D, E, NT, HIST, false>), dim3(a.n_ctx, a.hkv), dim3(NT), lds, s, k, k, cu_len, cu_k, q.q,
                        q.heads, q.group, a.total_len, sl.m_total, a.n_ctx, sl.n_sink, sl.n_local, a.scores, sl.idx,
                        sl.cu_k_dev, nullptr, nullptr);
   return hipGetLastError();
@@ -99,12 +107,12 @@ hipError_t run(const ScoreLaunch& a, const SelectLaunch& sl, const QuerySrc& q, 
 template <bool BF16, int D>
 hipError_t run_len(const ScoreLaunch& a, const SelectLaunch& sl, const QuerySrc& q, const PtrTable& k,
                    const IntTable& cu_len, const IntTable& cu_k, const GatherLaunch* ga, const PtrTable* v, hipStream_t s) {
-  // up to 4096 keys a row: 512 threads.  They halve the passes a wave makes over its share of the row's keys
-  // (2.3 us less per call at 1024 keys, 4 % at 4096 keys than 256 threads); 1024 threads lose it again in the
-  // selection's barriers.
-  if (a.max_len <= 1024) return run<BF16, D, 2, 512>(a, sl, q, k, cu_len, cu_k, ga, v, s);
-  if (a.max_len <= 4096) return run<BF16, D, 8, 512>(a, sl, q, k, cu_len, cu_k, ga, v, s);
-  return run<BF16, D, 32, 256>(a, sl, q, k, cu_len, cu_k, ga, v, s);
+  // 512 threads a row (256 make twice the passes over its keys, 1024 lose it again in the selection's barriers); above
+  // 1024 keys the threshold comes from histograms, as in launch_select (320 rows of 2048 keys with their gather: 50 -> 47 us)
+  if (a.max_len <= 1024) return run<BF16, D, 2, 512, false>(a, sl, q, k, cu_len, cu_k, ga, v, s);
+  if (a.max_len <= 2048) return run<BF16, D, 4, 512, true>(a, sl, q, k, cu_len, cu_k, ga, v, s);
+  if (a.max_len <= 4096) return run<BF16, D, 8, 512, true>(a, sl, q, k, cu_len, cu_k, ga, v, s);
+  return run<BF16, D, 16, 512, true>(a, sl, q, k, cu_len, cu_k, ga, v, s);
 }
 
 }  // namespace

@@ -96,29 +96,38 @@ __device__ __forceinline__ uint32_t order_key(float f) {
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
+// Which position of its row a thread's e-th key is: a wave owns 64 * E consecutive positions and takes them 64 at a time,
+// so that a wave-wide access touches consecutive words (global memory or LDS) and the order of positions is the order of
+// (e, lane).
+template <int E>
+__device__ __forceinline__ int key_position(int e) {
+  return (int)(threadIdx.x >> 6) * (64 * E) + e * 64 + (int)(threadIdx.x & 63);
+}
+
 // Forced positions (the first n_sink and last n_local of the row) get the largest key.
 template <int E>
-__device__ __forceinline__ void force_keys(uint32_t (&key)[E], int p0, int L, int n_sink, int n_local) {
+__device__ __forceinline__ void force_keys(uint32_t (&key)[E], int L, int n_sink, int n_local) {
 #pragma unroll
   for (int e = 0; e < E; ++e) {
-    const int p = p0 + e;
+    const int p = key_position<E>(e);
     if (p < L && (p < n_sink || p >= L - n_local)) key[e] = 0xFFFFFFFFu;
   }
 }
 
-// The k kept positions of a row whose order keys sit in registers (thread t owns positions p0 = t * E ... + E - 1,
-// keys of positions >= L are 0), written ascending to out[0..k).  cnt and wsum are LDS scratch of the workgroup.
+// The k-th largest key of a row, as far as the selection needs it: keys > T are kept and, of those == T, the first `need`.
+struct Threshold {
+  uint32_t T, need;
+};
+
+// One bit per pass from the top: ballot + popcount per key, the waves' counts meet in LDS (double-buffered, one barrier
+// per pass).  `bucket` = positions < L whose keys agree with the bits decided so far; kk of them are still to be kept.
+// Once bucket == kk every one of them is kept whatever the remaining bits say, so the walk stops there (distinct keys:
+// after about log2(L) bits below the ones all keys share; rows of equal keys walk all 32).
 template <int E, int NT>
-__device__ __forceinline__ void select_from_keys(uint32_t (&key)[E], int p0, int L, int k, int32_t* out,
-                                                 uint32_t (*cnt)[NT / 64], uint64_t* wsum) {
+__device__ __forceinline__ Threshold threshold_by_bits(const uint32_t (&key)[E], int L, int k, uint32_t (*cnt)[NT / 64]) {
   constexpr int NW = NT / 64;
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-  // ---- k-th largest key, bit by bit ------------------------------------------------------------
-  // `bucket` = positions < L whose keys agree with the bits decided so far; kk of them are still to be kept.  Once
-  // bucket == kk every one of them is kept whatever the remaining bits say, so the walk stops there (distinct keys:
-  // after about log2(L) bits below the ones all keys share; rows of equal keys walk all 32).
-  uint32_t prefix = 0;
-  uint32_t kk = (uint32_t)k, bucket = (uint32_t)L;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint32_t prefix = 0, kk = (uint32_t)k, bucket = (uint32_t)L;
   for (int b = 31; b >= 0 && bucket != kk; --b) {
     // candidate: agrees with the decided bits above b and has bit b set (padding keys are 0: never)
     const uint32_t want = (prefix >> b) | 1u;
@@ -138,46 +147,112 @@ __device__ __forceinline__ void select_from_keys(uint32_t (&key)[E], int p0, int
       bucket -= tot;
     }
   }
-  // T: the decided bits, zeros below.  Stopped early: every key >= T is kept; walked to the end: keys > T and the
-  // first kk positions with key == T
-  const uint32_t T = prefix;
-  const uint32_t need = bucket == kk ? 0xFFFFFFFFu : kk;  // how many positions with key == T are kept
+  // stopped early: every key >= prefix (zeros below the decided bits) is kept; walked to the end: the first kk equal ones
+  return {prefix, bucket == kk ? 0xFFFFFFFFu : kk};
+}
 
-  // ---- ordered compaction ------------------------------------------------------------------------
-  uint32_t n_gt = 0, n_eq = 0;
+// The same threshold by 11 + 11 + 10 bits: a histogram in LDS per pass, in which only the keys of the bucket take part.
+// A pass costs one LDS atomic per key of the bucket and four barriers instead of 11 passes over all keys.  Scores crowd
+// into few values of the top bits, so the histogram exists four times (a lane uses copy lane % 4, 16 banks apart).
+constexpr int kHistBits = 11, kHistBins = 1 << kHistBits, kHistCopies = 4, kHistStride = kHistBins + 16;
+template <int NT>
+struct HistScratch {
+  uint32_t hist[kHistCopies * kHistStride];
+  uint32_t wave_sum[NT / 64];
+  uint32_t pick[3];  // chosen bin, keys of it still to be kept, keys in it
+};
+template <int E, int NT>
+__device__ __forceinline__ Threshold threshold_by_histogram(const uint32_t (&key)[E], int L, int k, HistScratch<NT>& sc) {
+  constexpr int NW = NT / 64, BPT = kHistBins / NT;
+  static_assert(kHistBins % NT == 0, "bins per thread");
+  if (k == 0) return {0xFFFFFFFFu, 0u};  // a document that keeps nothing
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  uint32_t prefix = 0, kk = (uint32_t)k, bucket = (uint32_t)L;
+  for (int top = 32; top > 0 && bucket != kk;) {
+    const int bits = top < kHistBits ? top : kHistBits, sh = top - bits;
+    for (int i = t; i < kHistCopies * kHistStride; i += NT) sc.hist[i] = 0;
+    __syncthreads();
+    uint32_t* own = sc.hist + (lane & (kHistCopies - 1)) * kHistStride;
 #pragma unroll
-  for (int e = 0; e < E; ++e) {
-    const bool ok = p0 + e < L;
-    n_gt += (ok && key[e] > T) ? 1u : 0u;
-    n_eq += (ok && key[e] == T) ? 1u : 0u;
-  }
-  // both counts can reach 65536 (a full-length row of equal keys kept whole): 32 bits each
-  uint64_t packed = (uint64_t)n_gt | ((uint64_t)n_eq << 32);
-  uint64_t incl = packed;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    uint64_t o = __shfl_up(incl, off);
-    if (lane >= off) incl += o;
-  }
-  if (lane == 63) wsum[wave] = incl;
-  __syncthreads();
-  uint64_t base = 0;
-#pragma unroll
-  for (int w = 0; w < NW; ++w) base += (w < wave) ? wsum[w] : 0ull;
-  const uint64_t excl = base + incl - packed;
-  uint32_t gt_before = (uint32_t)excl, eq_before = (uint32_t)(excl >> 32);
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
-    if (p0 + e < L) {
-      const bool is_eq = key[e] == T;
-      const bool take = key[e] > T || (is_eq && eq_before < need);
-      if (take) {
-        const uint32_t pos = gt_before + (eq_before < need ? eq_before : need);
-        out[pos] = p0 + e;
-      }
-      gt_before += key[e] > T ? 1u : 0u;
-      eq_before += is_eq ? 1u : 0u;
+    for (int e = 0; e < E; ++e) {
+      const bool in = key_position<E>(e) < L && (top == 32 || (key[e] >> (top & 31)) == prefix >> (top & 31));
+      if (in) atomicAdd(own + ((key[e] >> sh) & ((1u << bits) - 1u)), 1u);
     }
+    __syncthreads();
+    // thread t holds bins (from the highest down) t * BPT ...: exclusive count of the keys above its bins
+    uint32_t n[BPT], sum = 0;
+#pragma unroll
+    for (int j = 0; j < BPT; ++j) {
+      const int bin = kHistBins - 1 - (t * BPT + j);
+      n[j] = 0;
+#pragma unroll
+      for (int c = 0; c < kHistCopies; ++c) n[j] += sc.hist[c * kHistStride + bin];
+      sum += n[j];
+    }
+    uint32_t incl = sum;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const uint32_t o = __shfl_up(incl, off);
+      if (lane >= off) incl += o;
+    }
+    if (lane == 63) sc.wave_sum[wave] = incl;
+    __syncthreads();
+    uint32_t above = incl - sum;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) above += w < wave ? sc.wave_sum[w] : 0u;
+#pragma unroll
+    for (int j = 0; j < BPT; ++j) {
+      if (above < kk && kk <= above + n[j]) {  // exactly one bin
+        sc.pick[0] = (uint32_t)(kHistBins - 1 - (t * BPT + j));
+        sc.pick[1] = kk - above;
+        sc.pick[2] = n[j];
+      }
+      above += n[j];
+    }
+    __syncthreads();
+    prefix |= sc.pick[0] << sh;
+    kk = sc.pick[1];
+    bucket = sc.pick[2];
+    top = sh;
+  }
+  return {prefix, bucket == kk ? 0xFFFFFFFFu : kk};
+}
+
+// Writes the kept positions of a row whose order keys sit in registers (keys of positions >= L are 0), ascending, to
+// out[0..k).  wsum is LDS scratch of the workgroup.
+template <int E, int NT>
+__device__ __forceinline__ void write_kept(const uint32_t (&key)[E], int L, Threshold th, int32_t* out, uint2* wsum) {
+  constexpr int NW = NT / 64;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const uint64_t below = (1ull << lane) - 1ull;
+  // per lane, both counts in one word (at most 64 each), summed over the wave
+  uint32_t n = 0;
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const bool ok = key_position<E>(e) < L;
+    n += (ok && key[e] > th.T ? 1u : 0u) + (ok && key[e] == th.T ? 0x10000u : 0u);
+  }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) n += __shfl_xor(n, off);
+  if (lane == 0) wsum[wave] = make_uint2(n & 0xFFFFu, n >> 16);
+  __syncthreads();
+  uint32_t T = th.T;
+  asm volatile("" : "+v"(T));  // the comparisons below are made anew: 2 E masks kept from above would not fit the registers
+  uint32_t gt = 0, eq = 0;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) {
+    gt += w < wave ? wsum[w].x : 0u;
+    eq += w < wave ? wsum[w].y : 0u;
+  }
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int p = key_position<E>(e);
+    const bool is_gt = p < L && key[e] > T, is_eq = p < L && key[e] == T;
+    const uint64_t m_gt = __ballot(is_gt), m_eq = __ballot(is_eq);
+    const uint32_t g = gt + __popcll(m_gt & below), q = eq + __popcll(m_eq & below);
+    if (is_gt || (is_eq && q < th.need)) out[g + (q < th.need ? q : th.need)] = p;
+    gt += __popcll(m_gt);
+    eq += __popcll(m_eq);
   }
 }
 
