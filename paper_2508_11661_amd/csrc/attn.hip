@@ -351,7 +351,7 @@ __global__ __launch_bounds__(64 * NW, KG == 1 ? 2 : 1) void k_attn_bf16_pair(Att
   }
 }
 
-// ------------------------------------------------------ bf16, d = 128, asynchronous tile loads (LDS DMA)
+// --------------------------------------------------------------- bf16, asynchronous tile loads (LDS DMA)
 // Eight waves x 32 rows, one workgroup per compute unit; same arithmetic and operand layouts as
 // k_attn_bf16, with two changes to how a step is organised.
 //
@@ -370,7 +370,7 @@ __global__ __launch_bounds__(64 * NW, KG == 1 ? 2 : 1) void k_attn_bf16_pair(Att
 //     slots and three V slots, two tiles ahead of their use, so a load has two full steps to land.
 //
 // A wave-wide DMA instruction fills 1 KB of LDS contiguously (lane i -> base + 16 i), i.e. four 256-byte
-// rows with no room for padding, so the tiles are stored unpadded and XOR-swizzled instead: the 16-byte
+// rows (eight 128-byte rows at d = 64) with no room for padding, so the tiles are stored unpadded and XOR-swizzled instead: the 16-byte
 // chunk c of row r sits at chunk position c ^ (r & 15) for K (16 consecutive rows of one fragment read
 // land in 16 different bank groups) and at c ^ 4 (r & 3) for V: a transposing read takes, from each of 8 rows,
 // the 64 bytes of one 4-chunk group, and LDS serves 32 lanes (4 of those rows) per cycle over its 64 banks, so the
@@ -378,12 +378,33 @@ __global__ __launch_bounds__(64 * NW, KG == 1 ? 2 : 1) void k_attn_bf16_pair(Att
 // counters showed every such read paying two extra cycles of bank conflicts.)  Which global chunk a lane fetches
 // is free, so the swizzle costs nothing on the load side; on the read side it is folded into per-lane address
 // registers.
-template <bool CAUSAL>
+//
+// d = 64: two rows share the 256 bytes that one access cycle covers, so the swizzle goes by the row pair: K chunk c at
+// c ^ ((r >> 1) & 7), V chunk c at c ^ 4 ((r >> 1) & 1).  A wave needs about half the registers and LDS, so two
+// workgroups share a compute unit and overlap each other's products and weights: no software pipeline, whose second
+// set of scores would cost that (128 registers per wave).  What bounds it is the vector ALU: 133 instructions, 32 of
+// them exponentials, per 16 products.  Against the register-staged eight-wave kernel it replaces, whole pair calls: 24
+// heads x 6450 rows 185 -> 180 us, 32 x 4120 113 -> 105, 56 x 9000 689 -> 651, 32 x 20000 (causal call alone)
+// 1768 -> 1695 (0.97 PFLOP/s).
+template <int D>
+struct DmaCfg {
+  static constexpr int NW = 8, BK = 64, NSLOT = 3;
+  static constexpr int ROWB = D * 2, CPR = ROWB / 16;  // bytes and 16-byte chunks per row
+  static constexpr int TILE = BK * ROWB;               // unpadded
+  static constexpr int LDS_BYTES = 2 * NSLOT * TILE;
+  static constexpr int NI = TILE / 1024 / NW, RPI = 1024 / ROWB;  // requests per wave and tile, rows per request
+  static constexpr int WGS = D == 128 ? 1 : 2;                    // workgroups per compute unit
+  static constexpr bool PIPE = WGS == 1;                          // software pipeline inside a wave (1)
+  static __device__ __forceinline__ int kswz(int row) { return D == 128 ? row & 15 : (row >> 1) & 7; }
+  static __device__ __forceinline__ int vswz(int row) { return D == 128 ? 4 * (row & 3) : 4 * ((row >> 1) & 1); }
+};
+
+template <int D, bool CAUSAL>
 __device__ __forceinline__ void attn_bf16_dma_body(const AttnArgs a, int bx, int by, int bz, int grid_y) {
-  constexpr int D = 128, NW = 8, BQ = 32 * NW, BK = 64;
+  using C = DmaCfg<D>;
+  constexpr int NW = C::NW, BQ = 32 * NW, BK = C::BK, ROWB = C::ROWB, CPR = C::CPR, NI = C::NI;
   constexpr int ND = D / 16, NV = D / 32;
-  constexpr int TILE = BK * D * 2;  // 16 KB, unpadded
-  constexpr int NSLOT = 3;
+  constexpr int TILE = C::TILE, NSLOT = C::NSLOT;
   constexpr float TAU = 8.f;
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   // K(j) in slot j % 3 at smem + slot * TILE; V(j) in slot j % 3 at smem + (3 + slot) * TILE
@@ -392,7 +413,10 @@ __device__ __forceinline__ void attn_bf16_dma_body(const AttnArgs a, int bx, int
   const int rw = lane & 31, h = lane >> 5;
   int kvh, batch, qt;
   map_block(a, CAUSAL, bx, by, grid_y, &kvh, &batch, &qt);
-  const int q0 = qt * BQ;
+  // Row tiles of a causal problem start so that the first one, which walks the fewest keys, is the one with few rows:
+  // its rows are the remainder, rounded up to whole key tiles (d = 128, 32 heads x 4120 rows: 171 -> 166 us as a pair
+  // call, x 8200: 532 -> 522; multiples of 256 unchanged).
+  const int q0 = qt * BQ - (CAUSAL ? (BQ - (a.rows % BQ + BK - 1) / BK * BK) % BQ : 0);
   const int split = bz;
   const int kv_begin = CAUSAL ? 0 : split * a.chunk;
   const int kv_end = CAUSAL ? min(a.m, q0 + BQ) : min(a.m, kv_begin + a.chunk);
@@ -400,13 +424,13 @@ __device__ __forceinline__ void attn_bf16_dma_body(const AttnArgs a, int bx, int
   const int n_tiles = (span + BK - 1) / BK;
 
   const int r = q0 + wave * 32 + rw;
-  const int r_c = min(r, a.rows - 1);
+  const int r_c = max(0, min(r, a.rows - 1));
   const int wave_first = q0 + wave * 32;
   // A wave whose rows all lie past the last row (the ragged last row tile of a problem: 4120 rows are 16 tiles and
   // 24 rows) computes nothing: no full tiles, no tail.  It still sends its share of the tile requests and meets the
   // barriers.  The last row tile is the one with the longest key range, so this is the most expensive workgroup of
   // every head, and its SIMDs are left to the waves that have rows.
-  const bool has_rows = wave_first < a.rows;
+  const bool has_rows = wave_first >= 0 && wave_first < a.rows;
   const int n_full = !has_rows ? 0
                      : CAUSAL  ? min((wave_first + 1) / BK, span / BK)
                                : min((wave_first + (1 << 24)) / BK, span / BK);
@@ -421,16 +445,16 @@ __device__ __forceinline__ void attn_bf16_dma_body(const AttnArgs a, int bx, int
   const char* kbase = static_cast<const char*>(a.k) + ((size_t)kvh * a.m + kv_begin) * D * 2;
   const char* vbase = static_cast<const char*>(a.v) + ((size_t)kvh * a.m + kv_begin) * D * 2;
 
-  // ---- DMA side: wave w, instruction i fills rows 4 (2w + i) .. + 3 of a tile; lane L lands at chunk
-  //      position L & 15 of row 4 (2w + i) + (L >> 4) and therefore fetches the chunk that belongs there
-  uint32_t goff_k[2], goff_v[2];
-  int grow[2];
+  // ---- DMA side: wave w, instruction i fills rows RPI (NI w + i) .. + RPI - 1 of a tile; lane L lands at chunk
+  //      position L % CPR of row RPI (NI w + i) + L / CPR and therefore fetches the chunk that belongs there
+  uint32_t goff_k[NI], goff_v[NI];
+  int grow[NI];
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int row = 4 * (2 * wave + i) + (lane >> 4), pos = lane & 15;
+  for (int i = 0; i < NI; ++i) {
+    const int row = C::RPI * (NI * wave + i) + lane / CPR, pos = lane % CPR;
     grow[i] = row;
-    goff_k[i] = (uint32_t)(row * (D * 2) + ((pos ^ (row & 15)) * 16));
-    goff_v[i] = (uint32_t)(row * (D * 2) + ((pos ^ (4 * (row & 3))) * 16));
+    goff_k[i] = (uint32_t)(row * ROWB + ((pos ^ C::kswz(row)) * 16));
+    goff_v[i] = (uint32_t)(row * ROWB + ((pos ^ C::vswz(row)) * 16));
   }
   // The DMA is issued through inline assembly on purpose: the compiler then neither orders later LDS
   // reads behind it (it would drain every outstanding load before each fragment read) nor counts it in
@@ -439,7 +463,7 @@ __device__ __forceinline__ void attn_bf16_dma_body(const AttnArgs a, int bx, int
   // would drag a null check and 64-bit arithmetic into every request.  wave_rows: where this wave's rows start
   // inside a tile, as a scalar of its own; the row and mask arithmetic above keeps the per-lane `wave`.
   const uint32_t smem_at = (uint32_t)(size_t)(const __attribute__((address_space(3))) char*)smem;
-  const uint32_t wave_rows = __builtin_amdgcn_readfirstlane((uint32_t)(2 * wave * 1024));
+  const uint32_t wave_rows = __builtin_amdgcn_readfirstlane((uint32_t)(NI * wave * 1024));
   auto dma16 = [&](const char* tile_base, uint32_t byte_off, uint32_t lds_off) {  // lds_off: byte offset into smem
     const uint32_t m0v = __builtin_amdgcn_readfirstlane(smem_at + lds_off);
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
@@ -447,19 +471,19 @@ __device__ __forceinline__ void attn_bf16_dma_body(const AttnArgs a, int bx, int
                  : "s"(m0v), "v"(byte_off), "s"(tile_base)
                  : "memory", "m0");
   };
-  auto dma_tile = [&](const char* base, int j, uint32_t slot, const uint32_t (&goff)[2], bool is_v) {
+  auto dma_tile = [&](const char* base, int j, uint32_t slot, const uint32_t (&goff)[NI], bool is_v) {
     const int k0 = j * BK;
     const char* tp = base + (size_t)k0 * (D * 2);
     if (kv_begin + k0 + BK <= a.m) {
 #pragma unroll
-      for (int i = 0; i < 2; ++i) dma16(tp, goff[i], slot + wave_rows + i * 1024);
+      for (int i = 0; i < NI; ++i) dma16(tp, goff[i], slot + wave_rows + i * 1024);
     } else {
       // last tile of the cache: rows past the final key re-read that key (their scores are masked)
       const int last = a.m - 1 - kv_begin - k0;
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int row = grow[i], pos = lane & 15;
-        const int src_chunk = is_v ? (pos ^ (4 * (row & 3))) : (pos ^ (row & 15));
+      for (int i = 0; i < NI; ++i) {
+        const int row = grow[i], pos = lane % CPR;
+        const int src_chunk = pos ^ (is_v ? C::vswz(row) : C::kswz(row));
         const uint32_t off = (uint32_t)(min(row, last) * (D * 2) + src_chunk * 16);
         dma16(tp, off, slot + wave_rows + i * 1024);
       }
@@ -473,16 +497,16 @@ __device__ __forceinline__ void attn_bf16_dma_body(const AttnArgs a, int bx, int
   // ---- read side: per-lane swizzled byte offsets inside a slot
   uint32_t kaddr[ND], vaddr[NV];
   {
-    const int x = rw & 15;
+    const int x = C::kswz(rw);
 #pragma unroll
-    for (int dc = 0; dc < ND; ++dc) kaddr[dc] = (uint32_t)(rw * 256 + (((2 * dc + h) ^ x) * 16));
+    for (int dc = 0; dc < ND; ++dc) kaddr[dc] = (uint32_t)(rw * ROWB + (((2 * dc + h) ^ x) * 16));
     const int i16 = lane & 15, q2 = (lane >> 4) & 1;
-    const int vrow = 4 * h + (i16 >> 2);       // + kb*32 + s2*16 (+8): multiples of 8, do not change row & 3
-    const int xv = 4 * (vrow & 3);
+    const int vrow = 4 * h + (i16 >> 2);       // + kb*32 + s2*16 (+8): multiples of 8, do not change the swizzle
+    const int xv = C::vswz(vrow);
 #pragma unroll
     for (int dvb = 0; dvb < NV; ++dvb) {
       const int c = 4 * dvb + 2 * q2 + ((i16 & 3) >> 1);
-      vaddr[dvb] = (uint32_t)(vrow * 256 + ((c ^ xv) * 16) + 8 * (i16 & 1));
+      vaddr[dvb] = (uint32_t)(vrow * ROWB + ((c ^ xv) * 16) + 8 * (i16 & 1));
     }
   }
 
@@ -517,15 +541,15 @@ __device__ __forceinline__ void attn_bf16_dma_body(const AttnArgs a, int bx, int
   };
   auto kfrags = [&](const char* ks, int kb, bf16x8 (&ak)[ND]) {
 #pragma unroll
-    for (int dc = 0; dc < ND; ++dc) ak[dc] = *reinterpret_cast<const bf16x8*>(ks + kaddr[dc] + kb * 32 * 256);
+    for (int dc = 0; dc < ND; ++dc) ak[dc] = *reinterpret_cast<const bf16x8*>(ks + kaddr[dc] + kb * 32 * ROWB);
   };
   // V^T fragments of key group g (16 keys) for the NV blocks of O^T: two transposing reads each
   auto vfrags = [&](const char* vs, int g, f16x8 (&av)[NV]) {
 #pragma unroll
     for (int dvb = 0; dvb < NV; ++dvb) {
-      const char* vp = vs + vaddr[dvb] + g * 16 * 256;
+      const char* vp = vs + vaddr[dvb] + g * 16 * ROWB;
       const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(vp));
-      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(vp + 8 * 256));
+      const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(vp + 8 * ROWB));
       union { struct { s16x4 lo, hi; } s; f16x8 v; } u;
       u.s.lo = lo;
       u.s.hi = hi;
@@ -568,74 +592,120 @@ __device__ __forceinline__ void attn_bf16_dma_body(const AttnArgs a, int bx, int
     }
   };
 
-  // ---- prologue: K(0), V(0), K(1) must have landed; V(1), K(2) stay in flight
-  dma_tile(kbase, 0, kslot_off(0), goff_k, false);
-  dma_tile(vbase, 0, vslot_off(0), goff_v, true);
-  if (n_tiles > 1) dma_tile(kbase, 1, kslot_off(1), goff_k, false);
-  if (n_tiles > 1) dma_tile(vbase, 1, vslot_off(1), goff_v, true);
-  if (n_tiles > 2) dma_tile(kbase, 2, kslot_off(2), goff_k, false);
-  if (n_tiles > 2) __builtin_amdgcn_s_waitcnt(0x0F70 | 4);        // vmcnt(4): everything but V(1), K(2)
-  else if (n_tiles > 1) __builtin_amdgcn_s_waitcnt(0x0F70 | 2);   // vmcnt(2): everything but V(1)
-  else __builtin_amdgcn_s_waitcnt(0x0F70);                         // vmcnt(0)
-  __builtin_amdgcn_s_barrier();
-  f32x16 sA[2], sB[2];
-  {
-    bf16x8 ak0[ND], ak1[ND];
-    kfrags(kslot(0), 0, ak0);
-    kfrags(kslot(0), 1, ak1);
+  // the masked tile: scores of keys past the row (causal) or past the last key do not count
+  auto mask = [&](int tile, f32x16 (&sc)[2]) {
+    // number of keys of the tile that count for this lane's row, less the lane's first key: made here, not ahead of the loop
+    int n_ok = (CAUSAL ? min(kv_end, r + 1) : kv_end) - (kv_begin + tile * BK) - 4 * h;
+    asm volatile("" : "+v"(n_ok));
 #pragma unroll
-    for (int j = 0; j < 16; ++j) { sA[0][j] = 0.f; sA[1][j] = 0.f; }
+    for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-    for (int dc = 0; dc < ND; ++dc) sA[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ak0[dc], bq[dc], sA[0], 0, 0, 0);
-#pragma unroll
-    for (int dc = 0; dc < ND; ++dc) sA[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ak1[dc], bq[dc], sA[1], 0, 0, 0);
-  }
-  __builtin_amdgcn_s_barrier();  // K(0) has been read by every wave before step 0 refills its slot with K(3)
-
-  // step `tile`: S(tile) is in sc; computes S(tile + 1) into sn and adds tile's V contribution
-  auto step = [&](int tile, f32x16 (&sc)[2], f32x16 (&sn)[2]) {
-    const bool more_k = tile + 3 < n_tiles, more_v = tile + 2 < n_tiles;
-    if (more_k) dma_tile(kbase, tile + 3, kslot_off(tile + 3), goff_k, false);
-    if (more_v) dma_tile(vbase, tile + 2, vslot_off(tile + 2), goff_v, true);
-    const char* k_next = kslot(tile + 1);
-    const char* v_cur = vslot(tile);
-    if (tile < n_full) {
-      bf16x8 ak0[ND], ak1[ND];
-      kfrags(k_next, 0, ak0);
-      lift(row_max(sc));
-      kfrags(k_next, 1, ak1);
-#pragma unroll
-      for (int j = 0; j < 16; ++j) { sn[0][j] = 0.f; sn[1][j] = 0.f; }
-#pragma unroll
-      for (int dc = 0; dc < ND; ++dc) sn[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ak0[dc], bq[dc], sn[0], 0, 0, 0);
-#pragma unroll
-      for (int dc = 0; dc < ND; ++dc) sn[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ak1[dc], bq[dc], sn[1], 0, 0, 0);
-      weights_pv(sc, v_cur, m_ref);
-    } else if (tile == n_full && has_tail) {
-      const int k0 = kv_begin + tile * BK;
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-          const int key = k0 + kb * 32 + 8 * (j >> 2) + 4 * h + (j & 3);
-          if (key >= kv_end || (CAUSAL && key > r)) sc[kb][j] = -INFINITY;
-        }
-      lift(row_max(sc));
-      weights_pv(sc, v_cur, m_ref == -INFINITY ? 0.f : m_ref);
-    }
-    // the tiles needed by the next step were requested one step ago: wait for all but this step's loads
-    if (more_k) __builtin_amdgcn_s_waitcnt(0x0F70 | 4);
-    else if (more_v) __builtin_amdgcn_s_waitcnt(0x0F70 | 2);
-    else __builtin_amdgcn_s_waitcnt(0x0F70);
-    __builtin_amdgcn_s_barrier();
+      for (int j = 0; j < 16; ++j)
+        if (kb * 32 + 8 * (j >> 2) + (j & 3) >= n_ok) sc[kb][j] = -INFINITY;
   };
-  for (int tile = 0; tile < n_tiles; tile += 2) {
-    step(tile, sA, sB);
-    if (tile + 1 < n_tiles) step(tile + 1, sB, sA);
+  auto scores = [&](const char* ks, f32x16 (&s)[2]) {
+    bf16x8 ak0[ND], ak1[ND];
+    kfrags(ks, 0, ak0);
+    kfrags(ks, 1, ak1);
+#pragma unroll
+    for (int j = 0; j < 16; ++j) { s[0][j] = 0.f; s[1][j] = 0.f; }
+#pragma unroll
+    for (int dc = 0; dc < ND; ++dc) {
+      s[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ak0[dc], bq[dc], s[0], 0, 0, 0);
+      s[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ak1[dc], bq[dc], s[1], 0, 0, 0);
+    }
+  };
+  if constexpr (!C::PIPE) {
+    // K(0), V(0) must have landed; K(1), V(1) stay in flight
+    dma_tile(kbase, 0, kslot_off(0), goff_k, false);
+    dma_tile(vbase, 0, vslot_off(0), goff_v, true);
+    if (n_tiles > 1) {
+      dma_tile(kbase, 1, kslot_off(1), goff_k, false);
+      dma_tile(vbase, 1, vslot_off(1), goff_v, true);
+      __builtin_amdgcn_s_waitcnt(0x0F70 | 2 * NI);
+    } else {
+      __builtin_amdgcn_s_waitcnt(0x0F70);
+    }
+    __builtin_amdgcn_s_barrier();
+    for (int tile = 0; tile < n_tiles; ++tile) {
+      const bool more = tile + 2 < n_tiles;  // into the slots that step tile - 1 has left
+      if (more) {
+        dma_tile(kbase, tile + 2, kslot_off(tile + 2), goff_k, false);
+        dma_tile(vbase, tile + 2, vslot_off(tile + 2), goff_v, true);
+      }
+      const uint32_t at = __builtin_amdgcn_readfirstlane(kslot_off(tile));
+      const char* ks = smem + at;
+      const char* vs = smem + NSLOT * TILE + at;
+      if (tile < n_full) {
+        f32x16 s[2];
+        scores(ks, s);
+        lift(row_max(s));
+        weights_pv(s, vs, m_ref == -INFINITY ? 0.f : m_ref);
+      } else if (tile == n_full && has_tail) {
+        f32x16 s[2];
+        scores(ks, s);
+        mask(tile, s);
+        lift(row_max(s));
+        weights_pv(s, vs, m_ref == -INFINITY ? 0.f : m_ref);
+      }
+      if (more) __builtin_amdgcn_s_waitcnt(0x0F70 | 2 * NI);
+      else __builtin_amdgcn_s_waitcnt(0x0F70);
+      __builtin_amdgcn_s_barrier();
+    }
+  } else {
+    // ---- prologue: K(0), V(0), K(1) must have landed; V(1), K(2) stay in flight
+    dma_tile(kbase, 0, kslot_off(0), goff_k, false);
+    dma_tile(vbase, 0, vslot_off(0), goff_v, true);
+    if (n_tiles > 1) dma_tile(kbase, 1, kslot_off(1), goff_k, false);
+    if (n_tiles > 1) dma_tile(vbase, 1, vslot_off(1), goff_v, true);
+    if (n_tiles > 2) dma_tile(kbase, 2, kslot_off(2), goff_k, false);
+    if (n_tiles > 2) __builtin_amdgcn_s_waitcnt(0x0F70 | 2 * NI);   // vmcnt: everything but V(1), K(2)
+    else if (n_tiles > 1) __builtin_amdgcn_s_waitcnt(0x0F70 | NI);  // vmcnt: everything but V(1)
+    else __builtin_amdgcn_s_waitcnt(0x0F70);                         // vmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    f32x16 sA[2], sB[2];
+    scores(kslot(0), sA);
+    __builtin_amdgcn_s_barrier();  // K(0) has been read by every wave before step 0 refills its slot with K(3)
+
+    // step `tile`: S(tile) is in sc; computes S(tile + 1) into sn and adds tile's V contribution
+    auto step = [&](int tile, f32x16 (&sc)[2], f32x16 (&sn)[2]) {
+      const bool more_k = tile + 3 < n_tiles, more_v = tile + 2 < n_tiles;
+      if (more_k) dma_tile(kbase, tile + 3, kslot_off(tile + 3), goff_k, false);
+      if (more_v) dma_tile(vbase, tile + 2, vslot_off(tile + 2), goff_v, true);
+      const char* k_next = kslot(tile + 1);
+      const char* v_cur = vslot(tile);
+      if (tile < n_full) {
+        bf16x8 ak0[ND], ak1[ND];
+        kfrags(k_next, 0, ak0);
+        lift(row_max(sc));
+        kfrags(k_next, 1, ak1);
+#pragma unroll
+        for (int j = 0; j < 16; ++j) { sn[0][j] = 0.f; sn[1][j] = 0.f; }
+#pragma unroll
+        for (int dc = 0; dc < ND; ++dc) sn[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ak0[dc], bq[dc], sn[0], 0, 0, 0);
+#pragma unroll
+        for (int dc = 0; dc < ND; ++dc) sn[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ak1[dc], bq[dc], sn[1], 0, 0, 0);
+        weights_pv(sc, v_cur, m_ref);
+      } else if (tile == n_full && has_tail) {
+        mask(tile, sc);
+        lift(row_max(sc));
+        weights_pv(sc, v_cur, m_ref == -INFINITY ? 0.f : m_ref);
+      }
+      // the tiles needed by the next step were requested one step ago: wait for all but this step's loads
+      if (more_k) __builtin_amdgcn_s_waitcnt(0x0F70 | 2 * NI);
+      else if (more_v) __builtin_amdgcn_s_waitcnt(0x0F70 | NI);
+      else __builtin_amdgcn_s_waitcnt(0x0F70);
+      __builtin_amdgcn_s_barrier();
+    };
+    for (int tile = 0; tile < n_tiles; tile += 2) {
+      step(tile, sA, sB);
+      if (tile + 1 < n_tiles) step(tile + 1, sB, sA);
+    }
   }
 
   const float l_tot = sum_across_halves(l_run);
   const float inv = a.v_unscale[kvh] / l_tot;
+  if (!has_rows) return;
   const size_t row0 = (size_t)batch * a.rows + wave_first;
   float* op0;
   float* lp0;
@@ -647,26 +717,27 @@ __device__ __forceinline__ void attn_bf16_dma_body(const AttnArgs a, int bx, int
     op0 = a.out + row0 * D;
     lp0 = a.lse + row0;
   }
-  // whole rows through the wave's 12 KB share of the tile slots (free: the last step ended with every request
+  // whole rows through the wave's share (12 KB; 6 KB at d = 64) of the tile slots (free: the last step ended with every request
   // landed and a barrier), 16 rows at a time
-  store_rows_via_lds<D, 2>(o, inv, op0, a.rows - wave_first, smem + wave * (2 * NSLOT * TILE / NW), lane);
+  store_rows_via_lds<D, 2>(o, inv, op0, a.rows - wave_first, smem + wave * (C::LDS_BYTES / NW), lane);
   if (r < a.rows && h == 0) lp0[rw] = (m_ref + __log2f(l_tot)) * kLn2;
 }
 
-template <bool CAUSAL>
-__global__ __launch_bounds__(512, 2) void k_attn_bf16_dma(AttnArgs a) {
-  attn_bf16_dma_body<CAUSAL>(a, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.y);
+template <int D, bool CAUSAL>
+__global__ __launch_bounds__(512, 2 * DmaCfg<D>::WGS) void k_attn_bf16_dma(AttnArgs a) {
+  attn_bf16_dma_body<D, CAUSAL>(a, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.y);
 }
 
 // the pair launch (see k_attn_bf16_pair) of the asynchronous kernel
-__global__ __launch_bounds__(512, 2) void k_attn_bf16_dma_pair(AttnArgs ac, AttnArgs aq, PairGrid g) {
+template <int D>
+__global__ __launch_bounds__(512, 2 * DmaCfg<D>::WGS) void k_attn_bf16_dma_pair(AttnArgs ac, AttnArgs aq, PairGrid g) {
   const int bid = blockIdx.x;
   if (bid < g.n_q_pad) {
     if (bid >= g.n_q) return;
-    attn_bf16_dma_body<false>(aq, bid % g.q_gx, bid / g.q_gx, 0, g.q_gy);
+    attn_bf16_dma_body<D, false>(aq, bid % g.q_gx, bid / g.q_gx, 0, g.q_gy);
   } else {
     const int l = bid - g.n_q_pad;
-    attn_bf16_dma_body<true>(ac, l % g.c_gx, l / g.c_gx, 0, g.c_gy);
+    attn_bf16_dma_body<D, true>(ac, l % g.c_gx, l / g.c_gx, 0, g.c_gy);
   }
 }
 
@@ -746,8 +817,6 @@ __global__ __launch_bounds__(256) void k_attn_merge(AttnArgs a, int d) {
   if (c4 == 0) a.lse[row] = mx + logf(den);
 }
 
-constexpr int kDmaLdsBytes = 6 * 64 * 256;
-
 template <int D, bool CAUSAL, int NW, int KG = 1, bool SPLIT = false>
 hipError_t raise_lds_limit() {
   return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attn_bf16<D, CAUSAL, NW, KG, SPLIT>),
@@ -759,6 +828,17 @@ hipError_t raise_lds_limit_pair() {
                              hipFuncAttributeMaxDynamicSharedMemorySize, Bf16Cfg<D, NW, KG>::LDS_BYTES);
 }
 
+template <int D>
+hipError_t raise_lds_limit_dma() {
+  const void* all[] = {reinterpret_cast<const void*>(&k_attn_bf16_dma<D, true>), reinterpret_cast<const void*>(&k_attn_bf16_dma<D, false>),
+                       reinterpret_cast<const void*>(&k_attn_bf16_dma_pair<D>)};
+  for (const void* f : all) {
+    const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, DmaCfg<D>::LDS_BYTES);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 template <int D, bool CAUSAL, int NW, int KG = 1, bool SPLIT = false>
 hipError_t run_bf16(const AttnLaunch& l, hipStream_t s) {
   using C = Bf16Cfg<D, NW, KG>;
@@ -768,19 +848,19 @@ hipError_t run_bf16(const AttnLaunch& l, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <bool CAUSAL>
+template <int D, bool CAUSAL>
 hipError_t run_bf16_dma(const AttnLaunch& l, hipStream_t s) {
   AttnArgs a = make_args(l);
   dim3 grid = attn_grid(&a, (l.rows + 255) / 256);
-  hipLaunchKernelGGL((k_attn_bf16_dma<CAUSAL>), grid, dim3(512), kDmaLdsBytes, s, a);
+  hipLaunchKernelGGL((k_attn_bf16_dma<D, CAUSAL>), grid, dim3(512), DmaCfg<D>::LDS_BYTES, s, a);
   return hipGetLastError();
 }
 
 // Which bf16 kernel serves a problem.
-enum class Shape { kDma, kWaves8, kWaves8Keys2, kWaves4 };
+enum class Shape { kDma, kWaves8Keys2, kWaves4 };
 Shape bf16_shape(const AttnLaunch& l) {
-  // the asynchronous kernel serves the long problems (d = 128, enough row tiles for 8 waves)
-  if (attn_bf16_waves(l.causal, l.n_batch, l.rows) == 8) return l.d == 128 ? Shape::kDma : Shape::kWaves8;
+  // the asynchronous kernel serves the long problems (enough row tiles for 8 waves)
+  if (attn_bf16_waves(l.causal, l.n_batch, l.rows) == 8) return Shape::kDma;
   // short causal problems (at most two workgroups per compute unit): 128 rows per workgroup as with four waves, but
   // two key groups halve the chain of steps of the longest row tile, which is what such a launch waits for
   if (l.causal && l.rows > 256 && (long long)l.n_batch * ((l.rows + 127) / 128) <= 512) return Shape::kWaves8Keys2;
@@ -791,10 +871,7 @@ template <int D, bool CAUSAL>
 hipError_t run_bf16_nw(const AttnLaunch& l, hipStream_t s) {
   if (attn_bf16_reads_v16(l) != (l.v_unscale != nullptr)) return hipErrorInvalidValue;  // V prepared iff the shape reads the copy
   switch (bf16_shape(l)) {
-    case Shape::kDma:
-      if constexpr (D == 128) return run_bf16_dma<CAUSAL>(l, s);
-      return hipErrorInvalidValue;
-    case Shape::kWaves8: return run_bf16<D, CAUSAL, 8>(l, s);
+    case Shape::kDma: return run_bf16_dma<D, CAUSAL>(l, s);
     case Shape::kWaves8Keys2:
       if constexpr (CAUSAL) return run_bf16<D, CAUSAL, 8, 2>(l, s);
       return hipErrorInvalidValue;
@@ -827,22 +904,20 @@ hipError_t run_pair(const AttnLaunch& c, const AttnLaunch& q, hipStream_t s) {
   return hipGetLastError();
 }
 
+template <int D>
 hipError_t run_pair_dma(const AttnLaunch& c, const AttnLaunch& q, hipStream_t s) {
   AttnArgs ac = make_args(c), aq = make_args(q);
   PairGrid g;
   unsigned total;
   if (!pair_grid(&ac, &aq, 256, &g, &total)) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_attn_bf16_dma_pair, dim3(total), dim3(512), kDmaLdsBytes, s, ac, aq, g);
+  hipLaunchKernelGGL(k_attn_bf16_dma_pair<D>, dim3(total), dim3(512), DmaCfg<D>::LDS_BYTES, s, ac, aq, g);
   return hipGetLastError();
 }
 
 template <int D>
 hipError_t run_pair_d(const AttnLaunch& c, const AttnLaunch& q, hipStream_t s) {
   switch (bf16_shape(c)) {
-    case Shape::kDma:
-      if constexpr (D == 128) return run_pair_dma(c, q, s);
-      return hipErrorInvalidValue;
-    case Shape::kWaves8: return run_pair<D, 8, 1>(c, q, s);
+    case Shape::kDma: return run_pair_dma<D>(c, q, s);
     case Shape::kWaves8Keys2: return run_pair<D, 8, 2>(c, q, s);
     default: return run_pair<D, 4, 1>(c, q, s);
   }
@@ -864,18 +939,10 @@ hipError_t attn_prepare_device() {
   std::lock_guard<std::mutex> lock(mu);
   if (done[dev]) return hipSuccess;
   const hipError_t all[] = {
-      raise_lds_limit<128, true, 8>(),     raise_lds_limit<128, false, 8>(), raise_lds_limit<128, true, 4>(),
-      raise_lds_limit<128, false, 4, 1, true>(), raise_lds_limit<128, true, 8, 2>(), raise_lds_limit<64, true, 8>(),
-      raise_lds_limit<64, false, 8>(),     raise_lds_limit<64, true, 4>(),   raise_lds_limit<64, false, 4, 1, true>(),
-      raise_lds_limit<64, true, 8, 2>(),
-      hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attn_bf16_dma<true>),
-                          hipFuncAttributeMaxDynamicSharedMemorySize, kDmaLdsBytes),
-      hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attn_bf16_dma<false>),
-                          hipFuncAttributeMaxDynamicSharedMemorySize, kDmaLdsBytes),
-      raise_lds_limit_pair<128, 8, 1>(),   raise_lds_limit_pair<128, 8, 2>(), raise_lds_limit_pair<128, 4, 1>(),
-      raise_lds_limit_pair<64, 8, 1>(),    raise_lds_limit_pair<64, 8, 2>(),  raise_lds_limit_pair<64, 4, 1>(),
-      hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attn_bf16_dma_pair),
-                          hipFuncAttributeMaxDynamicSharedMemorySize, kDmaLdsBytes),
+      raise_lds_limit<128, true, 4>(), raise_lds_limit<128, false, 4, 1, true>(), raise_lds_limit<128, true, 8, 2>(),
+      raise_lds_limit<64, true, 4>(),  raise_lds_limit<64, false, 4, 1, true>(),  raise_lds_limit<64, true, 8, 2>(),
+      raise_lds_limit_pair<128, 8, 2>(), raise_lds_limit_pair<128, 4, 1>(), raise_lds_limit_pair<64, 8, 2>(),
+      raise_lds_limit_pair<64, 4, 1>(), raise_lds_limit_dma<128>(), raise_lds_limit_dma<64>(),
       attn_f32_raise_limits()};
   for (hipError_t x : all)
     if (x != hipSuccess) return x;

@@ -117,9 +117,9 @@ SplitPlan plan_splits(int dtype, int n_batch, int rows, int m, int d) {
   const int bk = dtype == SAMKV_BF16 ? 64 : 128;
   const long long base = (long long)((rows + bq - 1) / bq) * n_batch;
   const int key_tiles = (m + bk - 1) / bk;
-  // aim at as many workgroups as are resident at once: one per compute unit for the eight-wave kernel (256 rows),
-  // two for the four-wave one; a second round of workgroups only adds partial results to merge
-  const int wg_target = bq == 256 ? 256 : 512;
+  // aim at as many workgroups as are resident at once: one per compute unit for the eight-wave kernel (256 rows) at
+  // d = 128, otherwise two; a second round of workgroups only adds partial results to merge
+  const int wg_target = bq == 256 && d == 128 ? 256 : 512;
   long long want = (wg_target + base - 1) / base;
   if (want > 64) want = 64;
   if (want < 1) want = 1;

@@ -1,0 +1,31 @@
+"""The asynchronous-load attention kernels where their tiling can go wrong: row counts around the remainder that sets
+where the causal row tiles start (0, 1, 63 .. 65, 192 .. 255 rows beyond a multiple of 256), one to four key tiles,
+both head dimensions, the pair launch, and query problems of 256-row tiles with and without key chunks."""
+import pytest
+
+from tests import test_gpu_attention_edges as E
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d,hq,hkv,m", [
+    (64, 384, 8, 1), (64, 384, 8, 63), (64, 384, 8, 64), (64, 384, 8, 65), (64, 400, 8, 129), (64, 384, 8, 193),
+    (64, 384, 8, 255), (64, 384, 8, 256), (64, 192, 8, 257), (64, 195, 5, 320), (64, 200, 8, 321), (64, 128, 8, 577),
+    (64, 48, 8, 2049), (64, 48, 8, 2303),
+    (128, 384, 8, 192), (128, 384, 8, 193), (128, 192, 8, 257), (128, 192, 8, 320), (128, 195, 5, 321),
+    (128, 48, 8, 2049), (128, 48, 8, 2303),
+])
+def test_recompute(d, hq, hkv, m):
+    E.test_recompute_attention_shapes("bf16", d, hq, hkv, m)
+
+
+@pytest.mark.parametrize("d,hq,hkv,lq,m", [
+    (64, 16, 2, 64, 1), (64, 16, 2, 64, 64), (64, 16, 2, 65, 130), (64, 16, 2, 100, 1000), (64, 24, 8, 256, 3001),
+])
+def test_query(d, hq, hkv, lq, m):
+    E.test_query_attention_shapes("bf16", d, hq, hkv, lq, m)
+
+
+@pytest.mark.parametrize("d,hq,hkv,lq,m", [(64, 200, 8, 3, 321), (64, 48, 8, 45, 2100), (128, 200, 8, 3, 321)])
+def test_both_in_one_call(d, hq, hkv, lq, m):
+    E.test_both_attentions_in_one_call("bf16", d, hq, hkv, lq, m)
