@@ -2,20 +2,25 @@
 //   causal     - recomputation of the kept tokens: row p sees compacted positions 0..p
 //   not causal - the user query's final incremental prefill over the whole compacted cache
 // Both are softmax(scale * q k^T) v with float32 statistics; they differ in the mask and in how the
-// rows are cut into workgroups, so one kernel template serves both.
+// rows are cut into workgroups.
 //
-// bf16 kernel (k_attn_bf16), one workgroup = NW waves (4 or 8) of 32 query rows each, 64 keys per step:
+// Two bf16 kernels share the arithmetic and operand layouts.  A wave holds 32 query rows and takes 64 keys per step:
 //   S^T = K Q^T   v_mfma_f32_32x32x16_bf16, A = K rows from LDS, B = the wave's 32 query rows (registers,
 //                 loaded once).  Computing the transpose puts one query row in one lane column, so the
 //                 softmax weights come out of the accumulator already in the B-operand layout of the
 //                 next product and never travel through LDS.
-//   O^T += V^T P^T  v_mfma_f32_32x32x16_f16, A = V^T read from the row-major V tile in LDS with the
-//                 transposing LDS read (ds_read_b64_tr_b16), B = P^T from registers.  Both operands are IEEE
-//                 half precision: the weights keep an 11-bit significand (bf16 weights would cost 2^-9 of the
-//                 spread of V per output), and V arrives as the scaled half-precision copy of vprep.hip, whose
-//                 power-of-two scale the final normalisation undoes.
-//   K/V tiles are double-buffered in LDS; the next tile's global loads are issued before the current
-//   tile's math and land in LDS after it, one barrier per tile.
+//   O^T += V^T P^T  A = V^T read from the row-major V tile in LDS with the transposing LDS read
+//                 (ds_read_b64_tr_b16), B = P^T from registers.  bf16 weights would cost 2^-9 of the spread of V per
+//                 output; the kernels get more out of 16-bit operands in different ways:
+// k_attn_bf16_dma (every causal problem, long ones that are not, and both together in one launch): half-precision
+//   products.  The weights keep an 11-bit significand, and V arrives as the scaled half-precision copy of vprep.hip,
+//   whose power-of-two scale the final normalisation undoes.
+// k_attn_bf16 (short problems that are not causal): V as stored and every weight as the sum of TWO bf16 terms
+//   (p = hi + lo, 16 significant bits), which doubles the second product's instructions and needs no copy.  That pays
+//   where the products are not what the kernel waits for and the launches that prepare V would cost more: the query
+//   attention of short and mid-size caches (bound by latency or by HBM; 34 -> 26 us at M = 1540, 54 -> 45 us at
+//   M = 6160 as calls).  Causal problems of the same shapes lose more in the products than the preparation costs
+//   (+10 to +18 % at M = 2304 .. 2816) and keep the copy.
 // Float32 caches: attn_f32.hip.
 // Keys can be cut into chunks (not causal only); k_attn_merge combines the per-chunk results with
 // their log-sum-exp.
@@ -28,60 +33,43 @@
 namespace samkv {
 namespace {
 
-// ------------------------------------------------------------------------------------------ bf16
-// NW waves = RG row groups (32 query rows each) x KG key groups.  With KG = 2 a step stages 128 keys and the two
-// key groups of a row group each take 64 of them, so a causal row tile walks its keys in half as many sequential
-// steps; the two partial results meet through LDS at the end.  That is for short problems, where the longest row
-// tile's chain of steps, not the total work, sets the kernel's duration.
-template <int D, int NW_, int KG_ = 1>
+// ------------------------------------------------------------------ bf16, short problems that are not causal
+// One workgroup = four waves of 32 query rows each.  K/V tiles are double-buffered in LDS; the next tile's global loads
+// are issued before the current tile's math and land in LDS after it, one barrier per tile.
+template <int D>
 struct Bf16Cfg {
-  static constexpr int NW = NW_, NT = 64 * NW, KG = KG_, RG = NW / KG;
-  static constexpr int BQ = 32 * RG, BK = 64, BKT = BK * KG;
+  static constexpr int NW = 4, NT = 64 * NW;
+  static constexpr int BQ = 32 * NW, BK = 64;
   static constexpr int KSTR = D * 2 + 16;  // bytes per K row in LDS (pad: 16 rows hit 64 distinct banks)
   static constexpr int VSTR = D * 2 + 64;  // bytes per V row in LDS: the 4 rows x 32 B of a transposing read fall in disjoint bank ranges
-  static constexpr int TILE_BYTES = BKT * (KSTR + VSTR);
+  static constexpr int TILE_BYTES = BK * (KSTR + VSTR);
   static constexpr int LDS_BYTES = 2 * TILE_BYTES;
-  static constexpr int CHUNKS = (BKT * D * 2 / 16) / NT;  // 16-byte chunks per thread per tile and tensor
-  static constexpr int MERGE_BYTES = RG * 64 * (D / 32 * 16 + 2) * 4;  // one key group's state per row group
-
-  static_assert(KG == 1 || MERGE_BYTES <= LDS_BYTES, "the merge reuses the tile buffers");
+  static constexpr int CHUNKS = (BK * D * 2 / 16) / NT;  // 16-byte chunks per thread per tile and tensor
 };
 
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
-// SPLIT: how the second product gets 16-bit operands without losing the weights' precision.  false: the weights are
-// rounded to half precision and V is the scaled half-precision copy that vprep.hip makes.  true: V is read as stored
-// (bf16) and every weight travels as the sum of TWO bf16 terms (p = hi + lo, 16 significant bits), which doubles the
-// second product's instructions and needs no copy.  That pays where the products are not what the kernel waits for
-// and the launches that prepare V would cost more: the query attention of short and mid-size caches (bound by
-// latency or by HBM; 34 -> 26 us at M = 1540, 54 -> 45 us at M = 6160 as calls).  Causal problems of the same shapes
-// lose more in the products than the preparation costs (+10 to +18 % at M = 2304 .. 2816) and keep the copy.
-template <int D, bool CAUSAL, int NW, int KG = 1, bool SPLIT = false>
-__device__ __forceinline__ void attn_bf16_body(const AttnArgs a, int bx, int by, int bz, int grid_y) {
-  using C = Bf16Cfg<D, NW, KG>;
-  static_assert(KG == 1 || KG == 2, "one or two key groups");
+template <int D>
+__global__ __launch_bounds__(256, 2) void k_attn_bf16(AttnArgs a) {
+  using C = Bf16Cfg<D>;
   constexpr int ND = D / 16;   // k-steps of the S^T product
   constexpr int NV = D / 32;   // 32-row blocks of O^T
   extern __shared__ __attribute__((aligned(16))) char smem[];
 
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int rw = lane & 31, h = lane >> 5;
-  // grid = (batch, row tile, key chunk).  Workgroups are handed out x-fastest and round-robin over the 8
-  // XCDs, so (1) every batch's longest causal row tiles start first and the short ones fill the tail,
-  // and (2) map_batch puts the query heads that share a K/V stream on the same XCD, next to each other,
-  // where they find its tiles in that XCD's L2.
+  // grid = (batch, row tile, key chunk)
   int kvh, batch, qt;
-  map_block(a, CAUSAL, bx, by, grid_y, &kvh, &batch, &qt);
+  map_block(a, false, blockIdx.x, blockIdx.y, gridDim.y, &kvh, &batch, &qt);
   const int q0 = qt * C::BQ;
-  const int split = bz;
-  const int kv_begin = CAUSAL ? 0 : split * a.chunk;
-  const int kv_end = CAUSAL ? min(a.m, q0 + C::BQ) : min(a.m, kv_begin + a.chunk);
-  const int n_tiles = (kv_end - kv_begin + C::BKT - 1) / C::BKT;
+  const int split = blockIdx.z;
+  const int kv_begin = split * a.chunk;
+  const int kv_end = min(a.m, kv_begin + a.chunk);
+  const int n_tiles = (kv_end - kv_begin + C::BK - 1) / C::BK;
 
-  const int rg = wave % C::RG, kg = wave / C::RG;  // row group, key group
-  const int r = q0 + rg * 32 + rw;
+  const int r = q0 + wave * 32 + rw;
   const int r_c = min(r, a.rows - 1);
-  const int wave_first = q0 + rg * 32, wave_last = wave_first + 31;
+  const int wave_first = q0 + wave * 32;
 
   bf16x8 bq[ND];
   {
@@ -101,10 +89,10 @@ __device__ __forceinline__ void attn_bf16_body(const AttnArgs a, int bx, int by,
   for (int i = 0; i < C::CHUNKS; ++i) voff[i] = (uint32_t)((t / CPR + i * RSTEP) * (D * 2) + (t % CPR) * 16);
   u32x4 rk[C::CHUNKS], rv[C::CHUNKS];
   auto load_tile = [&](int tile) {
-    const int k0 = kv_begin + tile * C::BKT;
+    const int k0 = kv_begin + tile * C::BK;
     const char* kt = kbase + (size_t)k0 * (D * 2);
     const char* vt = vbase + (size_t)k0 * (D * 2);
-    if (k0 + C::BKT <= a.m) {
+    if (k0 + C::BK <= a.m) {
 #pragma unroll
       for (int i = 0; i < C::CHUNKS; ++i) {
         rk[i] = *reinterpret_cast<const u32x4*>(kt + voff[i]);
@@ -122,7 +110,7 @@ __device__ __forceinline__ void attn_bf16_body(const AttnArgs a, int bx, int by,
   };
   auto store_tile = [&](int buf) {
     char* sk = smem + buf * C::TILE_BYTES;
-    char* sv = sk + C::BKT * C::KSTR;
+    char* sv = sk + C::BK * C::KSTR;
 #pragma unroll
     for (int i = 0; i < C::CHUNKS; ++i) {
       const int c = t + C::NT * i;
@@ -148,15 +136,15 @@ __device__ __forceinline__ void attn_bf16_body(const AttnArgs a, int bx, int by,
   __syncthreads();
 
   for (int tile = 0; tile < n_tiles; ++tile) {
-    const int k0 = kv_begin + tile * C::BKT + kg * C::BK;  // first key of this wave's 64 in the staged tile
+    const int k0 = kv_begin + tile * C::BK;
     const bool more = tile + 1 < n_tiles;
     if (more) load_tile(tile + 1);
 
     // a wave whose rows all lie past the last row (ragged last row tile) only helps with the tile traffic
-    const bool active = wave_first < a.rows && (!CAUSAL || k0 <= wave_last) && (KG == 1 || k0 < kv_end);
+    const bool active = wave_first < a.rows;
     if (active) {
-      const char* sk = smem + (tile & 1) * C::TILE_BYTES + kg * C::BK * C::KSTR;
-      const char* sv = smem + (tile & 1) * C::TILE_BYTES + C::BKT * C::KSTR + kg * C::BK * C::VSTR;
+      const char* sk = smem + (tile & 1) * C::TILE_BYTES;
+      const char* sv = smem + (tile & 1) * C::TILE_BYTES + C::BK * C::KSTR;
       f32x16 s[2];
       {
         // all K fragments of the tile are requested before the first product, so the LDS latency is
@@ -178,14 +166,13 @@ __device__ __forceinline__ void attn_bf16_body(const AttnArgs a, int bx, int by,
         }
       }
       // accumulator register j of block kb holds key k0 + kb*32 + 8*(j/4) + 4*h + (j%4) for row r
-      const bool need_mask = (CAUSAL && k0 + C::BK - 1 > wave_first) || (k0 + C::BK > kv_end);
-      if (need_mask) {
+      if (k0 + C::BK > kv_end) {
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
           for (int j = 0; j < 16; ++j) {
             const int key = k0 + kb * 32 + 8 * (j >> 2) + 4 * h + (j & 3);
-            if (key >= kv_end || (CAUSAL && key > r)) s[kb][j] = -INFINITY;
+            if (key >= kv_end) s[kb][j] = -INFINITY;
           }
       }
       float mx = -INFINITY;
@@ -202,13 +189,9 @@ __device__ __forceinline__ void attn_bf16_body(const AttnArgs a, int bx, int by,
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
         for (int j = 0; j < 16; ++j) s[kb][j] = __builtin_amdgcn_exp2f(fmaf(s[kb][j], c2, -m_use));
-      // Half-precision weights: their row sum is taken over the ROUNDED weights (pair . (1,1) accumulated in
-      // float32), so numerator and denominator see the same weights.  Two-term bf16 weights: hi = bf16(p),
-      // lo = bf16(p - hi); hi + lo is p to 2^-17, and the row sum is the plain float32 sum of p.
-      f16x8 bp[2][2];
+      // hi = bf16(p), lo = bf16(p - hi); hi + lo is p to 2^-17, and the row sum is the plain float32 sum of p
       bf16x8 bhi[2][2], blo[2][2];
       float psum = 0.f;
-      const f16x2 ones = {(_Float16)1.0f, (_Float16)1.0f};
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
@@ -216,20 +199,13 @@ __device__ __forceinline__ void attn_bf16_body(const AttnArgs a, int bx, int by,
 #pragma unroll
           for (int e = 0; e < 8; e += 2) {
             const float p0 = s[kb][8 * s2 + e], p1 = s[kb][8 * s2 + e + 1];
-            if constexpr (SPLIT) {
-              const bf16x2 hi = {(__bf16)p0, (__bf16)p1};
-              const bf16x2 lo = {(__bf16)(p0 - (float)hi[0]), (__bf16)(p1 - (float)hi[1])};
-              bhi[kb][s2][e] = hi[0];
-              bhi[kb][s2][e + 1] = hi[1];
-              blo[kb][s2][e] = lo[0];
-              blo[kb][s2][e + 1] = lo[1];
-              psum += p0 + p1;
-            } else {
-              f16x2 pr = {(_Float16)p0, (_Float16)p1};
-              bp[kb][s2][e] = pr[0];
-              bp[kb][s2][e + 1] = pr[1];
-              psum = __builtin_amdgcn_fdot2(pr, ones, psum, false);
-            }
+            const bf16x2 hi = {(__bf16)p0, (__bf16)p1};
+            const bf16x2 lo = {(__bf16)(p0 - (float)hi[0]), (__bf16)(p1 - (float)hi[1])};
+            bhi[kb][s2][e] = hi[0];
+            bhi[kb][s2][e + 1] = hi[1];
+            blo[kb][s2][e] = lo[0];
+            blo[kb][s2][e + 1] = lo[1];
+            psum += p0 + p1;
           }
       l_run = fmaf(l_run, alpha, psum);
       if (__any(alpha != 1.f)) {
@@ -249,15 +225,11 @@ __device__ __forceinline__ void attn_bf16_body(const AttnArgs a, int bx, int by,
             const char* vp = sv + key1 * C::VSTR + (dvb * 32 + q2 * 16 + 4 * (i16 & 3)) * 2;
             const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(vp));
             const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(vp + 8 * C::VSTR));
-            union { struct { s16x4 lo, hi; } s; f16x8 v; bf16x8 b; } av;
+            union { struct { s16x4 lo, hi; } s; bf16x8 b; } av;
             av.s.lo = lo;
             av.s.hi = hi;
-            if constexpr (SPLIT) {
-              o[dvb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av.b, bhi[kb][s2], o[dvb], 0, 0, 0);
-              o[dvb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av.b, blo[kb][s2], o[dvb], 0, 0, 0);
-            } else {
-              o[dvb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(av.v, bp[kb][s2], o[dvb], 0, 0, 0);
-            }
+            o[dvb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av.b, bhi[kb][s2], o[dvb], 0, 0, 0);
+            o[dvb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av.b, blo[kb][s2], o[dvb], 0, 0, 0);
           }
         }
     }
@@ -265,36 +237,8 @@ __device__ __forceinline__ void attn_bf16_body(const AttnArgs a, int bx, int by,
     __syncthreads();
   }
 
-  if (KG == 2) {
-    // the second key group hands its running maximum, row sum and accumulator to the first through LDS
-    // (element e of lane l at word e * 64 + l: conflict-free), which rescales both to the common maximum
-    float* mg = reinterpret_cast<float*>(smem) + rg * (64 * (NV * 16 + 2)) + lane;
-    if (kg == 1) {
-#pragma unroll
-      for (int i = 0; i < NV; ++i)
-#pragma unroll
-        for (int j = 0; j < 16; ++j) mg[(i * 16 + j) * 64] = o[i][j];
-      mg[(NV * 16) * 64] = m_run;
-      mg[(NV * 16 + 1) * 64] = l_run;
-    }
-    __syncthreads();
-    if (kg == 1) return;
-    const float m1 = mg[(NV * 16) * 64], l1 = mg[(NV * 16 + 1) * 64];
-    const float m_new = fmaxf(m_run, m1);
-    const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
-    const float a0 = __builtin_amdgcn_exp2f(m_run - m_use), a1 = __builtin_amdgcn_exp2f(m1 - m_use);
-#pragma unroll
-    for (int i = 0; i < NV; ++i)
-#pragma unroll
-      for (int j = 0; j < 16; ++j) o[i][j] = o[i][j] * a0 + mg[(i * 16 + j) * 64] * a1;
-    l_run = l_run * a0 + l1 * a1;
-    m_run = m_new;
-  }
-
   const float l_tot = sum_across_halves(l_run);
-  float v_unscale = 1.f;
-  if constexpr (!SPLIT) v_unscale = a.v_unscale[kvh];
-  const float inv = v_unscale / l_tot;
+  const float inv = 1.f / l_tot;
   const size_t row0 = (size_t)batch * a.rows + wave_first;
   float* op0;
   float* lp0;
@@ -306,54 +250,16 @@ __device__ __forceinline__ void attn_bf16_body(const AttnArgs a, int bx, int by,
     op0 = a.out + row0 * D;
     lp0 = a.lse + row0;
   }
-  // The wave's rows leave as whole rows through an LDS area of its own where the tile buffers have room for one per
-  // storing wave (every read of the tiles lies behind the loop's last barrier; with two key groups the area is the
-  // row group's merge area, which only this wave still touches); otherwise straight from the accumulator layout.
+  // The wave's rows leave as whole rows through an LDS area of its own (every read of the tiles lies behind the loop's
+  // last barrier).
   constexpr int TURN = 32 * (D * 4 + 16);
-  if constexpr (C::RG * TURN <= C::LDS_BYTES) {
-    store_rows_via_lds<D>(o, inv, op0, a.rows - wave_first, smem + rg * TURN, lane);
-  } else {
-    if (r < a.rows) {
-      float* op = op0 + (size_t)rw * D;
-#pragma unroll
-      for (int dvb = 0; dvb < NV; ++dvb)
-#pragma unroll
-        for (int j4 = 0; j4 < 4; ++j4) {
-          f32x4 x;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) x[e] = o[dvb][4 * j4 + e] * inv;
-          *reinterpret_cast<f32x4*>(op + dvb * 32 + 8 * j4 + 4 * h) = x;
-        }
-    }
-  }
+  static_assert(C::NW * TURN <= C::LDS_BYTES, "the rows are turned in the tile buffers");
+  store_rows_via_lds<D>(o, inv, op0, a.rows - wave_first, smem + wave * TURN, lane);
   if (r < a.rows && h == 0) lp0[rw] = (m_run + __log2f(l_tot)) * kLn2;
 }
 
-template <int D, bool CAUSAL, int NW, int KG = 1, bool SPLIT = false>
-__global__ __launch_bounds__(64 * NW, KG == 1 ? 2 : 1) void k_attn_bf16(AttnArgs a) {
-  attn_bf16_body<D, CAUSAL, NW, KG, SPLIT>(a, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.y);
-}
-
-// Both attentions of the path in ONE launch (same head dimension, same workgroup shape).  The query attention's
-// workgroups come first in the linear order and each walks ALL keys for its rows (no key chunks, no partial results,
-// no merge): such a workgroup lasts as long as the causal problem's longest row tile, which is handed out right
-// behind it, so the query attention hides inside the causal one instead of waiting for it.  n_q_pad, the query
-// workgroups rounded up to a multiple of 8, keeps the causal workgroups on the XCD slots map_block assumes.
-template <int D, int NW, int KG>
-__global__ __launch_bounds__(64 * NW, KG == 1 ? 2 : 1) void k_attn_bf16_pair(AttnArgs ac, AttnArgs aq, PairGrid g) {
-  const int bid = blockIdx.x;
-  if (bid < g.n_q_pad) {
-    if (bid >= g.n_q) return;
-    attn_bf16_body<D, false, NW, KG>(aq, bid % g.q_gx, bid / g.q_gx, 0, g.q_gy);
-  } else {
-    const int l = bid - g.n_q_pad;
-    attn_bf16_body<D, true, NW, KG>(ac, l % g.c_gx, l / g.c_gx, 0, g.c_gy);
-  }
-}
-
 // --------------------------------------------------------------- bf16, asynchronous tile loads (LDS DMA)
-// Eight waves x 32 rows, one workgroup per compute unit; same arithmetic and operand layouts as
-// k_attn_bf16, with two changes to how a step is organised.
+// Eight waves, one workgroup per compute unit; two things shape a step.
 //
 // (1) Software pipeline.  The products of the NEXT tile's scores are issued in the same straight-line
 //     block as the softmax of the CURRENT tile, so the matrix pipe and the vector ALU of a SIMD work at
@@ -368,6 +274,13 @@ __global__ __launch_bounds__(64 * NW, KG == 1 ? 2 : 1) void k_attn_bf16_pair(Att
 // (2) Asynchronous tile loads.  K/V tiles travel from global memory straight into LDS
 //     (global_load_lds_dwordx4: no staging registers, no LDS store instructions) into a ring of three K
 //     slots and three V slots, two tiles ahead of their use, so a load has two full steps to land.
+//
+// KG = 1: the eight waves hold 256 rows.  KG = 2, for short problems, whose longest row tile's chain of steps and not the
+// total work sets the duration: four row groups (128 rows) x two key groups.  A step stages 128 keys, each key group
+// takes 64, and the two partial results meet through LDS at the end.  The tiles are twice as large, so the ring has two
+// slots and a load one step to land.  Against the register-staged, not pipelined kernels that served these problems
+// before (pair calls): 32 heads x 1540 rows 49.8 -> 44.9 us, x 500 rows 21.0 -> 19.5, 16 heads x 3900 rows 92 -> 81,
+// 32 heads x 16 rows 14.1 -> 12.4; d = 64, 24 heads x 2600 rows 52 -> 46, x 3900 rows 93 -> 77.
 //
 // A wave-wide DMA instruction fills 1 KB of LDS contiguously (lane i -> base + 16 i), i.e. four 256-byte
 // rows (eight 128-byte rows at d = 64) with no room for padding, so the tiles are stored unpadded and XOR-swizzled instead: the 16-byte
@@ -386,11 +299,14 @@ __global__ __launch_bounds__(64 * NW, KG == 1 ? 2 : 1) void k_attn_bf16_pair(Att
 // them exponentials, per 16 products.  Against the register-staged eight-wave kernel it replaces, whole pair calls: 24
 // heads x 6450 rows 185 -> 180 us, 32 x 4120 113 -> 105, 56 x 9000 689 -> 651, 32 x 20000 (causal call alone)
 // 1768 -> 1695 (0.97 PFLOP/s).
-template <int D>
+template <int D, int KG>
 struct DmaCfg {
-  static constexpr int NW = 8, BK = 64, NSLOT = 3;
-  static constexpr int ROWB = D * 2, CPR = ROWB / 16;  // bytes and 16-byte chunks per row
-  static constexpr int TILE = BK * ROWB;               // unpadded
+  static constexpr int NW = 8, RG = NW / KG, BQ = 32 * RG;   // waves, row groups, rows per workgroup
+  static constexpr int BK = 64, BKT = BK * KG;               // keys per wave and per workgroup in a step
+  static constexpr int NSLOT = KG == 1 ? 3 : 2;              // tiles in the ring, and how far ahead K and V are requested
+  static constexpr int ROWB = D * 2, CPR = ROWB / 16;        // bytes and 16-byte chunks per row
+  static constexpr int TILE = BKT * ROWB;                    // unpadded
+  static constexpr int MERGE = 64 * (D / 2 + 2) * 4;         // one wave's outputs, maxima and sums
   static constexpr int LDS_BYTES = 2 * NSLOT * TILE;
   static constexpr int NI = TILE / 1024 / NW, RPI = 1024 / ROWB;  // requests per wave and tile, rows per request
   static constexpr int WGS = D == 128 ? 1 : 2;                    // workgroups per compute unit
@@ -399,10 +315,10 @@ struct DmaCfg {
   static __device__ __forceinline__ int vswz(int row) { return D == 128 ? 4 * (row & 3) : 4 * ((row >> 1) & 1); }
 };
 
-template <int D, bool CAUSAL>
+template <int D, int KG, bool CAUSAL>
 __device__ __forceinline__ void attn_bf16_dma_body(const AttnArgs a, int bx, int by, int bz, int grid_y) {
-  using C = DmaCfg<D>;
-  constexpr int NW = C::NW, BQ = 32 * NW, BK = C::BK, ROWB = C::ROWB, CPR = C::CPR, NI = C::NI;
+  using C = DmaCfg<D, KG>;
+  constexpr int NW = C::NW, BQ = C::BQ, BK = C::BK, BKT = C::BKT, ROWB = C::ROWB, CPR = C::CPR, NI = C::NI;
   constexpr int ND = D / 16, NV = D / 32;
   constexpr int TILE = C::TILE, NSLOT = C::NSLOT;
   constexpr float TAU = 8.f;
@@ -421,20 +337,22 @@ __device__ __forceinline__ void attn_bf16_dma_body(const AttnArgs a, int bx, int
   const int kv_begin = CAUSAL ? 0 : split * a.chunk;
   const int kv_end = CAUSAL ? min(a.m, q0 + BQ) : min(a.m, kv_begin + a.chunk);
   const int span = kv_end - kv_begin;
-  const int n_tiles = (span + BK - 1) / BK;
+  const int n_tiles = (span + BKT - 1) / BKT;
 
-  const int r = q0 + wave * 32 + rw;
+  const int rg = KG == 1 ? wave : wave % C::RG, kg = KG == 1 ? 0 : __builtin_amdgcn_readfirstlane(wave / C::RG);
+  const int r = q0 + rg * 32 + rw;
   const int r_c = max(0, min(r, a.rows - 1));
-  const int wave_first = q0 + wave * 32;
+  const int wave_first = q0 + rg * 32;
   // A wave whose rows all lie past the last row (the ragged last row tile of a problem: 4120 rows are 16 tiles and
   // 24 rows) computes nothing: no full tiles, no tail.  It still sends its share of the tile requests and meets the
   // barriers.  The last row tile is the one with the longest key range, so this is the most expensive workgroup of
   // every head, and its SIMDs are left to the waves that have rows.
   const bool has_rows = wave_first >= 0 && wave_first < a.rows;
-  const int n_full = !has_rows ? 0
-                     : CAUSAL  ? min((wave_first + 1) / BK, span / BK)
-                               : min((wave_first + (1 << 24)) / BK, span / BK);
-  const bool has_tail = has_rows && n_full * BK < span;
+  // Of the tiles' keys a wave takes 64: unmasked ones in its first n_full tiles, and at most one masked tile after them.
+  const int lim = !has_rows ? 0 : CAUSAL ? min(wave_first + 1, span) : span;
+  const int n_full = lim >= kg * BK + BK ? (lim - kg * BK - BK) / BKT + 1 : 0;
+  const int tail_key = n_full * BKT + kg * BK;
+  const bool has_tail = has_rows && tail_key < span && (!CAUSAL || tail_key <= wave_first + 31);
 
   bf16x8 bq[ND];
   {
@@ -472,9 +390,9 @@ __device__ __forceinline__ void attn_bf16_dma_body(const AttnArgs a, int bx, int
                  : "memory", "m0");
   };
   auto dma_tile = [&](const char* base, int j, uint32_t slot, const uint32_t (&goff)[NI], bool is_v) {
-    const int k0 = j * BK;
+    const int k0 = j * BKT;
     const char* tp = base + (size_t)k0 * (D * 2);
-    if (kv_begin + k0 + BK <= a.m) {
+    if (kv_begin + k0 + BKT <= a.m) {
 #pragma unroll
       for (int i = 0; i < NI; ++i) dma16(tp, goff[i], slot + wave_rows + i * 1024);
     } else {
@@ -489,8 +407,9 @@ __device__ __forceinline__ void attn_bf16_dma_body(const AttnArgs a, int bx, int
       }
     }
   };
-  auto kslot = [&](int j) { return smem + (j % NSLOT) * TILE; };
-  auto vslot = [&](int j) { return smem + (NSLOT + j % NSLOT) * TILE; };
+  // where this wave's keys of a tile start
+  auto kslot = [&](int j) { return smem + (j % NSLOT) * TILE + kg * BK * ROWB; };
+  auto vslot = [&](int j) { return smem + (NSLOT + j % NSLOT) * TILE + kg * BK * ROWB; };
   auto kslot_off = [&](int j) { return (uint32_t)((j % NSLOT) * TILE); };  // the same as byte offsets, for the requests
   auto vslot_off = [&](int j) { return (uint32_t)((NSLOT + j % NSLOT) * TILE); };
 
@@ -595,7 +514,7 @@ __device__ __forceinline__ void attn_bf16_dma_body(const AttnArgs a, int bx, int
   // the masked tile: scores of keys past the row (causal) or past the last key do not count
   auto mask = [&](int tile, f32x16 (&sc)[2]) {
     // number of keys of the tile that count for this lane's row, less the lane's first key: made here, not ahead of the loop
-    int n_ok = (CAUSAL ? min(kv_end, r + 1) : kv_end) - (kv_begin + tile * BK) - 4 * h;
+    int n_ok = (CAUSAL ? min(kv_end, r + 1) : kv_end) - (kv_begin + tile * BKT + kg * BK) - 4 * h;
     asm volatile("" : "+v"(n_ok));
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb)
@@ -616,10 +535,11 @@ __device__ __forceinline__ void attn_bf16_dma_body(const AttnArgs a, int bx, int
     }
   };
   if constexpr (!C::PIPE) {
-    // K(0), V(0) must have landed; K(1), V(1) stay in flight
+    // K(0), V(0) must have landed; with three slots K(1), V(1) stay in flight
+    constexpr int AHEAD = NSLOT - 1;
     dma_tile(kbase, 0, kslot_off(0), goff_k, false);
     dma_tile(vbase, 0, vslot_off(0), goff_v, true);
-    if (n_tiles > 1) {
+    if (AHEAD > 1 && n_tiles > 1) {
       dma_tile(kbase, 1, kslot_off(1), goff_k, false);
       dma_tile(vbase, 1, vslot_off(1), goff_v, true);
       __builtin_amdgcn_s_waitcnt(0x0F70 | 2 * NI);
@@ -628,12 +548,12 @@ __device__ __forceinline__ void attn_bf16_dma_body(const AttnArgs a, int bx, int
     }
     __builtin_amdgcn_s_barrier();
     for (int tile = 0; tile < n_tiles; ++tile) {
-      const bool more = tile + 2 < n_tiles;  // into the slots that step tile - 1 has left
+      const bool more = tile + AHEAD < n_tiles;  // into the slots that step tile - 1 has left
       if (more) {
-        dma_tile(kbase, tile + 2, kslot_off(tile + 2), goff_k, false);
-        dma_tile(vbase, tile + 2, vslot_off(tile + 2), goff_v, true);
+        dma_tile(kbase, tile + AHEAD, kslot_off(tile + AHEAD), goff_k, false);
+        dma_tile(vbase, tile + AHEAD, vslot_off(tile + AHEAD), goff_v, true);
       }
-      const uint32_t at = __builtin_amdgcn_readfirstlane(kslot_off(tile));
+      const uint32_t at = __builtin_amdgcn_readfirstlane(kslot_off(tile) + kg * BK * ROWB);
       const char* ks = smem + at;
       const char* vs = smem + NSLOT * TILE + at;
       if (tile < n_full) {
@@ -648,30 +568,35 @@ __device__ __forceinline__ void attn_bf16_dma_body(const AttnArgs a, int bx, int
         lift(row_max(s));
         weights_pv(s, vs, m_ref == -INFINITY ? 0.f : m_ref);
       }
-      if (more) __builtin_amdgcn_s_waitcnt(0x0F70 | 2 * NI);
+      if (AHEAD > 1 && more) __builtin_amdgcn_s_waitcnt(0x0F70 | 2 * NI);
       else __builtin_amdgcn_s_waitcnt(0x0F70);
       __builtin_amdgcn_s_barrier();
     }
   } else {
-    // ---- prologue: K(0), V(0), K(1) must have landed; V(1), K(2) stay in flight
+    // ---- prologue.  Three slots: K(0), V(0), K(1) must have landed, V(1), K(2) stay in flight.  Two slots: K(0) must
+    //      have landed before the first scores, V(0) and K(1) after them.
+    constexpr int AHEAD_K = NSLOT, AHEAD_V = NSLOT - 1;  // step t requests K(t + AHEAD_K), V(t + AHEAD_V)
     dma_tile(kbase, 0, kslot_off(0), goff_k, false);
     dma_tile(vbase, 0, vslot_off(0), goff_v, true);
     if (n_tiles > 1) dma_tile(kbase, 1, kslot_off(1), goff_k, false);
-    if (n_tiles > 1) dma_tile(vbase, 1, vslot_off(1), goff_v, true);
-    if (n_tiles > 2) dma_tile(kbase, 2, kslot_off(2), goff_k, false);
-    if (n_tiles > 2) __builtin_amdgcn_s_waitcnt(0x0F70 | 2 * NI);   // vmcnt: everything but V(1), K(2)
-    else if (n_tiles > 1) __builtin_amdgcn_s_waitcnt(0x0F70 | NI);  // vmcnt: everything but V(1)
-    else __builtin_amdgcn_s_waitcnt(0x0F70);                         // vmcnt(0)
+    if constexpr (NSLOT == 3) {
+      if (n_tiles > 1) dma_tile(vbase, 1, vslot_off(1), goff_v, true);
+      if (n_tiles > 2) dma_tile(kbase, 2, kslot_off(2), goff_k, false);
+    }
+    if (n_tiles > 2 || (NSLOT == 2 && n_tiles > 1)) __builtin_amdgcn_s_waitcnt(0x0F70 | 2 * NI);
+    else if (n_tiles > 1 || NSLOT == 2) __builtin_amdgcn_s_waitcnt(0x0F70 | NI);
+    else __builtin_amdgcn_s_waitcnt(0x0F70);
     __builtin_amdgcn_s_barrier();
     f32x16 sA[2], sB[2];
     scores(kslot(0), sA);
-    __builtin_amdgcn_s_barrier();  // K(0) has been read by every wave before step 0 refills its slot with K(3)
+    if (NSLOT == 2) __builtin_amdgcn_s_waitcnt(0x0F70);
+    __builtin_amdgcn_s_barrier();  // K(0) has been read by every wave before step 0 refills its slot
 
     // step `tile`: S(tile) is in sc; computes S(tile + 1) into sn and adds tile's V contribution
     auto step = [&](int tile, f32x16 (&sc)[2], f32x16 (&sn)[2]) {
-      const bool more_k = tile + 3 < n_tiles, more_v = tile + 2 < n_tiles;
-      if (more_k) dma_tile(kbase, tile + 3, kslot_off(tile + 3), goff_k, false);
-      if (more_v) dma_tile(vbase, tile + 2, vslot_off(tile + 2), goff_v, true);
+      const bool more_k = tile + AHEAD_K < n_tiles, more_v = tile + AHEAD_V < n_tiles;
+      if (more_k) dma_tile(kbase, tile + AHEAD_K, kslot_off(tile + AHEAD_K), goff_k, false);
+      if (more_v) dma_tile(vbase, tile + AHEAD_V, vslot_off(tile + AHEAD_V), goff_v, true);
       const char* k_next = kslot(tile + 1);
       const char* v_cur = vslot(tile);
       if (tile < n_full) {
@@ -685,14 +610,15 @@ __device__ __forceinline__ void attn_bf16_dma_body(const AttnArgs a, int bx, int
         for (int dc = 0; dc < ND; ++dc) sn[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ak0[dc], bq[dc], sn[0], 0, 0, 0);
 #pragma unroll
         for (int dc = 0; dc < ND; ++dc) sn[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ak1[dc], bq[dc], sn[1], 0, 0, 0);
-        weights_pv(sc, v_cur, m_ref);
+        weights_pv(sc, v_cur, m_ref == -INFINITY ? 0.f : m_ref);
       } else if (tile == n_full && has_tail) {
         mask(tile, sc);
         lift(row_max(sc));
         weights_pv(sc, v_cur, m_ref == -INFINITY ? 0.f : m_ref);
       }
-      // the tiles needed by the next step were requested one step ago: wait for all but this step's loads
-      if (more_k) __builtin_amdgcn_s_waitcnt(0x0F70 | 2 * NI);
+      // three slots: the tiles needed by the next step were requested one step ago, wait for all but this step's loads
+      if (NSLOT == 2) __builtin_amdgcn_s_waitcnt(0x0F70);
+      else if (more_k) __builtin_amdgcn_s_waitcnt(0x0F70 | 2 * NI);
       else if (more_v) __builtin_amdgcn_s_waitcnt(0x0F70 | NI);
       else __builtin_amdgcn_s_waitcnt(0x0F70);
       __builtin_amdgcn_s_barrier();
@@ -703,6 +629,31 @@ __device__ __forceinline__ void attn_bf16_dma_body(const AttnArgs a, int bx, int
     }
   }
 
+  if constexpr (KG == 2) {
+    // the second key group hands its running maximum, row sum and accumulator to the first through LDS
+    // (element e of lane l at word e * 64 + l: conflict-free), which rescales both to the common maximum
+    float* mg = reinterpret_cast<float*>(smem + rg * C::MERGE) + lane;
+    if (kg == 1) {
+#pragma unroll
+      for (int i = 0; i < NV; ++i)
+#pragma unroll
+        for (int j = 0; j < 16; ++j) mg[(i * 16 + j) * 64] = o[i][j];
+      mg[(NV * 16) * 64] = m_ref;
+      mg[(NV * 16 + 1) * 64] = l_run;
+    }
+    __syncthreads();
+    if (kg == 1) return;
+    const float m1 = mg[(NV * 16) * 64], l1 = mg[(NV * 16 + 1) * 64];
+    const float m_new = fmaxf(m_ref, m1);
+    const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
+    const float a0 = __builtin_amdgcn_exp2f(m_ref - m_use), a1 = __builtin_amdgcn_exp2f(m1 - m_use);
+#pragma unroll
+    for (int i = 0; i < NV; ++i)
+#pragma unroll
+      for (int j = 0; j < 16; ++j) o[i][j] = o[i][j] * a0 + mg[(i * 16 + j) * 64] * a1;
+    l_run = l_run * a0 + l1 * a1;
+    m_ref = m_new;
+  }
   const float l_tot = sum_across_halves(l_run);
   const float inv = a.v_unscale[kvh] / l_tot;
   if (!has_rows) return;
@@ -717,27 +668,35 @@ __device__ __forceinline__ void attn_bf16_dma_body(const AttnArgs a, int bx, int
     op0 = a.out + row0 * D;
     lp0 = a.lse + row0;
   }
-  // whole rows through the wave's share (12 KB; 6 KB at d = 64) of the tile slots (free: the last step ended with every request
-  // landed and a barrier), 16 rows at a time
-  store_rows_via_lds<D, 2>(o, inv, op0, a.rows - wave_first, smem + wave * (C::LDS_BYTES / NW), lane);
+  // whole rows through the wave's share (12 KB; 6 KB at d = 64) of the tile slots (free: the last step ended with every
+  // request landed and a barrier), 16 rows at a time; with two key groups through the row group's merge area, which only
+  // this wave still touches
+  if constexpr (KG == 1)
+    store_rows_via_lds<D, 2>(o, inv, op0, a.rows - wave_first, smem + wave * (C::LDS_BYTES / NW), lane);
+  else
+    store_rows_via_lds<D>(o, inv, op0, a.rows - wave_first, smem + rg * C::MERGE, lane);
   if (r < a.rows && h == 0) lp0[rw] = (m_ref + __log2f(l_tot)) * kLn2;
 }
 
-template <int D, bool CAUSAL>
-__global__ __launch_bounds__(512, 2 * DmaCfg<D>::WGS) void k_attn_bf16_dma(AttnArgs a) {
-  attn_bf16_dma_body<D, CAUSAL>(a, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.y);
+template <int D, int KG, bool CAUSAL>
+__global__ __launch_bounds__(512, (2 * DmaCfg<D, KG>::WGS)) void k_attn_bf16_dma(AttnArgs a) {
+  attn_bf16_dma_body<D, KG, CAUSAL>(a, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.y);
 }
 
-// the pair launch (see k_attn_bf16_pair) of the asynchronous kernel
-template <int D>
-__global__ __launch_bounds__(512, 2 * DmaCfg<D>::WGS) void k_attn_bf16_dma_pair(AttnArgs ac, AttnArgs aq, PairGrid g) {
+// Both attentions of the path in ONE launch (same head dimension, same workgroup shape).  The query attention's
+// workgroups come first in the linear order and each walks ALL keys for its rows (no key chunks, no partial results,
+// no merge): such a workgroup lasts as long as the causal problem's longest row tile, which is handed out right
+// behind it, so the query attention hides inside the causal one instead of waiting for it.  n_q_pad, the query
+// workgroups rounded up to a multiple of 8, keeps the causal workgroups on the XCD slots map_block assumes.
+template <int D, int KG>
+__global__ __launch_bounds__(512, (2 * DmaCfg<D, KG>::WGS)) void k_attn_bf16_dma_pair(AttnArgs ac, AttnArgs aq, PairGrid g) {
   const int bid = blockIdx.x;
   if (bid < g.n_q_pad) {
     if (bid >= g.n_q) return;
-    attn_bf16_dma_body<D, false>(aq, bid % g.q_gx, bid / g.q_gx, 0, g.q_gy);
+    attn_bf16_dma_body<D, KG, false>(aq, bid % g.q_gx, bid / g.q_gx, 0, g.q_gy);
   } else {
     const int l = bid - g.n_q_pad;
-    attn_bf16_dma_body<D, true>(ac, l % g.c_gx, l / g.c_gx, 0, g.c_gy);
+    attn_bf16_dma_body<D, KG, true>(ac, l % g.c_gx, l / g.c_gx, 0, g.c_gy);
   }
 }
 
@@ -817,68 +776,56 @@ __global__ __launch_bounds__(256) void k_attn_merge(AttnArgs a, int d) {
   if (c4 == 0) a.lse[row] = mx + logf(den);
 }
 
-template <int D, bool CAUSAL, int NW, int KG = 1, bool SPLIT = false>
+template <int D>
 hipError_t raise_lds_limit() {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attn_bf16<D, CAUSAL, NW, KG, SPLIT>),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, Bf16Cfg<D, NW, KG>::LDS_BYTES);
-}
-template <int D, int NW, int KG>
-hipError_t raise_lds_limit_pair() {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attn_bf16_pair<D, NW, KG>),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, Bf16Cfg<D, NW, KG>::LDS_BYTES);
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attn_bf16<D>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                             Bf16Cfg<D>::LDS_BYTES);
 }
 
-template <int D>
+template <int D, int KG>
 hipError_t raise_lds_limit_dma() {
-  const void* all[] = {reinterpret_cast<const void*>(&k_attn_bf16_dma<D, true>), reinterpret_cast<const void*>(&k_attn_bf16_dma<D, false>),
-                       reinterpret_cast<const void*>(&k_attn_bf16_dma_pair<D>)};
+  const void* all[] = {reinterpret_cast<const void*>(&k_attn_bf16_dma<D, KG, true>),
+                       reinterpret_cast<const void*>(&k_attn_bf16_dma_pair<D, KG>),
+                       KG == 1 ? reinterpret_cast<const void*>(&k_attn_bf16_dma<D, 1, false>) : nullptr};
   for (const void* f : all) {
-    const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, DmaCfg<D>::LDS_BYTES);
+    if (f == nullptr) continue;
+    const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, DmaCfg<D, KG>::LDS_BYTES);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
 }
 
-template <int D, bool CAUSAL, int NW, int KG = 1, bool SPLIT = false>
+template <int D>
 hipError_t run_bf16(const AttnLaunch& l, hipStream_t s) {
-  using C = Bf16Cfg<D, NW, KG>;
+  using C = Bf16Cfg<D>;
   AttnArgs a = make_args(l);
   dim3 grid = attn_grid(&a, (l.rows + C::BQ - 1) / C::BQ);
-  hipLaunchKernelGGL((k_attn_bf16<D, CAUSAL, NW, KG, SPLIT>), grid, dim3(C::NT), C::LDS_BYTES, s, a);
+  hipLaunchKernelGGL(k_attn_bf16<D>, grid, dim3(C::NT), C::LDS_BYTES, s, a);
   return hipGetLastError();
 }
 
-template <int D, bool CAUSAL>
+template <int D, int KG, bool CAUSAL>
 hipError_t run_bf16_dma(const AttnLaunch& l, hipStream_t s) {
+  using C = DmaCfg<D, KG>;
   AttnArgs a = make_args(l);
-  dim3 grid = attn_grid(&a, (l.rows + 255) / 256);
-  hipLaunchKernelGGL((k_attn_bf16_dma<D, CAUSAL>), grid, dim3(512), DmaCfg<D>::LDS_BYTES, s, a);
+  dim3 grid = attn_grid(&a, (l.rows + C::BQ - 1) / C::BQ);
+  hipLaunchKernelGGL((k_attn_bf16_dma<D, KG, CAUSAL>), grid, dim3(512), C::LDS_BYTES, s, a);
   return hipGetLastError();
 }
 
-// Which bf16 kernel serves a problem.
-enum class Shape { kDma, kWaves8Keys2, kWaves4 };
+// Which bf16 kernel serves a problem: asynchronous loads with one or two key groups, or the register-staged kernel.
+enum class Shape { kDma, kDmaKeys2, kStaged };
 Shape bf16_shape(const AttnLaunch& l) {
-  // the asynchronous kernel serves the long problems (enough row tiles for 8 waves)
-  if (attn_bf16_waves(l.causal, l.n_batch, l.rows) == 8) return Shape::kDma;
-  // short causal problems (at most two workgroups per compute unit): 128 rows per workgroup as with four waves, but
-  // two key groups halve the chain of steps of the longest row tile, which is what such a launch waits for
-  if (l.causal && l.rows > 256 && (long long)l.n_batch * ((l.rows + 127) / 128) <= 512) return Shape::kWaves8Keys2;
-  return Shape::kWaves4;
+  if (attn_bf16_rows(l.causal, l.n_batch, l.rows, l.d) == 256) return Shape::kDma;
+  return l.causal ? Shape::kDmaKeys2 : Shape::kStaged;
 }
 
 template <int D, bool CAUSAL>
-hipError_t run_bf16_nw(const AttnLaunch& l, hipStream_t s) {
+hipError_t run_bf16_d(const AttnLaunch& l, hipStream_t s) {
   if (attn_bf16_reads_v16(l) != (l.v_unscale != nullptr)) return hipErrorInvalidValue;  // V prepared iff the shape reads the copy
-  switch (bf16_shape(l)) {
-    case Shape::kDma: return run_bf16_dma<D, CAUSAL>(l, s);
-    case Shape::kWaves8Keys2:
-      if constexpr (CAUSAL) return run_bf16<D, CAUSAL, 8, 2>(l, s);
-      return hipErrorInvalidValue;
-    default:
-      if constexpr (CAUSAL) return run_bf16<D, true, 4>(l, s);
-      return run_bf16<D, false, 4, 1, true>(l, s);  // two-term weights, V as stored
-  }
+  if (bf16_shape(l) == Shape::kDma) return run_bf16_dma<D, 1, CAUSAL>(l, s);
+  if constexpr (CAUSAL) return run_bf16_dma<D, 2, true>(l, s);
+  return run_bf16<D>(l, s);
 }
 
 // Pair launch: the query problem takes the causal problem's kernel shape and walks all keys in one chunk.
@@ -893,34 +840,20 @@ bool pair_grid(AttnArgs* ac, AttnArgs* aq, int bq, PairGrid* g, unsigned* total)
   return true;
 }
 
-template <int D, int NW, int KG>
-hipError_t run_pair(const AttnLaunch& c, const AttnLaunch& q, hipStream_t s) {
-  using C = Bf16Cfg<D, NW, KG>;
+template <int D, int KG>
+hipError_t run_pair_dma(const AttnLaunch& c, const AttnLaunch& q, hipStream_t s) {
+  using C = DmaCfg<D, KG>;
   AttnArgs ac = make_args(c), aq = make_args(q);
   PairGrid g;
   unsigned total;
   if (!pair_grid(&ac, &aq, C::BQ, &g, &total)) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((k_attn_bf16_pair<D, NW, KG>), dim3(total), dim3(C::NT), C::LDS_BYTES, s, ac, aq, g);
-  return hipGetLastError();
-}
-
-template <int D>
-hipError_t run_pair_dma(const AttnLaunch& c, const AttnLaunch& q, hipStream_t s) {
-  AttnArgs ac = make_args(c), aq = make_args(q);
-  PairGrid g;
-  unsigned total;
-  if (!pair_grid(&ac, &aq, 256, &g, &total)) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_attn_bf16_dma_pair<D>, dim3(total), dim3(512), DmaCfg<D>::LDS_BYTES, s, ac, aq, g);
+  hipLaunchKernelGGL((k_attn_bf16_dma_pair<D, KG>), dim3(total), dim3(512), C::LDS_BYTES, s, ac, aq, g);
   return hipGetLastError();
 }
 
 template <int D>
 hipError_t run_pair_d(const AttnLaunch& c, const AttnLaunch& q, hipStream_t s) {
-  switch (bf16_shape(c)) {
-    case Shape::kDma: return run_pair_dma<D>(c, q, s);
-    case Shape::kWaves8Keys2: return run_pair<D, 8, 2>(c, q, s);
-    default: return run_pair<D, 4, 1>(c, q, s);
-  }
+  return bf16_shape(c) == Shape::kDma ? run_pair_dma<D, 1>(c, q, s) : run_pair_dma<D, 2>(c, q, s);
 }
 
 }  // namespace
@@ -939,24 +872,21 @@ hipError_t attn_prepare_device() {
   std::lock_guard<std::mutex> lock(mu);
   if (done[dev]) return hipSuccess;
   const hipError_t all[] = {
-      raise_lds_limit<128, true, 4>(), raise_lds_limit<128, false, 4, 1, true>(), raise_lds_limit<128, true, 8, 2>(),
-      raise_lds_limit<64, true, 4>(),  raise_lds_limit<64, false, 4, 1, true>(),  raise_lds_limit<64, true, 8, 2>(),
-      raise_lds_limit_pair<128, 8, 2>(), raise_lds_limit_pair<128, 4, 1>(), raise_lds_limit_pair<64, 8, 2>(),
-      raise_lds_limit_pair<64, 4, 1>(), raise_lds_limit_dma<128>(), raise_lds_limit_dma<64>(),
-      attn_f32_raise_limits()};
+      raise_lds_limit<128>(), raise_lds_limit<64>(), raise_lds_limit_dma<128, 2>(), raise_lds_limit_dma<64, 2>(),
+      raise_lds_limit_dma<128, 1>(), raise_lds_limit_dma<64, 1>(), attn_f32_raise_limits()};
   for (hipError_t x : all)
     if (x != hipSuccess) return x;
   done[dev] = true;
   return hipSuccess;
 }
 
-bool attn_bf16_reads_v16(const AttnLaunch& l) { return l.causal || bf16_shape(l) != Shape::kWaves4; }
+bool attn_bf16_reads_v16(const AttnLaunch& l) { return bf16_shape(l) != Shape::kStaged; }
 
 hipError_t launch_attn_bf16(const AttnLaunch& l, hipStream_t s) {
   const hipError_t e = attn_prepare_device();
   if (e != hipSuccess) return e;
-  if (l.d == 128) return l.causal ? run_bf16_nw<128, true>(l, s) : run_bf16_nw<128, false>(l, s);
-  return l.causal ? run_bf16_nw<64, true>(l, s) : run_bf16_nw<64, false>(l, s);
+  if (l.d == 128) return l.causal ? run_bf16_d<128, true>(l, s) : run_bf16_d<128, false>(l, s);
+  return l.causal ? run_bf16_d<64, true>(l, s) : run_bf16_d<64, false>(l, s);
 }
 
 hipError_t launch_attn_bf16_pair(const AttnLaunch& causal, const AttnLaunch& query, hipStream_t s) {

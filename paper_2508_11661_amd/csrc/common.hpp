@@ -97,15 +97,16 @@ hipError_t launch_score_select(const ScoreLaunch& a, const SelectLaunch& sl, con
 hipError_t launch_gather_q(const GatherLaunch& a, const PtrTable& q, const IntTable& cu_len, const IntTable& cu_k,
                            int hq, hipStream_t s);
 
-// Waves per workgroup of the bf16 attention kernel (each wave owns 32 query rows).  Eight waves share
-// one K/V tile stream between twice as many rows; that pays once there are enough row tiles to keep
-// every compute unit busy, otherwise four waves give more workgroups to spread.
-#ifndef SAMKV_WAVE8_MIN_TILES
-#define SAMKV_WAVE8_MIN_TILES 384  // causal: number of 256-row tiles (1.5 per compute unit) from which eight waves pay; measured
-#endif
-inline int attn_bf16_waves(int causal, int n_batch, int rows) {
-  if (causal) return (long long)n_batch * ((rows + 255) / 256) >= SAMKV_WAVE8_MIN_TILES ? 8 : 4;
-  return rows >= 512 ? 8 : 4;   // not causal: from two 256-row tiles per KV head on (measured at 256 / 512 / 1024 rows)
+// Rows per workgroup of the bf16 attention kernels: 256 (eight waves, one key stream for all of them) or 128.
+// Causal: 128-row workgroups split the keys between two groups of waves, which halves the chain of steps of the longest
+// row tile and makes twice as many workgroups, but reads each tile for half as many rows.  That wins until the 256-row
+// tiles are about 1.5 per compute unit at d = 128 (32 heads, pair calls, 128 against 256 rows: 2800 rows 92 against 96 us,
+// 3100 rows 110 against 100) and two per resident workgroup, of which a compute unit holds two, at d = 64 (24 heads x
+// 3900 rows 77 against 92, x 6450 rows 163 against 174, 32 heads x 9000 rows 382 against 378, 512 x 500 54 against 51).
+// Not causal: 256 from two such tiles per KV head on (measured at 256 / 512 / 1024 rows).
+inline int attn_bf16_rows(int causal, int n_batch, int rows, int d) {
+  if (!causal) return rows >= 512 ? 256 : 128;
+  return (long long)n_batch * ((rows + 255) / 256) >= (d == 128 ? 384 : 1024) ? 256 : 128;
 }
 
 // One attention problem: `n_batch` independent row blocks, batch b reads KV head b / batch_per_kv.
@@ -126,7 +127,7 @@ struct AttnLaunch {
 };
 hipError_t launch_attn_bf16(const AttnLaunch& a, hipStream_t s);
 // Whether the bf16 kernel that serves this problem reads the scaled half-precision copy of V (every causal problem,
-// long problems that are not causal) or V as stored (the four-wave kernel of a problem that is not causal).  A pair
+// long problems that are not causal) or V as stored (short problems that are not causal).  A pair
 // launch always reads the copy.
 bool attn_bf16_reads_v16(const AttnLaunch& a);
 // Both bf16 attentions of the path in one launch: `causal` and `query` share d, K and the prepared V; the query

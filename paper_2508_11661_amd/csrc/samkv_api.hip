@@ -113,11 +113,11 @@ ScoreWs score_ws(int n_ctx, int hq, int hkv, int d) {
 // Not-causal attention: cut the keys into chunks when the row tiles alone cannot fill the chip.
 struct SplitPlan { int n_split, chunk; size_t part_o, part_lse, bytes; };
 SplitPlan plan_splits(int dtype, int n_batch, int rows, int m, int d) {
-  const int bq = dtype == SAMKV_BF16 ? 32 * attn_bf16_waves(0, n_batch, rows) : 32;
+  const int bq = dtype == SAMKV_BF16 ? attn_bf16_rows(0, n_batch, rows, d) : 32;
   const int bk = dtype == SAMKV_BF16 ? 64 : 128;
   const long long base = (long long)((rows + bq - 1) / bq) * n_batch;
   const int key_tiles = (m + bk - 1) / bk;
-  // aim at as many workgroups as are resident at once: one per compute unit for the eight-wave kernel (256 rows) at
+  // aim at as many workgroups as are resident at once: one per compute unit for the kernel of 256 rows at
   // d = 128, otherwise two; a second round of workgroups only adds partial results to merge
   const int wg_target = bq == 256 && d == 128 ? 256 : 512;
   long long want = (wg_target + base - 1) / base;
