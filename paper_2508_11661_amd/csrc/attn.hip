@@ -34,7 +34,8 @@ namespace samkv {
 namespace {
 
 // ------------------------------------------------------------------ bf16, short problems that are not causal
-// One workgroup = four waves of 32 query rows each.  K/V tiles are double-buffered in LDS; the next tile's global loads
+// One workgroup = four waves of 32 query rows each; one (row tile, part) per workgroup, a part being a chunk of the
+// cache's keys or, behind them, the query tokens' own keys with their causal mask.  K/V tiles are double-buffered in LDS; the next tile's global loads
 // are issued before the current tile's math and land in LDS after it, one barrier per tile.
 template <int D>
 struct Bf16Cfg {
@@ -63,8 +64,10 @@ __global__ __launch_bounds__(256, 2) void k_attn_bf16(AttnArgs a) {
   map_block(a, false, blockIdx.x, blockIdx.y, gridDim.y, &kvh, &batch, &qt);
   const int q0 = qt * C::BQ;
   const int split = blockIdx.z;
-  const int kv_begin = split * a.chunk;
-  const int kv_end = min(a.m, kv_begin + a.chunk);
+  const bool own = a.n_self > 0 && split == a.n_split - 1;  // the query tokens' own keys, causally
+  const int m = own ? a.n_self : a.m;
+  const int kv_begin = own ? 0 : split * a.chunk;
+  const int kv_end = own ? m : min(m, kv_begin + a.chunk);
   const int n_tiles = (kv_end - kv_begin + C::BK - 1) / C::BK;
 
   const int r = q0 + wave * 32 + rw;
@@ -77,8 +80,8 @@ __global__ __launch_bounds__(256, 2) void k_attn_bf16(AttnArgs a) {
 #pragma unroll
     for (int dc = 0; dc < ND; ++dc) bq[dc] = *reinterpret_cast<const bf16x8*>(qp + dc * 32);
   }
-  const char* kbase = static_cast<const char*>(a.k) + (size_t)kvh * a.m * D * 2;
-  const char* vbase = static_cast<const char*>(a.v) + (size_t)kvh * a.m * D * 2;
+  const char* kbase = static_cast<const char*>(own ? a.k_self : a.k) + (size_t)kvh * m * D * 2;
+  const char* vbase = static_cast<const char*>(own ? a.v_self : a.v) + (size_t)kvh * m * D * 2;
 
   // Tile loads: thread t fetches chunk (row t/CPR + i*RSTEP, 16-byte column t%CPR) of K and of V.  The
   // byte offsets inside a tile are per-thread constants; the tile base is uniform, so a full tile
@@ -92,7 +95,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_bf16(AttnArgs a) {
     const int k0 = kv_begin + tile * C::BK;
     const char* kt = kbase + (size_t)k0 * (D * 2);
     const char* vt = vbase + (size_t)k0 * (D * 2);
-    if (k0 + C::BK <= a.m) {
+    if (k0 + C::BK <= m) {
 #pragma unroll
       for (int i = 0; i < C::CHUNKS; ++i) {
         rk[i] = *reinterpret_cast<const u32x4*>(kt + voff[i]);
@@ -101,7 +104,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_bf16(AttnArgs a) {
     } else {
 #pragma unroll
       for (int i = 0; i < C::CHUNKS; ++i) {
-        const int row = min(t / CPR + i * RSTEP, a.m - 1 - k0);
+        const int row = min(t / CPR + i * RSTEP, m - 1 - k0);
         const uint32_t off = (uint32_t)(row * (D * 2) + (t % CPR) * 16);
         rk[i] = *reinterpret_cast<const u32x4*>(kt + off);
         rv[i] = *reinterpret_cast<const u32x4*>(vt + off);
@@ -119,6 +122,8 @@ __global__ __launch_bounds__(256, 2) void k_attn_bf16(AttnArgs a) {
       *reinterpret_cast<u32x4*>(sv + row * C::VSTR + col * 16) = rv[i];
     }
   };
+
+  const int key_end = own ? r % a.n_self + 1 : kv_end;  // one past the last key that counts for this lane's row
 
   f32x16 o[NV];
 #pragma unroll
@@ -166,13 +171,13 @@ __global__ __launch_bounds__(256, 2) void k_attn_bf16(AttnArgs a) {
         }
       }
       // accumulator register j of block kb holds key k0 + kb*32 + 8*(j/4) + 4*h + (j%4) for row r
-      if (k0 + C::BK > kv_end) {
+      if (own || k0 + C::BK > kv_end) {
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
           for (int j = 0; j < 16; ++j) {
             const int key = k0 + kb * 32 + 8 * (j >> 2) + 4 * h + (j & 3);
-            if (key >= kv_end) s[kb][j] = -INFINITY;
+            if (key >= key_end) s[kb][j] = -INFINITY;
           }
       }
       float mx = -INFINITY;
@@ -704,7 +709,8 @@ __global__ __launch_bounds__(512, (2 * DmaCfg<D, KG>::WGS)) void k_attn_bf16_dma
 // channels each; with many chunks, S groups of them share a row: group g takes the chunks g, g + S, ..., eight requested
 // at a time, and the groups meet in LDS.  Every order is fixed, so the result is deterministic.
 // One thread walking all chunks of its channels spends a memory round trip on each: 35 us for 64 rows x 64 chunks, 6 us
-// with S = 8.
+// with S = 8.  Few chunks take fewer groups: eight of them for 9 chunks request mostly the same words (8128 rows x 9
+// chunks, whole query call with its own keys: 86 us with S = 8, 72 with S = 2).
 template <int S>
 __global__ __launch_bounds__(256) void k_attn_merge(AttnArgs a, int d) {
   constexpr int U = 8;
@@ -816,6 +822,7 @@ hipError_t run_bf16_dma(const AttnLaunch& l, hipStream_t s) {
 // Which bf16 kernel serves a problem: asynchronous loads with one or two key groups, or the register-staged kernel.
 enum class Shape { kDma, kDmaKeys2, kStaged };
 Shape bf16_shape(const AttnLaunch& l) {
+  if (l.n_self > 0) return Shape::kStaged;
   if (attn_bf16_rows(l.causal, l.n_batch, l.rows, l.d) == 256) return Shape::kDma;
   return l.causal ? Shape::kDmaKeys2 : Shape::kStaged;
 }
@@ -910,7 +917,11 @@ static hipError_t run_merge(const AttnLaunch& l, hipStream_t s) {
 }
 
 hipError_t launch_attn_merge(const AttnLaunch& l, hipStream_t s) {
-  return l.n_split <= 8 ? run_merge<1>(l, s) : run_merge<8>(l, s);  // one batch of requests per thread up to 64 chunks
+  // one batch of eight requests per thread up to 64 chunks, spread over no more groups than that takes
+  if (l.n_split <= 8) return run_merge<1>(l, s);
+  if (l.n_split <= 16) return run_merge<2>(l, s);
+  if (l.n_split <= 32) return run_merge<4>(l, s);
+  return run_merge<8>(l, s);
 }
 
 }  // namespace samkv

@@ -17,6 +17,9 @@ struct AttnArgs {
   float* part_o;
   float* part_lse;
   int rows, m, batch_per_kv, n_batch, n_split, chunk;
+  int n_self;          // > 0: the last part is the query tokens' own n_self keys, k_self and v_self (k_attn_bf16)
+  const void* k_self;
+  const void* v_self;
   int kv_groups;  // > 0: KV heads are walked in groups of 8 (one per XCD), see map_block
   float scale;
 };
@@ -113,6 +116,7 @@ inline AttnArgs make_args(const AttnLaunch& l) {
   a.rows = l.rows; a.m = l.m; a.batch_per_kv = l.batch_per_kv; a.n_batch = l.n_batch;
   a.n_split = l.causal ? 1 : l.n_split;
   a.chunk = l.chunk; a.scale = l.scale;
+  a.n_self = l.n_self; a.k_self = l.k_self; a.v_self = l.v_self;
   a.kv_groups = 0;
   return a;
 }

@@ -109,6 +109,15 @@ inline int attn_bf16_rows(int causal, int n_batch, int rows, int d) {
   return (long long)n_batch * ((rows + 255) / 256) >= (d == 128 ? 384 : 1024) ? 256 : 128;
 }
 
+// Whether the attention of query tokens over a cache AND their own keys runs as one launch of the short kernel, the own
+// keys being one more part beside the key chunks: no copy of V for the cache or for the own values, one merge.
+// Problems of 512 rows per KV head and more pay for that with the doubled second product once they are large: one launch
+// against preparation, two attentions and merge, 8 KV heads, d = 128: 512 rows x 3000 keys 31 against 53 us, x 20000
+// 78 / 99, 1016 rows x 7040 61 / 72, x 14000 108 / 104; 1600 rows x 7040 94 / 110; d = 64, 600 rows x 30000 83 / 92.
+inline bool attn_self_in_kernel(int dtype, int n_kv, int rows, int m, int d) {
+  return dtype == SAMKV_BF16 && (rows < 512 || (long long)rows * m * n_kv * d <= 12000000000ll);
+}
+
 // One attention problem: `n_batch` independent row blocks, batch b reads KV head b / batch_per_kv.
 // Row r of a batch attends keys [0, r] (causal) or [0, m) (not causal).
 struct AttnLaunch {
@@ -124,6 +133,11 @@ struct AttnLaunch {
   int n_split, chunk;  // keys are cut into n_split chunks of `chunk` keys (not causal only)
   float* part_o;       // [n_split][n_batch][rows][d]   workspace when n_split > 1
   float* part_lse;     // [n_split][n_batch][rows]
+  // attn_self_in_kernel problems only: the last of the n_split parts is the query tokens' own keys, of which row r of a
+  // batch (query head r / n_self, token r % n_self) sees the first r % n_self + 1
+  int n_self;
+  const void* k_self;  // [n_batch][n_self][d]
+  const void* v_self;
 };
 hipError_t launch_attn_bf16(const AttnLaunch& a, hipStream_t s);
 // Whether the bf16 kernel that serves this problem reads the scaled half-precision copy of V (every causal problem,

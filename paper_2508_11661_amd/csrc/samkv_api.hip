@@ -112,8 +112,9 @@ ScoreWs score_ws(int n_ctx, int hq, int hkv, int d) {
 
 // Not-causal attention: cut the keys into chunks when the row tiles alone cannot fill the chip.
 struct SplitPlan { int n_split, chunk; size_t part_o, part_lse, bytes; };
-SplitPlan plan_splits(int dtype, int n_batch, int rows, int m, int d) {
-  const int bq = dtype == SAMKV_BF16 ? attn_bf16_rows(0, n_batch, rows, d) : 32;
+// `own`: one more part, the query tokens' own keys, follows in the same launch (attn_self_in_kernel).
+SplitPlan plan_splits(int dtype, int n_batch, int rows, int m, int d, bool own = false) {
+  const int bq = dtype != SAMKV_BF16 ? 32 : own ? 128 : attn_bf16_rows(0, n_batch, rows, d);
   const int bk = dtype == SAMKV_BF16 ? 64 : 128;
   const long long base = (long long)((rows + bq - 1) / bq) * n_batch;
   const int key_tiles = (m + bk - 1) / bk;
@@ -121,6 +122,7 @@ SplitPlan plan_splits(int dtype, int n_batch, int rows, int m, int d) {
   // d = 128, otherwise two; a second round of workgroups only adds partial results to merge
   const int wg_target = bq == 256 && d == 128 ? 256 : 512;
   long long want = (wg_target + base - 1) / base;
+  if (own) want -= 1;
   if (want > 64) want = 64;
   if (want < 1) want = 1;
   int tiles_per = (int)((key_tiles + want - 1) / want);
@@ -177,19 +179,23 @@ hipError_t prepare_v(AttnLaunch* a, const VPrepWs& vp, char* at, int hkv, hipStr
   return e;
 }
 
-// Workspace of samkv_query_attn_self: two result slots [2][Hq*Lq][d] + [2][Hq*Lq] (cache part, self part),
-// followed by whatever the cache part itself needs for its key chunks.
-struct SelfWs { size_t part_o, part_lse, inner, bytes; };
+// Workspace of samkv_query_attn_self: one partial result per key chunk of the cache and one of the query tokens' own
+// keys, [n_split + 1][Hq*Lq][d] and [n_split + 1][Hq*Lq], then the prepared V of the cache or of the query tokens (one
+// after the other on the stream) where a kernel needs it.
+struct SelfWs { SplitPlan split; VPrepWs vp, vp_own; size_t part_o, part_lse, inner, bytes; };
 SelfWs self_ws(int hq, int hkv, int d, int n_q_tok, int m_total, int dtype) {
   SelfWs w;
   const size_t n_rows = (size_t)hq * n_q_tok;
+  const int rows = (hq / hkv) * n_q_tok;
+  const bool in_kernel = attn_self_in_kernel(dtype, hkv, rows, m_total, d);
+  w.split = plan_splits(dtype, hkv, rows, m_total, d, in_kernel);
+  const size_t parts = w.split.n_split + 1;
   w.part_o = 0;
-  w.part_lse = align_up(2 * n_rows * d * 4);
-  w.inner = align_up(w.part_lse + 2 * n_rows * 4);
-  // the two partial attentions run one after the other on the stream and share the inner region
-  const size_t cache_part = attn_ws(dtype, false, hkv, (hq / hkv) * n_q_tok, m_total, d).bytes;
-  const size_t self_part = attn_ws(dtype, true, hkv, 0, n_q_tok, d).bytes;
-  w.bytes = w.inner + (cache_part > self_part ? cache_part : self_part);
+  w.part_lse = align_up(parts * n_rows * d * 4);
+  w.inner = align_up(w.part_lse + parts * n_rows * 4);
+  w.vp = vprep_ws(in_kernel ? SAMKV_F32 : dtype, hkv, m_total, d);
+  w.vp_own = vprep_ws(in_kernel ? SAMKV_F32 : dtype, hkv, n_q_tok, d);
+  w.bytes = w.inner + (w.vp.bytes > w.vp_own.bytes ? w.vp.bytes : w.vp_own.bytes);
   return w;
 }
 
@@ -828,20 +834,33 @@ int samkv_query_attn_self(const void* q_tok, int32_t n_q_tok, const void* k_c, c
   if (ws == nullptr || ((uintptr_t)ws % kAlign) != 0 || ws_bytes < w.bytes) return SAMKV_EWORKSPACE;
   char* base = static_cast<char*>(ws);
   const size_t n_rows = (size_t)n_q_heads * n_q_tok;
+  const int rows = (n_q_heads / n_kv_heads) * n_q_tok, n_cache = w.split.n_split;
   float* part_o = reinterpret_cast<float*>(base + w.part_o);
   float* part_lse = reinterpret_cast<float*>(base + w.part_lse);
-  // slot 0: the query over the compacted cache (no mask); slot 1: the query over its own K/V (causal)
-  rc = samkv_query_attn(q_tok, n_q_tok, k_c, v_c, m_total, n_q_heads, n_kv_heads, head_dim, dtype, scale, part_o,
-                        part_lse, base + w.inner, ws_bytes - w.inner, stream);
-  if (rc != SAMKV_OK) return rc;
-  rc = samkv_recompute_attn(q_tok, k_self, v_self, n_q_tok, n_q_heads, n_kv_heads, head_dim, dtype, scale,
-                            part_o + n_rows * head_dim, part_lse + n_rows, base + w.inner, ws_bytes - w.inner, stream);
-  if (rc != SAMKV_OK) return rc;
-  AttnLaunch a;
-  memset(&a, 0, sizeof(a));
-  a.d = head_dim; a.n_batch = n_q_heads; a.batch_per_kv = n_q_heads / n_kv_heads; a.rows = n_q_tok;
-  a.out = out; a.lse = lse; a.n_split = 2; a.part_o = part_o; a.part_lse = part_lse;
-  return dev(launch_attn_merge(a, static_cast<hipStream_t>(stream)));
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  // parts 0 .. n_cache - 1: the query over the chunks of the compacted cache (no mask); part n_cache: over its own K/V
+  // (causal).  With a single chunk the cache part is written as that kernel's only result.
+  AttnLaunch a = query_launch(q_tok, n_q_tok, k_c, v_c, m_total, n_q_heads, n_kv_heads, head_dim, dtype, scale, part_o,
+                              part_lse, w.split, ws);
+  a.part_o = part_o;
+  a.part_lse = part_lse;
+  hipError_t e;
+  if (attn_self_in_kernel(dtype, n_kv_heads, rows, m_total, head_dim)) {
+    a.n_split = n_cache + 1;
+    a.n_self = n_q_tok; a.k_self = k_self; a.v_self = v_self;
+    e = launch_attn_bf16(a, s);
+  } else {
+    AttnLaunch own = recompute_launch(q_tok, k_self, v_self, n_q_tok, n_q_heads, n_kv_heads, head_dim, dtype, scale,
+                                      part_o + n_cache * n_rows * head_dim, part_lse + n_cache * n_rows);
+    e = prepare_v(&a, w.vp, base + w.inner, n_kv_heads, s);
+    if (e == hipSuccess) e = dtype == SAMKV_BF16 ? launch_attn_bf16(a, s) : launch_attn_f32(a, s);
+    if (e == hipSuccess) e = prepare_v(&own, w.vp_own, base + w.inner, n_kv_heads, s);
+    if (e == hipSuccess) e = dtype == SAMKV_BF16 ? launch_attn_bf16(own, s) : launch_attn_f32(own, s);
+  }
+  if (e != hipSuccess) return dev(e);
+  a.n_split = n_cache + 1;
+  a.out = out; a.lse = lse;
+  return dev(launch_attn_merge(a, s));
 }
 
 int samkv_kv_update(void* k_c, void* v_c, const void* k_new, const void* v_new, int32_t m_total, int32_t n_kv_heads,
