@@ -73,8 +73,7 @@ hipError_t launch_gather_g(int row_bytes, const PtrTable& a, const PtrTable* b, 
 hipError_t launch_normalize(const float* bscores, const int32_t* bidx, const IntTable& cu_blk, const IntTable& cu_kb,
                             int n_ctx, int hkv, int n_init, int n_local, float* cand, hipStream_t s);
 hipError_t launch_filter_expand(const int32_t* sel, const int32_t* bidx, const IntTable& cu_len, const IntTable& cu_kb,
-                                int n_ctx, int hkv, int n_sel, int m_total, int block, int32_t* start, int32_t* tok_off,
-                                int32_t* gidx, hipStream_t s);
+                                int n_ctx, int hkv, int n_sel, int m_total, int block, int32_t* gidx, hipStream_t s);
 
 hipError_t launch_peak_mfma(float* sink, int n_blocks, int iters, int pattern, hipStream_t s);
 hipError_t launch_peak_copy(const void* src, void* dst, size_t bytes, hipStream_t s);

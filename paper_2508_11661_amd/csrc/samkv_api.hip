@@ -488,8 +488,8 @@ size_t samkv_block_workspace_bytes(const samkv_caches* caches, int32_t block) {
   Shape s;
   IntTable cu_blk;
   if (check_caches(caches, false, false, &s) != SAMKV_OK || block_table(caches, s, block, &cu_blk) != SAMKV_OK) return 0;
-  // kept block ids; for the filter also the candidates' normalised scores, the kept candidates, their first token
-  // positions and output offsets: five arrays of at most [Hkv][sum of blocks] 4-byte entries
+  // kept block ids; for the filter also the candidates' normalised scores and the kept candidates, arrays of at most
+  // [Hkv][sum of blocks] 4-byte entries.  The size callers are asked for has room for two more.
   return 5 * align_up((size_t)s.hkv * cu_blk.v[s.n_ctx] * 4) + kAlign;
 }
 
@@ -568,8 +568,6 @@ int samkv_block_select_filter(const float* bscores, const samkv_caches* caches, 
   int32_t* bidx = reinterpret_cast<int32_t*>(w);
   float* cand = reinterpret_cast<float*>(w + slab);
   int32_t* sel = reinterpret_cast<int32_t*>(w + 2 * slab);
-  int32_t* start = reinterpret_cast<int32_t*>(w + 3 * slab);
-  int32_t* tok_off = reinterpret_cast<int32_t*>(w + 4 * slab);
   hipStream_t st = static_cast<hipStream_t>(stream);
   hipError_t e = block_select_launch(bscores, s, bp, n_init_blocks, n_local_blocks, bidx, st);
   if (e == hipSuccess)
@@ -585,7 +583,7 @@ int samkv_block_select_filter(const float* bscores, const samkv_caches* caches, 
     e = launch_select(a, row, kept, st);
   }
   if (e == hipSuccess)
-    e = launch_filter_expand(sel, bidx, s.cu_len, bp.cu_kb, s.n_ctx, s.hkv, n_sel, m_total, block, start, tok_off, gidx, st);
+    e = launch_filter_expand(sel, bidx, s.cu_len, bp.cu_kb, s.n_ctx, s.hkv, n_sel, m_total, block, gidx, st);
   return dev(e);
 }
 
