@@ -102,9 +102,12 @@ hipError_t launch_gather_q(const GatherLaunch& a, const PtrTable& q, const IntTa
 // tiles are about 1.5 per compute unit at d = 128 (32 heads, pair calls, 128 against 256 rows: 2800 rows 92 against 96 us,
 // 3100 rows 110 against 100) and two per resident workgroup, of which a compute unit holds two, at d = 64 (24 heads x
 // 3900 rows 77 against 92, x 6450 rows 163 against 174, 32 heads x 9000 rows 382 against 378, 512 x 500 54 against 51).
+// Up to 512 rows the chain is short anyway, and with 128 heads and more there are workgroups enough: 128 heads x 140 rows 17.0
+// against 20.5 us, x 300 rows 21.9 / 27.0, 256 x 140 25.5 / 29.1; d = 64, 512 x 140 21.5 / 26.0 (64 heads: x 300 20.9 / 18.0).
 // Not causal: 256 from two such tiles per KV head on (measured at 256 / 512 / 1024 rows).
 inline int attn_bf16_rows(int causal, int n_batch, int rows, int d) {
   if (!causal) return rows >= 512 ? 256 : 128;
+  if (rows <= 512 && n_batch >= 128) return 256;
   return (long long)n_batch * ((rows + 255) / 256) >= (d == 128 ? 384 : 1024) ? 256 : 128;
 }
 

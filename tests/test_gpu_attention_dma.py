@@ -15,6 +15,7 @@ pytestmark = pytest.mark.gpu
     (64, 120, 8, 2049), (64, 120, 8, 2303),
     (128, 384, 8, 192), (128, 384, 8, 193), (128, 192, 8, 257), (128, 192, 8, 320), (128, 195, 5, 321),
     (128, 48, 8, 2049), (128, 48, 8, 2303), (64, 80, 8, 3329), (64, 512, 8, 257),
+    (128, 128, 8, 140), (64, 130, 10, 300), (128, 136, 8, 512), (128, 127, 127, 300),  # many heads, few rows
     # two key groups: one key, one and both groups' first tiles, remainders of 128
     (128, 8, 2, 1), (128, 8, 2, 32), (128, 8, 2, 33), (128, 7, 1, 64), (128, 8, 2, 65), (128, 6, 2, 127), (128, 8, 8, 128),
     (128, 8, 2, 129), (128, 5, 5, 192), (128, 8, 2, 193), (128, 8, 2, 256), (128, 4, 2, 257), (128, 8, 2, 1000),
