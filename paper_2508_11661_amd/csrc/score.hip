@@ -132,81 +132,14 @@ __global__ void k_qtilde(const float* que, const float* bias, const float* loc, 
   qt[((size_t)i * hkv + g) * d + c] = acc / (float)G;
 }
 
-// Sums over rows by one wave, 64 / LPR rows per step (LPR lanes of 16 bytes share a row): issue_rows requests rows r0,
-// r0 + step, ... (< n_rows) of `src`, U loads in flight per lane, take_rows adds them; add_rows does both over all rows
-// from `first` on.  fold_rows sums over the row groups of the wave: lanes that differ in the bits above log2(LPR).
-template <bool BF16, int D, int U>
-__device__ __forceinline__ void issue_rows(const char* src, int r0, int step, int n_rows, u32x4 (&x)[U]) {
-  constexpr size_t ROW_BYTES = (size_t)D * (BF16 ? 2 : 4);
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    const int r = r0 + u * step;
-    x[u] = *reinterpret_cast<const u32x4*>(src + (size_t)(r < n_rows ? r : n_rows - 1) * ROW_BYTES);
-  }
-}
-template <bool BF16, int U, int EPL>
-__device__ __forceinline__ void take_rows(int r0, int step, int n_rows, const u32x4 (&x)[U], float (&acc)[EPL]) {
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    float f[EPL];
-    unpack16<BF16>(x[u], f);
-    const float keep = (r0 + u * step < n_rows) ? 1.f : 0.f;
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) acc[e] = fmaf(f[e], keep, acc[e]);
-  }
-}
-template <bool BF16, int D, int EPL>
-__device__ __forceinline__ void add_rows(const char* src, int first, int step, int n_rows, float (&acc)[EPL]) {
-  constexpr int U = 16;
-  for (int r0 = first; r0 < n_rows; r0 += U * step) {
-    u32x4 x[U];
-    issue_rows<BF16, D>(src, r0, step, n_rows, x);
-    take_rows<BF16>(r0, step, n_rows, x, acc);
-  }
-}
-template <int LPR, int EPL>
-__device__ __forceinline__ void fold_rows(float (&acc)[EPL]) {
-#pragma unroll
-  for (int off = LPR; off < 64; off <<= 1)
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) acc[e] += __shfl_xor(acc[e], off);
-}
-
-// Mean of the w_loc rows at `src` by one wave; the lanes of row group 0 write D floats to dst.
-template <bool BF16, int D>
-__device__ __forceinline__ void pool_by_wave(const char* src, int w_loc, float* dst) {
-  constexpr int EPL = BF16 ? 8 : 4, LPR = D / EPL, RPW = 64 / LPR;
-  const int lane = threadIdx.x & 63, sub = lane % LPR, rgp = lane / LPR;
-  float acc[EPL];
-#pragma unroll
-  for (int e = 0; e < EPL; ++e) acc[e] = 0.f;
-  add_rows<BF16, D>(src + sub * 16, rgp, RPW, w_loc, acc);
-  fold_rows<LPR>(acc);
-  if (rgp == 0)
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) dst[sub * EPL + e] = acc[e] / (float)w_loc;
-}
-
-// The local Q caches' means by themselves, a wave per (document, query head): step 1 of k_prologue spread over the chip,
-// for more documents than its workgroups have waves.
-template <bool BF16, int D>
-__global__ __launch_bounds__(256) void k_pool_waves(const void* q_loc, int w_loc, int n_ctx, int hq, float* loc) {
-  constexpr size_t ROW_BYTES = (size_t)D * (BF16 ? 2 : 4);
-  const int h = blockIdx.x, j = blockIdx.y * 4 + (threadIdx.x >> 6);
-  if (j >= n_ctx) return;
-  const size_t at = (size_t)j * hq + h;
-  pool_by_wave<BF16, D>(static_cast<const char*>(q_loc) + at * w_loc * ROW_BYTES, w_loc, loc + at * D);
-}
-
 // The three launches above in one, for short inputs (one workgroup of 16 waves per query head; the head's local
 // Q caches of all documents pass through that one workgroup, so this is for inputs of up to about a megabyte per
 // head, where launch latency and not bandwidth is what the three launches cost).  Writes Eq. 1 per QUERY head,
 // qhat[i][h][:]; k_score folds the heads of a KV group.
-//   1. wave w takes documents w, w + 16, ...: mean of the document's local rows, into LDS.  POOLED: the means are read
-//      from qhat, where k_pool_waves has put them.
+//   1. wave w takes documents w, w + 16, ...: mean of the document's local rows, into LDS.
 //   2. Q_que[h]: the 16 waves split the user query's rows (requested ahead of step 1); partial sums meet in LDS.
 //   3. w_j = |cos(Q_que, Q_loc_j)|, bias = sum_j w_j Q_loc_j, then Q^_i = Q_que + (bias - w_i Q_loc_i) / (N - 1).
-template <bool BF16, int D, bool POOLED>
+template <bool BF16, int D>
 __global__ __launch_bounds__(1024) void k_prologue(const void* q_tok, int n_q_tok, const void* q_loc, int w_loc, int n_ctx,
                                                    int hq, int with_bias, float* qhat) {
   constexpr int EPL = BF16 ? 8 : 4;
@@ -222,26 +155,69 @@ __global__ __launch_bounds__(1024) void k_prologue(const void* q_tok, int n_q_to
   const int h = blockIdx.x, t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int sub = lane % LPR, rgp = lane / LPR;
 
+  // acc += rows r0, r0 + step, ... (< n_rows) of `src`, U 16-byte loads in flight per lane; the loads of the first
+  // batch can be issued ahead (issue_rows) and consumed later (take_rows), with other loads in between
+  auto issue_rows = [&](const char* src, int r0, int step, int n_rows, auto& x) {
+    constexpr int U = sizeof(x) / sizeof(x[0]);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int r = r0 + u * step;
+      x[u] = *reinterpret_cast<const u32x4*>(src + (size_t)(r < n_rows ? r : n_rows - 1) * ROW_BYTES);
+    }
+  };
+  auto take_rows = [&](int r0, int step, int n_rows, const auto& x, float* acc) {
+    constexpr int U = sizeof(x) / sizeof(x[0]);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      float f[EPL];
+      unpack16<BF16>(x[u], f);
+      const float keep = (r0 + u * step < n_rows) ? 1.f : 0.f;
+#pragma unroll
+      for (int e = 0; e < EPL; ++e) acc[e] = fmaf(f[e], keep, acc[e]);
+    }
+  };
+  auto add_rows = [&](const char* src, int first, int step, int n_rows, float* acc) {
+    constexpr int U = 16;
+    for (int r0 = first; r0 < n_rows; r0 += U * step) {
+      u32x4 x[U];
+      issue_rows(src, r0, step, n_rows, x);
+      take_rows(r0, step, n_rows, x, acc);
+    }
+  };
+  // sum over the row groups of a wave: lanes that differ in the bits above log2(LPR)
+  auto fold_rows = [&](float* acc) {
+#pragma unroll
+    for (int off = LPR; off < 64; off <<= 1)
+#pragma unroll
+      for (int e = 0; e < EPL; ++e) acc[e] += __shfl_xor(acc[e], off);
+  };
   // The user query's rows and the documents' local rows are independent inputs: the first batch of the former is
   // requested before the latter are pooled, so the two memory round trips overlap.
   constexpr int UQ = 2;
   const char* tok_src = static_cast<const char*>(q_tok) + (size_t)h * n_q_tok * ROW_BYTES + sub * 16;
   const int tok_first = wave * RPW + rgp, tok_step = 16 * RPW;
   u32x4 xq[UQ];
-  issue_rows<BF16, D>(tok_src, tok_first, tok_step, n_q_tok, xq);
-  if constexpr (POOLED) {
-    for (int x = t; x < n_ctx * D; x += 1024) s_loc[x] = qhat[((size_t)(x / D) * hq + h) * D + x % D];
-  } else if (with_bias) {
-    for (int j = wave; j < n_ctx; j += 16)
-      pool_by_wave<BF16, D>(static_cast<const char*>(q_loc) + ((size_t)j * hq + h) * w_loc * ROW_BYTES, w_loc, s_loc + j * D);
+  issue_rows(tok_src, tok_first, tok_step, n_q_tok, xq);
+  if (with_bias) {
+    for (int j = wave; j < n_ctx; j += 16) {
+      const char* src = static_cast<const char*>(q_loc) + ((size_t)j * hq + h) * w_loc * ROW_BYTES + sub * 16;
+      float acc[EPL];
+#pragma unroll
+      for (int e = 0; e < EPL; ++e) acc[e] = 0.f;
+      add_rows(src, rgp, RPW, w_loc, acc);
+      fold_rows(acc);
+      if (rgp == 0)
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) s_loc[j * D + sub * EPL + e] = acc[e] / (float)w_loc;
+    }
   }
   {
     float acc[EPL];
 #pragma unroll
     for (int e = 0; e < EPL; ++e) acc[e] = 0.f;
-    take_rows<BF16>(tok_first, tok_step, n_q_tok, xq, acc);
-    add_rows<BF16, D>(tok_src, tok_first + UQ * tok_step, tok_step, n_q_tok, acc);
-    fold_rows<LPR>(acc);
+    take_rows(tok_first, tok_step, n_q_tok, xq, acc);
+    add_rows(tok_src, tok_first + UQ * tok_step, tok_step, n_q_tok, acc);
+    fold_rows(acc);
     if (rgp == 0)
 #pragma unroll
       for (int e = 0; e < EPL; ++e) red[wave * D + sub * EPL + e] = acc[e];
@@ -337,16 +313,8 @@ hipError_t run_prologue(const ScoreLaunch& a, hipStream_t s, QuerySrc* out) {
   const size_t per_head = ((size_t)a.n_q_tok + (bias ? (size_t)a.n_ctx * a.w_loc : 0)) * D * (BF16 ? 2 : 4);
   if (a.n_ctx <= 64 && per_head <= (1u << 20)) {
     const size_t lds = (size_t)(2 * D + 16 * D + SAMKV_MAX_CTX + a.n_ctx * D) * sizeof(float);
-    // More documents than a workgroup has waves, and too few heads to fill the chip: the means by a launch of their own.
-    if (bias && a.n_ctx > 16 && a.hq < 256) {
-      hipLaunchKernelGGL((k_pool_waves<BF16, D>), dim3(a.hq, (a.n_ctx + 3) / 4), dim3(256), 0, s, a.q_loc, a.w_loc, a.n_ctx,
-                         a.hq, a.ws_loc);
-      hipLaunchKernelGGL((k_prologue<BF16, D, true>), dim3(a.hq), dim3(1024), lds, s, a.q_tok, a.n_q_tok, a.q_loc, a.w_loc,
-                         a.n_ctx, a.hq, 1, a.ws_loc);
-    } else {
-      hipLaunchKernelGGL((k_prologue<BF16, D, false>), dim3(a.hq), dim3(1024), lds, s, a.q_tok, a.n_q_tok, a.q_loc, a.w_loc,
-                         a.n_ctx, a.hq, bias ? 1 : 0, a.ws_loc);
-    }
+    hipLaunchKernelGGL((k_prologue<BF16, D>), dim3(a.hq), dim3(1024), lds, s, a.q_tok, a.n_q_tok, a.q_loc, a.w_loc, a.n_ctx,
+                       a.hq, bias ? 1 : 0, a.ws_loc);
     out->q = a.ws_loc; out->heads = a.hq; out->group = a.hq / a.hkv;
     return hipGetLastError();
   }
