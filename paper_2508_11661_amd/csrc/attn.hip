@@ -594,8 +594,10 @@ __device__ __forceinline__ void attn_bf16_dma_body(const AttnArgs a, int bx, int
     __builtin_amdgcn_s_barrier();
     f32x16 sA[2], sB[2];
     scores(kslot(0), sA);
-    if (NSLOT == 2) __builtin_amdgcn_s_waitcnt(0x0F70);
-    __builtin_amdgcn_s_barrier();  // K(0) has been read by every wave before step 0 refills its slot
+    // K(0) has been read by every wave before step 0 refills its slot: the reads' arrival is waited for here (lgkmcnt(0),
+    // with two slots vmcnt(0) too), because the products that use them may be scheduled behind the barrier
+    __builtin_amdgcn_s_waitcnt(NSLOT == 2 ? 0x0070 : 0xC07F);
+    __builtin_amdgcn_s_barrier();
 
     // step `tile`: S(tile) is in sc; computes S(tile + 1) into sn and adds tile's V contribution
     auto step = [&](int tile, f32x16 (&sc)[2], f32x16 (&sn)[2]) {
