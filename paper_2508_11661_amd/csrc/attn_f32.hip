@@ -175,12 +175,13 @@ __device__ __forceinline__ void attn_f32_body(const AttnArgs a, int bx, int by, 
     const float* st = reinterpret_cast<const float*>(smem + C::STATS) + row * 2;
     float m_all = st[0];
 #pragma unroll
-    for (int g = 1; g < KG; ++g) m_all = fmaxf(m_all, st[g * 64]);  // the first group has an unmasked key in every row
+    for (int g = 1; g < KG; ++g) m_all = fmaxf(m_all, st[g * 64]);
+    const float m_use = m_all == -INFINITY ? 0.f : m_all;  // no mass in any group: every score is -inf
     float den = 0.f;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int g = 0; g < KG; ++g) {
-      const float w = __builtin_amdgcn_exp2f(st[g * 64] - m_all);
+      const float w = __builtin_amdgcn_exp2f(st[g * 64] - m_use);
       const f32x4 x = *reinterpret_cast<const f32x4*>(smem + (g * 32 + row) * C::ROW + c4 * 16);
       den = fmaf(st[g * 64 + 1], w, den);
 #pragma unroll

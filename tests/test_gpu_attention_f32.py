@@ -30,3 +30,16 @@ def test_query(d, hq, hkv, lq, m):
 ])
 def test_both_in_one_call(d, hq, hkv, lq, m):
     E.test_both_attentions_in_one_call("f32", d, hq, hkv, lq, m)
+
+
+@pytest.mark.parametrize("d,m", [(64, 5), (128, 100), (128, 200)])
+def test_row_without_mass(d, m):
+    """Every score of the row is -inf (a product beyond float32): its log-sum-exp is -inf, whichever waves hold keys."""
+    import torch
+    from paper_2508_11661_amd import samkv as S
+    q, k, v = E._data(d, "f32", 1, 1, 1, m, d)
+    q[..., 0], k[..., 0] = 4.0, -2.0 ** 127
+    out, lse = torch.zeros((1, 1, d), device="cuda"), torch.zeros((1, 1), device="cuda")
+    ws = torch.empty((S.samkv_workspace_bytes(1, 1, 1, d, 1, m),), dtype=torch.uint8, device="cuda")
+    S.samkv_query_attn(E.H.to_dev(q, "f32"), E.H.to_dev(k, "f32"), E.H.to_dev(v, "f32"), d ** -0.5, out, lse, ws)
+    assert torch.isneginf(lse).all()
