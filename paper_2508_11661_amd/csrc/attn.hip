@@ -709,7 +709,9 @@ __global__ __launch_bounds__(512, (2 * DmaCfg<D, KG>::WGS)) void k_attn_bf16_dma
 
 // out = sum_s w_s * part_o[s] with w_s = exp(lse_s - lse), lse = log sum_s exp(lse_s).  d/4 threads per row, four
 // channels each; with many chunks, S groups of them share a row: group g takes the chunks g, g + S, ..., eight requested
-// at a time, and the groups meet in LDS.  Every order is fixed, so the result is deterministic.
+// at a time, and the groups meet in LDS.  Every order is fixed, so the result is deterministic.  A chunk without mass
+// (lse = -inf: every score -inf, outputs 0 / 0) and a request past the last chunk are left out and not multiplied by a
+// weight of zero, which would turn infinite or undefined outputs into NaN.
 // One thread walking all chunks of its channels spends a memory round trip on each: 35 us for 64 rows x 64 chunks, 6 us
 // with S = 8.  Few chunks take fewer groups: eight of them for 9 chunks request mostly the same words (8128 rows x 9
 // chunks, whole query call with its own keys: 86 us with S = 8, 72 with S = 2).
@@ -740,16 +742,18 @@ __global__ __launch_bounds__(256) void k_attn_merge(AttnArgs a, int d) {
       if (s0 + u * S >= a.n_split) l[u] = -INFINITY;
       m_new = fmaxf(m_new, l[u]);
     }
-    const float w0 = expf(mx - m_new);
+    const float m_use = m_new == -INFINITY ? 0.f : m_new;
+    const float w0 = expf(mx - m_use);
     den *= w0;
 #pragma unroll
     for (int e = 0; e < 4; ++e) acc[e] *= w0;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const float w = expf(l[u] - m_new);
+      const bool counts = l[u] != -INFINITY;
+      const float w = counts ? expf(l[u] - m_use) : 0.f;
       den += w;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) acc[e] = fmaf(w, x[u][e], acc[e]);
+      for (int e = 0; e < 4; ++e) acc[e] = counts ? fmaf(w, x[u][e], acc[e]) : acc[e];
     }
     mx = m_new;
   }
@@ -762,13 +766,14 @@ __global__ __launch_bounds__(256) void k_attn_merge(AttnArgs a, int d) {
     float m_all = mx;
 #pragma unroll
     for (int g = 1; g < S; ++g) m_all = fmaxf(m_all, s_mx[threadIdx.x + g * tpr]);
-    const float w0 = expf(mx - m_all);
+    const float m_use = m_all == -INFINITY ? 0.f : m_all;
+    const float w0 = expf(mx - m_use);
     den *= w0;
 #pragma unroll
     for (int e = 0; e < 4; ++e) acc[e] *= w0;
 #pragma unroll
     for (int g = 1; g < S; ++g) {
-      const float w = expf(s_mx[threadIdx.x + g * tpr] - m_all);
+      const float w = expf(s_mx[threadIdx.x + g * tpr] - m_use);
       const f32x4 x = s_acc[threadIdx.x + g * tpr];
       den = fmaf(w, s_den[threadIdx.x + g * tpr], den);
 #pragma unroll
