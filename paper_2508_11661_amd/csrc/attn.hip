@@ -445,7 +445,7 @@ __device__ __forceinline__ void attn_bf16_dma_body(const AttnArgs a, int bx, int
   auto lift = [&](float mx) {
     if (__any(mx > m_ref + TAU)) {
       const float m_new = fmaxf(m_ref, mx);
-      const float al = __builtin_amdgcn_exp2f(m_ref - m_new);
+      const float al = __builtin_amdgcn_exp2f(m_ref - (m_new == -INFINITY ? 0.f : m_new));  // a row still without mass: 0, not NaN
       l_run *= al;
 #pragma unroll
       for (int i = 0; i < NV; ++i)

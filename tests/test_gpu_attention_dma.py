@@ -36,3 +36,24 @@ def test_query(d, hq, hkv, lq, m):
                                            (64, 8, 2, 3, 321), (128, 8, 2, 40, 130), (128, 8, 2, 1, 1), (64, 8, 2, 70, 65)])
 def test_both_in_one_call(d, hq, hkv, lq, m):
     E.test_both_attentions_in_one_call("bf16", d, hq, hkv, lq, m)
+
+
+@pytest.mark.parametrize("d,hq,hkv,m", [(128, 8, 2, 400), (64, 8, 2, 400), (128, 64, 8, 1600), (64, 256, 8, 1200)])
+def test_rows_without_mass_in_the_first_tile(d, hq, hkv, m):
+    """Odd rows have only scores of -inf (products beyond float32) in the first 64 keys, even rows of the same wave do not:
+    from key 64 on the odd rows are ordinary ones."""
+    import numpy as np
+    import torch
+    from paper_2508_11661_amd import samkv as S
+    q, k, v = E._data(m, "bf16", hq, hkv, m, m, d)
+    q[:, ::2, 0], q[:, 1::2, 0] = 0.0, 4.0
+    k[..., 0] = 0.0
+    k[:, :64, 0] = np.float32(-2.0 ** 127)
+    out, lse = torch.full((hq, m, d), float("nan"), device="cuda"), torch.full((hq, m), float("nan"), device="cuda")
+    ws = torch.empty((S.samkv_workspace_bytes(1, hq, hkv, d, 1, m),), dtype=torch.uint8, device="cuda")
+    S.samkv_recompute_attn(E.H.to_dev(q, "bf16"), E.H.to_dev(k, "bf16"), E.H.to_dev(v, "bf16"), d ** -0.5, out, lse, ws)
+    rows = np.array([0, 30, 62, 64, 65, 67, 95, 96, 127, 128, 129, 200, 321, 399, m - 2, m - 1])
+    for h in (0, hq // 2 + 1, hq - 1):
+        g = h // (hq // hkv)
+        o_ref, l_ref = E.O.attention(q[h:h + 1], k[g:g + 1], v[g:g + 1], d ** -0.5, True, rows=rows)
+        E.H.check_attention(out[h:h + 1, rows].cpu().numpy(), lse[h:h + 1, rows].cpu().numpy(), o_ref, l_ref, "bf16", f"head {h}")
