@@ -154,6 +154,7 @@ hipError_t launch_attn_f32(const AttnLaunch& a, hipStream_t s);
 // is one, stays a launch of its own).
 hipError_t launch_attn_f32_pair(const AttnLaunch& causal, const AttnLaunch& query, hipStream_t s);
 hipError_t attn_f32_raise_limits();  // part of attn_prepare_device
+constexpr int kMaxParts = 64;  // partial results that one merge takes: key chunks and, for query_attn_self, the own keys
 hipError_t launch_attn_merge(const AttnLaunch& a, hipStream_t s);
 
 // Half-precision copy of a bf16 V tensor [n_kv][m][d] for the attention kernels, one power-of-two scale per KV head.

@@ -112,8 +112,8 @@ ScoreWs score_ws(int n_ctx, int hq, int hkv, int d) {
 
 // Not-causal attention: cut the keys into chunks when the row tiles alone cannot fill the chip.
 struct SplitPlan { int n_split, chunk; size_t part_o, part_lse, bytes; };
-// `own`: one more part, the query tokens' own keys, follows in the same launch (attn_self_in_kernel).
-SplitPlan plan_splits(int dtype, int n_batch, int rows, int m, int d, bool own = false) {
+// `own_part`: one more part, the query tokens' own keys, follows; `own`: in the same launch (attn_self_in_kernel).
+SplitPlan plan_splits(int dtype, int n_batch, int rows, int m, int d, bool own_part = false, bool own = false) {
   const int bq = dtype != SAMKV_BF16 ? 32 : own ? 128 : attn_bf16_rows(0, n_batch, rows, d);
   const int bk = dtype == SAMKV_BF16 ? 64 : 128;
   const long long base = (long long)((rows + bq - 1) / bq) * n_batch;
@@ -123,7 +123,8 @@ SplitPlan plan_splits(int dtype, int n_batch, int rows, int m, int d, bool own =
   const int wg_target = bq == 256 && d == 128 ? 256 : 512;
   long long want = (wg_target + base - 1) / base;
   if (own) want -= 1;
-  if (want > 64) want = 64;
+  const int most = kMaxParts - (own_part ? 1 : 0);
+  if (want > most) want = most;
   if (want < 1) want = 1;
   int tiles_per = (int)((key_tiles + want - 1) / want);
   if (tiles_per * bk < 256) tiles_per = 256 / bk;  // a shorter chunk costs more in the merge than it gains
@@ -188,7 +189,7 @@ SelfWs self_ws(int hq, int hkv, int d, int n_q_tok, int m_total, int dtype) {
   const size_t n_rows = (size_t)hq * n_q_tok;
   const int rows = (hq / hkv) * n_q_tok;
   const bool in_kernel = attn_self_in_kernel(dtype, hkv, rows, m_total, d);
-  w.split = plan_splits(dtype, hkv, rows, m_total, d, in_kernel);
+  w.split = plan_splits(dtype, hkv, rows, m_total, d, true, in_kernel);
   const size_t parts = w.split.n_split + 1;
   w.part_o = 0;
   w.part_lse = align_up(parts * n_rows * d * 4);

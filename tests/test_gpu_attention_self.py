@@ -1,6 +1,7 @@
 """Query attention with the query tokens' own keys where its parts change shape: one token, own keys around one and two
 64-key tiles, a row tile of 128 that cuts a head's tokens, one key in the cache, one chunk and several with and without a
-ragged last one, 512 rows per KV head and more, and the sizes beyond which the own keys run as a launch of their own."""
+ragged last one, as many as there can be, 512 rows per KV head and more, and the sizes beyond which the own keys run as a
+launch of their own."""
 import pytest
 
 from tests import test_gpu_attention_edges as E
@@ -13,6 +14,7 @@ pytestmark = pytest.mark.gpu
     ("bf16", 64, 12, 4, 65, 257), ("bf16", 128, 7, 1, 43, 511), ("bf16", 64, 14, 2, 37, 4099), ("bf16", 128, 16, 16, 127, 1000),
     ("bf16", 128, 4, 1, 128, 700), ("bf16", 64, 16, 2, 129, 2050), ("bf16", 128, 4, 4, 600, 333),
     ("bf16", 128, 64, 8, 256, 6100), ("f32", 128, 8, 2, 33, 40), ("f32", 64, 14, 2, 5, 2100),
+    ("bf16", 128, 8, 1, 1, 16384), ("bf16", 64, 4, 2, 1, 20000), ("f32", 128, 8, 1, 1, 16384),  # the most chunks there are
 ])
 def test_parts(dtype, d, hq, hkv, lq, m):
     E.test_query_attention_with_self_tail(dtype, d, hq, hkv, lq, m)
