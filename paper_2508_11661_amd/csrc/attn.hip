@@ -708,16 +708,16 @@ __global__ __launch_bounds__(512, (2 * DmaCfg<D, KG>::WGS)) void k_attn_bf16_dma
 }
 
 // out = sum_s w_s * part_o[s] with w_s = exp(lse_s - lse), lse = log sum_s exp(lse_s).  d/4 threads per row, four
-// channels each; with many chunks, S groups of them share a row: group g takes the chunks g, g + S, ..., eight requested
-// at a time, and the groups meet in LDS.  Every order is fixed, so the result is deterministic.  A chunk without mass
-// (lse = -inf: every score -inf, outputs 0 / 0) and a request past the last chunk are left out and not multiplied by a
-// weight of zero, which would turn infinite or undefined outputs into NaN.
+// channels each; with many chunks, S groups of them share a row: group g takes the chunks g, g + S, ..., all U of them
+// requested at once (S * U chunks at most), and the groups meet in LDS.  Every order is fixed, so the result is
+// deterministic.  A chunk without mass (lse = -inf: every score -inf, outputs 0 / 0) and a request past the last chunk are
+// left out and not multiplied by a weight of zero, which would turn infinite or undefined outputs into NaN.
 // One thread walking all chunks of its channels spends a memory round trip on each: 35 us for 64 rows x 64 chunks, 6 us
-// with S = 8.  Few chunks take fewer groups: eight of them for 9 chunks request mostly the same words (8128 rows x 9
-// chunks, whole query call with its own keys: 86 us with S = 8, 72 with S = 2).
-template <int S>
+// with S = 8.  Few chunks take fewer groups and requests: eight groups for 9 chunks request mostly the same words (8128
+// rows x 9 chunks, whole query call with its own keys: 86 us with S = 8, 72 with S = 2), and so do eight requests for two
+// chunks.
+template <int S, int U>
 __global__ __launch_bounds__(256) void k_attn_merge(AttnArgs a, int d) {
-  constexpr int U = 8;
   __shared__ f32x4 s_acc[256];
   __shared__ float s_mx[256], s_den[256];
   const int tpr = d / 4, c4 = threadIdx.x % tpr;
@@ -725,37 +725,30 @@ __global__ __launch_bounds__(256) void k_attn_merge(AttnArgs a, int d) {
   const size_t n_rows = (size_t)a.n_batch * a.rows;
   const size_t row = (size_t)blockIdx.x * (256 / tpr / S) + slot / S;
   const size_t row_c = row < n_rows ? row : n_rows - 1;
-  float mx = -INFINITY, den = 0.f;
+  float l[U];
+  f32x4 x[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const size_t at = (size_t)min(sg + u * S, a.n_split - 1) * n_rows + row_c;
+    l[u] = a.part_lse[at];
+    x[u] = *reinterpret_cast<const f32x4*>(a.part_o + at * d + c4 * 4);
+  }
+  float mx = -INFINITY;
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    if (sg + u * S >= a.n_split) l[u] = -INFINITY;
+    mx = fmaxf(mx, l[u]);
+  }
+  const float m_use = mx == -INFINITY ? 0.f : mx;
+  float den = 0.f;
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  for (int s0 = sg; s0 < a.n_split; s0 += S * U) {
-    float l[U];
-    f32x4 x[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const size_t at = (size_t)min(s0 + u * S, a.n_split - 1) * n_rows + row_c;
-      l[u] = a.part_lse[at];
-      x[u] = *reinterpret_cast<const f32x4*>(a.part_o + at * d + c4 * 4);
-    }
-    float m_new = mx;
+  for (int u = 0; u < U; ++u) {
+    const bool counts = l[u] != -INFINITY;
+    const float w = counts ? expf(l[u] - m_use) : 0.f;
+    den += w;
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      if (s0 + u * S >= a.n_split) l[u] = -INFINITY;
-      m_new = fmaxf(m_new, l[u]);
-    }
-    const float m_use = m_new == -INFINITY ? 0.f : m_new;
-    const float w0 = expf(mx - m_use);
-    den *= w0;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) acc[e] *= w0;
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const bool counts = l[u] != -INFINITY;
-      const float w = counts ? expf(l[u] - m_use) : 0.f;
-      den += w;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) acc[e] = counts ? fmaf(w, x[u][e], acc[e]) : acc[e];
-    }
-    mx = m_new;
+    for (int e = 0; e < 4; ++e) acc[e] = counts ? fmaf(w, x[u][e], acc[e]) : acc[e];
   }
   if constexpr (S > 1) {
     s_acc[threadIdx.x] = acc;
@@ -915,20 +908,23 @@ hipError_t launch_attn_bf16_pair(const AttnLaunch& causal, const AttnLaunch& que
   return causal.d == 128 ? run_pair_d<128>(causal, q, s) : run_pair_d<64>(causal, q, s);
 }
 
-template <int S>
+template <int S, int U>
 static hipError_t run_merge(const AttnLaunch& l, hipStream_t s) {
   const int rpb = 256 / (l.d / 4) / S;
   const size_t n_rows = (size_t)l.n_batch * l.rows;
-  hipLaunchKernelGGL(k_attn_merge<S>, dim3((unsigned)((n_rows + rpb - 1) / rpb)), dim3(256), 0, s, make_args(l), l.d);
+  hipLaunchKernelGGL((k_attn_merge<S, U>), dim3((unsigned)((n_rows + rpb - 1) / rpb)), dim3(256), 0, s, make_args(l), l.d);
   return hipGetLastError();
 }
 
 hipError_t launch_attn_merge(const AttnLaunch& l, hipStream_t s) {
-  // one batch of eight requests per thread up to 64 chunks, spread over no more groups than that takes
-  if (l.n_split <= 8) return run_merge<1>(l, s);
-  if (l.n_split <= 16) return run_merge<2>(l, s);
-  if (l.n_split <= 32) return run_merge<4>(l, s);
-  return run_merge<8>(l, s);
+  // all chunks in one batch of requests, spread over no more groups of threads and no more requests than that takes
+  if (l.n_split <= 2) return run_merge<1, 2>(l, s);
+  if (l.n_split <= 4) return run_merge<1, 4>(l, s);
+  if (l.n_split <= 8) return run_merge<1, 8>(l, s);
+  if (l.n_split <= 16) return run_merge<2, 8>(l, s);
+  if (l.n_split <= 32) return run_merge<4, 8>(l, s);
+  if (l.n_split <= kMaxParts) return run_merge<8, 8>(l, s);
+  return hipErrorInvalidValue;
 }
 
 }  // namespace samkv

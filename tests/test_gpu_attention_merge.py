@@ -1,5 +1,6 @@
-"""Merge of the query attention's key chunks: 8 chunks (the last count that one thread per four channels walks alone), 9,
-one batch of requests per group (64), a ragged last chunk, fewer rows than a workgroup holds, both head dimensions."""
+"""Merge of the query attention's key chunks on both sides of every count at which it takes more groups of threads or
+requests (2, 4, 8, 16, 32 and 64 chunks), a ragged last chunk, fewer rows than a workgroup holds, both head dimensions;
+chunks with infinite outputs and without mass."""
 import numpy as np
 import pytest
 
@@ -10,6 +11,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("dtype,d,hq,hkv,lq,m", [
     ("bf16", 128, 8, 1, 1, 2048), ("bf16", 128, 8, 1, 1, 2049), ("bf16", 128, 8, 1, 1, 16384), ("bf16", 128, 3, 1, 1, 5000),
+    ("bf16", 128, 8, 1, 1, 512), ("f32", 64, 8, 1, 1, 513), ("bf16", 64, 8, 1, 1, 1024), ("bf16", 128, 8, 1, 1, 1025),
+    ("bf16", 128, 8, 1, 1, 4096), ("f32", 128, 8, 1, 1, 4097), ("bf16", 64, 8, 1, 1, 8192), ("bf16", 128, 8, 1, 1, 8193),
     ("bf16", 64, 8, 2, 3, 2100), ("bf16", 64, 1, 1, 1, 16001), ("f32", 128, 2, 1, 1, 9000), ("f32", 64, 5, 5, 1, 2400),
 ])
 def test_many_key_chunks(dtype, d, hq, hkv, lq, m):
