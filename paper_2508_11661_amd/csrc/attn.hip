@@ -66,13 +66,20 @@ __global__ __launch_bounds__(256, 2) void k_attn_bf16(AttnArgs a) {
   const int split = blockIdx.z;
   const bool own = a.n_self > 0 && split == a.n_split - 1;  // the query tokens' own keys, causally
   const int m = own ? a.n_self : a.m;
+  // own keys: row r belongs to token r % n_self of its head and sees the keys up to it, so nothing past the largest token of
+  // the row tile is walked, and of that a wave skips what lies past its own
+  auto last_token = [&](int first, int n) {  // of the rows first .. first + n - 1
+    const int t0 = first % a.n_self;
+    return min(t0 + n, a.n_self) - 1;  // rows that go on into the next head include that head's largest token
+  };
   const int kv_begin = own ? 0 : split * a.chunk;
-  const int kv_end = own ? m : min(m, kv_begin + a.chunk);
+  const int kv_end = own ? last_token(q0, min(C::BQ, a.rows - q0)) + 1 : min(m, kv_begin + a.chunk);
   const int n_tiles = (kv_end - kv_begin + C::BK - 1) / C::BK;
 
   const int r = q0 + wave * 32 + rw;
   const int r_c = min(r, a.rows - 1);
   const int wave_first = q0 + wave * 32;
+  const int wave_end = own ? last_token(wave_first, 32) + 1 : kv_end;
 
   bf16x8 bq[ND];
   {
@@ -145,8 +152,9 @@ __global__ __launch_bounds__(256, 2) void k_attn_bf16(AttnArgs a) {
     const bool more = tile + 1 < n_tiles;
     if (more) load_tile(tile + 1);
 
-    // a wave whose rows all lie past the last row (ragged last row tile) only helps with the tile traffic
-    const bool active = wave_first < a.rows;
+    // a wave whose rows all lie past the last row (ragged last row tile) or before the tile's keys only helps with the
+    // tile traffic
+    const bool active = wave_first < a.rows && k0 < wave_end;
     if (active) {
       const char* sk = smem + (tile & 1) * C::TILE_BYTES;
       const char* sv = smem + (tile & 1) * C::TILE_BYTES + C::BK * C::KSTR;

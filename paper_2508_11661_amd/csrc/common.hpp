@@ -111,13 +111,19 @@ inline int attn_bf16_rows(int causal, int n_batch, int rows, int d) {
   return (long long)n_batch * ((rows + 255) / 256) >= (d == 128 ? 384 : 1024) ? 256 : 128;
 }
 
-// Whether the attention of query tokens over a cache AND their own keys runs as one launch of the short kernel, the own
-// keys being one more part beside the key chunks: no copy of V for the cache or for the own values, one merge.
+// Whether the attention of query tokens over a cache AND their n_self own keys runs as one launch of the short kernel, the
+// own keys being one more part beside the key chunks: no copy of V for the cache or for the own values, one merge.
 // Problems of 512 rows per KV head and more pay for that with the doubled second product once they are large: one launch
-// against preparation, two attentions and merge, 8 KV heads, d = 128: 512 rows x 3000 keys 31 against 53 us, x 20000
-// 78 / 99, 1016 rows x 7040 61 / 72, x 14000 108 / 104; 1600 rows x 7040 94 / 110; d = 64, 600 rows x 30000 83 / 92.
-inline bool attn_self_in_kernel(int dtype, int n_kv, int rows, int m, int d) {
-  return dtype == SAMKV_BF16 && (rows < 512 || (long long)rows * m * n_kv * d <= 12000000000ll);
+// against preparation, two attentions and merge, 8 KV heads: d = 128, 512 rows x 3000 keys 31 against 53 us, x 20000
+// 78 / 99, 1600 rows of 200 tokens x 7000 95 / 109, 1024 of 128 x 25000 178 / 160; d = 64, 2048 of 256 x 4000 45 / 61,
+// x 25000 198 / 163.  One workgroup per row tile walks the own keys, without chunks, so they count three times (the rule
+// that came closest to the faster side over 600 shapes, within 2.5 % of the slower one where it misses): 8192 rows of 1024
+// tokens x 500 keys, d = 64, 66 / 66, d = 128 104 / 88.  Beyond 1024 own keys that chain is longer than what it saves: 8
+// heads x 4096 tokens, d = 64, x 1500 keys 113 / 97, 6000 rows of 1500 tokens x 100 58 / 55.
+inline bool attn_self_in_kernel(int dtype, int n_kv, int rows, int m, int n_self, int d) {
+  if (dtype != SAMKV_BF16) return false;
+  if (rows < 512) return true;
+  return n_self <= 1024 && (long long)rows * (m + 3ll * n_self) * n_kv * d <= (d == 128 ? 22000000000ll : 12000000000ll);
 }
 
 // One attention problem: `n_batch` independent row blocks, batch b reads KV head b / batch_per_kv.

@@ -112,8 +112,8 @@ ScoreWs score_ws(int n_ctx, int hq, int hkv, int d) {
 
 // Not-causal attention: cut the keys into chunks when the row tiles alone cannot fill the chip.
 struct SplitPlan { int n_split, chunk; size_t part_o, part_lse, bytes; };
-// `own_part`: one more part, the query tokens' own keys, follows; `own`: in the same launch (attn_self_in_kernel).
-SplitPlan plan_splits(int dtype, int n_batch, int rows, int m, int d, bool own_part = false, bool own = false) {
+// `n_own` > 0: one more part, the query tokens' n_own own keys, follows; `own`: in the same launch (attn_self_in_kernel).
+SplitPlan plan_splits(int dtype, int n_batch, int rows, int m, int d, int n_own = 0, bool own = false) {
   const int bq = dtype != SAMKV_BF16 ? 32 : own ? 128 : attn_bf16_rows(0, n_batch, rows, d);
   const int bk = dtype == SAMKV_BF16 ? 64 : 128;
   const long long base = (long long)((rows + bq - 1) / bq) * n_batch;
@@ -122,8 +122,12 @@ SplitPlan plan_splits(int dtype, int n_batch, int rows, int m, int d, bool own_p
   // d = 128, otherwise two; a second round of workgroups only adds partial results to merge
   const int wg_target = bq == 256 && d == 128 ? 256 : 512;
   long long want = (wg_target + base - 1) / base;
-  if (own) want -= 1;
-  const int most = kMaxParts - (own_part ? 1 : 0);
+  // The own keys' workgroups come last.  With one chunk less they are resident beside the others, without they wait for
+  // a free place: one less where longer chunks, m / (want - 1) - m / want keys, cost less than the own keys behind them.
+  // 256 own keys count as many more for a workgroup's start and end (8 heads x 256 tokens, d = 64, 25000 keys: 3 chunks
+  // 237 us, 4 chunks 198; 64 heads x 512 tokens, d = 128, 500 keys: 1 chunk 42, 2 chunks 49).
+  if (own && m < want * (want - 1) * (n_own + 256)) want -= 1;
+  const int most = kMaxParts - (n_own > 0 ? 1 : 0);
   if (want > most) want = most;
   if (want < 1) want = 1;
   int tiles_per = (int)((key_tiles + want - 1) / want);
@@ -188,8 +192,8 @@ SelfWs self_ws(int hq, int hkv, int d, int n_q_tok, int m_total, int dtype) {
   SelfWs w;
   const size_t n_rows = (size_t)hq * n_q_tok;
   const int rows = (hq / hkv) * n_q_tok;
-  const bool in_kernel = attn_self_in_kernel(dtype, hkv, rows, m_total, d);
-  w.split = plan_splits(dtype, hkv, rows, m_total, d, true, in_kernel);
+  const bool in_kernel = attn_self_in_kernel(dtype, hkv, rows, m_total, n_q_tok, d);
+  w.split = plan_splits(dtype, hkv, rows, m_total, d, n_q_tok, in_kernel);
   const size_t parts = w.split.n_split + 1;
   w.part_o = 0;
   w.part_lse = align_up(parts * n_rows * d * 4);
@@ -844,7 +848,7 @@ int samkv_query_attn_self(const void* q_tok, int32_t n_q_tok, const void* k_c, c
   a.part_o = part_o;
   a.part_lse = part_lse;
   hipError_t e;
-  if (attn_self_in_kernel(dtype, n_kv_heads, rows, m_total, head_dim)) {
+  if (attn_self_in_kernel(dtype, n_kv_heads, rows, m_total, n_q_tok, head_dim)) {
     a.n_split = n_cache + 1;
     a.n_self = n_q_tok; a.k_self = k_self; a.v_self = v_self;
     e = launch_attn_bf16(a, s);
