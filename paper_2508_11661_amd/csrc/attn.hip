@@ -12,15 +12,14 @@
 //   O^T += V^T P^T  A = V^T read from the row-major V tile in LDS with the transposing LDS read
 //                 (ds_read_b64_tr_b16), B = P^T from registers.  bf16 weights would cost 2^-9 of the spread of V per
 //                 output; the kernels get more out of 16-bit operands in different ways:
-// k_attn_bf16_dma (every causal problem, long ones that are not, and both together in one launch): half-precision
-//   products.  The weights keep an 11-bit significand, and V arrives as the scaled half-precision copy of vprep.hip,
-//   whose power-of-two scale the final normalisation undoes.
-// k_attn_bf16 (short problems that are not causal): V as stored and every weight as the sum of TWO bf16 terms
-//   (p = hi + lo, 16 significant bits), which doubles the second product's instructions and needs no copy.  That pays
+// Half-precision products (k_attn_bf16_dma, k_attn_bf16 for causal problems and both problems in one launch): the weights
+//   keep an 11-bit significand, and V arrives as the scaled half-precision copy of vprep.hip, whose power-of-two scale the
+//   final normalisation undoes.
+// Two-term products (k_attn_bf16 for problems that are not causal): V as stored and every weight as the sum of TWO bf16
+//   terms (p = hi + lo, 16 significant bits), which doubles the second product's instructions and needs no copy.  That pays
 //   where the products are not what the kernel waits for and the launches that prepare V would cost more: the query
 //   attention of short and mid-size caches (bound by latency or by HBM; 34 -> 26 us at M = 1540, 54 -> 45 us at
-//   M = 6160 as calls).  Causal problems of the same shapes lose more in the products than the preparation costs
-//   (+10 to +18 % at M = 2304 .. 2816) and keep the copy.
+//   M = 6160 as calls).
 // Float32 caches: attn_f32.hip.
 // Keys can be cut into chunks (not causal only); k_attn_merge combines the per-chunk results with
 // their log-sum-exp.
@@ -33,10 +32,11 @@
 namespace samkv {
 namespace {
 
-// ------------------------------------------------------------------ bf16, short problems that are not causal
-// One workgroup = four waves of 32 query rows each; one (row tile, part) per workgroup, a part being a chunk of the
-// cache's keys or, behind them, the query tokens' own keys with their causal mask.  K/V tiles are double-buffered in LDS; the next tile's global loads
-// are issued before the current tile's math and land in LDS after it, one barrier per tile.
+// ------------------------------------------------------------------ bf16, short problems
+// One workgroup = four waves of 32 query rows each; one (row tile, part) per workgroup, a part being all keys of a causal
+// problem, a chunk of the cache's keys or, behind them, the query tokens' own keys with their causal mask.  K/V tiles are
+// double-buffered in LDS; the next tile's global loads are issued before the current tile's math and land in LDS after it,
+// one barrier per tile.  SPLIT: two-term products.
 template <int D>
 struct Bf16Cfg {
   static constexpr int NW = 4, NT = 64 * NW;
@@ -50,9 +50,10 @@ struct Bf16Cfg {
 
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
-template <int D>
-__global__ __launch_bounds__(256, 2) void k_attn_bf16(AttnArgs a) {
+template <int D, bool CAUSAL, bool SPLIT>
+__device__ __forceinline__ void attn_bf16_body(const AttnArgs a, int bx, int by, int bz, int grid_y) {
   using C = Bf16Cfg<D>;
+  static_assert(!(CAUSAL && SPLIT), "causal problems read the half-precision copy of V");
   constexpr int ND = D / 16;   // k-steps of the S^T product
   constexpr int NV = D / 32;   // 32-row blocks of O^T
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -61,10 +62,10 @@ __global__ __launch_bounds__(256, 2) void k_attn_bf16(AttnArgs a) {
   const int rw = lane & 31, h = lane >> 5;
   // grid = (batch, row tile, key chunk)
   int kvh, batch, qt;
-  map_block(a, false, blockIdx.x, blockIdx.y, gridDim.y, &kvh, &batch, &qt);
+  map_block(a, CAUSAL, bx, by, grid_y, &kvh, &batch, &qt);
   const int q0 = qt * C::BQ;
-  const int split = blockIdx.z;
-  const bool own = a.n_self > 0 && split == a.n_split - 1;  // the query tokens' own keys, causally
+  const int split = bz;
+  const bool own = SPLIT && a.n_self > 0 && split == a.n_split - 1;  // the query tokens' own keys, causally
   const int m = own ? a.n_self : a.m;
   // own keys: row r belongs to token r % n_self of its head and sees the keys up to it, so nothing past the largest token of
   // the row tile is walked, and of that a wave skips what lies past its own
@@ -72,14 +73,16 @@ __global__ __launch_bounds__(256, 2) void k_attn_bf16(AttnArgs a) {
     const int t0 = first % a.n_self;
     return min(t0 + n, a.n_self) - 1;  // rows that go on into the next head include that head's largest token
   };
-  const int kv_begin = own ? 0 : split * a.chunk;
-  const int kv_end = own ? last_token(q0, min(C::BQ, a.rows - q0)) + 1 : min(m, kv_begin + a.chunk);
+  const int kv_begin = CAUSAL || own ? 0 : split * a.chunk;
+  const int kv_end = CAUSAL ? min(m, q0 + C::BQ)
+                     : own  ? last_token(q0, min(C::BQ, a.rows - q0)) + 1
+                            : min(m, kv_begin + a.chunk);
   const int n_tiles = (kv_end - kv_begin + C::BK - 1) / C::BK;
 
   const int r = q0 + wave * 32 + rw;
   const int r_c = min(r, a.rows - 1);
   const int wave_first = q0 + wave * 32;
-  const int wave_end = own ? last_token(wave_first, 32) + 1 : kv_end;
+  const int wave_end = CAUSAL ? wave_first + 32 : own ? last_token(wave_first, 32) + 1 : kv_end;  // no row of the wave sees more
 
   bf16x8 bq[ND];
   {
@@ -130,7 +133,8 @@ __global__ __launch_bounds__(256, 2) void k_attn_bf16(AttnArgs a) {
     }
   };
 
-  const int key_end = own ? r % a.n_self + 1 : kv_end;  // one past the last key that counts for this lane's row
+  // one past the last key that counts for this lane's row
+  const int key_end = CAUSAL ? min(kv_end, r + 1) : own ? r % a.n_self + 1 : kv_end;
 
   f32x16 o[NV];
 #pragma unroll
@@ -179,7 +183,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_bf16(AttnArgs a) {
         }
       }
       // accumulator register j of block kb holds key k0 + kb*32 + 8*(j/4) + 4*h + (j%4) for row r
-      if (own || k0 + C::BK > kv_end) {
+      if (own || (CAUSAL && k0 + C::BK - 1 > wave_first) || k0 + C::BK > kv_end) {
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
@@ -202,9 +206,13 @@ __global__ __launch_bounds__(256, 2) void k_attn_bf16(AttnArgs a) {
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
         for (int j = 0; j < 16; ++j) s[kb][j] = __builtin_amdgcn_exp2f(fmaf(s[kb][j], c2, -m_use));
-      // hi = bf16(p), lo = bf16(p - hi); hi + lo is p to 2^-17, and the row sum is the plain float32 sum of p
+      // Two-term weights: hi = bf16(p), lo = bf16(p - hi); hi + lo is p to 2^-17, and the row sum is the plain float32 sum
+      // of p.  Half-precision weights: the row sum is taken over the rounded weights (pair . (1, 1) accumulated in
+      // float32), so numerator and denominator see the same ones.
+      f16x8 bp[2][2];
       bf16x8 bhi[2][2], blo[2][2];
       float psum = 0.f;
+      const f16x2 ones = {(_Float16)1.0f, (_Float16)1.0f};
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
@@ -212,13 +220,20 @@ __global__ __launch_bounds__(256, 2) void k_attn_bf16(AttnArgs a) {
 #pragma unroll
           for (int e = 0; e < 8; e += 2) {
             const float p0 = s[kb][8 * s2 + e], p1 = s[kb][8 * s2 + e + 1];
-            const bf16x2 hi = {(__bf16)p0, (__bf16)p1};
-            const bf16x2 lo = {(__bf16)(p0 - (float)hi[0]), (__bf16)(p1 - (float)hi[1])};
-            bhi[kb][s2][e] = hi[0];
-            bhi[kb][s2][e + 1] = hi[1];
-            blo[kb][s2][e] = lo[0];
-            blo[kb][s2][e + 1] = lo[1];
-            psum += p0 + p1;
+            if constexpr (SPLIT) {
+              const bf16x2 hi = {(__bf16)p0, (__bf16)p1};
+              const bf16x2 lo = {(__bf16)(p0 - (float)hi[0]), (__bf16)(p1 - (float)hi[1])};
+              bhi[kb][s2][e] = hi[0];
+              bhi[kb][s2][e + 1] = hi[1];
+              blo[kb][s2][e] = lo[0];
+              blo[kb][s2][e + 1] = lo[1];
+              psum += p0 + p1;
+            } else {
+              const f16x2 pr = {(_Float16)p0, (_Float16)p1};
+              bp[kb][s2][e] = pr[0];
+              bp[kb][s2][e + 1] = pr[1];
+              psum = __builtin_amdgcn_fdot2(pr, ones, psum, false);
+            }
           }
       l_run = fmaf(l_run, alpha, psum);
       if (__any(alpha != 1.f)) {
@@ -238,11 +253,15 @@ __global__ __launch_bounds__(256, 2) void k_attn_bf16(AttnArgs a) {
             const char* vp = sv + key1 * C::VSTR + (dvb * 32 + q2 * 16 + 4 * (i16 & 3)) * 2;
             const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(vp));
             const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(vp + 8 * C::VSTR));
-            union { struct { s16x4 lo, hi; } s; bf16x8 b; } av;
+            union { struct { s16x4 lo, hi; } s; f16x8 v; bf16x8 b; } av;
             av.s.lo = lo;
             av.s.hi = hi;
-            o[dvb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av.b, bhi[kb][s2], o[dvb], 0, 0, 0);
-            o[dvb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av.b, blo[kb][s2], o[dvb], 0, 0, 0);
+            if constexpr (SPLIT) {
+              o[dvb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av.b, bhi[kb][s2], o[dvb], 0, 0, 0);
+              o[dvb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av.b, blo[kb][s2], o[dvb], 0, 0, 0);
+            } else {
+              o[dvb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(av.v, bp[kb][s2], o[dvb], 0, 0, 0);
+            }
           }
         }
     }
@@ -251,7 +270,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_bf16(AttnArgs a) {
   }
 
   const float l_tot = sum_across_halves(l_run);
-  const float inv = 1.f / l_tot;
+  const float inv = (SPLIT ? 1.f : a.v_unscale[kvh]) / l_tot;
   const size_t row0 = (size_t)batch * a.rows + wave_first;
   float* op0;
   float* lp0;
@@ -269,6 +288,24 @@ __global__ __launch_bounds__(256, 2) void k_attn_bf16(AttnArgs a) {
   static_assert(C::NW * TURN <= C::LDS_BYTES, "the rows are turned in the tile buffers");
   store_rows_via_lds<D>(o, inv, op0, a.rows - wave_first, smem + wave * TURN, lane);
   if (r < a.rows && h == 0) lp0[rw] = (m_run + __log2f(l_tot)) * kLn2;
+}
+
+template <int D, bool CAUSAL>
+__global__ __launch_bounds__(256, 2) void k_attn_bf16(AttnArgs a) {
+  attn_bf16_body<D, CAUSAL, !CAUSAL>(a, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.y);
+}
+
+// Both attentions in one launch, see k_attn_bf16_dma_pair; the query attention reads the copy of V as well.
+template <int D>
+__global__ __launch_bounds__(256, 2) void k_attn_bf16_pair(AttnArgs ac, AttnArgs aq, PairGrid g) {
+  const int bid = blockIdx.x;
+  if (bid < g.n_q_pad) {
+    if (bid >= g.n_q) return;
+    attn_bf16_body<D, false, false>(aq, bid % g.q_gx, bid / g.q_gx, 0, g.q_gy);
+  } else {
+    const int l = bid - g.n_q_pad;
+    attn_bf16_body<D, true, false>(ac, l % g.c_gx, l / g.c_gx, 0, g.c_gy);
+  }
 }
 
 // --------------------------------------------------------------- bf16, asynchronous tile loads (LDS DMA)
@@ -792,8 +829,13 @@ __global__ __launch_bounds__(256) void k_attn_merge(AttnArgs a, int d) {
 
 template <int D>
 hipError_t raise_lds_limit() {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attn_bf16<D>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                             Bf16Cfg<D>::LDS_BYTES);
+  const void* all[] = {reinterpret_cast<const void*>(&k_attn_bf16<D, true>), reinterpret_cast<const void*>(&k_attn_bf16<D, false>),
+                       reinterpret_cast<const void*>(&k_attn_bf16_pair<D>)};
+  for (const void* f : all) {
+    const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, Bf16Cfg<D>::LDS_BYTES);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 template <int D, int KG>
@@ -809,12 +851,12 @@ hipError_t raise_lds_limit_dma() {
   return hipSuccess;
 }
 
-template <int D>
+template <int D, bool CAUSAL>
 hipError_t run_bf16(const AttnLaunch& l, hipStream_t s) {
   using C = Bf16Cfg<D>;
   AttnArgs a = make_args(l);
   dim3 grid = attn_grid(&a, (l.rows + C::BQ - 1) / C::BQ);
-  hipLaunchKernelGGL(k_attn_bf16<D>, grid, dim3(C::NT), C::LDS_BYTES, s, a);
+  hipLaunchKernelGGL((k_attn_bf16<D, CAUSAL>), grid, dim3(C::NT), C::LDS_BYTES, s, a);
   return hipGetLastError();
 }
 
@@ -827,20 +869,19 @@ hipError_t run_bf16_dma(const AttnLaunch& l, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Which bf16 kernel serves a problem: asynchronous loads with one or two key groups, or the register-staged kernel.
-enum class Shape { kDma, kDmaKeys2, kStaged };
-Shape bf16_shape(const AttnLaunch& l) {
-  if (l.n_self > 0) return Shape::kStaged;
-  if (attn_bf16_rows(l.causal, l.n_batch, l.rows, l.d) == 256) return Shape::kDma;
-  return l.causal ? Shape::kDmaKeys2 : Shape::kStaged;
+AttnShape bf16_shape(const AttnLaunch& l) {
+  return l.n_self > 0 ? AttnShape::kStaged : attn_bf16_shape(l.causal, l.n_batch, l.rows, l.d);
 }
 
 template <int D, bool CAUSAL>
 hipError_t run_bf16_d(const AttnLaunch& l, hipStream_t s) {
   if (attn_bf16_reads_v16(l) != (l.v_unscale != nullptr)) return hipErrorInvalidValue;  // V prepared iff the shape reads the copy
-  if (bf16_shape(l) == Shape::kDma) return run_bf16_dma<D, 1, CAUSAL>(l, s);
-  if constexpr (CAUSAL) return run_bf16_dma<D, 2, true>(l, s);
-  return run_bf16<D>(l, s);
+  const AttnShape shape = bf16_shape(l);
+  if (shape == AttnShape::kDma) return run_bf16_dma<D, 1, CAUSAL>(l, s);
+  if constexpr (CAUSAL) {
+    if (shape == AttnShape::kDmaKeys2) return run_bf16_dma<D, 2, true>(l, s);
+  }
+  return run_bf16<D, CAUSAL>(l, s);
 }
 
 // Pair launch: the query problem takes the causal problem's kernel shape and walks all keys in one chunk.
@@ -867,8 +908,23 @@ hipError_t run_pair_dma(const AttnLaunch& c, const AttnLaunch& q, hipStream_t s)
 }
 
 template <int D>
+hipError_t run_pair_staged(const AttnLaunch& c, const AttnLaunch& q, hipStream_t s) {
+  using C = Bf16Cfg<D>;
+  AttnArgs ac = make_args(c), aq = make_args(q);
+  PairGrid g;
+  unsigned total;
+  if (!pair_grid(&ac, &aq, C::BQ, &g, &total)) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_attn_bf16_pair<D>, dim3(total), dim3(C::NT), C::LDS_BYTES, s, ac, aq, g);
+  return hipGetLastError();
+}
+
+template <int D>
 hipError_t run_pair_d(const AttnLaunch& c, const AttnLaunch& q, hipStream_t s) {
-  return bf16_shape(c) == Shape::kDma ? run_pair_dma<D, 1>(c, q, s) : run_pair_dma<D, 2>(c, q, s);
+  switch (bf16_shape(c)) {
+    case AttnShape::kDma: return run_pair_dma<D, 1>(c, q, s);
+    case AttnShape::kDmaKeys2: return run_pair_dma<D, 2>(c, q, s);
+    default: return run_pair_staged<D>(c, q, s);
+  }
 }
 
 }  // namespace
@@ -895,7 +951,7 @@ hipError_t attn_prepare_device() {
   return hipSuccess;
 }
 
-bool attn_bf16_reads_v16(const AttnLaunch& l) { return bf16_shape(l) != Shape::kStaged; }
+bool attn_bf16_reads_v16(const AttnLaunch& l) { return l.causal || bf16_shape(l) != AttnShape::kStaged; }
 
 hipError_t launch_attn_bf16(const AttnLaunch& l, hipStream_t s) {
   const hipError_t e = attn_prepare_device();

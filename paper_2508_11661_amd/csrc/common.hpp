@@ -96,19 +96,26 @@ hipError_t launch_score_select(const ScoreLaunch& a, const SelectLaunch& sl, con
 hipError_t launch_gather_q(const GatherLaunch& a, const PtrTable& q, const IntTable& cu_len, const IntTable& cu_k,
                            int hq, hipStream_t s);
 
-// Rows per workgroup of the bf16 attention kernels: 256 (eight waves, one key stream for all of them) or 128.
-// Causal: 128-row workgroups split the keys between two groups of waves, which halves the chain of steps of the longest
-// row tile and makes twice as many workgroups, but reads each tile for half as many rows.  That wins until the 256-row
-// tiles are about 1.5 per compute unit at d = 128 (32 heads, pair calls, 128 against 256 rows: 2800 rows 92 against 96 us,
-// 3100 rows 110 against 100) and two per resident workgroup, of which a compute unit holds two, at d = 64 (24 heads x
-// 3900 rows 77 against 92, x 6450 rows 163 against 174, 32 heads x 9000 rows 382 against 378, 512 x 500 54 against 51).
-// Up to 512 rows the chain is short anyway, and with 128 heads and more there are workgroups enough: 128 heads x 140 rows 17.0
-// against 20.5 us, x 300 rows 21.9 / 27.0, 256 x 140 25.5 / 29.1; d = 64, 512 x 140 21.5 / 26.0 (64 heads: x 300 20.9 / 18.0).
-// Not causal: 256 from two such tiles per KV head on (measured at 256 / 512 / 1024 rows).
-inline int attn_bf16_rows(int causal, int n_batch, int rows, int d) {
-  if (!causal) return rows >= 512 ? 256 : 128;
-  if (rows <= 512 && n_batch >= 128) return 256;
-  return (long long)n_batch * ((rows + 255) / 256) >= (d == 128 ? 384 : 1024) ? 256 : 128;
+// Which bf16 attention kernel serves a problem: kDma, asynchronous loads, 256 rows per workgroup (eight waves, one key
+// stream for all of them); kDmaKeys2, the same with 128 rows, whose keys two groups of waves share; kStaged, four waves,
+// 128 rows, register-staged loads, two workgroups per compute unit.
+// Causal: two key groups halve the chain of steps of the longest row tile and make twice as many workgroups, but read each
+// tile for half as many rows.  That wins until the 256-row tiles are about 1.5 per compute unit at d = 128 (32 heads, pair
+// calls, kDmaKeys2 against kDma: 2800 rows 92 against 96 us, 3100 rows 110 against 100) and two per resident workgroup, of
+// which a compute unit holds two, at d = 64 (24 heads x 3900 rows 77 against 92, x 6450 rows 163 against 174, 32 heads x
+// 9000 rows 382 against 378, 512 x 500 54 against 51).
+// Few rows are start and end of workgroups rather than steps, and most waves of an eight-wave workgroup hold no row: kStaged
+// up to 320 rows (device time of pair calls, kDma / kDmaKeys2 / kStaged: 32 heads x 40 rows 11.1 / 12.0 / 10.1 us, x 140
+// 15.3 / 14.8 / 13.9, x 300 19.9 / 16.8 / 16.9, x 330 21.1 / 17.1 / 18.5; 256 heads x 40 16.9 / 18.3 / 12.3, x 128 22.9 /
+// 23.5 / 17.9; d = 64, 32 heads x 300 16.2 / 13.9 / 13.2, x 460 19.7 / 15.5 / 16.1) and, where the heads fill the chip, up to
+// 512 (128 heads x 400 29.1 / 31.6 / 27.4, 256 x 460 51.3 / 54.6 / 46.7, 128 x 700 48.3 / 48.1 / 48.3; d = 64, 256 x 400
+// 29.5 / 31.1 / 28.5).
+// Not causal: kDma from two 256-row tiles per KV head on (measured at 256 / 512 / 1024 rows).
+enum class AttnShape { kDma, kDmaKeys2, kStaged };
+inline AttnShape attn_bf16_shape(int causal, int n_batch, int rows, int d) {
+  if (!causal) return rows >= 512 ? AttnShape::kDma : AttnShape::kStaged;
+  if (rows <= 320 || (rows <= 512 && n_batch >= 128)) return AttnShape::kStaged;
+  return (long long)n_batch * ((rows + 255) / 256) >= (d == 128 ? 384 : 1024) ? AttnShape::kDma : AttnShape::kDmaKeys2;
 }
 
 // Whether the attention of query tokens over a cache AND their n_self own keys runs as one launch of the short kernel, the
@@ -148,9 +155,8 @@ struct AttnLaunch {
   const void* v_self;
 };
 hipError_t launch_attn_bf16(const AttnLaunch& a, hipStream_t s);
-// Whether the bf16 kernel that serves this problem reads the scaled half-precision copy of V (every causal problem,
-// long problems that are not causal) or V as stored (short problems that are not causal).  A pair
-// launch always reads the copy.
+// Whether the bf16 kernel that serves this problem reads the scaled half-precision copy of V (every causal problem, long
+// problems that are not causal) or V as stored (short problems that are not causal).  A pair launch always reads the copy.
 bool attn_bf16_reads_v16(const AttnLaunch& a);
 // Both bf16 attentions of the path in one launch: `causal` and `query` share d, K and the prepared V; the query
 // attention runs without key chunks whatever `query` says (its n_split, chunk and partial buffers are ignored).

@@ -1,7 +1,8 @@
-"""The asynchronous-load attention kernels where their tiling can go wrong: row counts around the remainder that sets
-where the causal row tiles start (0, 1, 63 .. 65, 192 .. 255 rows beyond a multiple of 256), one to four key tiles,
-one and two key groups, both head dimensions, the pair launch, and query problems of 256-row tiles with and without
-key chunks."""
+"""The bf16 attention kernels where their tiling can go wrong.  Asynchronous loads: row counts around the remainder that
+sets where the causal row tiles start (0, 1, 63 .. 65, 192 .. 255 rows beyond a multiple of 256), two key groups at
+remainders of 128, both head dimensions, the pair launch, and query problems of 256-row tiles with and without key chunks.
+Register-staged loads: one to four key tiles, remainders of 128, many heads, and the row counts at which one kernel gives
+way to the other (320, and 512 with 128 heads)."""
 import pytest
 
 from tests import test_gpu_attention_edges as E
@@ -16,7 +17,12 @@ pytestmark = pytest.mark.gpu
     (128, 384, 8, 192), (128, 384, 8, 193), (128, 192, 8, 257), (128, 192, 8, 320), (128, 195, 5, 321),
     (128, 48, 8, 2049), (128, 48, 8, 2303), (64, 80, 8, 3329), (64, 512, 8, 257),
     (128, 128, 8, 140), (64, 130, 10, 300), (128, 136, 8, 512), (128, 127, 127, 300),  # many heads, few rows
-    # two key groups: one key, one and both groups' first tiles, remainders of 128
+    (128, 128, 8, 513), (64, 130, 10, 512), (64, 130, 10, 513), (128, 127, 127, 512),
+    # two key groups: from 321 rows on, remainders of 128, both groups' first tiles
+    (128, 8, 2, 321), (128, 7, 1, 384), (64, 8, 2, 321), (64, 7, 1, 384), (128, 5, 5, 449), (64, 8, 8, 512), (128, 2, 2, 640),
+    (64, 127, 127, 513), (128, 6, 2, 767), (64, 4, 4, 895),
+    # four waves: one key, tiles of one and two key tiles, remainders of 128, the last row count
+    (128, 8, 2, 320), (64, 8, 2, 320),
     (128, 8, 2, 1), (128, 8, 2, 32), (128, 8, 2, 33), (128, 7, 1, 64), (128, 8, 2, 65), (128, 6, 2, 127), (128, 8, 8, 128),
     (128, 8, 2, 129), (128, 5, 5, 192), (128, 8, 2, 193), (128, 8, 2, 256), (128, 4, 2, 257), (128, 8, 2, 1000),
     (64, 8, 2, 1), (64, 8, 2, 64), (64, 8, 2, 65), (64, 7, 1, 129), (64, 8, 2, 193), (64, 8, 2, 385), (64, 16, 2, 1030),
