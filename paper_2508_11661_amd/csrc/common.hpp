@@ -172,7 +172,8 @@ hipError_t launch_attn_merge(const AttnLaunch& a, hipStream_t s);
 // Half-precision copy of a bf16 V tensor [n_kv][m][d] for the attention kernels, one power-of-two scale per KV head.
 // part: [n_kv][v_prep_chunks(n_kv, m)] scratch words; unscale: [n_kv] factors that undo the scale.
 int v_prep_chunks(int n_kv, int m);
-hipError_t launch_v_prep(const void* v, int n_kv, int m, int d, void* v16, uint32_t* part, float* unscale, hipStream_t s);
+hipError_t launch_v_prep(const void* v, int n_kv, int m, int d, bool causal, void* v16, uint32_t* part, float* unscale,
+                         hipStream_t s);
 
 // Raises the dynamic-LDS limit of every attention kernel variant that needs it on the current device (once per device).
 hipError_t attn_prepare_device();

@@ -13,12 +13,15 @@
 // Heads of at most kOneLaunchPieces 16-byte pieces (short compacted caches, where a launch costs more than the work)
 // take ONE launch instead: k_v_prep_small, a few large workgroups per head, each of which finds the head's maximum
 // itself (the head is read from L2 a few times over) and converts its share.
-// Where V fits the eight L2s the heads are the fastest grid dimension: with workgroups handed out round-robin over the
-// XCDs, those of a head (a head count that is a multiple of 8) run on ONE XCD, so its L2 keeps the head from the first pass
-// to the second and the copy for the attention kernels, which walk the head's tiles on the same XCD (pair calls, 32 heads x
-// 1540 rows 45.7 -> 44.3 us, x 4120 rows 167 -> 165).  5 x 24000 ragged tokens at 10 %: both
-// passes 17.0 -> 14.3 us.  Larger tensors are streamed in memory order with non-temporal loads (256 heads x 6160 rows:
-// first pass 62 us, 81 with ordinary loads).
+// Where V fits the eight L2s and the head count is a multiple of 8, the heads are the fastest grid dimension: with
+// workgroups handed out round-robin over the XCDs, those of a head run on ONE XCD, so its L2 keeps the head from the first
+// pass to the second and the copy for the attention kernels, which walk the head's tiles on the same XCD (pair calls, 32
+// heads x 1540 rows 45.7 -> 44.3 us, x 4120 rows 167 -> 165; 5 x 24000 ragged tokens at 10 %: both passes 17.0 -> 14.3 us).
+// Larger tensors are streamed in memory order with non-temporal loads (256 heads x 6160 rows: first pass 62 us, 81 with
+// ordinary loads).  In ONE launch a head that another order would read once comes back once per chunk (127 heads x 2000
+// rows, pair call: 354 us by heads, 282 in memory order), and for problems that are not causal that launch keeps memory
+// order too: their workgroups of one head all start at once, and one L2 alone feeds them (8 KV heads x 1500 keys, 800 rows:
+// 34.5 us by heads, 31.0 in memory order).
 #include "common.hpp"
 
 namespace samkv {
@@ -96,9 +99,9 @@ __global__ __launch_bounds__(NT) void k_v_to_f16(const u32x4* __restrict__ v, co
 constexpr int NT1 = 1024;
 constexpr int kSmallChunk = 2048;   // 16-byte pieces converted per workgroup (32 KB)
 __global__ __launch_bounds__(NT1) void k_v_prep_small(const u32x4* __restrict__ v, u32x4* __restrict__ v16,
-                                                      float* __restrict__ unscale, int total, int per) {
+                                                      float* __restrict__ unscale, int total, int per, bool by_head) {
   __shared__ uint32_t lds[NT1 / 64];
-  const int c = blockIdx.y, g = blockIdx.x;
+  const int c = by_head ? blockIdx.y : blockIdx.x, g = by_head ? blockIdx.x : blockIdx.y;
   const u32x4* src = v + (size_t)g * total;
   uint32_t mx = 0;
   constexpr int U = 16;  // loads in flight per thread: a head of 512 KB is two round trips
@@ -153,18 +156,20 @@ int v_prep_chunks(int n_kv, int m) {
   return n < 1 ? 1 : n;
 }
 
-hipError_t launch_v_prep(const void* v, int n_kv, int m, int d, void* v16, uint32_t* part, float* unscale, hipStream_t s) {
+hipError_t launch_v_prep(const void* v, int n_kv, int m, int d, bool causal, void* v16, uint32_t* part, float* unscale,
+                         hipStream_t s) {
   const long long total = (long long)m * d * 2 / 16;  // 16-byte pieces per head
+  const bool keep = n_kv % 8 == 0 && total * 16 * n_kv <= (24ll << 20);  // of the 32 MB of L2
   if (total <= kOneLaunchPieces) {
     const int c1 = (int)((total + kSmallChunk - 1) / kSmallChunk);
     const int per1 = kSmallChunk;
-    hipLaunchKernelGGL(k_v_prep_small, dim3(n_kv, c1), dim3(NT1), 0, s, static_cast<const u32x4*>(v),
-                       static_cast<u32x4*>(v16), unscale, (int)total, per1);
+    const bool by_head = keep && causal;
+    hipLaunchKernelGGL(k_v_prep_small, by_head ? dim3(n_kv, c1) : dim3(c1, n_kv), dim3(NT1), 0, s,
+                       static_cast<const u32x4*>(v), static_cast<u32x4*>(v16), unscale, (int)total, per1, by_head);
     return hipGetLastError();
   }
   const int n_chunks = v_prep_chunks(n_kv, m);
   const long long per = (total + n_chunks - 1) / n_chunks;
-  const bool keep = total * 16 * n_kv <= (24ll << 20);  // of the 32 MB of L2
   const dim3 grid((unsigned)n_kv * n_chunks);
   if (keep)
     hipLaunchKernelGGL(k_v_absmax<true>, grid, dim3(NT), 0, s, static_cast<const u32x4*>(v), part, total, per, n_kv, n_chunks);

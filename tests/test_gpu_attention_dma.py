@@ -63,3 +63,29 @@ def test_rows_without_mass_in_the_first_tile(d, hq, hkv, m):
         g = h // (hq // hkv)
         o_ref, l_ref = E.O.attention(q[h:h + 1], k[g:g + 1], v[g:g + 1], d ** -0.5, True, rows=rows)
         E.H.check_attention(out[h:h + 1, rows].cpu().numpy(), lse[h:h + 1, rows].cpu().numpy(), o_ref, l_ref, "bf16", f"head {h}")
+
+
+@pytest.mark.parametrize("causal,d,hq,hkv,lq,m", [
+    (True, 128, 16, 16, 0, 700), (True, 128, 9, 9, 0, 700), (True, 64, 8, 8, 0, 3000), (True, 64, 5, 5, 0, 4200),
+    (False, 128, 64, 8, 1300, 300), (False, 128, 56, 7, 1500, 300), (False, 128, 64, 8, 200, 2100), (False, 64, 56, 7, 600, 4200),
+])
+def test_value_scales(causal, d, hq, hkv, lq, m):
+    """The half-precision copy of V in every order in which its preparation walks heads and chunks (one or two launches, a
+    head count that is a multiple of 8 or not, causal or not): heads of very different magnitude, each with its own scale."""
+    import numpy as np
+    import torch
+    from paper_2508_11661_amd import samkv as S
+    rows = m if causal else lq
+    q, k, v = E._data(m + hkv, "bf16", hq, hkv, rows, m, d)
+    mag = np.array([2.0 ** (7 * (g % 5) - 14) for g in range(hkv)], np.float32)
+    v = v * mag[:, None, None]
+    out, lse = torch.full((hq, rows, d), float("nan"), device="cuda"), torch.full((hq, rows), float("nan"), device="cuda")
+    ws = torch.empty((S.samkv_workspace_bytes(1, hq, hkv, d, rows, m),), dtype=torch.uint8, device="cuda")
+    args = (E.H.to_dev(q, "bf16"), E.H.to_dev(k, "bf16"), E.H.to_dev(v, "bf16"), d ** -0.5, out, lse, ws)
+    S.samkv_recompute_attn(*args) if causal else S.samkv_query_attn(*args)
+    pick = np.array([0, 63, 64, rows // 2, rows - 1])
+    for g in range(hkv):
+        h = g * (hq // hkv)
+        o_ref, l_ref = E.O.attention(q[h:h + 1], k[g:g + 1], v[g:g + 1], d ** -0.5, causal, rows=pick)
+        got = out[h:h + 1, pick].cpu().numpy() / mag[g]
+        E.H.check_attention(got, lse[h:h + 1, pick].cpu().numpy(), o_ref / mag[g], l_ref, "bf16", f"KV head {g}")
