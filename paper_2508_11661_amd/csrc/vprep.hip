@@ -13,15 +13,19 @@
 // Heads of at most kOneLaunchPieces 16-byte pieces (short compacted caches, where a launch costs more than the work)
 // take ONE launch instead: k_v_prep_small, a few large workgroups per head, each of which finds the head's maximum
 // itself (the head is read from L2 a few times over) and converts its share.
-// Where V fits the eight L2s and the head count is a multiple of 8, the heads are the fastest grid dimension: with
-// workgroups handed out round-robin over the XCDs, those of a head run on ONE XCD, so its L2 keeps the head from the first
-// pass to the second and the copy for the attention kernels, which walk the head's tiles on the same XCD (pair calls, 32
-// heads x 1540 rows 45.7 -> 44.3 us, x 4120 rows 167 -> 165; 5 x 24000 ragged tokens at 10 %: both passes 17.0 -> 14.3 us).
-// Larger tensors are streamed in memory order with non-temporal loads (256 heads x 6160 rows: first pass 62 us, 81 with
-// ordinary loads).  In ONE launch a head that another order would read once comes back once per chunk (127 heads x 2000
-// rows, pair call: 354 us by heads, 282 in memory order), and for problems that are not causal that launch keeps memory
-// order too: their workgroups of one head all start at once, and one L2 alone feeds them (8 KV heads x 1500 keys, 800 rows:
-// 34.5 us by heads, 31.0 in memory order).
+// Which workgroups work on a head.  With the heads as the fastest grid dimension, and workgroups handed out round-robin over
+// the XCDs, those of a head run on ONE XCD (a head count that is a multiple of 8; on two of them for a multiple of 4), so its
+// L2 keeps the head from one pass to the next and the copy for the attention kernels, which walk the head's tiles on the same
+// XCD.  Otherwise chunks are the fastest dimension: memory order.
+//   Two launches: by heads where V fits the eight L2s (32 heads x 4120 rows, pair call: 167 -> 165 us; 5 x 24000 ragged
+//   tokens at 10 %: both passes 17.0 -> 14.3 us); larger tensors are streamed in memory order with non-temporal loads (256
+//   heads x 6160 rows: first pass 62 us, 81 with ordinary loads).
+//   One launch, whose workgroups all scan their head: by heads up to 56 MB (multiple of 8; causal calls, memory order -> by
+//   heads: 32 heads x 1540 rows, 8 KV heads 43.4 -> 41.9 us, 64 KV heads x 900 rows 63.8 -> 48.3, 128 x 1540 198.7 -> 189.9,
+//   beyond it 256 x 1540, 96 MB, 381 -> 436) or 24 MB (multiple of 4; 28 x 900 34.2 -> 28.7, 100 x 900 82.7 -> 73.7, 100 x
+//   1540, 38 MB, 150 -> 159); other head counts gain nothing and lose where a head is scanned often (127 heads x 2000 rows
+//   269 -> 348).  Problems that are not causal keep memory order: their workgroups of one head all start at once, and one L2
+//   alone feeds them (8 KV heads x 1500 keys, 800 rows: 31.0 us, 34.5 by heads).
 #include "common.hpp"
 
 namespace samkv {
@@ -159,17 +163,18 @@ int v_prep_chunks(int n_kv, int m) {
 hipError_t launch_v_prep(const void* v, int n_kv, int m, int d, bool causal, void* v16, uint32_t* part, float* unscale,
                          hipStream_t s) {
   const long long total = (long long)m * d * 2 / 16;  // 16-byte pieces per head
-  const bool keep = n_kv % 8 == 0 && total * 16 * n_kv <= (24ll << 20);  // of the 32 MB of L2
   if (total <= kOneLaunchPieces) {
     const int c1 = (int)((total + kSmallChunk - 1) / kSmallChunk);
     const int per1 = kSmallChunk;
-    const bool by_head = keep && causal;
+    const long long most = n_kv % 8 == 0 ? 56ll << 20 : n_kv % 4 == 0 ? 24ll << 20 : 0;
+    const bool by_head = causal && total * 16 * n_kv <= most;
     hipLaunchKernelGGL(k_v_prep_small, by_head ? dim3(n_kv, c1) : dim3(c1, n_kv), dim3(NT1), 0, s,
                        static_cast<const u32x4*>(v), static_cast<u32x4*>(v16), unscale, (int)total, per1, by_head);
     return hipGetLastError();
   }
   const int n_chunks = v_prep_chunks(n_kv, m);
   const long long per = (total + n_chunks - 1) / n_chunks;
+  const bool keep = total * 16 * n_kv <= (24ll << 20);  // of the 32 MB of L2
   const dim3 grid((unsigned)n_kv * n_chunks);
   if (keep)
     hipLaunchKernelGGL(k_v_absmax<true>, grid, dim3(NT), 0, s, static_cast<const u32x4*>(v), part, total, per, n_kv, n_chunks);
