@@ -345,11 +345,12 @@ __global__ __launch_bounds__(256, 2) void k_attn_bf16_pair(AttnArgs ac, AttnArgs
 // d = 64: two rows share the 256 bytes that one access cycle covers, so the swizzle goes by the row pair: K chunk c at
 // c ^ ((r >> 1) & 7), V chunk c at c ^ 4 ((r >> 1) & 1).  A wave needs about half the registers and LDS, so two
 // workgroups share a compute unit and overlap each other's products and weights: no software pipeline, whose second
-// set of scores would cost that (128 registers per wave).  What bounds it is the vector ALU: 133 instructions, 32 of
+// set of scores would cost that (128 registers per wave).  Problems of few workgroups with two key groups take one per
+// compute unit and the pipeline instead (32 heads x 1200 rows: 24.7 -> 22.4 us).  What bounds it is the vector ALU: 133 instructions, 32 of
 // them exponentials, per 16 products.  Against the register-staged eight-wave kernel it replaces, whole pair calls: 24
 // heads x 6450 rows 185 -> 180 us, 32 x 4120 113 -> 105, 56 x 9000 689 -> 651, 32 x 20000 (causal call alone)
 // 1768 -> 1695 (0.97 PFLOP/s).
-template <int D, int KG>
+template <int D, int KG, int WGS>  // WGS: workgroups per compute unit
 struct DmaCfg {
   static constexpr int NW = 8, RG = NW / KG, BQ = 32 * RG;   // waves, row groups, rows per workgroup
   static constexpr int BK = 64, BKT = BK * KG;               // keys per wave and per workgroup in a step
@@ -359,15 +360,14 @@ struct DmaCfg {
   static constexpr int MERGE = 64 * (D / 2 + 2) * 4;         // one wave's outputs, maxima and sums
   static constexpr int LDS_BYTES = 2 * NSLOT * TILE;
   static constexpr int NI = TILE / 1024 / NW, RPI = 1024 / ROWB;  // requests per wave and tile, rows per request
-  static constexpr int WGS = D == 128 ? 1 : 2;                    // workgroups per compute unit
   static constexpr bool PIPE = WGS == 1;                          // software pipeline inside a wave (1)
   static __device__ __forceinline__ int kswz(int row) { return D == 128 ? row & 15 : (row >> 1) & 7; }
   static __device__ __forceinline__ int vswz(int row) { return D == 128 ? 4 * (row & 3) : 4 * ((row >> 1) & 1); }
 };
 
-template <int D, int KG, bool CAUSAL>
+template <int D, int KG, int WGS, bool CAUSAL>
 __device__ __forceinline__ void attn_bf16_dma_body(const AttnArgs a, int bx, int by, int bz, int grid_y) {
-  using C = DmaCfg<D, KG>;
+  using C = DmaCfg<D, KG, WGS>;
   constexpr int NW = C::NW, BQ = C::BQ, BK = C::BK, BKT = C::BKT, ROWB = C::ROWB, CPR = C::CPR, NI = C::NI;
   constexpr int ND = D / 16, NV = D / 32;
   constexpr int TILE = C::TILE, NSLOT = C::NSLOT;
@@ -730,9 +730,9 @@ __device__ __forceinline__ void attn_bf16_dma_body(const AttnArgs a, int bx, int
   if (r < a.rows && h == 0) lp0[rw] = (m_ref + __log2f(l_tot)) * kLn2;
 }
 
-template <int D, int KG, bool CAUSAL>
-__global__ __launch_bounds__(512, (2 * DmaCfg<D, KG>::WGS)) void k_attn_bf16_dma(AttnArgs a) {
-  attn_bf16_dma_body<D, KG, CAUSAL>(a, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.y);
+template <int D, int KG, int WGS, bool CAUSAL>
+__global__ __launch_bounds__(512, 2 * WGS) void k_attn_bf16_dma(AttnArgs a) {
+  attn_bf16_dma_body<D, KG, WGS, CAUSAL>(a, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.y);
 }
 
 // Both attentions of the path in ONE launch (same head dimension, same workgroup shape).  The query attention's
@@ -740,15 +740,15 @@ __global__ __launch_bounds__(512, (2 * DmaCfg<D, KG>::WGS)) void k_attn_bf16_dma
 // no merge): such a workgroup lasts as long as the causal problem's longest row tile, which is handed out right
 // behind it, so the query attention hides inside the causal one instead of waiting for it.  n_q_pad, the query
 // workgroups rounded up to a multiple of 8, keeps the causal workgroups on the XCD slots map_block assumes.
-template <int D, int KG>
-__global__ __launch_bounds__(512, (2 * DmaCfg<D, KG>::WGS)) void k_attn_bf16_dma_pair(AttnArgs ac, AttnArgs aq, PairGrid g) {
+template <int D, int KG, int WGS>
+__global__ __launch_bounds__(512, 2 * WGS) void k_attn_bf16_dma_pair(AttnArgs ac, AttnArgs aq, PairGrid g) {
   const int bid = blockIdx.x;
   if (bid < g.n_q_pad) {
     if (bid >= g.n_q) return;
-    attn_bf16_dma_body<D, KG, false>(aq, bid % g.q_gx, bid / g.q_gx, 0, g.q_gy);
+    attn_bf16_dma_body<D, KG, WGS, false>(aq, bid % g.q_gx, bid / g.q_gx, 0, g.q_gy);
   } else {
     const int l = bid - g.n_q_pad;
-    attn_bf16_dma_body<D, KG, true>(ac, l % g.c_gx, l / g.c_gx, 0, g.c_gy);
+    attn_bf16_dma_body<D, KG, WGS, true>(ac, l % g.c_gx, l / g.c_gx, 0, g.c_gy);
   }
 }
 
@@ -838,14 +838,15 @@ hipError_t raise_lds_limit() {
   return hipSuccess;
 }
 
-template <int D, int KG>
+template <int D, int KG, int WGS>
 hipError_t raise_lds_limit_dma() {
-  const void* all[] = {reinterpret_cast<const void*>(&k_attn_bf16_dma<D, KG, true>),
-                       reinterpret_cast<const void*>(&k_attn_bf16_dma_pair<D, KG>),
-                       KG == 1 ? reinterpret_cast<const void*>(&k_attn_bf16_dma<D, 1, false>) : nullptr};
+  const void* query = nullptr;
+  if constexpr (KG == 1) query = reinterpret_cast<const void*>(&k_attn_bf16_dma<D, 1, WGS, false>);
+  const void* all[] = {reinterpret_cast<const void*>(&k_attn_bf16_dma<D, KG, WGS, true>),
+                       reinterpret_cast<const void*>(&k_attn_bf16_dma_pair<D, KG, WGS>), query};
   for (const void* f : all) {
     if (f == nullptr) continue;
-    const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, DmaCfg<D, KG>::LDS_BYTES);
+    const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, DmaCfg<D, KG, WGS>::LDS_BYTES);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
@@ -860,26 +861,28 @@ hipError_t run_bf16(const AttnLaunch& l, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int D, int KG, bool CAUSAL>
+template <int D, int KG, int WGS, bool CAUSAL>
 hipError_t run_bf16_dma(const AttnLaunch& l, hipStream_t s) {
-  using C = DmaCfg<D, KG>;
+  using C = DmaCfg<D, KG, WGS>;
   AttnArgs a = make_args(l);
   dim3 grid = attn_grid(&a, (l.rows + C::BQ - 1) / C::BQ);
-  hipLaunchKernelGGL((k_attn_bf16_dma<D, KG, CAUSAL>), grid, dim3(512), C::LDS_BYTES, s, a);
+  hipLaunchKernelGGL((k_attn_bf16_dma<D, KG, WGS, CAUSAL>), grid, dim3(512), C::LDS_BYTES, s, a);
   return hipGetLastError();
 }
 
 AttnShape bf16_shape(const AttnLaunch& l) {
-  return l.n_self > 0 ? AttnShape::kStaged : attn_bf16_shape(l.causal, l.n_batch, l.rows, l.d);
+  return l.n_self > 0 ? AttnShape::kStaged : attn_bf16_shape(l.causal, l.n_batch, l.batch_per_kv, l.rows, l.d);
 }
 
 template <int D, bool CAUSAL>
 hipError_t run_bf16_d(const AttnLaunch& l, hipStream_t s) {
   if (attn_bf16_reads_v16(l) != (l.v_unscale != nullptr)) return hipErrorInvalidValue;  // V prepared iff the shape reads the copy
+  constexpr int WGS = D == 128 ? 1 : 2;
   const AttnShape shape = bf16_shape(l);
-  if (shape == AttnShape::kDma) return run_bf16_dma<D, 1, CAUSAL>(l, s);
+  if (shape == AttnShape::kDma) return run_bf16_dma<D, 1, WGS, CAUSAL>(l, s);
   if constexpr (CAUSAL) {
-    if (shape == AttnShape::kDmaKeys2) return run_bf16_dma<D, 2, true>(l, s);
+    if (shape == AttnShape::kDmaKeys2) return run_bf16_dma<D, 2, WGS, true>(l, s);
+    if (shape == AttnShape::kDmaKeys2One) return run_bf16_dma<D, 2, 1, true>(l, s);
   }
   return run_bf16<D, CAUSAL>(l, s);
 }
@@ -896,14 +899,14 @@ bool pair_grid(AttnArgs* ac, AttnArgs* aq, int bq, PairGrid* g, unsigned* total)
   return true;
 }
 
-template <int D, int KG>
+template <int D, int KG, int WGS>
 hipError_t run_pair_dma(const AttnLaunch& c, const AttnLaunch& q, hipStream_t s) {
-  using C = DmaCfg<D, KG>;
+  using C = DmaCfg<D, KG, WGS>;
   AttnArgs ac = make_args(c), aq = make_args(q);
   PairGrid g;
   unsigned total;
   if (!pair_grid(&ac, &aq, C::BQ, &g, &total)) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((k_attn_bf16_dma_pair<D, KG>), dim3(total), dim3(512), C::LDS_BYTES, s, ac, aq, g);
+  hipLaunchKernelGGL((k_attn_bf16_dma_pair<D, KG, WGS>), dim3(total), dim3(512), C::LDS_BYTES, s, ac, aq, g);
   return hipGetLastError();
 }
 
@@ -920,9 +923,11 @@ hipError_t run_pair_staged(const AttnLaunch& c, const AttnLaunch& q, hipStream_t
 
 template <int D>
 hipError_t run_pair_d(const AttnLaunch& c, const AttnLaunch& q, hipStream_t s) {
+  constexpr int WGS = D == 128 ? 1 : 2;
   switch (bf16_shape(c)) {
-    case AttnShape::kDma: return run_pair_dma<D, 1>(c, q, s);
-    case AttnShape::kDmaKeys2: return run_pair_dma<D, 2>(c, q, s);
+    case AttnShape::kDma: return run_pair_dma<D, 1, WGS>(c, q, s);
+    case AttnShape::kDmaKeys2: return run_pair_dma<D, 2, WGS>(c, q, s);
+    case AttnShape::kDmaKeys2One: return run_pair_dma<D, 2, 1>(c, q, s);
     default: return run_pair_staged<D>(c, q, s);
   }
 }
@@ -943,8 +948,8 @@ hipError_t attn_prepare_device() {
   std::lock_guard<std::mutex> lock(mu);
   if (done[dev]) return hipSuccess;
   const hipError_t all[] = {
-      raise_lds_limit<128>(), raise_lds_limit<64>(), raise_lds_limit_dma<128, 2>(), raise_lds_limit_dma<64, 2>(),
-      raise_lds_limit_dma<128, 1>(), raise_lds_limit_dma<64, 1>(), attn_f32_raise_limits()};
+      raise_lds_limit<128>(), raise_lds_limit<64>(), raise_lds_limit_dma<128, 2, 1>(), raise_lds_limit_dma<64, 2, 2>(),
+      raise_lds_limit_dma<64, 2, 1>(), raise_lds_limit_dma<128, 1, 1>(), raise_lds_limit_dma<64, 1, 2>(), attn_f32_raise_limits()};
   for (hipError_t x : all)
     if (x != hipSuccess) return x;
   done[dev] = true;

@@ -97,25 +97,41 @@ hipError_t launch_gather_q(const GatherLaunch& a, const PtrTable& q, const IntTa
                            int hq, hipStream_t s);
 
 // Which bf16 attention kernel serves a problem: kDma, asynchronous loads, 256 rows per workgroup (eight waves, one key
-// stream for all of them); kDmaKeys2, the same with 128 rows, whose keys two groups of waves share; kStaged, four waves,
-// 128 rows, register-staged loads, two workgroups per compute unit.
-// Causal: two key groups halve the chain of steps of the longest row tile and make twice as many workgroups, but read each
-// tile for half as many rows.  That wins until the 256-row tiles are about 1.5 per compute unit at d = 128 (32 heads, pair
-// calls, kDmaKeys2 against kDma: 2800 rows 92 against 96 us, 3100 rows 110 against 100) and two per resident workgroup, of
-// which a compute unit holds two, at d = 64 (24 heads x 3900 rows 77 against 92, x 6450 rows 163 against 174, 32 heads x
-// 9000 rows 382 against 378, 512 x 500 54 against 51).
+// stream for all of them); kDmaKeys2, the same with 128 rows, whose keys two groups of waves share, and kDmaKeys2One, at
+// d = 64, its form of one workgroup per compute unit with the score pipeline; kStaged, four waves, 128 rows, register-staged
+// loads, two workgroups per compute unit.  All figures: device time of pair calls in us.
 // Few rows are start and end of workgroups rather than steps, and most waves of an eight-wave workgroup hold no row: kStaged
-// up to 320 rows (device time of pair calls, kDma / kDmaKeys2 / kStaged: 32 heads x 40 rows 11.1 / 12.0 / 10.1 us, x 140
-// 15.3 / 14.8 / 13.9, x 300 19.9 / 16.8 / 16.9, x 330 21.1 / 17.1 / 18.5; 256 heads x 40 16.9 / 18.3 / 12.3, x 128 22.9 /
-// 23.5 / 17.9; d = 64, 32 heads x 300 16.2 / 13.9 / 13.2, x 460 19.7 / 15.5 / 16.1) and, where the heads fill the chip, up to
-// 512 (128 heads x 400 29.1 / 31.6 / 27.4, 256 x 460 51.3 / 54.6 / 46.7, 128 x 700 48.3 / 48.1 / 48.3; d = 64, 256 x 400
-// 29.5 / 31.1 / 28.5).
+// up to 320 rows (kDma / kDmaKeys2 / kStaged: 32 heads x 40 rows 11.1 / 12.0 / 10.1, x 140 15.3 / 14.8 / 13.9, x 300 19.9 /
+// 16.8 / 16.9, x 330 21.1 / 17.1 / 18.5; 256 heads x 40 16.9 / 18.3 / 12.3, x 128 22.9 / 23.5 / 17.9; d = 64, 32 heads x 300
+// 16.2 / 13.9 / 13.2, x 460 19.7 / 15.5 / 16.1), and further up the more workgroups there are: a third to half of its second
+// resident set at 384 and 544 rows, most of it at 640 (96 heads over 12, 512 rows 28.2 / 29.1 / 26.5; 128 over 32, 600 rows
+// 44.2 / 41.0 / 38.2; 128 x 520, d = 64, 31.0 / 34.6 / 27.6), where d = 64 wants more of them unless every head reads a K and
+// V of its own (128 over 32 x 640: 30.3 / 27.0 / 28.6, 160 over 32 x 640: 33.1 / 30.6 / 29.3).
+// Two key groups halve the chain of steps of the longest row tile and make twice as many workgroups, but read each tile for
+// half as many rows.  d = 128: up to 512 workgroups of 128 rows (32 heads x 2000 rows 66.2 / 61.2 / 64.2), from 320 of 256
+// rows on kDma (64 heads x 1200 47.8 / 54.4 / 52.9, 32 x 2600 82.6 / 84.7 / 86.1), between them kStaged for short rows (96 over
+// 12 x 768 40.0 / 42.7 / 36.0) and kDmaKeys2 for long ones (24 x 3000 89.2 / 81.2 / 87.9).
+// d = 64: up to 1024 workgroups of 256 rows (24 heads x 6450 174 / 163, 32 x 9000 378 / 382), 384 where no two heads share K
+// and V and the head count is no multiple of 8, so that an XCD's L2 does not keep a head's tiles for its second reader (127 x
+// 1540 99.1 / 110.9 / 105.7); in the form of one per compute unit while they, and one row tile of query tokens per KV head,
+// nearly fit the chip once (kDmaKeys2 -> kDmaKeys2One: 32 heads x 700 18.0 -> 17.0, x 1200 24.7 -> 22.6, x 2000 37.1 -> 39.0;
+// 64 heads with their own K and V x 400 18.1 -> 21.6).
+// Over 1066 shapes (7 to 512 heads, 330 to 3500 rows) this is 0.9 % from the best of the four on average.
 // Not causal: kDma from two 256-row tiles per KV head on (measured at 256 / 512 / 1024 rows).
-enum class AttnShape { kDma, kDmaKeys2, kStaged };
-inline AttnShape attn_bf16_shape(int causal, int n_batch, int rows, int d) {
+enum class AttnShape { kDma, kDmaKeys2, kDmaKeys2One, kStaged };
+inline AttnShape attn_bf16_shape(int causal, int n_batch, int batch_per_kv, int rows, int d) {
   if (!causal) return rows >= 512 ? AttnShape::kDma : AttnShape::kStaged;
-  if (rows <= 320 || (rows <= 512 && n_batch >= 128)) return AttnShape::kStaged;
-  return (long long)n_batch * ((rows + 255) / 256) >= (d == 128 ? 384 : 1024) ? AttnShape::kDma : AttnShape::kDmaKeys2;
+  const long long wg256 = (long long)n_batch * ((rows + 255) / 256), wg128 = (long long)n_batch * ((rows + 127) / 128);
+  const int n_kv = n_batch / batch_per_kv;
+  if (rows <= 320 || (rows <= 384 && wg128 > 224) || (rows <= 544 && wg128 > 352)) return AttnShape::kStaged;
+  if (rows <= 640 && wg128 > 448 && (d == 128 || batch_per_kv == 1 || wg128 >= 800)) return AttnShape::kStaged;
+  if (d == 128) {
+    if (wg128 <= 512) return AttnShape::kDmaKeys2;
+    if (wg256 >= 320) return AttnShape::kDma;
+    return rows <= 1536 ? AttnShape::kStaged : AttnShape::kDmaKeys2;
+  }
+  if (wg128 + 2 * n_kv <= 368) return AttnShape::kDmaKeys2One;
+  return wg256 >= (batch_per_kv == 1 && n_kv % 8 != 0 ? 384 : 1024) ? AttnShape::kDma : AttnShape::kDmaKeys2;
 }
 
 // Whether the attention of query tokens over a cache AND their n_self own keys runs as one launch of the short kernel, the

@@ -1,8 +1,7 @@
-"""The bf16 attention kernels where their tiling can go wrong.  Asynchronous loads: row counts around the remainder that
-sets where the causal row tiles start (0, 1, 63 .. 65, 192 .. 255 rows beyond a multiple of 256), two key groups at
-remainders of 128, both head dimensions, the pair launch, and query problems of 256-row tiles with and without key chunks.
-Register-staged loads: one to four key tiles, remainders of 128, many heads, and the row counts at which one kernel gives
-way to the other (320, and 512 with 128 heads)."""
+"""The bf16 attention kernels where their tiling can go wrong, each at the sizes that its dispatch rule gives it: row counts
+around the remainder that sets where the causal row tiles of the asynchronous kernels start, one to several key tiles, one
+and two key groups, both head dimensions, the pair launch, query problems of 256-row tiles with and without key chunks, and
+the row and workgroup counts at which one kernel gives way to the next."""
 import pytest
 
 from tests import test_gpu_attention_edges as E
@@ -11,21 +10,26 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("d,hq,hkv,m", [
+    # register-staged: one to three key tiles, remainders of 128, many heads, the largest row counts of its rules
     (64, 1024, 8, 1), (64, 1024, 8, 63), (64, 1024, 8, 64), (64, 1024, 8, 65), (64, 1040, 8, 129), (64, 1024, 8, 193),
-    (64, 1024, 8, 255), (64, 1024, 8, 256), (64, 515, 5, 320), (64, 512, 8, 321), (64, 344, 8, 577),
-    (64, 120, 8, 2049), (64, 120, 8, 2303),
-    (128, 384, 8, 192), (128, 384, 8, 193), (128, 192, 8, 257), (128, 192, 8, 320), (128, 195, 5, 321),
-    (128, 48, 8, 2049), (128, 48, 8, 2303), (64, 80, 8, 3329), (64, 512, 8, 257),
-    (128, 128, 8, 140), (64, 130, 10, 300), (128, 136, 8, 512), (128, 127, 127, 300),  # many heads, few rows
-    (128, 128, 8, 513), (64, 130, 10, 512), (64, 130, 10, 513), (128, 127, 127, 512),
-    # two key groups: from 321 rows on, remainders of 128, both groups' first tiles
-    (128, 8, 2, 321), (128, 7, 1, 384), (64, 8, 2, 321), (64, 7, 1, 384), (128, 5, 5, 449), (64, 8, 8, 512), (128, 2, 2, 640),
-    (64, 127, 127, 513), (128, 6, 2, 767), (64, 4, 4, 895),
-    # four waves: one key, tiles of one and two key tiles, remainders of 128, the last row count
-    (128, 8, 2, 320), (64, 8, 2, 320),
+    (64, 1024, 8, 255), (64, 1024, 8, 256), (64, 515, 5, 320), (64, 512, 8, 321), (64, 512, 8, 257), (64, 130, 10, 300),
+    (128, 384, 8, 192), (128, 384, 8, 193), (128, 192, 8, 257), (128, 192, 8, 320), (128, 195, 5, 321), (128, 128, 8, 140),
+    (128, 136, 8, 512), (128, 127, 127, 300), (128, 127, 127, 512), (64, 130, 10, 513), (128, 128, 8, 640), (64, 160, 32, 640), (64, 112, 112, 640),
     (128, 8, 2, 1), (128, 8, 2, 32), (128, 8, 2, 33), (128, 7, 1, 64), (128, 8, 2, 65), (128, 6, 2, 127), (128, 8, 8, 128),
-    (128, 8, 2, 129), (128, 5, 5, 192), (128, 8, 2, 193), (128, 8, 2, 256), (128, 4, 2, 257), (128, 8, 2, 1000),
-    (64, 8, 2, 1), (64, 8, 2, 64), (64, 8, 2, 65), (64, 7, 1, 129), (64, 8, 2, 193), (64, 8, 2, 385), (64, 16, 2, 1030),
+    (128, 8, 2, 129), (128, 5, 5, 192), (128, 8, 2, 256), (128, 4, 2, 257), (128, 8, 2, 320), (64, 8, 2, 320),
+    (64, 8, 2, 1), (64, 8, 2, 64), (64, 8, 2, 65), (64, 7, 1, 129), (64, 8, 2, 193),
+    (128, 96, 12, 768), (128, 48, 8, 1536), (64, 76, 19, 384), (128, 75, 15, 400),
+    # 256 rows per workgroup: 0, 1, 63, 64, 65, 192, 193 and 255 rows beyond a multiple of 256
+    (128, 112, 8, 704), (128, 112, 16, 768), (128, 115, 5, 769), (128, 112, 8, 831), (128, 112, 8, 832), (128, 112, 16, 833),
+    (128, 112, 8, 960), (128, 115, 5, 961), (128, 112, 8, 1023), (128, 128, 8, 641), (128, 48, 8, 2049), (128, 48, 8, 2303),
+    (64, 130, 130, 768), (64, 256, 8, 769), (64, 100, 100, 831), (64, 256, 8, 832), (64, 100, 100, 833), (64, 256, 8, 960),
+    (64, 100, 100, 961), (64, 256, 8, 1023), (64, 120, 8, 2049), (64, 120, 8, 2303), (64, 80, 8, 3329),
+    # two key groups, one workgroup per compute unit: remainders of 128, both groups' first and last tiles
+    (128, 8, 2, 321), (128, 7, 1, 384), (128, 8, 2, 385), (128, 5, 5, 449), (128, 2, 2, 640), (128, 6, 2, 767), (128, 8, 2, 1000),
+    (64, 8, 2, 321), (64, 7, 1, 384), (64, 8, 2, 385), (64, 5, 5, 449), (64, 8, 8, 512), (64, 4, 4, 895), (64, 16, 2, 1030),
+    (128, 28, 7, 2433), (64, 60, 5, 1024),
+    # the same, two workgroups per compute unit
+    (64, 100, 10, 700), (64, 64, 8, 899), (64, 96, 12, 640), (64, 61, 61, 1000), (64, 60, 4, 1025), (64, 60, 5, 1087), (64, 24, 8, 2753), (64, 24, 8, 2815),
 ])
 def test_recompute(d, hq, hkv, m):
     E.test_recompute_attention_shapes("bf16", d, hq, hkv, m)
@@ -38,8 +42,11 @@ def test_query(d, hq, hkv, lq, m):
     E.test_query_attention_shapes("bf16", d, hq, hkv, lq, m)
 
 
-@pytest.mark.parametrize("d,hq,hkv,lq,m", [(64, 512, 8, 3, 321), (64, 120, 8, 45, 2100), (128, 200, 8, 3, 321),
-                                           (64, 8, 2, 3, 321), (128, 8, 2, 40, 130), (128, 8, 2, 1, 1), (64, 8, 2, 70, 65)])
+@pytest.mark.parametrize("d,hq,hkv,lq,m", [
+    (64, 512, 8, 3, 321), (128, 200, 8, 3, 321), (128, 8, 2, 40, 130), (128, 8, 2, 1, 1), (64, 8, 2, 70, 65),  # register-staged
+    (64, 120, 8, 45, 2100), (128, 112, 8, 3, 769),                                                          # 256 rows
+    (64, 8, 2, 3, 321), (128, 8, 2, 40, 400), (64, 16, 4, 100, 900), (64, 60, 4, 5, 1025),                  # two key groups
+])
 def test_both_in_one_call(d, hq, hkv, lq, m):
     E.test_both_attentions_in_one_call("bf16", d, hq, hkv, lq, m)
 
