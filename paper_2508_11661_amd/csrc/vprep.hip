@@ -24,8 +24,9 @@
 //   heads: 32 heads x 1540 rows, 8 KV heads 43.4 -> 41.9 us, 64 KV heads x 900 rows 63.8 -> 48.3, 128 x 1540 198.7 -> 189.9,
 //   beyond it 256 x 1540, 96 MB, 381 -> 436) or 24 MB (multiple of 4; 28 x 900 34.2 -> 28.7, 100 x 900 82.7 -> 73.7, 100 x
 //   1540, 38 MB, 150 -> 159); other head counts gain nothing and lose where a head is scanned often (127 heads x 2000 rows
-//   269 -> 348).  Problems that are not causal keep memory order: their workgroups of one head all start at once, and one L2
-//   alone feeds them (8 KV heads x 1500 keys, 800 rows: 31.0 us, 34.5 by heads).
+//   269 -> 348).  Problems that are not causal keep memory order below 16 heads, one per XCD:
+//   their workgroups of a head all start at once, and one L2 alone would feed them (8 KV heads x 1500 keys, 800 rows: 31.0 us,
+//   34.5 by heads; 32 heads x 1500 keys, 1024 rows, d = 128, 62.9 -> 58.8 by heads).
 #include "common.hpp"
 
 namespace samkv {
@@ -167,7 +168,7 @@ hipError_t launch_v_prep(const void* v, int n_kv, int m, int d, bool causal, voi
     const int c1 = (int)((total + kSmallChunk - 1) / kSmallChunk);
     const int per1 = kSmallChunk;
     const long long most = n_kv % 8 == 0 ? 56ll << 20 : n_kv % 4 == 0 ? 24ll << 20 : 0;
-    const bool by_head = causal && total * 16 * n_kv <= most;
+    const bool by_head = (causal || n_kv >= 16) && total * 16 * n_kv <= most;
     hipLaunchKernelGGL(k_v_prep_small, by_head ? dim3(n_kv, c1) : dim3(c1, n_kv), dim3(NT1), 0, s,
                        static_cast<const u32x4*>(v), static_cast<u32x4*>(v16), unscale, (int)total, per1, by_head);
     return hipGetLastError();
