@@ -871,7 +871,7 @@ hipError_t run_bf16_dma(const AttnLaunch& l, hipStream_t s) {
 }
 
 AttnShape bf16_shape(const AttnLaunch& l) {
-  return l.n_self > 0 ? AttnShape::kStaged : attn_bf16_shape(l.causal, l.n_batch, l.batch_per_kv, l.rows, l.d);
+  return l.n_self > 0 ? AttnShape::kStaged : attn_bf16_shape(l.causal, l.n_batch, l.batch_per_kv, l.rows, l.m, l.d);
 }
 
 template <int D, bool CAUSAL>

@@ -117,11 +117,18 @@ hipError_t launch_gather_q(const GatherLaunch& a, const PtrTable& q, const IntTa
 // nearly fit the chip once (kDmaKeys2 -> kDmaKeys2One: 32 heads x 700 18.0 -> 17.0, x 1200 24.7 -> 22.6, x 2000 37.1 -> 39.0;
 // 64 heads with their own K and V x 400 18.1 -> 21.6).
 // Over 1066 shapes (7 to 512 heads, 330 to 3500 rows) this is 0.9 % from the best of the four on average.
-// Not causal: kDma from two 256-row tiles per KV head on (measured at 256 / 512 / 1024 rows).
+// Not causal: kStaged (V as stored, two-term weights) below 512 rows per KV head, and beyond as long as preparing V would
+// cost more than the doubled second product (kStaged / kDma with its preparation, whole calls: 8 KV heads, d = 128, 800 rows
+// x 1500 keys 28.6 / 31.2, x 3000 33.8 / 35.6, x 7000 61.1 / 48.8; d = 64, 1024 rows x 3000 26.3 / 32.8, x 7000 39.6 / 40.5, x
+// 12000 56.2 / 51.5; 2 KV heads, d = 128, 512 rows x 20000 33.7 / 39.0), at d = 64 somewhat longer where there are workgroups
+// enough without chunks (32 KV heads, 2400 rows x 800 38.8 / 48.9; 16, 800 rows x 4500 45.3 / 40.5).
 enum class AttnShape { kDma, kDmaKeys2, kDmaKeys2One, kStaged };
-inline AttnShape attn_bf16_shape(int causal, int n_batch, int batch_per_kv, int rows, int d) {
-  if (!causal) return rows >= 512 ? AttnShape::kDma : AttnShape::kStaged;
+inline AttnShape attn_bf16_shape(int causal, int n_batch, int batch_per_kv, int rows, int m, int d) {
   const long long wg256 = (long long)n_batch * ((rows + 255) / 256), wg128 = (long long)n_batch * ((rows + 127) / 128);
+  if (!causal) {
+    const long long most = d == 128 ? 3000000000ll : wg128 >= 512 ? 4000000000ll : 3400000000ll;
+    return rows < 512 || (long long)rows * m * n_batch * d <= most ? AttnShape::kStaged : AttnShape::kDma;
+  }
   const int n_kv = n_batch / batch_per_kv;
   if (rows <= 320 || (rows <= 384 && wg128 > 224) || (rows <= 544 && wg128 > 352)) return AttnShape::kStaged;
   if (rows <= 640 && wg128 > 448 && (d == 128 || batch_per_kv == 1 || wg128 >= 800)) return AttnShape::kStaged;

@@ -114,7 +114,7 @@ ScoreWs score_ws(int n_ctx, int hq, int hkv, int d) {
 struct SplitPlan { int n_split, chunk; size_t part_o, part_lse, bytes; };
 // `n_own` > 0: one more part, the query tokens' n_own own keys, follows; `own`: in the same launch (attn_self_in_kernel).
 SplitPlan plan_splits(int dtype, int n_batch, int rows, int m, int d, int n_own = 0, bool own = false) {
-  const int bq = dtype != SAMKV_BF16 ? 32 : own || attn_bf16_shape(0, n_batch, 1, rows, d) != AttnShape::kDma ? 128 : 256;
+  const int bq = dtype != SAMKV_BF16 ? 32 : own || attn_bf16_shape(0, n_batch, 1, rows, m, d) != AttnShape::kDma ? 128 : 256;
   const int bk = dtype == SAMKV_BF16 ? 64 : 128;
   const long long base = (long long)((rows + bq - 1) / bq) * n_batch;
   const int key_tiles = (m + bk - 1) / bk;

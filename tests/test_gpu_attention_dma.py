@@ -36,7 +36,11 @@ def test_recompute(d, hq, hkv, m):
 
 
 @pytest.mark.parametrize("d,hq,hkv,lq,m", [
+    # register-staged: up to 511 rows per KV head, and more of them with few keys
     (64, 16, 2, 64, 1), (64, 16, 2, 64, 64), (64, 16, 2, 65, 130), (64, 16, 2, 100, 1000), (64, 24, 8, 256, 3001),
+    (128, 16, 2, 200, 1), (128, 16, 2, 65, 64), (128, 24, 8, 171, 1300), (128, 64, 8, 100, 3661), (64, 64, 8, 256, 3814),
+    # 256 rows per workgroup beyond: several chunks with a ragged last one, one chunk of two and three key tiles
+    (128, 64, 8, 100, 3663), (64, 64, 8, 256, 3816), (64, 64, 8, 257, 4001), (128, 256, 64, 1500, 65), (64, 256, 64, 1500, 164),
 ])
 def test_query(d, hq, hkv, lq, m):
     E.test_query_attention_shapes("bf16", d, hq, hkv, lq, m)
