@@ -218,26 +218,43 @@ __device__ __forceinline__ Threshold threshold_by_histogram(const uint32_t (&key
   return {prefix, bucket == kk ? 0xFFFFFFFFu : kk};
 }
 
+// n plus the number of lower lanes in `mask`
+__device__ __forceinline__ uint32_t lanes_below(uint64_t mask, uint32_t n) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, n));
+}
+
 // Writes the kept positions of a row whose order keys sit in registers (keys of positions >= L are 0), ascending, to
 // out[0..k).  wsum is LDS scratch of the workgroup.
 template <int E, int NT>
 __device__ __forceinline__ void write_kept(const uint32_t (&key)[E], int L, Threshold th, int32_t* out, uint2* wsum) {
   constexpr int NW = NT / 64;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const uint64_t below = (1ull << lane) - 1ull;
-  // per lane, both counts in one word (at most 64 each), summed over the wave
-  uint32_t n = 0;
+  uint32_t n_gt = 0, n_eq = 0, T = th.T;  // counts of the wave
+  if constexpr (E <= 8) {
+    // by ballots, whose masks stay in scalar registers for the second use below
 #pragma unroll
-  for (int e = 0; e < E; ++e) {
-    const bool ok = key_position<E>(e) < L;
-    n += (ok && key[e] > th.T ? 1u : 0u) + (ok && key[e] == th.T ? 0x10000u : 0u);
+    for (int e = 0; e < E; ++e) {
+      const bool ok = key_position<E>(e) < L;
+      n_gt += __popcll(__ballot(ok && key[e] > T));
+      n_eq += __popcll(__ballot(ok && key[e] == T));
+    }
+  } else {
+    // per lane, both counts in one word (at most 64 each), summed over the wave; the comparisons below are made anew: 2 E
+    // masks kept from above would not fit the registers
+    uint32_t n = 0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const bool ok = key_position<E>(e) < L;
+      n += (ok && key[e] > T ? 1u : 0u) + (ok && key[e] == T ? 0x10000u : 0u);
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) n += __shfl_xor(n, off);
+    n_gt = n & 0xFFFFu;
+    n_eq = n >> 16;
+    asm volatile("" : "+v"(T));
   }
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) n += __shfl_xor(n, off);
-  if (lane == 0) wsum[wave] = make_uint2(n & 0xFFFFu, n >> 16);
+  if (lane == 0) wsum[wave] = make_uint2(n_gt, n_eq);
   __syncthreads();
-  uint32_t T = th.T;
-  asm volatile("" : "+v"(T));  // the comparisons below are made anew: 2 E masks kept from above would not fit the registers
   uint32_t gt = 0, eq = 0;
 #pragma unroll
   for (int w = 0; w < NW; ++w) {
@@ -249,7 +266,7 @@ __device__ __forceinline__ void write_kept(const uint32_t (&key)[E], int L, Thre
     const int p = key_position<E>(e);
     const bool is_gt = p < L && key[e] > T, is_eq = p < L && key[e] == T;
     const uint64_t m_gt = __ballot(is_gt), m_eq = __ballot(is_eq);
-    const uint32_t g = gt + __popcll(m_gt & below), q = eq + __popcll(m_eq & below);
+    const uint32_t g = lanes_below(m_gt, gt), q = lanes_below(m_eq, eq);
     if (is_gt || (is_eq && q < th.need)) out[g + (q < th.need ? q : th.need)] = p;
     gt += __popcll(m_gt);
     eq += __popcll(m_eq);

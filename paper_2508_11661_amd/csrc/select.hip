@@ -57,13 +57,17 @@ hipError_t run(const SelectLaunch& a, const IntTable& cu_len, const IntTable& cu
 }  // namespace
 
 hipError_t launch_select(const SelectLaunch& a, const IntTable& cu_len, const IntTable& cu_k, hipStream_t s) {
-  // Bit passes for rows of up to 1024 keys: few keys per thread, and four waves keep the barrier rounds short.  Beyond,
-  // the histograms win at every number of rows measured (40, 160, 512 rows): 2048 keys 8.4, 8.9, 11.1 against 11.2, 12.0,
-  // 14.6 us, 4096 keys 8.1, 9.9, 12.8 against 11.0, 12.8, 15.5 us (16 keys per thread in 256 threads); at 1024 keys 7.1, 7.3,
-  // 8.0 us by bits against 6.7, 8.3, 11.2.  40 rows of 24000 keys: 97 -> 22 us, half of it from loading whole lines.
+  // Bit passes for rows of up to 1024 keys: few keys per thread, and four waves keep the barrier rounds short.  Up to
+  // 4096 keys the histograms shorten a row (bits / histograms: 40 rows of 1500 keys 8.0 / 6.7 us, 640 of 4096 17.9 /
+  // 16.3), but ask for twice the threads, an LDS pass to clear them and, where many scores are equal, atomics on one
+  // address.  Bits win where enough rows share a compute unit to hide their barriers: from one row per compute unit on up
+  // to 2048 keys (320 rows of 1500 9.6 / 10.4, 2560 of 2048 23.3 / 32.0), from three on up to 4096 (1280 rows of 4096
+  // 22.9 / 23.9; all scores equal, 2560 of 4096 51 / 65).  Beyond, histograms at every number of rows measured (40 to
+  // 5120): 40 rows of 24000 keys 97 -> 22 us, half of it from loading whole lines.
+  const long long rows = (long long)a.n_ctx * a.hkv;
   if (a.max_len <= 1024) return run<4, 256, false>(a, cu_len, cu_k, s);
-  if (a.max_len <= 2048) return run<4, 512, true>(a, cu_len, cu_k, s);
-  if (a.max_len <= 4096) return run<8, 512, true>(a, cu_len, cu_k, s);
+  if (a.max_len <= 2048) return rows < 256 ? run<4, 512, true>(a, cu_len, cu_k, s) : run<8, 256, false>(a, cu_len, cu_k, s);
+  if (a.max_len <= 4096) return rows < 768 ? run<8, 512, true>(a, cu_len, cu_k, s) : run<16, 256, false>(a, cu_len, cu_k, s);
   if (a.max_len <= 8192) return run<16, 512, true>(a, cu_len, cu_k, s);
   if (a.max_len <= 16384) return run<16, 1024, true>(a, cu_len, cu_k, s);
   if (a.max_len <= 32768) return run<32, 1024, true>(a, cu_len, cu_k, s);

@@ -50,6 +50,27 @@ def test_rows(length, pattern):
                 assert np.array_equal(got[g, o:o + ks[i]], _want(scores[g, a:a + n], ks[i], n_sink, n_local)), (g, i, ratio)
 
 
+@pytest.mark.parametrize("length,docs,heads", [(1025, 32, 8), (1500, 16, 16), (2048, 20, 13), (2049, 32, 32), (3001, 59, 13),
+                                              (4096, 77, 10)])
+@pytest.mark.parametrize("pattern", ["distinct", "ties", "equal", "last_bit"])
+def test_many_rows(length, docs, heads, pattern):
+    """Row counts from which the threshold comes from bit passes again (256 rows of up to 2048 keys, 768 of up to 4096)."""
+    import torch
+    from paper_2508_11661_amd import samkv as S
+    rng = np.random.default_rng(length)
+    lens = [length - 3 * (i % 7) for i in range(docs)]
+    scores = np.stack([np.concatenate([_rows(pattern, n, rng) for n in lens]) for _ in range(heads)])
+    caches = S.Caches([torch.zeros((heads, n, 64), dtype=torch.bfloat16, device="cuda") for n in lens], None, heads)
+    ks = [S.samkv_kept_count(n, 0.2) for n in lens]
+    idx = torch.full((heads, sum(ks)), -1, dtype=torch.int32, device="cuda")
+    S.samkv_topk_select(torch.from_numpy(scores).cuda(), caches, 0.2, 2, 3, idx, None)
+    got = idx.cpu().numpy()
+    for g in range(heads):
+        for i, n in enumerate(lens):
+            a, o = sum(lens[:i]), sum(ks[:i])
+            assert np.array_equal(got[g, o:o + ks[i]], _want(scores[g, a:a + n], ks[i], 2, 3)), (g, i)
+
+
 @pytest.mark.parametrize("dtype,d,length", [("bf16", 128, 1024), ("bf16", 64, 1025), ("bf16", 128, 2048), ("f32", 64, 2049),
                                             ("bf16", 128, 4096), ("bf16", 64, 4097), ("f32", 128, 8192)])
 def test_fused_rows(dtype, d, length):
