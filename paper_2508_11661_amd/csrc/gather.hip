@@ -11,17 +11,27 @@
 namespace samkv {
 namespace {
 
-// Rows per lane group of a workgroup: four (64 rows of 256 bytes per workgroup) against eight, K and V of 20 documents x 8 KV
-// heads, 340 kept rows each: 18.3 -> 16.0 us; stored Q rows of 32 heads 25.0 -> 23.7 us; 5120 rows' K and V 292 -> 282 us.
-// The copies are short, so more workgroups in flight count for more than loads in flight per lane.
-constexpr int kSteps = 4;
-
+// Steps per wave: 64 rows of 256 bytes per workgroup at four, 128 at eight.  The copies are short and each begins with
+// a chain of two loads, so four steps, with twice the workgroups, are the rule (eight / four: K and V of 20 documents x
+// 8 KV heads, 340 kept rows each, 18.3 / 16.0 us; stored Q rows of 32 heads 25.0 / 23.7 us; 5120 rows' K and V 292 /
+// 282 us).  But where a document's rows fit eight steps and not four, its second workgroup repeats that chain for the
+// few rows left over, which shows once the chip is full of workgroups (eight to four, rows that fill 55 and 75 % of
+// eight steps: 256 (document, head) pairs 0.91 to 0.96, 512 0.65 to 0.90, 1024 to 6400 0.71 to 0.93; 128 pairs 0.96 to
+// 1.07).  Rows that fill 97 % have nothing left over (0.79 to 1.16 either way), hence the bound of 7/8 on the average.
+constexpr int kStepsFew = 4, kStepsMany = 8;
 template <int ROW_BYTES>
+int gather_steps(const GatherLaunch& a, int heads) {
+  constexpr int rows = (64 / (ROW_BYTES / 16)) * kStepsMany * 4;  // of a workgroup
+  const bool one = a.max_k > rows / 2 && a.max_k <= rows;
+  const bool room = 8ll * a.m_total <= 7ll * rows * a.n_ctx;
+  return one && room && a.n_ctx * heads >= 256 ? kStepsMany : kStepsFew;
+}
+
+template <int ROW_BYTES, int STEPS>
 __global__ __launch_bounds__(256) void k_gather(PtrTable kt, PtrTable vt, IntTable cu_len, IntTable cu_k, int m_total,
                                                 const int32_t* idx, char* k_c, char* v_c) {
   constexpr int LPR = ROW_BYTES / 16;
   constexpr int RPS = 64 / LPR;  // rows per wave step
-  constexpr int STEPS = kSteps;
   constexpr int ROWS_PER_BLOCK = RPS * STEPS * 4;
   const int i = blockIdx.y, g = blockIdx.z;  // document and KV head are uniform over the block
   const int k_i = cu_k.v[i + 1] - cu_k.v[i];
@@ -60,12 +70,11 @@ __global__ __launch_bounds__(256) void k_gather(PtrTable kt, PtrTable vt, IntTab
 
 // Q-cache variant: one tensor, one row set per QUERY head h, indexed by the kept positions of its KV head
 // h / group (the stored per-document Q cache supplies the query states of the kept tokens).
-template <int ROW_BYTES>
+template <int ROW_BYTES, int STEPS>
 __global__ __launch_bounds__(256) void k_gather_q(PtrTable qt, IntTable cu_len, IntTable cu_k, int m_total, int group,
                                                   const int32_t* idx, char* q_rec) {
   constexpr int LPR = ROW_BYTES / 16;
   constexpr int RPS = 64 / LPR;
-  constexpr int STEPS = kSteps;
   constexpr int ROWS_PER_BLOCK = RPS * STEPS * 4;
   const int i = blockIdx.y, h = blockIdx.z, g = h / group;
   const int k_i = cu_k.v[i + 1] - cu_k.v[i];
@@ -171,21 +180,27 @@ hipError_t run_g(const PtrTable& a, const PtrTable* b, const IntTable& cu_len, i
 }
 
 template <int ROW_BYTES>
+dim3 gather_grid(const GatherLaunch& a, int steps, int heads) {
+  const int rows = (64 / (ROW_BYTES / 16)) * steps * 4;
+  return dim3((a.max_k + rows - 1) / rows, a.n_ctx, heads);
+}
+
+template <int ROW_BYTES>
 hipError_t run_q(const GatherLaunch& a, const PtrTable& q, const IntTable& cu_len, const IntTable& cu_k, int hq,
                  hipStream_t s) {
-  constexpr int ROWS_PER_BLOCK = (64 / (ROW_BYTES / 16)) * kSteps * 4;
-  dim3 grid((a.max_k + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK, a.n_ctx, hq);
-  hipLaunchKernelGGL((k_gather_q<ROW_BYTES>), grid, dim3(256), 0, s, q, cu_len, cu_k, a.m_total, hq / a.hkv, a.idx,
-                     static_cast<char*>(a.k_c));
+  const int steps = gather_steps<ROW_BYTES>(a, hq);
+  auto kernel = steps == kStepsMany ? k_gather_q<ROW_BYTES, kStepsMany> : k_gather_q<ROW_BYTES, kStepsFew>;
+  hipLaunchKernelGGL(kernel, gather_grid<ROW_BYTES>(a, steps, hq), dim3(256), 0, s, q, cu_len, cu_k, a.m_total, hq / a.hkv,
+                     a.idx, static_cast<char*>(a.k_c));
   return hipGetLastError();
 }
 
 template <int ROW_BYTES>
 hipError_t run(const GatherLaunch& a, const PtrTable& k, const PtrTable& v, const IntTable& cu_len,
                const IntTable& cu_k, hipStream_t s) {
-  constexpr int ROWS_PER_BLOCK = (64 / (ROW_BYTES / 16)) * kSteps * 4;
-  dim3 grid((a.max_k + ROWS_PER_BLOCK - 1) / ROWS_PER_BLOCK, a.n_ctx, a.hkv);
-  hipLaunchKernelGGL((k_gather<ROW_BYTES>), grid, dim3(256), 0, s, k, v, cu_len, cu_k, a.m_total, a.idx,
+  const int steps = gather_steps<ROW_BYTES>(a, a.hkv);
+  auto kernel = steps == kStepsMany ? k_gather<ROW_BYTES, kStepsMany> : k_gather<ROW_BYTES, kStepsFew>;
+  hipLaunchKernelGGL(kernel, gather_grid<ROW_BYTES>(a, steps, a.hkv), dim3(256), 0, s, k, v, cu_len, cu_k, a.m_total, a.idx,
                      static_cast<char*>(a.k_c), static_cast<char*>(a.v_c));
   return hipGetLastError();
 }
