@@ -1,6 +1,6 @@
 """Attention entry points on shapes chosen to reach every kernel variant and every prologue/tail case:
-one, two, three and four key tiles, ragged last tiles, many heads with few rows (the 8-wave asynchronous
-kernel is picked by row-tile count), key chunks with a merge, both head dims and both dtypes."""
+one, two, three and four key tiles, ragged last tiles, many heads with few rows (which kernel serves a causal problem
+depends on its rows and on the number of row tiles), key chunks with a merge, both head dims and both dtypes."""
 import math
 
 import numpy as np
@@ -119,13 +119,13 @@ def test_query_attention_with_self_tail(dtype, d, hq, hkv, lq, m):
 
 @pytest.mark.parametrize("dtype,d,hq,hkv,lq,m", [
     # one launch for both attentions, in every workgroup shape the causal problem can select (the query attention
-    # takes the same shape and walks all keys in one chunk): 128 rows x two key groups, four waves, the asynchronous
-    # kernel with KV heads in groups of 8 / in three such groups / not a multiple of 8, eight waves at d = 64
+    # takes the same shape and walks all keys in one chunk): 128 rows x two key groups, 128 rows register-staged, 256 rows,
+    # with KV heads in groups of 8 / in three such groups / not a multiple of 8
     ("bf16", 128, 32, 8, 32, 1540), ("bf16", 128, 8, 2, 5, 200), ("bf16", 128, 4, 4, 1, 1),
     ("bf16", 128, 64, 8, 256, 4200), ("bf16", 128, 48, 24, 7, 2300), ("bf16", 128, 40, 10, 33, 2600),
     ("bf16", 64, 64, 8, 130, 4200), ("bf16", 64, 16, 4, 64, 449), ("bf16", 64, 8, 2, 3, 100),
     ("bf16", 128, 32, 8, 300, 700),      # more query rows than one workgroup holds, short cache
-    ("f32", 64, 8, 2, 16, 156),          # float32: the call runs the two kernels one after the other
+    ("f32", 64, 8, 2, 16, 156),          # float32: one launch for both, and a merge where keys are chunked
 ])
 def test_both_attentions_in_one_call(dtype, d, hq, hkv, lq, m):
     """samkv_recompute_query_attn against the two separate calls and the oracle: the recompute attention runs the same
