@@ -14,17 +14,25 @@ namespace {
 // Steps per wave: 64 rows of 256 bytes per workgroup at four, 128 at eight.  The copies are short and each begins with
 // a chain of two loads, so four steps, with twice the workgroups, are the rule (eight / four: K and V of 20 documents x
 // 8 KV heads, 340 kept rows each, 18.3 / 16.0 us; stored Q rows of 32 heads 25.0 / 23.7 us; 5120 rows' K and V 292 /
-// 282 us).  But where a document's rows fit eight steps and not four, its second workgroup repeats that chain for the
-// few rows left over, which shows once the chip is full of workgroups (eight to four, rows that fill 55 and 75 % of
-// eight steps: 256 (document, head) pairs 0.91 to 0.96, 512 0.65 to 0.90, 1024 to 6400 0.71 to 0.93; 128 pairs 0.96 to
-// 1.07).  Rows that fill 97 % have nothing left over (0.79 to 1.16 either way), hence the bound of 7/8 on the average.
+// 282 us).  Two exceptions.
+//   Where a document's rows fit eight steps and not four, its second workgroup repeats that chain for the few rows left
+//   over, which shows once the chip is full of workgroups (eight to four, rows that fill 55 and 75 % of eight steps:
+//   256 (document, head) pairs 0.91 to 0.96, 512 0.65 to 0.90, 1024 to 6400 0.71 to 0.93; 128 pairs 0.96 to 1.07).
+//   Rows that fill 97 % have nothing left over (1.0 to 1.16, but for the second exception), hence the bound of 7/8 on
+//   the average.
+//   Where eight steps make two workgroups for every compute unit, evenly long, half as many chains do the same work in
+//   one go (512 workgroups, rows that fill 75 to 98 %, one to eight workgroups per document, 0.69 to 0.93; 480 0.91 to
+//   1.06; 384 and 640, 94 % and more, 0.95 to 1.22).
 constexpr int kStepsFew = 4, kStepsMany = 8;
 template <int ROW_BYTES>
-int gather_steps(const GatherLaunch& a, int heads) {
+int gather_steps(const GatherLaunch& a, const IntTable& cu_k, int heads) {
   constexpr int rows = (64 / (ROW_BYTES / 16)) * kStepsMany * 4;  // of a workgroup
-  const bool one = a.max_k > rows / 2 && a.max_k <= rows;
-  const bool room = 8ll * a.m_total <= 7ll * rows * a.n_ctx;
-  return one && room && a.n_ctx * heads >= 256 ? kStepsMany : kStepsFew;
+  const int per_doc = (a.max_k + rows - 1) / rows;
+  const long long wgs = (long long)per_doc * a.n_ctx * heads;
+  if (a.max_k > rows / 2 && per_doc == 1 && 8ll * a.m_total <= 7ll * rows * a.n_ctx) return wgs >= 256 ? kStepsMany : kStepsFew;
+  bool even = wgs > 448 && wgs <= 512 && a.max_k > rows / 2;
+  for (int i = 0; even && i < a.n_ctx; ++i) even = cu_k.v[i + 1] - cu_k.v[i] > (per_doc - 1) * rows + rows / 2;
+  return even ? kStepsMany : kStepsFew;
 }
 
 template <int ROW_BYTES, int STEPS>
@@ -188,7 +196,7 @@ dim3 gather_grid(const GatherLaunch& a, int steps, int heads) {
 template <int ROW_BYTES>
 hipError_t run_q(const GatherLaunch& a, const PtrTable& q, const IntTable& cu_len, const IntTable& cu_k, int hq,
                  hipStream_t s) {
-  const int steps = gather_steps<ROW_BYTES>(a, hq);
+  const int steps = gather_steps<ROW_BYTES>(a, cu_k, hq);
   auto kernel = steps == kStepsMany ? k_gather_q<ROW_BYTES, kStepsMany> : k_gather_q<ROW_BYTES, kStepsFew>;
   hipLaunchKernelGGL(kernel, gather_grid<ROW_BYTES>(a, steps, hq), dim3(256), 0, s, q, cu_len, cu_k, a.m_total, hq / a.hkv,
                      a.idx, static_cast<char*>(a.k_c));
@@ -198,7 +206,7 @@ hipError_t run_q(const GatherLaunch& a, const PtrTable& q, const IntTable& cu_le
 template <int ROW_BYTES>
 hipError_t run(const GatherLaunch& a, const PtrTable& k, const PtrTable& v, const IntTable& cu_len,
                const IntTable& cu_k, hipStream_t s) {
-  const int steps = gather_steps<ROW_BYTES>(a, a.hkv);
+  const int steps = gather_steps<ROW_BYTES>(a, cu_k, a.hkv);
   auto kernel = steps == kStepsMany ? k_gather<ROW_BYTES, kStepsMany> : k_gather<ROW_BYTES, kStepsFew>;
   hipLaunchKernelGGL(kernel, gather_grid<ROW_BYTES>(a, steps, a.hkv), dim3(256), 0, s, k, v, cu_len, cu_k, a.m_total, a.idx,
                      static_cast<char*>(a.k_c), static_cast<char*>(a.v_c));

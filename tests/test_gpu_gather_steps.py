@@ -1,21 +1,22 @@
 """Gathers of the kept rows on both sides of the rule for the rows per workgroup: half a large workgroup and one row more,
-7/8 of it and one row more, all of it and one row more, 120 to 272 (document, head) pairs, and documents of mixed counts,
-some of which keep nothing.  Copies: exact."""
+7/8 of it and one row more, all of it and one row more, 120 to 272 (document, head) pairs, three large workgroups per
+document the last of which is half full or one row more, 504 and 512 large workgroups in all, and documents of mixed
+counts, some of which keep nothing.  Copies: exact."""
 import pytest
 
 pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("dtype,d", [("bf16", 64), ("bf16", 128), ("f32", 64), ("f32", 128)])
-@pytest.mark.parametrize("docs,group", [(32, 1), (15, 2), (17, 2)])
-@pytest.mark.parametrize("fill", ["half", "half+1", "most", "most+1", "full", "full+1", "mixed"])
+@pytest.mark.parametrize("docs,group", [(32, 1), (15, 2), (17, 2), (21, 1), (64, 1)])
+@pytest.mark.parametrize("fill", ["half", "half+1", "most", "most+1", "full", "full+1", "three", "three+1", "mixed"])
 def test_gather_steps(dtype, d, docs, group, fill):
     import torch
     from paper_2508_11661_amd import samkv as S
     dt = torch.bfloat16 if dtype == "bf16" else torch.float32
     rows = 64 // (d * dt.itemsize // 16) * 8 * 4
-    hkv, length = 8, rows + 40
-    n = {"half": rows // 2, "most": rows * 7 // 8, "full": rows}.get(fill.split("+")[0], 0) + ("+" in fill)
+    hkv, length = 8, 3 * rows + 40
+    n = {"half": rows // 2, "most": rows * 7 // 8, "full": rows, "three": rows * 5 // 2}.get(fill.split("+")[0], 0) + ("+" in fill)
     ks = [n] * docs if fill != "mixed" else [(0, 1, rows, 5, rows // 2 + 1)[i % 5] for i in range(docs)]
     gen = torch.Generator("cuda").manual_seed(docs)
     def rand(*shape):
