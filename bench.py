@@ -24,6 +24,7 @@ import argparse
 import json
 import math
 import os
+import re
 import sys
 import time
 
@@ -96,30 +97,23 @@ def kernel_row(name, w, work, ms, layers_per_call=1):
 def read_traffic(workload, kernel: str):
     """HBM bytes per launch (read + write) of a call's main kernel(s), from the committed rocprofv3 --pmc summary of
     this workload (profiles/bench_<workload>.txt: FETCH_SIZE and WRITE_SIZE runs scaled by a plain copy), or None."""
-    causal = ["k_attn_%s<%d, true" % (workload.dtype, workload.head_dim), "k_attn_%s_dma<true" % workload.dtype]
-    plain = ["k_attn_%s<%d, false" % (workload.dtype, workload.head_dim), "k_attn_%s_dma<false" % workload.dtype]
-    pair = ["k_attn_%s_pair<%d" % (workload.dtype, workload.head_dim), "k_attn_%s_dma_pair" % workload.dtype]
-    groups = {"score": [["k_score<"]], "select": [["k_select"]], "gather": [["k_gather<"]],
-              "score_select": [["k_score_select"]], "score_select_gather": [["k_score_select"]],
-              "recompute_attn": [causal], "query_attn": [plain],
-              # bf16: one launch runs both attentions; float32: the two kernels one after the other
-              "recompute_query_attn": [pair] if workload.dtype == "bf16" else [causal, plain]}[kernel]
+    attn = r"k_attn_%s(_dma)?%%s<%d%%s" % (workload.dtype, workload.head_dim)
+    pattern = {"score": r"k_score<", "select": r"k_select<", "gather": r"k_gather<",
+               # the selection alone, and with the gather in the same launch
+               "score_select": r"k_score_select<.*, false>", "score_select_gather": r"k_score_select<.*, true>",
+               "recompute_attn": attn % ("", r"(, \d+)*, true>"), "query_attn": attn % ("", r"(, \d+)*, false>"),
+               "recompute_query_attn": attn % ("_pair", "")}[kernel]
     try:
         lines = open(os.path.join(ROOT, "profiles", f"bench_{workload.name}.txt")).read().splitlines()
     except OSError:
         return None
-    total = 0.0
-    for prefixes in groups:
-        for line in lines:
-            if any(line.startswith(p) for p in prefixes):
-                try:
-                    total += (float(line.split()[-2]) + float(line.split()[-1])) * 1e6
-                except ValueError:
-                    return None
-                break
-        else:
-            return None
-    return total
+    for line in lines:
+        if re.match(pattern, line):
+            try:
+                return (float(line.split()[-2]) + float(line.split()[-1])) * 1e6
+            except ValueError:
+                return None
+    return None
 
 
 def cpu_baseline(layer, ratio, n_sample_rows, budget_s=30.0):
