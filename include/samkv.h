@@ -301,9 +301,10 @@ int samkv_query_attn(const void* q_tok, int32_t n_q_tok, const void* k_c, const 
  * chunk (no partial results, no merge), which takes as long as the causal problem's longest row tile, so the query
  * attention hides inside the causal one.  The recompute outputs are bit-identical to samkv_recompute_attn's; the query
  * outputs follow the same definition as samkv_query_attn's but sum the keys in one chunk instead of several, so they
- * agree with it to rounding (both within the stated precision), not bit for bit.  float32: one launch as well, with the
- * query attention's key chunks as in samkv_query_attn, bit-identical to the two calls.  Arguments as in the two calls; ws as for samkv_query_attn.  A caller
- * that updates the cache between the two attentions (samkv_kv_update) uses the separate calls. */
+ * agree with it to rounding (both within the stated precision), not bit for bit.  float32: one launch for both attentions,
+ * and a merge behind it where the query attention's keys are cut into chunks as in samkv_query_attn; bit-identical to the
+ * two calls.  Arguments as in the two calls; ws as for samkv_query_attn.  A caller that updates the cache between the two
+ * attentions (samkv_kv_update) uses the separate calls. */
 int samkv_recompute_query_attn(const void* q_rec, const void* q_tok, int32_t n_q_tok, const void* k_c, const void* v_c,
                                int32_t m_total, int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim, int32_t dtype,
                                float scale, float* rec_out, float* rec_lse, float* q_out, float* q_lse, void* ws,
@@ -313,7 +314,10 @@ int samkv_recompute_query_attn(const void* q_rec, const void* q_tok, int32_t n_q
  * cache and to query tokens 0..t (itself included), which is what an incremental prefill of the query
  * after the cached documents computes (Sec. 3.3, last paragraph).
  *   k_self, v_self  [Hkv][n_q_tok][d]  the query tokens' own K/V, dtype as the other tensors
- * Computed as two partial attentions (cache: no mask; self: causal) merged by their log-sum-exp.
+ * Computed as one partial attention per key chunk of the cache (no mask) and one over the own keys (causal), merged once
+ * by their log-sum-exp.  bf16: where all parts run in one launch (fewer than 512 query rows per KV head, or as many as
+ * rewriting V would not pay for, with at most 1024 own keys) V is read as stored and the weights are two bf16 terms, as in
+ * samkv_query_attn; otherwise as in samkv_recompute_attn.
  * Needs a workspace (samkv_workspace_bytes covers it). */
 int samkv_query_attn_self(const void* q_tok, int32_t n_q_tok, const void* k_c, const void* v_c,
                           int32_t m_total, const void* k_self, const void* v_self, int32_t n_q_heads,

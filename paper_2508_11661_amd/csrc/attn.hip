@@ -323,14 +323,15 @@ __global__ __launch_bounds__(256, 2) void k_attn_bf16_pair(AttnArgs ac, AttnArgs
 //     rescale of O becomes a rare side branch ahead of the block.
 // (2) Asynchronous tile loads.  K/V tiles travel from global memory straight into LDS
 //     (global_load_lds_dwordx4: no staging registers, no LDS store instructions) into a ring of three K
-//     slots and three V slots, two tiles ahead of their use, so a load has two full steps to land.
+//     slots and three V slots, two tiles ahead of their use, so a load has two full steps to land
+//     (KG = 2: two slots of each, one tile ahead).
 //
 // KG = 1: the eight waves hold 256 rows.  KG = 2, for short problems, whose longest row tile's chain of steps and not the
 // total work sets the duration: four row groups (128 rows) x two key groups.  A step stages 128 keys, each key group
 // takes 64, and the two partial results meet through LDS at the end.  The tiles are twice as large, so the ring has two
-// slots and a load one step to land.  Against the register-staged, not pipelined kernels that served these problems
-// before (pair calls): 32 heads x 1540 rows 49.8 -> 44.9 us, x 500 rows 21.0 -> 19.5, 16 heads x 3900 rows 92 -> 81,
-// 32 heads x 16 rows 14.1 -> 12.4; d = 64, 24 heads x 2600 rows 52 -> 46, x 3900 rows 93 -> 77.
+// slots and a load one step to land.  Against register-staged, not pipelined kernels with two key groups (pair calls): 32
+// heads x 1540 rows 49.8 -> 44.9 us, x 500 rows 21.0 -> 19.5, 16 heads x 3900 rows 92 -> 81; d = 64, 24 heads x 2600 rows
+// 52 -> 46, x 3900 rows 93 -> 77.  Which problems take which kernel: attn_bf16_shape.
 //
 // A wave-wide DMA instruction fills 1 KB of LDS contiguously (lane i -> base + 16 i), i.e. four 256-byte
 // rows (eight 128-byte rows at d = 64) with no room for padding, so the tiles are stored unpadded and XOR-swizzled instead: the 16-byte
@@ -346,10 +347,10 @@ __global__ __launch_bounds__(256, 2) void k_attn_bf16_pair(AttnArgs ac, AttnArgs
 // c ^ ((r >> 1) & 7), V chunk c at c ^ 4 ((r >> 1) & 1).  A wave needs about half the registers and LDS, so two
 // workgroups share a compute unit and overlap each other's products and weights: no software pipeline, whose second
 // set of scores would cost that (128 registers per wave).  Problems of few workgroups with two key groups take one per
-// compute unit and the pipeline instead (32 heads x 1200 rows: 24.7 -> 22.4 us).  What bounds it is the vector ALU: 133 instructions, 32 of
-// them exponentials, per 16 products.  Against the register-staged eight-wave kernel it replaces, whole pair calls: 24
-// heads x 6450 rows 185 -> 180 us, 32 x 4120 113 -> 105, 56 x 9000 689 -> 651, 32 x 20000 (causal call alone)
-// 1768 -> 1695 (0.97 PFLOP/s).
+// compute unit and the pipeline instead (32 heads x 1200 rows: 24.7 -> 22.4 us).  The vector ALU is its busiest unit: nine
+// vector instructions per product, issued in 55 % of the SIMD cycles, against 36 % for the matrix unit (24 heads over 8 x
+// 6450 rows).  Against a register-staged eight-wave kernel, whole pair calls: 24 heads x 6450 rows 185 -> 180 us, 32 x 4120
+// 113 -> 105, 56 x 9000 689 -> 651, 32 x 20000 (causal call alone) 1768 -> 1695 (0.97 PFLOP/s).
 template <int D, int KG, int WGS>  // WGS: workgroups per compute unit
 struct DmaCfg {
   static constexpr int NW = 8, RG = NW / KG, BQ = 32 * RG;   // waves, row groups, rows per workgroup
@@ -373,7 +374,7 @@ __device__ __forceinline__ void attn_bf16_dma_body(const AttnArgs a, int bx, int
   constexpr int TILE = C::TILE, NSLOT = C::NSLOT;
   constexpr float TAU = 8.f;
   extern __shared__ __attribute__((aligned(1024))) char smem[];
-  // K(j) in slot j % 3 at smem + slot * TILE; V(j) in slot j % 3 at smem + (3 + slot) * TILE
+  // K(j) in slot j % NSLOT at smem + slot * TILE; V(j) in slot j % NSLOT at smem + (NSLOT + slot) * TILE
 
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int rw = lane & 31, h = lane >> 5;
@@ -393,10 +394,9 @@ __device__ __forceinline__ void attn_bf16_dma_body(const AttnArgs a, int bx, int
   const int r = q0 + rg * 32 + rw;
   const int r_c = max(0, min(r, a.rows - 1));
   const int wave_first = q0 + rg * 32;
-  // A wave whose rows all lie past the last row (the ragged last row tile of a problem: 4120 rows are 16 tiles and
-  // 24 rows) computes nothing: no full tiles, no tail.  It still sends its share of the tile requests and meets the
-  // barriers.  The last row tile is the one with the longest key range, so this is the most expensive workgroup of
-  // every head, and its SIMDs are left to the waves that have rows.
+  // A wave all of whose rows lie before the first or past the last one (the ragged row tile of a problem: the first of a
+  // causal one, the last of another) computes nothing: no full tiles, no tail.  It still sends its share of the tile
+  // requests and meets the barriers; its SIMD is left to the waves that have rows.
   const bool has_rows = wave_first >= 0 && wave_first < a.rows;
   // Of the tiles' keys a wave takes 64: unmasked ones in its first n_full tiles, and at most one masked tile after them.
   const int lim = !has_rows ? 0 : CAUSAL ? min(wave_first + 1, span) : span;

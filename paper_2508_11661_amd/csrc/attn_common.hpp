@@ -10,7 +10,7 @@ namespace samkv {
 struct AttnArgs {
   const void* q;
   const void* k;
-  const void* v;           // half-precision copy of V (bf16 kernels)
+  const void* v;           // V, or its half-precision copy for the bf16 kernels that read one (every one but SPLIT)
   const float* v_unscale;  // per KV head: undoes the copy's scale
   float* out;
   float* lse;

@@ -11,8 +11,8 @@
 // What bounds it: the matrix unit, 64 cycles per product and 128 products per tile at d = 128.  A product needs so
 // little (a K chunk per 256 cycles, a V value per 64) that the operands come straight from L2 into registers, requested
 // up to 8 chunks or 32 values ahead (K in groups of four chunks, which together take whole 128-byte lines of their 32
-// rows: spread out, the lines left L1 between their four quarters): no LDS tiles, hence no barrier in the loop and no lockstep, and the two waves of a SIMD
-// (two workgroups per compute unit) fill each other's softmax, start and merge.
+// rows: spread out, the lines left L1 between their four quarters): no LDS tiles, hence no barrier in the loop and no
+// lockstep, and the two waves of a SIMD (two workgroups per compute unit) fill each other's softmax, start and merge.
 // Measured, 32 heads over 8 KV heads, d = 128: 2307 -> 203 us at M = 1540 (8.4 -> 96 TFLOP/s; the matrix unit is busy 70 %
 // of the cycles, the rest is what 6 workgroups per compute unit spend starting and merging), 133 TFLOP/s at M = 6144,
 // 137 at M = 12288, of 157 at the matrix unit's rate.  Tiles staged in LDS by asynchronous loads, two barriers per step:

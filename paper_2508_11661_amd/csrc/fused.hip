@@ -108,7 +108,9 @@ template <bool BF16, int D>
 hipError_t run_len(const ScoreLaunch& a, const SelectLaunch& sl, const QuerySrc& q, const PtrTable& k,
                    const IntTable& cu_len, const IntTable& cu_k, const GatherLaunch* ga, const PtrTable* v, hipStream_t s) {
   // 512 threads a row (256 make twice the passes over its keys, 1024 lose it again in the selection's barriers); above
-  // 1024 keys the threshold comes from histograms, as in launch_select (320 rows of 2048 keys with their gather: 50 -> 47 us)
+  // 1024 keys the threshold comes from histograms (320 rows of 2048 keys with their gather: 50 -> 47 us), at every number of
+  // rows: here a row's neighbours on the compute unit stream their K meanwhile (1280 rows of 4000 keys 358 -> 361 us, of 2000
+  // 185 -> 183, 20 rows of 8000 99 -> 75)
   if (a.max_len <= 1024) return run<BF16, D, 2, 512, false>(a, sl, q, k, cu_len, cu_k, ga, v, s);
   if (a.max_len <= 2048) return run<BF16, D, 4, 512, true>(a, sl, q, k, cu_len, cu_k, ga, v, s);
   if (a.max_len <= 4096) return run<BF16, D, 8, 512, true>(a, sl, q, k, cu_len, cu_k, ga, v, s);
