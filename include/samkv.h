@@ -284,7 +284,7 @@ int samkv_recompute_attn(const void* q_rec, const void* k_c, const void* v_c, in
  *   q_tok [Hq][n_q_tok][d]; out [Hq][n_q_tok][d], lse [Hq][n_q_tok] float32.
  * Arithmetic as in samkv_recompute_attn, with one difference for bf16 with fewer than 512 query rows per KV head
  * (G * n_q_tok < 512) or so few rows and keys that rewriting V would cost more than the products (G * n_q_tok * M * Hkv * d
- * up to some 3e9): V is read as stored and every softmax weight enters the second product as the sum of two bf16 terms
+ * up to 3e9 to 4e9): V is read as stored and every softmax weight enters the second product as the sum of two bf16 terms
  * (16 significant bits), on the bf16 matrix cores; no copy of V is made.  Long caches are cut into key chunks whose
  * partial results are merged by their log-sum-exp, in chunk order (deterministic).
  * ws: samkv_workspace_bytes(...) bytes, 256-byte aligned: the half-precision copy of V (bf16, when made) and the
