@@ -114,13 +114,15 @@ ScoreWs score_ws(int n_ctx, int hq, int hkv, int d) {
 struct SplitPlan { int n_split, chunk; size_t part_o, part_lse, bytes; };
 // `n_own` > 0: one more part, the query tokens' n_own own keys, follows; `own`: in the same launch (attn_self_in_kernel).
 SplitPlan plan_splits(int dtype, int n_batch, int rows, int m, int d, int n_own = 0, bool own = false) {
-  const int bq = dtype != SAMKV_BF16 ? 32 : own || attn_bf16_shape(0, n_batch, 1, rows, m, d) != AttnShape::kDma ? 128 : 256;
+  const AttnF32Shape f32 = attn_f32_shape(0, n_batch, rows, m, d);
+  const int bq = dtype != SAMKV_BF16 ? (f32 == AttnF32Shape::kPlain ? 32 : f32 == AttnF32Shape::kSplit ? 256 : 128)
+                 : own || attn_bf16_shape(0, n_batch, 1, rows, m, d) != AttnShape::kDma ? 128 : 256;
   const int bk = dtype == SAMKV_BF16 ? 64 : 128;
   const long long base = (long long)((rows + bq - 1) / bq) * n_batch;
   const int key_tiles = (m + bk - 1) / bk;
   // aim at as many workgroups as are resident at once: one per compute unit for the kernel of 256 rows at
   // d = 128, otherwise two; a second round of workgroups only adds partial results to merge
-  const int wg_target = bq == 256 && d == 128 ? 256 : 512;
+  const int wg_target = (bq == 256 && d == 128) || (dtype != SAMKV_BF16 && f32 != AttnF32Shape::kPlain) ? 256 : 512;
   long long want = (wg_target + base - 1) / base;
   // The own keys' workgroups come last.  With one chunk less they are resident beside the others, without they wait for
   // a free place: one less where longer chunks, m / (want - 1) - m / want keys, cost less than the own keys behind them.

@@ -1,0 +1,120 @@
+"""Float32 attention on products of half-precision terms, at the edges of its kernels: eight waves of 32 query rows, as 256
+rows of a workgroup (one stream of keys, 32 a step) or as 128 rows whose keys two groups of waves share (64 a step).  The
+sizes are beyond those that `attn_f32_shape` leaves to the float32 products.  The inputs that terms do not hold (infinities,
+NaN, magnitudes past 2^60, neighbours more than 2^12 apart) must come out as exactly as with float32 products."""
+import math
+
+import pytest
+
+from tests import test_gpu_attention_edges as E
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("m", [319, 320, 321, 351, 352, 353, 383, 384, 385])
+def test_recompute_keys2_edges(d, m):
+    """128 rows per workgroup: last row tiles and last steps of 1, 31, 32, 33, 63 and 64 keys."""
+    E.test_recompute_attention_shapes("f32", d, 72, 8, m)
+
+
+@pytest.mark.parametrize("d,hq,hkv,m", [
+    (128, 136, 8, 129), (64, 200, 8, 129), (128, 136, 17, 161), (128, 136, 8, 255), (128, 136, 8, 256),  # one row tile
+    (128, 400, 8, 65), (64, 400, 8, 96),                                                                # a quarter of one
+    (128, 200, 8, 257), (128, 192, 24, 289), (64, 256, 8, 321), (128, 128, 8, 513), (64, 96, 8, 1000),  # several
+    (128, 8, 8, 1700), (64, 6, 3, 2700),                                                                # few heads, keys2
+])
+def test_recompute(d, hq, hkv, m):
+    E.test_recompute_attention_shapes("f32", d, hq, hkv, m)
+
+
+@pytest.mark.parametrize("d,hq,hkv,lq,m", [
+    (128, 16, 2, 16, 8800), (128, 8, 2, 33, 9001), (64, 8, 1, 5, 75001), (64, 16, 4, 50, 4033),       # 128 rows
+    (128, 64, 16, 40, 3001), (64, 64, 16, 40, 3021), (128, 256, 256, 150, 70),                        # 256 rows
+])
+def test_query(d, hq, hkv, lq, m):
+    E.test_query_attention_shapes("f32", d, hq, hkv, lq, m)
+
+
+@pytest.mark.parametrize("d,hq,hkv,lq,m", [
+    (128, 64, 8, 4, 321), (64, 72, 8, 7, 385),       # query on float32 products: an odd number of units, and an even one
+    (128, 64, 8, 64, 600), (64, 64, 8, 96, 700),     # 128 rows for both
+    (128, 128, 8, 8, 700), (64, 128, 8, 40, 1100),   # 256 rows, and the query on either
+])
+def test_both_in_one_call(d, hq, hkv, lq, m):
+    E.test_both_attentions_in_one_call("f32", d, hq, hkv, lq, m)
+
+
+KINDS = ["k_inf", "k_past", "v_inf", "v_nan", "q_past", "k_rows", "k_chunks", "k_inside", "v_rows", "v_chunks", "v_far", "v_tiny",
+         "products", "zero"]
+
+
+@pytest.mark.parametrize("hq,m", [(72, 330), (136, 200)])  # 128 rows per workgroup, and 256
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("kind", KINDS)
+def test_odd_inputs(kind, d, hq, m):
+    import torch
+    from paper_2508_11661_amd import samkv as S
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    normal = lambda *s: torch.randn(s, device="cuda", generator=gen)
+    power = lambda lo, hi, *s: torch.exp2(torch.randint(lo, hi, s, device="cuda", generator=gen).float())
+    q, k, v = normal(hq, m, d), normal(1, m, d), normal(1, m, d)
+    bad = None  # a row and channel of V that is no number
+    if kind == "k_inf":
+        q[..., 5] = -q[..., 5].abs() - 0.1
+        k[0, 150, 5] = math.inf                               # a score of -inf for the rows behind it
+    if kind == "k_past":
+        q[..., 0], k[0, 100:140, 0] = 4.0, -2.0 ** 127        # -inf by overflow
+    if kind in ("v_inf", "v_nan"):
+        bad = (120, 7)
+        v[0, 120, 7] = -math.inf if kind == "v_inf" else math.nan
+    if kind == "q_past":
+        # its scores stay of order 10: at 2^70 x 2^-60 they reach 2^13, whose float32 rounding alone, 2^13 x 2^-24 = 5e-4,
+        # is past the bar
+        q[:, 170] *= 2.0 ** 70
+        k[0, :, :] *= 2.0 ** -70
+    if kind == "k_rows":
+        k *= power(-20, 3, 1, m, 1)
+    if kind == "k_chunks":
+        k *= power(-20, 3, 1, 1, d // 4).repeat_interleave(4, 2)
+    if kind == "k_inside":                                    # within what the terms hold
+        k *= power(-11, 0, 1, 1, d // 4).repeat_interleave(4, 2)
+        q *= power(-5, 5, 1, m, 1)
+    if kind == "v_rows":
+        v *= power(-30, 30, 1, m, 1)
+    if kind == "v_chunks":
+        v *= power(-24, 0, 1, 1, d // 4).repeat_interleave(4, 2)
+    if kind == "v_far":                                       # every four rows alike, far from the others
+        v *= power(-30, 0, 1, (m + 3) // 4, 1).repeat_interleave(4, 1)[:, :m]
+    if kind == "v_tiny":
+        v *= 2.0 ** -100
+    if kind == "products":
+        q *= 2.0 ** 55
+        k *= 2.0 ** -55
+    if kind == "zero":
+        v.zero_()
+    scale = d ** -0.5
+    s = (q.double() @ k[0].double().T)
+    s = torch.where(s < -3.4e38, -math.inf, s) * scale        # what float32 products overflow to
+    s.masked_fill_(torch.ones((m, m), device="cuda", dtype=torch.bool).triu(1), -math.inf)
+    lse_ref = torch.logsumexp(s, 2)
+    p = torch.exp(s - lse_ref[..., None])
+    vv = v[0].double()
+    if bad is not None:
+        vv[bad] = 0.0
+    ref = p @ vv
+    out, lse = torch.full((hq, m, d), 7.0, device="cuda"), torch.zeros((hq, m), device="cuda")
+    S.samkv_recompute_attn(q, k, v, scale, out, lse, None)
+    torch.cuda.synchronize()
+    got = out.double()
+    if bad is not None:
+        col = got[:, bad[0]:, bad[1]]                          # every row that sees it
+        assert (torch.isneginf(col) if kind == "v_inf" else torch.isnan(col)).all()
+        got[..., bad[1]] = ref[..., bad[1]]
+    # per row: the output's error against its largest value, 1e-4 as in the repository's float32 bar; channels that differ in
+    # magnitude are held to their own
+    per = d // 4 if kind == "v_chunks" else 1
+    err = (got - ref).abs().reshape(hq, m, per, -1).amax(3)
+    top = ref.abs().reshape(hq, m, per, -1).amax(3)
+    assert (err <= 1e-4 * top).all(), (err / top.clamp_min(1e-300)).max().item()
+    assert ((lse.double() - lse_ref).abs() <= 1e-4 * lse_ref.abs().clamp_min(1.0)).all()
