@@ -223,10 +223,10 @@ __device__ __forceinline__ uint32_t lanes_below(uint64_t mask, uint32_t n) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, n));
 }
 
-// Writes the kept positions of a row whose order keys sit in registers (keys of positions >= L are 0), ascending, to
-// out[0..k).  wsum is LDS scratch of the workgroup.
-template <int E, int NT>
-__device__ __forceinline__ void write_kept(const uint32_t (&key)[E], int L, Threshold th, int32_t* out, uint2* wsum) {
+// Emits the kept positions of a row whose order keys sit in registers (keys of positions >= L are 0): emit(place, position),
+// places 0 .. k - 1 in ascending order of the positions.  wsum is LDS scratch of the workgroup.
+template <int E, int NT, class Emit>
+__device__ __forceinline__ void write_kept(const uint32_t (&key)[E], int L, Threshold th, Emit emit, uint2* wsum) {
   constexpr int NW = NT / 64;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   uint32_t n_gt = 0, n_eq = 0, T = th.T;  // counts of the wave
@@ -267,7 +267,50 @@ __device__ __forceinline__ void write_kept(const uint32_t (&key)[E], int L, Thre
     const bool is_gt = p < L && key[e] > T, is_eq = p < L && key[e] == T;
     const uint64_t m_gt = __ballot(is_gt), m_eq = __ballot(is_eq);
     const uint32_t g = lanes_below(m_gt, gt), q = lanes_below(m_eq, eq);
-    if (is_gt || (is_eq && q < th.need)) out[g + (q < th.need ? q : th.need)] = p;
+    if (is_gt || (is_eq && q < th.need)) emit((int)(g + (q < th.need ? q : th.need)), p);
+    gt += __popcll(m_gt);
+    eq += __popcll(m_eq);
+  }
+}
+
+// Rows of up to 64 E keys by ONE wave that holds all of them, its e-th the position 64 e + lane: no barrier, no LDS.  Key `cand`
+// is kept if k keys reach it; a bit of the threshold takes a comparison and a popcount per key of the lane.
+template <int E>
+__device__ __forceinline__ Threshold threshold_in_wave(const uint32_t (&key)[E], int L, int k) {
+  if (k == 0) return {0xFFFFFFFFu, 0u};
+  uint32_t T = 0, n = (uint32_t)L;  // keys that reach T (padding keys are 0 and reach no candidate)
+#pragma unroll 1
+  for (uint32_t bit = 0x80000000u; bit != 0 && n != (uint32_t)k; bit >>= 1) {
+    const uint32_t cand = T | bit;
+    uint32_t c = 0;
+#pragma unroll
+    for (int e = 0; e < E; ++e) c += __popcll(__ballot(key[e] >= cand));
+    if (c >= (uint32_t)k) {
+      T = cand;
+      n = c;
+    }
+  }
+  if (n == (uint32_t)k) return {T, 0xFFFFFFFFu};
+  uint32_t above = 0;
+#pragma unroll
+  for (int e = 0; e < E; ++e) above += __popcll(__ballot(key[e] > T));
+  return {T, (uint32_t)k - above};
+}
+
+// The kept positions of such a row in ascending order: emit(place, position) for the keys e with own(e).
+template <int E, class Own, class Emit>
+__device__ __forceinline__ void emit_kept(const uint32_t (&key)[E], int L, Threshold th, Own own, Emit emit) {
+  const int lane = threadIdx.x & 63;
+  uint32_t gt = 0, eq = 0;
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    const int p = e * 64 + lane;
+    const bool is_gt = p < L && key[e] > th.T, is_eq = p < L && key[e] == th.T;
+    const uint64_t m_gt = __ballot(is_gt), m_eq = __ballot(is_eq);
+    if (own(e)) {
+      const uint32_t g = lanes_below(m_gt, gt), q = lanes_below(m_eq, eq);
+      if (is_gt || (is_eq && q < th.need)) emit((int)(g + (q < th.need ? q : th.need)), p);
+    }
     gt += __popcll(m_gt);
     eq += __popcll(m_eq);
   }

@@ -90,3 +90,59 @@ def test_fused_rows(dtype, d, length):
     S.samkv_gather(caches, b.idx, 0.2, b.k_c, b.v_c)
     for x in ("idx", "cu_k_dev", "k_c", "v_c"):
         assert torch.equal(getattr(a, x), getattr(b, x)), x
+
+
+WAVE_EDGES = [2, 127, 128, 129, 255, 256, 257, 511, 512, 513]
+
+
+@pytest.mark.parametrize("length", WAVE_EDGES)
+@pytest.mark.parametrize("pattern", ["distinct", "ties", "equal", "last_bit"])
+def test_rows_of_one_wave(length, pattern):
+    """Rows of up to 512 scores are selected by one wave: the edges of its keys per lane (2, 4, 8)."""
+    test_rows(length, pattern)
+
+
+@pytest.mark.parametrize("length", WAVE_EDGES)
+def test_shares_of_short_rows(length):
+    """Shares from nothing at all to everything, forced positions among them: a document may keep no position."""
+    import torch
+    from paper_2508_11661_amd import samkv as S
+    rng = np.random.default_rng(7 * length)
+    heads, lens = 3, [length] * 4
+    scores = np.stack([np.concatenate([_rows(p, length, rng) for p in ("distinct", "ties", "equal", "last_bit")]) for _ in range(heads)])
+    caches = S.Caches([torch.zeros((heads, n, 64), dtype=torch.bfloat16, device="cuda") for n in lens], None, heads)
+    dev = torch.from_numpy(scores).cuda()
+    for shares, n_sink, n_local in (([0.0, 0.5, 0.0, 1.0], 0, 0), ([0.3, 0.0, 1.0, 0.01], 1, 1)):
+        ks = [S.samkv_kept_count_mid(n, p, n_sink, n_local) for n, p in zip(lens, shares)]
+        idx = torch.full((heads, sum(ks)), -1, dtype=torch.int32, device="cuda")
+        S.samkv_topk_select_v(dev, caches, shares, n_sink, n_local, idx, None)
+        got = idx.cpu().numpy()
+        for g in range(heads):
+            for i, n in enumerate(lens):
+                o = sum(ks[:i])
+                assert np.array_equal(got[g, o:o + ks[i]], _want(scores[g, i * n:(i + 1) * n], ks[i], n_sink, n_local)), (g, i)
+
+
+@pytest.mark.parametrize("length", [64, 255, 256, 257, 511, 512, 513, 8192])
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f32", 64)])
+def test_fused_short_rows(length, dtype, d):
+    """Score, selection and compaction in one call at the edges of its selections, everything kept among the shares: the same
+    as the separate calls bit for bit."""
+    import torch
+    from paper_2508_11661_amd import samkv as S
+    dt = {"f32": torch.float32, "bf16": torch.bfloat16}[dtype]
+    gen = torch.Generator(device="cuda").manual_seed(length)
+    R = lambda *s: torch.randn(s, device="cuda", generator=gen).to(dt)
+    hkv, group, lens = 2, 2, [length, max(1, length - 3), max(1, length // 3)]
+    k, v = [R(hkv, n, d) for n in lens], [R(hkv, n, d) for n in lens]
+    k[0][:, length // 2:] = k[0][:, :1]                       # many equal scores
+    caches = S.Caches(k, v, hkv * group)
+    q_tok, q_loc = R(hkv * group, 5, d), R(len(lens), hkv * group, 7, d)
+    for ratio, n_sink, n_local in ((0.2, 0, 0), (1.0, 0, 0), (0.5, 4, 6)):
+        a, b = S.alloc_layer_buffers(caches, 5, ratio), S.alloc_layer_buffers(caches, 5, ratio)
+        S.samkv_score_select_gather(caches, q_tok, q_loc, ratio, n_sink, n_local, a.scores, a.idx, a.cu_k_dev, a.k_c, a.v_c, a.ws)
+        S.samkv_score(caches, q_tok, q_loc, b.scores, b.ws)
+        S.samkv_topk_select(b.scores, caches, ratio, n_sink, n_local, b.idx, b.cu_k_dev, b.ws)
+        S.samkv_gather(caches, b.idx, ratio, b.k_c, b.v_c)
+        for x in ("scores", "idx", "cu_k_dev", "k_c", "v_c"):
+            assert torch.equal(getattr(a, x), getattr(b, x)), (ratio, x)
