@@ -310,6 +310,16 @@ int samkv_recompute_query_attn(const void* q_rec, const void* q_tok, int32_t n_q
                                float scale, float* rec_out, float* rec_lse, float* q_out, float* q_lse, void* ws,
                                size_t ws_bytes, void* stream);
 
+/* samkv_score_select_gather followed by samkv_recompute_query_attn over the cache it has compacted, as one call: the whole
+ * path of a layer.  Arguments as in the two calls (m_total is what the ratio keeps); the results are the same bits.  bf16: the
+ * compaction also finds the largest magnitude of each KV head's kept V rows, which the half-precision copy of V is scaled by,
+ * so that V is read once less; that takes room in the workspace which samkv_workspace_bytes includes, and is left out
+ * where ws_bytes ends before it. */
+int samkv_hot_path(const samkv_caches* caches, const void* q_tok, int32_t n_q_tok, const void* q_loc, int32_t w_loc,
+                   const void* q_rec, float ratio, int32_t n_sink, int32_t n_local, float scale, float* scores, int32_t* idx,
+                   int32_t* cu_k_dev, int32_t* cu_k_host, void* k_c, void* v_c, float* rec_out, float* rec_lse, float* q_out,
+                   float* q_lse, void* ws, size_t ws_bytes, void* stream);
+
 /* The same prefill with the query's own keys and values: query token t attends to the whole compacted
  * cache and to query tokens 0..t (itself included), which is what an incremental prefill of the query
  * after the cached documents computes (Sec. 3.3, last paragraph).

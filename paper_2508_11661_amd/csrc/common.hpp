@@ -61,7 +61,14 @@ struct SelectLaunch {
 hipError_t launch_select(const SelectLaunch& a, const IntTable& cu_len, const IntTable& cu_k, hipStream_t s);
 
 constexpr int kFusedMaxLen = 8192;
+constexpr int kFusedWaves = 8;  // of a workgroup of launch_score_select
 constexpr int kFusedGatherMaxRows = 2048;  // (document, KV head) rows up to which the fused call also compacts in-kernel
+
+// whether launch_score_select compacts in its own kernel: with thousands of rows (many layers stacked as heads) the streaming
+// kernel is faster (0.84 against 0.91 ms at 5120 rows); below that the row's workgroup does it and a launch is saved
+inline bool score_select_gathers(int n_ctx, int hkv, int max_len) {
+  return max_len <= kFusedMaxLen && (long long)n_ctx * hkv <= kFusedGatherMaxRows;
+}
 
 hipError_t launch_block_scores(const float* scores, const IntTable& cu_len, const IntTable& cu_blk, int n_ctx, int hkv,
                                int total_len, int block, float* bscores, hipStream_t s);
@@ -84,7 +91,10 @@ struct GatherLaunch {
   const int32_t* idx;
   void* k_c;
   void* v_c;
+  uint32_t* v_max;  // null, or [Hkv][gather_v_parts]: the largest magnitudes of the bf16 V rows that a wave copies, for launch_v_prep
 };
+// Waves per KV head that write a v_max, by the kernel of launch_gather, or by launch_score_select's own (fused).
+int gather_v_parts(const GatherLaunch& a, const IntTable& cu_k, bool fused);
 hipError_t launch_gather(const GatherLaunch& a, const PtrTable& k, const PtrTable& v, const IntTable& cu_len,
                          const IntTable& cu_k, hipStream_t s);
 // Score and selection in one pass over K (rows of at most kFusedMaxLen tokens): a.scores may be null.  With `ga`
@@ -223,8 +233,9 @@ hipError_t launch_attn_merge(const AttnLaunch& a, hipStream_t s);
 // Half-precision copy of a bf16 V tensor [n_kv][m][d] for the attention kernels, one power-of-two scale per KV head.
 // part: [n_kv][v_prep_chunks(n_kv, m)] scratch words; unscale: [n_kv] factors that undo the scale.
 int v_prep_chunks(int n_kv, int m);
+// v_max: null, or [n_kv][n_v_max] bf16 magnitudes (bit patterns) whose largest is the head's.
 hipError_t launch_v_prep(const void* v, int n_kv, int m, int d, bool causal, void* v16, uint32_t* part, float* unscale,
-                         hipStream_t s);
+                         const uint32_t* v_max, int n_v_max, hipStream_t s);
 
 // Raises the dynamic-LDS limit of every attention kernel variant that needs it on the current device (once per device).
 hipError_t attn_prepare_device();

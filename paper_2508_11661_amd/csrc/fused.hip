@@ -26,11 +26,12 @@ template <bool BF16, int D, int E, int NT, int EA, bool GATHER>
 __global__ __launch_bounds__(NT) void k_score_select(PtrTable kt, PtrTable vt, IntTable cu_len, IntTable cu_k, const float* qsrc,
                                                      int heads, int group, int total_len, int m_total, int n_ctx, int n_sink,
                                                      int n_local, float* scores, int32_t* idx, int32_t* cu_k_dev, char* k_c,
-                                                     char* v_c) {
+                                                     char* v_c, uint32_t* v_max) {
   constexpr int EPL = BF16 ? 8 : 4;
   constexpr int LPR = D / EPL;
   constexpr int ROWS_PER_WAVE = (64 / LPR) * 8 * 2;
   constexpr int NW = NT / 64;
+  static_assert(NW == kFusedWaves, "waves that write a v_max");
   constexpr size_t ROW_BYTES = (size_t)D * (BF16 ? 2 : 4);
   extern __shared__ __attribute__((aligned(16))) char smem[];
   float* s_sc = reinterpret_cast<float*>(smem);  // the row's scores, then the selection's histograms
@@ -90,6 +91,7 @@ __global__ __launch_bounds__(NT) void k_score_select(PtrTable kt, PtrTable vt, I
     // LPR lanes copy one K row and one V row; U rows per thread in flight
     constexpr int RPP = NT / LPR, U = 4;
     const int rg = t / LPR;
+    uint32_t mx = 0;
     const char* vsrc = static_cast<const char*>(vt.p[i]) + (size_t)g * L * ROW_BYTES + sub * 16;
     const size_t out0 = ((size_t)g * m_total + cu_k.v[i]) * ROW_BYTES + sub * 16;
     for (int r0 = rg; r0 < k; r0 += RPP * U) {
@@ -102,6 +104,10 @@ __global__ __launch_bounds__(NT) void k_score_select(PtrTable kt, PtrTable vt, I
         xk[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(base + (size_t)pos * ROW_BYTES));
         xv[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(vsrc + (size_t)pos * ROW_BYTES));
       }
+      if (BF16) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) mx = bf16_max(mx, xv[u]);  // (rows past the last repeat it)
+      }
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int r = r0 + u * RPP;
@@ -111,6 +117,7 @@ __global__ __launch_bounds__(NT) void k_score_select(PtrTable kt, PtrTable vt, I
         }
       }
     }
+    if (BF16 && v_max != nullptr) write_max(v_max + ((size_t)g * n_ctx + i) * NW + wave, mx);
   }
 }
 
@@ -122,11 +129,11 @@ hipError_t run(const ScoreLaunch& a, const SelectLaunch& sl, const QuerySrc& q, 
   if (ga != nullptr)
     hipLaunchKernelGGL((k_score_select<BF16, D, E, NT, EA, true>), dim3(a.n_ctx, a.hkv), dim3(NT), lds, s, k, *v, cu_len, cu_k, q.q,
                        q.heads, q.group, a.total_len, sl.m_total, a.n_ctx, sl.n_sink, sl.n_local, a.scores, sl.idx,
-                       sl.cu_k_dev, static_cast<char*>(ga->k_c), static_cast<char*>(ga->v_c));
+                       sl.cu_k_dev, static_cast<char*>(ga->k_c), static_cast<char*>(ga->v_c), ga->v_max);
   else
     hipLaunchKernelGGL((k_score_select<BF16, D, E, NT, EA, false>), dim3(a.n_ctx, a.hkv), dim3(NT), lds, s, k, k, cu_len, cu_k, q.q,
                        q.heads, q.group, a.total_len, sl.m_total, a.n_ctx, sl.n_sink, sl.n_local, a.scores, sl.idx,
-                       sl.cu_k_dev, nullptr, nullptr);
+                       sl.cu_k_dev, nullptr, nullptr, nullptr);
   return hipGetLastError();
 }
 
@@ -161,9 +168,7 @@ hipError_t launch_score_select(const ScoreLaunch& a, const SelectLaunch& sl, con
   QuerySrc q;
   hipError_t e = launch_score_prologue(a, s, &q);
   if (e != hipSuccess) return e;
-  // With thousands of rows (many layers stacked as heads) the compaction is faster as its own streaming kernel
-  // (0.84 against 0.91 ms at 5120 rows); below that the row's workgroup does it and a launch is saved.
-  const GatherLaunch* in_kernel = (long long)a.n_ctx * a.hkv <= kFusedGatherMaxRows ? ga : nullptr;
+  const GatherLaunch* in_kernel = score_select_gathers(a.n_ctx, a.hkv, a.max_len) ? ga : nullptr;
   if (a.dtype == SAMKV_BF16)
     e = a.d == 128 ? run_len<true, 128>(a, sl, q, k, cu_len, cu_k, in_kernel, v, s)
                    : run_len<true, 64>(a, sl, q, k, cu_len, cu_k, in_kernel, v, s);

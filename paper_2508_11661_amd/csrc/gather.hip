@@ -7,6 +7,7 @@
 // step and runs STEPS steps with all of its loads issued before the first store.  The grid is
 // (row chunk, document, KV head), so the document's base pointers are uniform over a workgroup.
 #include "common.hpp"
+#include "kernels_core.hpp"
 
 namespace samkv {
 namespace {
@@ -37,7 +38,7 @@ int gather_steps(const GatherLaunch& a, const IntTable& cu_k, int heads) {
 
 template <int ROW_BYTES, int STEPS>
 __global__ __launch_bounds__(256) void k_gather(PtrTable kt, PtrTable vt, IntTable cu_len, IntTable cu_k, int m_total,
-                                                const int32_t* idx, char* k_c, char* v_c) {
+                                                const int32_t* idx, char* k_c, char* v_c, uint32_t* v_max) {
   constexpr int LPR = ROW_BYTES / 16;
   constexpr int RPS = 64 / LPR;  // rows per wave step
   constexpr int ROWS_PER_BLOCK = RPS * STEPS * 4;
@@ -46,7 +47,11 @@ __global__ __launch_bounds__(256) void k_gather(PtrTable kt, PtrTable vt, IntTab
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int sub = lane % LPR, rg = lane / LPR;
   const int r0 = blockIdx.x * ROWS_PER_BLOCK + wave * (RPS * STEPS);
-  if (r0 >= k_i) return;
+  uint32_t* mx_at = v_max == nullptr ? nullptr : v_max + (((size_t)g * gridDim.y + i) * gridDim.x + blockIdx.x) * 4 + wave;
+  if (r0 >= k_i) {
+    if (mx_at != nullptr && lane == 0) *mx_at = 0;
+    return;
+  }
   const int L = cu_len.v[i + 1] - cu_len.v[i];
   const char* ksrc = static_cast<const char*>(kt.p[i]) + (size_t)g * L * ROW_BYTES + sub * 16;
   const char* vsrc = static_cast<const char*>(vt.p[i]) + (size_t)g * L * ROW_BYTES + sub * 16;
@@ -73,6 +78,12 @@ __global__ __launch_bounds__(256) void k_gather(PtrTable kt, PtrTable vt, IntTab
       __builtin_nontemporal_store(xk[s], reinterpret_cast<u32x4*>(k_c + out0 + (size_t)r * ROW_BYTES));
       __builtin_nontemporal_store(xv[s], reinterpret_cast<u32x4*>(v_c + out0 + (size_t)r * ROW_BYTES));
     }
+  }
+  if (mx_at != nullptr) {  // (rows past the last repeat it)
+    uint32_t mx = 0;
+#pragma unroll
+    for (int s = 0; s < STEPS; ++s) mx = bf16_max(mx, xv[s]);
+    write_max(mx_at, mx);
   }
 }
 
@@ -209,11 +220,18 @@ hipError_t run(const GatherLaunch& a, const PtrTable& k, const PtrTable& v, cons
   const int steps = gather_steps<ROW_BYTES>(a, cu_k, a.hkv);
   auto kernel = steps == kStepsMany ? k_gather<ROW_BYTES, kStepsMany> : k_gather<ROW_BYTES, kStepsFew>;
   hipLaunchKernelGGL(kernel, gather_grid<ROW_BYTES>(a, steps, a.hkv), dim3(256), 0, s, k, v, cu_len, cu_k, a.m_total, a.idx,
-                     static_cast<char*>(a.k_c), static_cast<char*>(a.v_c));
+                     static_cast<char*>(a.k_c), static_cast<char*>(a.v_c), a.v_max);
   return hipGetLastError();
 }
 
 }  // namespace
+
+int gather_v_parts(const GatherLaunch& a, const IntTable& cu_k, bool fused) {
+  if (fused) return a.n_ctx * kFusedWaves;
+  const dim3 grid = a.row_bytes == 128 ? gather_grid<128>(a, gather_steps<128>(a, cu_k, a.hkv), a.hkv)
+                                       : gather_grid<256>(a, gather_steps<256>(a, cu_k, a.hkv), a.hkv);
+  return (int)(grid.x * grid.y) * 4;
+}
 
 hipError_t launch_gather(const GatherLaunch& a, const PtrTable& k, const PtrTable& v, const IntTable& cu_len,
                          const IntTable& cu_k, hipStream_t s) {

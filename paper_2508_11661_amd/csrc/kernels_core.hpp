@@ -36,6 +36,23 @@ __device__ __forceinline__ void unpack16(const u32x4& x, float* f) {
   }
 }
 
+// The largest bf16 magnitude (bit pattern) of the halves of x so far, in both halves of `mx`.
+__device__ __forceinline__ uint32_t bf16_max(uint32_t mx, const u32x4& x) {
+  typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+  u16x2 m = __builtin_bit_cast(u16x2, mx);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, x[e] & 0x7FFF7FFFu));
+  return __builtin_bit_cast(uint32_t, m);
+}
+// The wave's largest into *at, a word of its own (atomics of all waves on one word per head took longer than a pass over V: 5600
+// of them 45 us).
+__device__ __forceinline__ void write_max(uint32_t* at, uint32_t mx) {
+  mx = max(mx & 0xFFFFu, mx >> 16);
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) mx = max(mx, (uint32_t)__shfl_xor((int)mx, off));
+  if ((threadIdx.x & 63) == 0) *at = mx;
+}
+
 // The vector a KV head scores its document's keys with: the mean of `group` consecutive head vectors of D floats
 // (1 when the fold over the KV group has already been done, G when src holds Eq. 1 per query head).  The lane
 // takes its EPL channels.

@@ -18,6 +18,9 @@ namespace {
 
 constexpr size_t kAlign = 256;
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
+// samkv_hot_path: the largest V magnitudes that the waves of its compaction find, behind everything else in its workspace: at
+// most a word per wave of the fused kernel, or per 16 kept rows of the longest document and document
+size_t v_max_bytes(int n_ctx, int hkv, int m_total) { return align_up((size_t)hkv * n_ctx * (m_total / 16 + kFusedWaves) * 4); }
 // every kernel moves tensor rows with 16-byte vector accesses
 bool aligned16(const void* p) { return ((uintptr_t)p % 16) == 0; }
 
@@ -177,11 +180,12 @@ AttnWs attn_ws(int dtype, bool causal, int hkv, int rows_per_kv, int m, int d) {
 }
 
 // Runs the V preparation of a bf16 attention call into its workspace slice and points the launch at the copy.
-hipError_t prepare_v(AttnLaunch* a, const VPrepWs& vp, char* at, int hkv, hipStream_t s) {
+hipError_t prepare_v(AttnLaunch* a, const VPrepWs& vp, char* at, int hkv, hipStream_t s, const uint32_t* v_max = nullptr,
+                     int n_v_max = 0) {
   if (a->dtype != SAMKV_BF16 || !attn_bf16_reads_v16(*a)) return hipSuccess;
   float* unscale = reinterpret_cast<float*>(at + vp.unscale);
   const hipError_t e = launch_v_prep(a->v, hkv, a->m, a->d, a->causal != 0, at + vp.v16, reinterpret_cast<uint32_t*>(at + vp.part),
-                                     unscale, s);
+                                     unscale, v_max, n_v_max, s);
   a->v = at + vp.v16;
   a->v_unscale = unscale;
   return e;
@@ -252,7 +256,7 @@ size_t samkv_workspace_bytes(int32_t n_ctx, int32_t n_q_heads, int32_t n_kv_head
   const size_t f = self_ws(n_q_heads, n_kv_heads, head_dim, n_q_tok, m_total, SAMKV_F32).bytes;
   if (e > b) b = e;
   if (f > b) b = f;
-  return (a > b ? a : b) + kAlign;
+  return (a > b ? a : b) + v_max_bytes(n_ctx, n_kv_heads, m_total) + kAlign;
 }
 
 static int score_setup(const samkv_caches* caches, const void* q_tok, int32_t n_q_tok, const void* q_loc, int32_t w_loc,
@@ -319,42 +323,61 @@ int samkv_score(const samkv_caches* caches, const void* q_tok, int32_t n_q_tok, 
   return dev(launch_score(a, kt, s.cu_len, static_cast<hipStream_t>(stream)));
 }
 
-// samkv_score_select, and with k_c/v_c the compaction as well
-static int score_select_common(const samkv_caches* caches, const void* q_tok, int32_t n_q_tok, const void* q_loc,
-                               int32_t w_loc, float ratio, int32_t n_sink, int32_t n_local, float* scores, int32_t* idx,
-                               int32_t* cu_k_dev, int32_t* cu_k_host, bool gather, void* k_c, void* v_c, void* ws,
-                               size_t ws_bytes, void* stream) {
+// samkv_score_select, and with k_c/v_c the compaction as well: checked arguments, ready to launch
+struct ScoreSelect {
   Shape s;
   ScoreLaunch a;
-  PtrTable kt;
-  if (idx == nullptr) return SAMKV_EINVAL;
-  int rc = score_setup(caches, q_tok, n_q_tok, q_loc, w_loc, scores, ws, ws_bytes, &s, &a, &kt);
-  if (rc != SAMKV_OK) return rc;
-  if (scores == nullptr && s.max_len > kFusedMaxLen) return SAMKV_EINVAL;
+  PtrTable kt, vt;
   IntTable cu_k;
-  rc = kept_table(caches, ratio, n_sink, n_local, &cu_k);
-  if (rc != SAMKV_OK) return rc;
-  PtrTable vt;
+  SelectLaunch sl;
   GatherLaunch ga;
+  bool gather;
+};
+static int score_select_setup(const samkv_caches* caches, const void* q_tok, int32_t n_q_tok, const void* q_loc,
+                              int32_t w_loc, float ratio, int32_t n_sink, int32_t n_local, float* scores, int32_t* idx,
+                              int32_t* cu_k_dev, bool gather, void* k_c, void* v_c, void* ws, size_t ws_bytes, ScoreSelect* x) {
+  if (idx == nullptr) return SAMKV_EINVAL;
+  int rc = score_setup(caches, q_tok, n_q_tok, q_loc, w_loc, scores, ws, ws_bytes, &x->s, &x->a, &x->kt);
+  if (rc != SAMKV_OK) return rc;
+  const Shape& s = x->s;
+  if (scores == nullptr && s.max_len > kFusedMaxLen) return SAMKV_EINVAL;
+  rc = kept_table(caches, ratio, n_sink, n_local, &x->cu_k);
+  if (rc != SAMKV_OK) return rc;
+  const int32_t* cu = x->cu_k.v;
+  x->gather = gather;
   if (gather) {
     Shape s2;
     rc = check_caches(caches, true, true, &s2);  // V is read as well
     if (rc != SAMKV_OK) return rc;
     if (k_c == nullptr || v_c == nullptr || !aligned16(k_c) || !aligned16(v_c)) return SAMKV_EINVAL;
-    memset(&vt, 0, sizeof(vt));
-    for (int i = 0; i < s.n_ctx; ++i) vt.p[i] = caches->v[i];
+    memset(&x->vt, 0, sizeof(x->vt));
+    for (int i = 0; i < s.n_ctx; ++i) x->vt.p[i] = caches->v[i];
+    GatherLaunch& ga = x->ga;
     ga.n_ctx = s.n_ctx; ga.hkv = s.hkv; ga.row_bytes = s.d * (s.dtype == SAMKV_BF16 ? 2 : 4);
-    ga.m_total = cu_k.v[s.n_ctx]; ga.idx = idx; ga.k_c = k_c; ga.v_c = v_c;
+    ga.m_total = cu[s.n_ctx]; ga.idx = idx; ga.k_c = k_c; ga.v_c = v_c; ga.v_max = nullptr;
     ga.max_k = 0;
-    for (int i = 0; i < s.n_ctx; ++i) ga.max_k = cu_k.v[i + 1] - cu_k.v[i] > ga.max_k ? cu_k.v[i + 1] - cu_k.v[i] : ga.max_k;
+    for (int i = 0; i < s.n_ctx; ++i) ga.max_k = cu[i + 1] - cu[i] > ga.max_k ? cu[i + 1] - cu[i] : ga.max_k;
   }
-  if (cu_k_host != nullptr) memcpy(cu_k_host, cu_k.v, sizeof(int32_t) * (s.n_ctx + 1));
-  SelectLaunch sl;
+  SelectLaunch& sl = x->sl;
   sl.n_ctx = s.n_ctx; sl.hkv = s.hkv; sl.max_len = s.max_len; sl.total_len = s.total_len;
-  sl.m_total = cu_k.v[s.n_ctx]; sl.n_sink = n_sink; sl.n_local = n_local;
+  sl.m_total = cu[s.n_ctx]; sl.n_sink = n_sink; sl.n_local = n_local;
   sl.scores = scores; sl.idx = idx; sl.cu_k_dev = cu_k_dev;
-  return dev(launch_score_select(a, sl, kt, s.cu_len, cu_k, static_cast<hipStream_t>(stream), gather ? &ga : nullptr,
-                                 gather ? &vt : nullptr));
+  return SAMKV_OK;
+}
+
+static hipError_t launch(const ScoreSelect& x, int32_t* cu_k_host, hipStream_t s) {
+  if (cu_k_host != nullptr) memcpy(cu_k_host, x.cu_k.v, sizeof(int32_t) * (x.s.n_ctx + 1));
+  return launch_score_select(x.a, x.sl, x.kt, x.s.cu_len, x.cu_k, s, x.gather ? &x.ga : nullptr, x.gather ? &x.vt : nullptr);
+}
+
+static int score_select_common(const samkv_caches* caches, const void* q_tok, int32_t n_q_tok, const void* q_loc,
+                               int32_t w_loc, float ratio, int32_t n_sink, int32_t n_local, float* scores, int32_t* idx,
+                               int32_t* cu_k_dev, int32_t* cu_k_host, bool gather, void* k_c, void* v_c, void* ws,
+                               size_t ws_bytes, void* stream) {
+  ScoreSelect x;
+  const int rc = score_select_setup(caches, q_tok, n_q_tok, q_loc, w_loc, ratio, n_sink, n_local, scores, idx, cu_k_dev, gather,
+                                    k_c, v_c, ws, ws_bytes, &x);
+  return rc != SAMKV_OK ? rc : dev(launch(x, cu_k_host, static_cast<hipStream_t>(stream)));
 }
 
 int samkv_score_select(const samkv_caches* caches, const void* q_tok, int32_t n_q_tok, const void* q_loc, int32_t w_loc,
@@ -661,7 +684,7 @@ static int gather_common(const samkv_caches* caches, const Shape& s, const IntTa
   GatherLaunch a;
   a.n_ctx = s.n_ctx; a.hkv = s.hkv; a.row_bytes = s.d * (s.dtype == SAMKV_BF16 ? 2 : 4);
   a.m_total = cu_k.v[s.n_ctx]; a.idx = idx; a.k_c = k_c; a.v_c = v_c;
-  a.max_k = 0;
+  a.max_k = 0; a.v_max = nullptr;
   for (int i = 0; i < s.n_ctx; ++i) a.max_k = cu_k.v[i + 1] - cu_k.v[i] > a.max_k ? cu_k.v[i + 1] - cu_k.v[i] : a.max_k;
   return dev(launch_gather(a, kt, vt, s.cu_len, cu_k, static_cast<hipStream_t>(stream)));
 }
@@ -688,7 +711,7 @@ static int gather_q_common(const samkv_caches* caches, const Shape& s, const Int
   GatherLaunch a;
   a.n_ctx = s.n_ctx; a.hkv = s.hkv; a.row_bytes = s.d * (s.dtype == SAMKV_BF16 ? 2 : 4);
   a.m_total = cu_k.v[s.n_ctx]; a.idx = idx; a.k_c = q_rec; a.v_c = nullptr;
-  a.max_k = 0;
+  a.max_k = 0; a.v_max = nullptr;
   for (int i = 0; i < s.n_ctx; ++i) a.max_k = cu_k.v[i + 1] - cu_k.v[i] > a.max_k ? cu_k.v[i + 1] - cu_k.v[i] : a.max_k;
   return dev(launch_gather_q(a, qt, s.cu_len, cu_k, s.hq, static_cast<hipStream_t>(stream)));
 }
@@ -801,32 +824,77 @@ int samkv_query_attn(const void* q_tok, int32_t n_q_tok, const void* k_c, const 
   return dev(e);
 }
 
-int samkv_recompute_query_attn(const void* q_rec, const void* q_tok, int32_t n_q_tok, const void* k_c, const void* v_c,
-                               int32_t m_total, int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim, int32_t dtype,
-                               float scale, float* rec_out, float* rec_lse, float* q_out, float* q_lse, void* ws,
-                               size_t ws_bytes, void* stream) {
+// Both attentions: checked arguments, ready to launch.
+struct PairSetup {
+  AttnWs w;
+  AttnLaunch rec, qry;
+};
+static int pair_setup(const void* q_rec, const void* q_tok, int32_t n_q_tok, const void* k_c, const void* v_c, int32_t m_total,
+                      int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim, int32_t dtype, float scale, float* rec_out,
+                      float* rec_lse, float* q_out, float* q_lse, void* ws, size_t ws_bytes, PairSetup* x) {
   int rc = check_attn(q_rec, k_c, v_c, m_total, m_total, n_q_heads, n_kv_heads, head_dim, dtype, scale, rec_out, rec_lse);
   if (rc != SAMKV_OK) return rc;
   rc = check_attn(q_tok, k_c, v_c, n_q_tok, m_total, n_q_heads, n_kv_heads, head_dim, dtype, scale, q_out, q_lse);
   if (rc != SAMKV_OK) return rc;
   // the workspace of the query attention holds the prepared V behind its key-chunk partials; the causal attention
   // needs nothing else, so one preparation serves both
-  const AttnWs w = attn_ws(dtype, false, n_kv_heads, (n_q_heads / n_kv_heads) * n_q_tok, m_total, head_dim);
-  if (w.bytes > 0 && (ws == nullptr || ((uintptr_t)ws % kAlign) != 0 || ws_bytes < w.bytes)) return SAMKV_EWORKSPACE;
-  AttnLaunch rec = recompute_launch(q_rec, k_c, v_c, m_total, n_q_heads, n_kv_heads, head_dim, dtype, scale, rec_out, rec_lse);
-  AttnLaunch qry = query_launch(q_tok, n_q_tok, k_c, v_c, m_total, n_q_heads, n_kv_heads, head_dim, dtype, scale, q_out,
-                                q_lse, w.split, ws);
-  hipStream_t s = static_cast<hipStream_t>(stream);
-  hipError_t e = prepare_v(&rec, w.vp, static_cast<char*>(ws) + w.vp_at, n_kv_heads, s);
-  qry.v = rec.v;
-  qry.v_unscale = rec.v_unscale;
-  if (dtype == SAMKV_BF16) {
-    if (e == hipSuccess) e = launch_attn_bf16_pair(rec, qry, s);
-  } else {
-    if (e == hipSuccess) e = launch_attn_f32_pair(rec, qry, s);
-    if (e == hipSuccess && qry.n_split > 1) e = launch_attn_merge(qry, s);
+  x->w = attn_ws(dtype, false, n_kv_heads, (n_q_heads / n_kv_heads) * n_q_tok, m_total, head_dim);
+  if (x->w.bytes > 0 && (ws == nullptr || ((uintptr_t)ws % kAlign) != 0 || ws_bytes < x->w.bytes)) return SAMKV_EWORKSPACE;
+  x->rec = recompute_launch(q_rec, k_c, v_c, m_total, n_q_heads, n_kv_heads, head_dim, dtype, scale, rec_out, rec_lse);
+  x->qry = query_launch(q_tok, n_q_tok, k_c, v_c, m_total, n_q_heads, n_kv_heads, head_dim, dtype, scale, q_out, q_lse,
+                        x->w.split, ws);
+  return SAMKV_OK;
+}
+
+static hipError_t launch(PairSetup* x, void* ws, const uint32_t* v_max, int n_v_max, hipStream_t s) {
+  hipError_t e = prepare_v(&x->rec, x->w.vp, static_cast<char*>(ws) + x->w.vp_at, x->rec.n_batch / x->rec.batch_per_kv, s, v_max,
+                           n_v_max);
+  x->qry.v = x->rec.v;
+  x->qry.v_unscale = x->rec.v_unscale;
+  if (e != hipSuccess) return e;
+  if (x->rec.dtype == SAMKV_BF16) return launch_attn_bf16_pair(x->rec, x->qry, s);
+  e = launch_attn_f32_pair(x->rec, x->qry, s);
+  return e == hipSuccess && x->qry.n_split > 1 ? launch_attn_merge(x->qry, s) : e;
+}
+
+int samkv_recompute_query_attn(const void* q_rec, const void* q_tok, int32_t n_q_tok, const void* k_c, const void* v_c,
+                               int32_t m_total, int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim, int32_t dtype,
+                               float scale, float* rec_out, float* rec_lse, float* q_out, float* q_lse, void* ws,
+                               size_t ws_bytes, void* stream) {
+  PairSetup x;
+  const int rc = pair_setup(q_rec, q_tok, n_q_tok, k_c, v_c, m_total, n_q_heads, n_kv_heads, head_dim, dtype, scale, rec_out,
+                            rec_lse, q_out, q_lse, ws, ws_bytes, &x);
+  return rc != SAMKV_OK ? rc : dev(launch(&x, ws, nullptr, 0, static_cast<hipStream_t>(stream)));
+}
+
+int samkv_hot_path(const samkv_caches* caches, const void* q_tok, int32_t n_q_tok, const void* q_loc, int32_t w_loc,
+                   const void* q_rec, float ratio, int32_t n_sink, int32_t n_local, float scale, float* scores, int32_t* idx,
+                   int32_t* cu_k_dev, int32_t* cu_k_host, void* k_c, void* v_c, float* rec_out, float* rec_lse, float* q_out,
+                   float* q_lse, void* ws, size_t ws_bytes, void* stream) {
+  ScoreSelect x;
+  int rc = score_select_setup(caches, q_tok, n_q_tok, q_loc, w_loc, ratio, n_sink, n_local, scores, idx, cu_k_dev, true, k_c,
+                              v_c, ws, ws_bytes, &x);
+  if (rc != SAMKV_OK) return rc;
+  PairSetup p;
+  rc = pair_setup(q_rec, q_tok, n_q_tok, k_c, v_c, x.cu_k.v[x.s.n_ctx], x.s.hq, x.s.hkv, x.s.d, x.s.dtype, scale, rec_out,
+                  rec_lse, q_out, q_lse, ws, ws_bytes, &p);
+  if (rc != SAMKV_OK) return rc;
+  // The attentions scale V by its heads' largest magnitudes: the compaction, which has the rows in its registers, finds them
+  // (10 x 1024 tokens, 32 heads: the preparation of V 10.0 -> 4.7 us).  Its words lie behind both steps' scratch; a workspace
+  // that ends before them leaves the search to the attentions.
+  const size_t score_bytes = score_ws(x.s.n_ctx, x.s.hq, x.s.hkv, x.s.d).bytes;
+  const size_t at = align_up(score_bytes > p.w.bytes ? score_bytes : p.w.bytes);
+  int n_v_max = 0;
+  if (x.s.dtype == SAMKV_BF16) {
+    const int n = gather_v_parts(x.ga, x.cu_k, score_select_gathers(x.s.n_ctx, x.s.hkv, x.s.max_len));
+    if (ws_bytes >= at + (size_t)x.s.hkv * n * 4) {
+      n_v_max = n;
+      x.ga.v_max = reinterpret_cast<uint32_t*>(static_cast<char*>(ws) + at);
+    }
   }
-  return dev(e);
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  const hipError_t e = launch(x, cu_k_host, s);
+  return dev(e != hipSuccess ? e : launch(&p, ws, x.ga.v_max, n_v_max, s));
 }
 
 int samkv_query_attn_self(const void* q_tok, int32_t n_q_tok, const void* k_c, const void* v_c, int32_t m_total,

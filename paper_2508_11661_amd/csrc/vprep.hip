@@ -10,6 +10,8 @@
 //   k_v_absmax   largest |v| per (KV head, row chunk), as the integer bit pattern of the bf16 magnitude
 //   k_v_to_f16   reduces a head's chunk maxima (every workgroup of the head does so redundantly), converts its own
 //                row chunk, and workgroup 0 of the head writes the factor that undoes the scale
+// A caller that has copied the rows itself may know the maxima already (samkv_hot_path: the gathers find them): then the
+// second launch is all there is.
 // Heads of at most kOneLaunchPieces 16-byte pieces (short compacted caches, where a launch costs more than the work)
 // take ONE launch instead: k_v_prep_small, a few large workgroups per head, each of which finds the head's maximum
 // itself (the head is read from L2 a few times over) and converts its share.
@@ -71,13 +73,13 @@ __global__ __launch_bounds__(NT) void k_v_absmax(const u32x4* __restrict__ v, ui
   if (threadIdx.x == 0) part[(size_t)g * n_chunks + c] = mx;
 }
 
-__global__ __launch_bounds__(NT) void k_v_to_f16(const u32x4* __restrict__ v, const uint32_t* __restrict__ part,
+__global__ __launch_bounds__(NT) void k_v_to_f16(const u32x4* __restrict__ v, const uint32_t* __restrict__ part, int n_part,
                                                  u32x4* __restrict__ v16, float* __restrict__ unscale, long long total,
                                                  long long per, int n_kv, int n_chunks, bool keep) {
   __shared__ uint32_t lds[4];
   const auto [g, c] = v_chunk(keep, n_kv, n_chunks);
   uint32_t mx = 0;
-  for (int i = threadIdx.x; i < n_chunks; i += NT) mx = max(mx, part[(size_t)g * n_chunks + i]);
+  for (int i = threadIdx.x; i < n_part; i += NT) mx = max(mx, part[(size_t)g * n_part + i]);
   mx = block_max_u32(mx, lds);
   // mx is the bf16 bit pattern of the head's largest magnitude: exponent field in bits 7..14.  The shift puts that
   // magnitude into [2^14, 2^15); it is kept inside +-113 so that both 2^shift and 2^-shift are normal floats.
@@ -88,15 +90,22 @@ __global__ __launch_bounds__(NT) void k_v_to_f16(const u32x4* __restrict__ v, co
   const u32x4* src = v + (size_t)g * total;
   u32x4* dst = v16 + (size_t)g * total;
   const long long begin = (long long)c * per, end = min(total, begin + per);
-  for (long long i = begin + threadIdx.x; i < end; i += NT) {
-    const u32x4 w = __builtin_nontemporal_load(src + i);
-    u32x4 o;
+  constexpr int U = 4;  // loads in flight per thread
+  for (long long i0 = begin + threadIdx.x; i0 < end; i0 += U * NT) {
+    u32x4 w[U];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const f16x2 h = {(_Float16)__builtin_ldexpf(bf16_lo(w[e]), shift), (_Float16)__builtin_ldexpf(bf16_hi(w[e]), shift)};
-      o[e] = __builtin_bit_cast(uint32_t, h);
+    for (int u = 0; u < U; ++u) w[u] = __builtin_nontemporal_load(src + min(i0 + u * NT, end - 1));
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const long long i = i0 + u * NT;
+      u32x4 o;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const f16x2 h = {(_Float16)__builtin_ldexpf(bf16_lo(w[u][e]), shift), (_Float16)__builtin_ldexpf(bf16_hi(w[u][e]), shift)};
+        o[e] = __builtin_bit_cast(uint32_t, h);
+      }
+      if (i < end) dst[i] = o;
     }
-    dst[i] = o;
   }
 }
 
@@ -162,9 +171,9 @@ int v_prep_chunks(int n_kv, int m) {
 }
 
 hipError_t launch_v_prep(const void* v, int n_kv, int m, int d, bool causal, void* v16, uint32_t* part, float* unscale,
-                         hipStream_t s) {
+                         const uint32_t* v_max, int n_v_max, hipStream_t s) {
   const long long total = (long long)m * d * 2 / 16;  // 16-byte pieces per head
-  if (total <= kOneLaunchPieces) {
+  if (v_max == nullptr && total <= kOneLaunchPieces) {
     const int c1 = (int)((total + kSmallChunk - 1) / kSmallChunk);
     const int per1 = kSmallChunk;
     const long long most = n_kv % 8 == 0 ? 56ll << 20 : n_kv % 4 == 0 ? 24ll << 20 : 0;
@@ -177,14 +186,19 @@ hipError_t launch_v_prep(const void* v, int n_kv, int m, int d, bool causal, voi
   const long long per = (total + n_chunks - 1) / n_chunks;
   const bool keep = total * 16 * n_kv <= (24ll << 20);  // of the 32 MB of L2
   const dim3 grid((unsigned)n_kv * n_chunks);
+  if (v_max != nullptr) {
+    hipLaunchKernelGGL(k_v_to_f16, grid, dim3(NT), 0, s, static_cast<const u32x4*>(v), v_max, n_v_max, static_cast<u32x4*>(v16),
+                       unscale, total, per, n_kv, n_chunks, keep);
+    return hipGetLastError();
+  }
   if (keep)
     hipLaunchKernelGGL(k_v_absmax<true>, grid, dim3(NT), 0, s, static_cast<const u32x4*>(v), part, total, per, n_kv, n_chunks);
   else
     hipLaunchKernelGGL(k_v_absmax<false>, grid, dim3(NT), 0, s, static_cast<const u32x4*>(v), part, total, per, n_kv, n_chunks);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_v_to_f16, grid, dim3(NT), 0, s, static_cast<const u32x4*>(v), part, static_cast<u32x4*>(v16), unscale,
-                     total, per, n_kv, n_chunks, keep);
+  hipLaunchKernelGGL(k_v_to_f16, grid, dim3(NT), 0, s, static_cast<const u32x4*>(v), part, n_chunks,
+                     static_cast<u32x4*>(v16), unscale, total, per, n_kv, n_chunks, keep);
   return hipGetLastError();
 }
 

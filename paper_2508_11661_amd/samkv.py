@@ -21,7 +21,7 @@ EXPORTS = ("samkv_strerror", "samkv_kept_count", "samkv_kept_count_mid", "samkv_
            "samkv_score", "samkv_score_noalloc", "samkv_score_select", "samkv_score_select_gather", "samkv_topk_select", "samkv_topk_select_v", "samkv_gather_v",
            "samkv_gather_q_v", "samkv_block_scores", "samkv_block_workspace_bytes", "samkv_block_select",
            "samkv_block_select_filter", "samkv_block_filter_count", "samkv_block_select_count", "samkv_gather_g", "samkv_gather_q_g",
-           "samkv_gather", "samkv_gather_q", "samkv_recompute_attn", "samkv_query_attn", "samkv_recompute_query_attn", "samkv_query_attn_self",
+           "samkv_gather", "samkv_gather_q", "samkv_recompute_attn", "samkv_query_attn", "samkv_recompute_query_attn", "samkv_hot_path", "samkv_query_attn_self",
            "samkv_kv_update", "samkv_peak_mfma_bf16", "samkv_peak_mfma_bf16_data", "samkv_peak_copy", "samkv_peak_read")
 SAMKV_OVERWRITE, SAMKV_FUSION = 0, 1
 
@@ -94,6 +94,8 @@ def _load() -> ctypes.CDLL:
     lib.samkv_query_attn.argtypes = [vp, i32, vp, vp, i32, i32, i32, i32, i32, f32, vp, vp, vp, sz, vp]
     lib.samkv_recompute_query_attn.restype = ctypes.c_int
     lib.samkv_recompute_query_attn.argtypes = [vp, vp, i32, vp, vp, i32, i32, i32, i32, i32, f32, vp, vp, vp, vp, vp, sz, vp]
+    lib.samkv_hot_path.restype = ctypes.c_int
+    lib.samkv_hot_path.argtypes = [cp, vp, i32, vp, i32, vp, f32, i32, i32, f32, vp, vp, vp, ctypes.POINTER(i32), vp, vp, vp, vp, vp, vp, vp, sz, vp]
     lib.samkv_query_attn_self.restype = ctypes.c_int
     lib.samkv_query_attn_self.argtypes = [vp, i32, vp, vp, i32, vp, vp, i32, i32, i32, i32, f32, vp, vp, vp, sz, vp]
     lib.samkv_peak_mfma_bf16.restype = ctypes.c_int
@@ -508,22 +510,45 @@ def alloc_layer_buffers(caches: Caches, n_q_tok: int, ratio: float) -> LayerBuff
     )
 
 
+def _hot_path(caches: Caches, q_tok: torch.Tensor, q_loc: Optional[torch.Tensor], q_rec: torch.Tensor, ratio: float,
+              n_sink: int, n_local: int, scale: float, b: LayerBuffers) -> None:
+    """samkv_score_select_gather and samkv_recompute_query_attn in one call of the library, with the checks of both."""
+    n_q_tok = int(q_tok.shape[1])
+    w_loc = int(q_loc.shape[2]) if q_loc is not None else 0
+    hkv, d = caches.n_kv_heads, caches.head_dim
+    m = sum(samkv_kept_count(n, ratio) for n in caches.lens)
+    assert b.scores is None or (b.scores.dtype == torch.float32 and tuple(b.scores.shape) == (hkv, caches.total_len))
+    assert b.idx.dtype == torch.int32 and tuple(b.idx.shape) == (hkv, m)
+    for x in (b.k_c, b.v_c):
+        assert x.is_contiguous() and tuple(x.shape) == (hkv, m, d) and x.dtype == q_tok.dtype
+    hq = q_rec.shape[0]
+    assert tuple(q_rec.shape) == (hq, m, d) and tuple(q_tok.shape) == (hq, n_q_tok, d)
+    assert tuple(b.rec_out.shape) == (hq, m, d) and tuple(b.rec_lse.shape) == (hq, m)
+    assert tuple(b.q_out.shape) == (hq, n_q_tok, d) and tuple(b.q_lse.shape) == (hq, n_q_tok)
+    for x in (b.rec_out, b.rec_lse, b.q_out, b.q_lse):
+        assert x.dtype == torch.float32
+    _check(_lib.samkv_hot_path(ctypes.byref(caches.c), _ptr(q_tok), n_q_tok, _ptr(q_loc), w_loc, _ptr(q_rec), ratio, n_sink,
+                               n_local, scale, _ptr(b.scores), _ptr(b.idx), _ptr(b.cu_k_dev), None, _ptr(b.k_c), _ptr(b.v_c),
+                               _ptr(b.rec_out), _ptr(b.rec_lse), _ptr(b.q_out), _ptr(b.q_lse), _ptr(b.ws),
+                               b.ws.numel() * b.ws.element_size(), _stream()), "samkv_hot_path")
+
+
 def hot_path(caches: Caches, q_tok: torch.Tensor, q_loc: Optional[torch.Tensor], q_rec: torch.Tensor,
              ratio: float, scale: float, buf: LayerBuffers, n_sink: int = 0, n_local: int = 0,
              fused: bool = True) -> None:
     """One pass of the whole hot path of a layer: score, select, gather, recompute, query attention.  `fused`
-    scores, selects and compacts in one call and runs both attentions in one call (same kept positions, same bits);
-    otherwise the five separate calls."""
-    if fused:
+    one call of the library scores, selects, compacts and runs both attentions (same kept positions, same bits); otherwise the
+    five separate calls."""
+    if fused and q_rec.shape[0] == caches.n_q_heads and _dtype_code(q_rec.dtype) == caches.dtype:
+        _hot_path(caches, q_tok, q_loc, q_rec, ratio, n_sink, n_local, scale, buf)
+    elif fused:  # query states of other heads than the caches were made for
         samkv_score_select_gather(caches, q_tok, q_loc, ratio, n_sink, n_local, buf.scores, buf.idx, buf.cu_k_dev,
                                   buf.k_c, buf.v_c, buf.ws)
+        samkv_recompute_query_attn(q_rec, q_tok, buf.k_c, buf.v_c, scale, buf.rec_out, buf.rec_lse, buf.q_out, buf.q_lse,
+                                   buf.ws)
     else:
         samkv_score(caches, q_tok, q_loc, buf.scores, buf.ws)
         samkv_topk_select(buf.scores, caches, ratio, n_sink, n_local, buf.idx, buf.cu_k_dev, buf.ws)
         samkv_gather(caches, buf.idx, ratio, buf.k_c, buf.v_c)
-    if fused:
-        samkv_recompute_query_attn(q_rec, q_tok, buf.k_c, buf.v_c, scale, buf.rec_out, buf.rec_lse, buf.q_out, buf.q_lse,
-                                   buf.ws)
-    else:
         samkv_recompute_attn(q_rec, buf.k_c, buf.v_c, scale, buf.rec_out, buf.rec_lse, buf.ws)
         samkv_query_attn(q_tok, buf.k_c, buf.v_c, scale, buf.q_out, buf.q_lse, buf.ws)

@@ -226,3 +226,25 @@ def test_binding_refuses_to_run_without_library(tmp_path, monkeypatch):
     with pytest.raises(ImportError):
         mod._load()
     importlib.reload(mod)
+
+
+def test_hot_path_reports_both_steps_errors(S):
+    """samkv_hot_path refuses what its two calls refuse, before any launch."""
+    fake, none = ctypes.c_void_p(0x1000), None
+    big = 1 << 30
+
+    def call(c=None, q_tok=fake, n_q_tok=4, w_loc=0, q_loc=none, q_rec=fake, ratio=0.5, scale=0.1, scores=fake, idx=fake, k_c=fake,
+             v_c=fake, rec_out=fake, q_lse=fake, ws=fake, ws_bytes=big):
+        c = _caches(S) if c is None else c
+        return S._lib.samkv_hot_path(ctypes.byref(c), q_tok, n_q_tok, q_loc, w_loc, q_rec, ratio, 0, 0, scale, scores, idx, none,
+                                     none, k_c, v_c, rec_out, fake, fake, q_lse, ws, ws_bytes, none)
+
+    odd = ctypes.c_void_p(0x1008)
+    for bad in (dict(q_tok=none), dict(n_q_tok=0), dict(q_loc=fake), dict(ratio=0.0), dict(idx=none), dict(k_c=none), dict(v_c=odd),
+                dict(q_rec=none), dict(q_rec=odd), dict(rec_out=none), dict(q_lse=none), dict(scale=0.0), dict(c=_caches(S, v=False)),
+                dict(c=_caches(S, lens=(8, 9000)), scores=none)):
+        assert call(**bad) == -1, bad
+    for bad in (dict(c=_caches(S, d=96)), dict(c=_caches(S, dtype=7))):
+        assert call(**bad) == -2, bad
+    for bad in (dict(ws=none), dict(ws_bytes=64), dict(ws=ctypes.c_void_p(0x1010))):
+        assert call(**bad) == -3, bad
