@@ -359,8 +359,10 @@ struct DmaCfg {
   static constexpr int ROWB = D * 2, CPR = ROWB / 16;        // bytes and 16-byte chunks per row
   static constexpr int TILE = BKT * ROWB;                    // unpadded
   static constexpr int MERGE = 64 * (D / 2 + 2) * 4;         // one wave's outputs, maxima and sums
-  static constexpr int LDS_BYTES = 2 * NSLOT * TILE;
+  static constexpr bool QLDS = KG == 2 && WGS == 1;                // the query rows come through LDS (dma_query)
+  static constexpr int QROWS = 2 * NSLOT * TILE, LDS_BYTES = QROWS + (QLDS ? BQ * ROWB : 0);  // they lie behind the ring
   static constexpr int NI = TILE / 1024 / NW, RPI = 1024 / ROWB;  // requests per wave and tile, rows per request
+  static constexpr int NQ = BQ * ROWB / 1024 / NW;                // requests per wave for the query rows
   static constexpr bool PIPE = WGS == 1;                          // software pipeline inside a wave (1)
   static __device__ __forceinline__ int kswz(int row) { return D == 128 ? row & 15 : (row >> 1) & 7; }
   static __device__ __forceinline__ int vswz(int row) { return D == 128 ? 4 * (row & 3) : 4 * ((row >> 1) & 1); }
@@ -392,7 +394,6 @@ __device__ __forceinline__ void attn_bf16_dma_body(const AttnArgs a, int bx, int
 
   const int rg = KG == 1 ? wave : wave % C::RG, kg = KG == 1 ? 0 : __builtin_amdgcn_readfirstlane(wave / C::RG);
   const int r = q0 + rg * 32 + rw;
-  const int r_c = max(0, min(r, a.rows - 1));
   const int wave_first = q0 + rg * 32;
   // A wave all of whose rows lie before the first or past the last one (the ragged row tile of a problem: the first of a
   // causal one, the last of another) computes nothing: no full tiles, no tail.  It still sends its share of the tile
@@ -405,8 +406,8 @@ __device__ __forceinline__ void attn_bf16_dma_body(const AttnArgs a, int bx, int
   const bool has_tail = has_rows && tail_key < span && (!CAUSAL || tail_key <= wave_first + 31);
 
   bf16x8 bq[ND];
-  {
-    const char* qp = static_cast<const char*>(a.q) + ((size_t)batch * a.rows + r_c) * D * 2 + h * 16;
+  if constexpr (!C::QLDS) {
+    const char* qp = static_cast<const char*>(a.q) + ((size_t)batch * a.rows + max(0, min(r, a.rows - 1))) * ROWB + h * 16;
 #pragma unroll
     for (int dc = 0; dc < ND; ++dc) bq[dc] = *reinterpret_cast<const bf16x8*>(qp + dc * 32);
   }
@@ -455,6 +456,24 @@ __device__ __forceinline__ void attn_bf16_dma_body(const AttnArgs a, int bx, int
         const uint32_t off = (uint32_t)(min(row, last) * (D * 2) + src_chunk * 16);
         dma16(tp, off, slot + wave_rows + i * 1024);
       }
+    }
+  };
+  // The query rows come the same way with two key groups and one workgroup per compute unit, as whole rows with the swizzle
+  // of K, and are read as fragments once they have landed.  Loaded as fragments from memory, 16 bytes from each of 32 rows
+  // per instruction and by both key groups, every line is requested eight times, and short workgroups wait for that
+  // (32 heads x 1540 rows, pair calls: 45.2 -> 42.8 us, x 700 22.8 -> 21.5, 64 x 1000 44.2 -> 40.7; d = 64, 24 x 1200 21.7 ->
+  // 21.3).  The other shapes keep the fragment loads, which are in flight beside the tiles: 256 rows, d = 128, 32 heads x 4120
+  // 1 % faster, x 2500 1.3 % slower, 64 x 20480 0.8 % slower; two workgroups per compute unit, d = 64, 24 x 2600 1 % faster,
+  // 32 x 4120 1.7 % slower.
+  auto dma_query = [&]() {
+    const int first = max(q0, 0);
+    const char* qp = static_cast<const char*>(a.q) + ((size_t)batch * a.rows + first) * ROWB;
+    const uint32_t to = __builtin_amdgcn_readfirstlane((uint32_t)(C::QROWS + C::NQ * wave * 1024));
+#pragma unroll
+    for (int i = 0; i < C::NQ; ++i) {
+      const int row = C::RPI * (C::NQ * wave + i) + lane / CPR;
+      const int src = max(q0 + row, 0) - first;  // rows before the first or past the last one re-read that one
+      dma16(qp, (uint32_t)(min(src, a.rows - 1 - first) * ROWB + ((lane % CPR) ^ C::kswz(row)) * 16), to + i * 1024);
     }
   };
   // where this wave's keys of a tile start
@@ -511,6 +530,11 @@ __device__ __forceinline__ void attn_bf16_dma_body(const AttnArgs a, int bx, int
   auto kfrags = [&](const char* ks, int kb, bf16x8 (&ak)[ND]) {
 #pragma unroll
     for (int dc = 0; dc < ND; ++dc) ak[dc] = *reinterpret_cast<const bf16x8*>(ks + kaddr[dc] + kb * 32 * ROWB);
+  };
+  auto qfrags = [&]() {
+    const char* qs = smem + C::QROWS + rg * 32 * ROWB;
+#pragma unroll
+    for (int dc = 0; dc < ND; ++dc) bq[dc] = *reinterpret_cast<const bf16x8*>(qs + kaddr[dc]);
   };
   // V^T fragments of key group g (16 keys) for the NV blocks of O^T: two transposing reads each
   auto vfrags = [&](const char* vs, int g, f16x8 (&av)[NV]) {
@@ -623,9 +647,9 @@ __device__ __forceinline__ void attn_bf16_dma_body(const AttnArgs a, int bx, int
       __builtin_amdgcn_s_barrier();
     }
   } else {
-    // ---- prologue.  Three slots: K(0), V(0), K(1) must have landed, V(1), K(2) stay in flight.  Two slots: K(0) must
-    //      have landed before the first scores, V(0) and K(1) after them.
+    // ---- prologue: Q and K(0) must have landed before the first scores, V(0) and K(1) before step 0
     constexpr int AHEAD_K = NSLOT, AHEAD_V = NSLOT - 1;  // step t requests K(t + AHEAD_K), V(t + AHEAD_V)
+    if constexpr (C::QLDS) dma_query();
     dma_tile(kbase, 0, kslot_off(0), goff_k, false);
     dma_tile(vbase, 0, vslot_off(0), goff_v, true);
     if (n_tiles > 1) dma_tile(kbase, 1, kslot_off(1), goff_k, false);
@@ -633,15 +657,19 @@ __device__ __forceinline__ void attn_bf16_dma_body(const AttnArgs a, int bx, int
       if (n_tiles > 1) dma_tile(vbase, 1, vslot_off(1), goff_v, true);
       if (n_tiles > 2) dma_tile(kbase, 2, kslot_off(2), goff_k, false);
     }
-    if (n_tiles > 2 || (NSLOT == 2 && n_tiles > 1)) __builtin_amdgcn_s_waitcnt(0x0F70 | 2 * NI);
-    else if (n_tiles > 1 || NSLOT == 2) __builtin_amdgcn_s_waitcnt(0x0F70 | NI);
-    else __builtin_amdgcn_s_waitcnt(0x0F70);
+    if (NSLOT == 3 && n_tiles > 2) __builtin_amdgcn_s_waitcnt(0x0F70 | 4 * NI);
+    else if (NSLOT == 3 && n_tiles > 1) __builtin_amdgcn_s_waitcnt(0x0F70 | 3 * NI);
+    else if (n_tiles > 1) __builtin_amdgcn_s_waitcnt(0x0F70 | 2 * NI);
+    else __builtin_amdgcn_s_waitcnt(0x0F70 | NI);
     __builtin_amdgcn_s_barrier();
+    if constexpr (C::QLDS) qfrags();
     f32x16 sA[2], sB[2];
     scores(kslot(0), sA);
-    // K(0) has been read by every wave before step 0 refills its slot: the reads' arrival is waited for here (lgkmcnt(0),
-    // with two slots vmcnt(0) too), because the products that use them may be scheduled behind the barrier
-    __builtin_amdgcn_s_waitcnt(NSLOT == 2 ? 0x0070 : 0xC07F);
+    // K(0) has been read by every wave before step 0 refills its slot: the reads' arrival is waited for here (lgkmcnt(0)),
+    // because the products that use them may be scheduled behind the barrier
+    if (NSLOT == 3 && n_tiles > 2) __builtin_amdgcn_s_waitcnt(0x0070 | 2 * NI);
+    else if (NSLOT == 3 && n_tiles > 1) __builtin_amdgcn_s_waitcnt(0x0070 | NI);
+    else __builtin_amdgcn_s_waitcnt(0x0070);
     __builtin_amdgcn_s_barrier();
 
     // step `tile`: S(tile) is in sc; computes S(tile + 1) into sn and adds tile's V contribution
