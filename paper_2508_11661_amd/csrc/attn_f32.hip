@@ -268,7 +268,7 @@ hipError_t run_pair(const AttnLaunch& c, const AttnLaunch& q, hipStream_t s) {
 // numbers all 2^-12 or more below the scale's magnitude, a four of V rows 2^-8 below `unit`.  The wave that meets one raises a
 // flag, and the whole workgroup starts again with float32 products (attn_f32_unit).
 //   What bounds it: the matrix unit and the device's power limit (M = 6850, 32 heads: 1100 us, 920 with all inputs zero), for short
-// problems the chain of steps.  32 heads over 8 KV heads, d = 128, float32 products -> these: M = 700 53 -> 39 us, 1540 178 -> 80,
+// problems the chain of steps.  32 heads over 8 KV heads, d = 128, float32 products -> these: M = 700 53 -> 38 us, 1540 178 -> 80,
 // 4120 1077 -> 403, 6850 2913 -> 1100 (350 TFLOP/s); 24 heads, d = 64, M = 1540 75 -> 49, 6450 1019 -> 459.
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 

@@ -537,9 +537,9 @@ def _hot_path(caches: Caches, q_tok: torch.Tensor, q_loc: Optional[torch.Tensor]
 def hot_path(caches: Caches, q_tok: torch.Tensor, q_loc: Optional[torch.Tensor], q_rec: torch.Tensor,
              ratio: float, scale: float, buf: LayerBuffers, n_sink: int = 0, n_local: int = 0,
              fused: bool = True) -> None:
-    """One pass of the whole hot path of a layer: score, select, gather, recompute, query attention.  `fused`
-    one call of the library scores, selects, compacts and runs both attentions (same kept positions, same bits); otherwise the
-    five separate calls."""
+    """One pass of the whole hot path of a layer: score, select, gather, recompute, query attention.  With
+    `fused`, one call of the library scores, selects, compacts and runs both attentions (same kept positions, same bits);
+    otherwise the five separate calls."""
     if fused and q_rec.shape[0] == caches.n_q_heads and _dtype_code(q_rec.dtype) == caches.dtype:
         _hot_path(caches, q_tok, q_loc, q_rec, ratio, n_sink, n_local, scale, buf)
     elif fused:  # query states of other heads than the caches were made for
