@@ -601,7 +601,7 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs a, int bx, int by
 #pragma unroll
       for (int j = 0; j < 16; ++j) s[j] += sl[j];
 #pragma unroll
-      for (int g = 0; g < 4; ++g) cg[g] = cq * fk[g];
+      for (int g = 0; g < 4; ++g) cg[g] = fmaxf(cq * fk[g], 0x1p-126f);  // not 0, which would make NaN of a masked score
     }
     if (masked) {
       const int n_ok = (CAUSAL ? min(kv_end, r + 1) : kv_end) - key0 - 4 * h;

@@ -118,3 +118,58 @@ def test_odd_inputs(kind, d, hq, m):
     top = ref.abs().reshape(hq, m, per, -1).amax(3)
     assert (err <= 1e-4 * top).all(), (err / top.clamp_min(1e-300)).max().item()
     assert ((lse.double() - lse_ref).abs() <= 1e-4 * lse_ref.abs().clamp_min(1.0)).all()
+
+
+def _reference(q, k, v, scale, causal):
+    """float64, every head of one KV head: outputs and log-sum-exp"""
+    import torch
+    s = (q.double() @ k[0].double().T) * scale
+    if causal:
+        s.masked_fill_(torch.ones(s.shape[1:], device="cuda", dtype=torch.bool).triu(1), -math.inf)
+    lse = torch.logsumexp(s, 2)
+    return torch.exp(s - lse[..., None]) @ v[0].double(), lse
+
+
+def _run(q, k, v, scale, causal):
+    import torch
+    from paper_2508_11661_amd import samkv as S
+    out, lse = torch.full_like(q, math.nan), torch.full(q.shape[:2], math.nan, device="cuda")
+    if causal:
+        S.samkv_recompute_attn(q, k, v, scale, out, lse, None)
+    else:
+        ws = torch.empty((S.samkv_workspace_bytes(1, q.shape[0], 1, q.shape[2], q.shape[1], k.shape[1]),), dtype=torch.uint8,
+                         device="cuda")
+        S.samkv_query_attn(q, k, v, scale, out, lse, ws)
+    torch.cuda.synchronize()
+    return out, lse
+
+
+# heads, rows, keys of a problem on 128 and on 256 rows per workgroup, the last step and row tile ragged
+SHAPES = {"causal128": (72, 330, 330), "causal256": (136, 200, 200), "query128": (8, 33, 12001), "query256": (136, 300, 3001)}
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("kind", ["zero", "zero_rows", "zero_rows_zero_keys", "tiny"])
+def test_scores_that_vanish(kind, d, shape):
+    """Products so small that the factor which undoes the operands' scales passes below float32: uniform weights, as the masked
+    scores of a diagonal or ragged tile must not meet a factor of zero.  Outputs of float32 rounding: 2^-24 per weight and sum."""
+    import torch
+    hq, rows, m = SHAPES[shape]
+    gen = torch.Generator(device="cuda").manual_seed(11)
+    normal = lambda *s: torch.randn(s, device="cuda", generator=gen)
+    q, k, v = normal(hq, rows, d), normal(1, m, d), normal(1, m, d)
+    if kind == "zero":
+        q.zero_(), k.zero_()
+    if kind in ("zero_rows", "zero_rows_zero_keys"):
+        q[:, ::3] = 0.0
+        k *= 1e-4
+    if kind == "zero_rows_zero_keys":
+        k[:, :70] = 0.0
+    if kind == "tiny":
+        q *= 2.0 ** -70
+        k *= 2.0 ** -70
+    out, lse = _run(q, k, v, d ** -0.5, shape.startswith("causal"))
+    ref, lse_ref = _reference(q, k, v, d ** -0.5, shape.startswith("causal"))
+    assert ((out.double() - ref).norm() <= 4e-6 * ref.norm()).item()
+    assert ((lse.double() - lse_ref).abs().max() <= 4e-6).item()
