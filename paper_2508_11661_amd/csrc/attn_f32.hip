@@ -331,7 +331,7 @@ constexpr int kHoldLds = 0x47F;  // LDS accesses may not be moved across such a 
 // whether the largest magnitude m of some numbers that are scaled by e is too large, or so small that they lose bits
 __device__ __forceinline__ bool outside(float m, uint32_t e) {
   const uint32_t u = __float_as_uint(m);
-  return u - 1u < ((e - kExpSpan) << 23) - 1u || u >= (e + kExpRoom) << 23;
+  return u - 1u < ((e - kExpSpan) << 23) - 1u || u >= min(e + kExpRoom, 255u) << 23;
 }
 
 template <int D, int NKG, bool CAUSAL>

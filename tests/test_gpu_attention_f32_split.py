@@ -173,3 +173,24 @@ def test_scores_that_vanish(kind, d, shape):
     ref, lse_ref = _reference(q, k, v, d ** -0.5, shape.startswith("causal"))
     assert ((out.double() - ref).norm() <= 4e-6 * ref.norm()).item()
     assert ((lse.double() - lse_ref).abs().max() <= 4e-6).item()
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("value", [math.inf, -math.inf, math.nan])
+def test_infinity_behind_a_large_value(value, d, shape):
+    """An infinity or NaN of V that follows, in the rows that a wave stages, a number of 2^126, so that no larger scale exists: it
+    comes out as itself.  (The other numbers are small enough for a sum of 3000 and within reach of that scale.)"""
+    import torch
+    hq, rows, m = SHAPES[shape]
+    gen = torch.Generator(device="cuda").manual_seed(12)
+    normal = lambda *s: torch.randn(s, device="cuda", generator=gen)
+    q, k, v = normal(hq, rows, d), normal(1, m, d), normal(1, m, d)
+    v *= 2.0 ** 119
+    v[0, 20, 3] = 2.0 ** 126
+    v[0, 150, 7] = value
+    causal = shape.startswith("causal")
+    out, lse = _run(q, k, v, d ** -0.5, causal)
+    col = out[:, 150 if causal else 0:, 7]
+    assert (torch.isnan(col) if math.isnan(value) else col == value).all()
+    assert torch.isfinite(lse).all()
