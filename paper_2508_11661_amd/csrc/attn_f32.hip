@@ -247,29 +247,30 @@ hipError_t run_pair(const AttnLaunch& c, const AttnLaunch& q, hipStream_t s) {
   return hipGetLastError();
 }
 
-// ---------------------------------------------------------------- products of half-precision terms
-// The half-precision matrix instructions do sixteen times the work of the float32 ones.  A float32 number x, scaled by a power
-// of two, is the sum of two half-precision terms, x = hi + lo with lo = half(x - hi), to 2^-23 of x, and a product of two such
-// numbers is hi hi' + hi lo' + lo hi' to 2^-22: three products, accumulated in float32, of which a sum takes 24 roundings at
-// d = 128 where the float32 instruction takes 64.  Errors against 64 bits over the sizes below: 3.2e-7 to 7.9e-7 of the
-// outputs' norm, 5.7e-7 to 1.6e-6 with float32 products; largest difference of a log-sum-exp 2.9e-6 to 6.5e-6, 7.3e-6 to
-// 1.2e-5.
+// ---------------------------------------------------------------- products of bf16 terms
+// The bf16 matrix instructions do sixteen times the work of the float32 ones.  A float32 number x is the sum of three bf16
+// terms, x = x1 + x2 + x3 with x1 = bf16(x), x2 = bf16(x - x1), x3 = bf16(x - x1 - x2): each holds eight more bits and bf16 has
+// float32's exponents, so the sum is x itself, whatever its neighbours are.  Of the nine products of two such numbers the six
+// whose size is 2^-16 or more are taken, small ones first and the largest in an accumulator of its own where scores are summed;
+// the others, x2 y3, x3 y2 and x3 y3, are below 2^-25 of the product.  The sums are float32, with fewer roundings than the
+// float32 instruction makes.  Weights and V are multiplied by 2^24 before they are split, so that the last bit of the smallest
+// one is still a bf16 number; a term of K or Q that is too small for one moves a score by less than 2^-126 x 2^60 x d.
+//   Against 64 bits the errors are below those of float32 products on the inputs tried (72 heads x 700 rows, error over the norm,
+// float32 products / these: Gaussian 3.1e-7 / 1.7e-7; channels scaled apart 1.2e-6 / 4.7e-7; a key without V that takes all but
+// e^-20 of the weight 2.6e-6 / 1.1e-6; a channel of V 2^-24 of the others, over its own norm, 4.4e-7 / 2.4e-7).  Two
+// half-precision terms and three products took 0.6 of the time, but the absolute end of their range showed in the last two:
+// 1.4e-3 and 1.9e-4.
+//   The terms leave out infinities, NaN and magnitudes whose sums might pass float32's range, 2^60 in K and Q and 2^48 in V: the
+// wave that meets one raises a flag, and the whole workgroup starts again with float32 products (attn_f32_unit).
 //   Eight waves of 32 query rows.  NKG = 1: 256 rows, one stream of keys, 32 a step.  NKG = 2, for short problems: 128 rows,
 // whose keys two groups of waves share, 64 a step; their results meet in LDS at the end.
-//   Staging: a step's K and V rows come as float32 into registers a step ahead; the next step turns them into two planes of
-// terms per tensor in LDS (double-buffered, one barrier per step), between the products of its scores, whose matrix
-// instructions leave room for five vector instructions each.  Planes and fragments are laid out and read as in attn.hip.
-//   Scales: a wave stages four consecutive rows of a key group (or two such fours) and scales all of them alike, K and V apart,
-// by the largest magnitude of the last rows that did not fit the scale in use; a lane whose numbers leave its range, most of
-// them only by the rows' first ones, makes the wave look for a new one.  The scales of a step's fours stand beside the planes:
-// a register of scores or weights belongs to one four.  A weight is multiplied by its four's V scale over the largest one met
-// so far, `unit`, before it is split, and the accumulator is in those units.  Query rows have a scale each.
-//   Numbers that the terms would not hold: an infinity or NaN, magnitudes whose scores might pass float32's range, a lane's
-// numbers all 2^-12 or more below the scale's magnitude, a four of V rows 2^-8 below `unit`.  The wave that meets one raises a
-// flag, and the whole workgroup starts again with float32 products (attn_f32_unit).
-//   What bounds it: the matrix unit and the device's power limit (M = 6850, 32 heads: 1100 us, 920 with all inputs zero), for short
-// problems the chain of steps.  32 heads over 8 KV heads, d = 128, float32 products -> these: M = 700 53 -> 38 us, 1540 178 -> 80,
-// 4120 1077 -> 403, 6850 2913 -> 1100 (350 TFLOP/s); 24 heads, d = 64, M = 1540 75 -> 49, 6450 1019 -> 459.
+//   Staging: K and V rows come as float32 into registers a step ahead and are turned into three planes of terms per tensor in
+// LDS.  There is one buffer of each: V(t) is written between the products of the scores of step t, K(t + 1) between those of
+// its outputs, a barrier behind each.  The third term of the query rows stays in LDS, which leaves the registers for the
+// fragments.  Planes and fragments are laid out and read as in attn.hip.
+//   What bounds it: the matrix unit and the device's power limit (1.2 PFLOP/s of bf16 products at M = 6850), for short problems
+// the chain of steps.  32 heads over 8 KV heads, d = 128, float32 products -> these: M = 1540 176 -> 127 us, 4120 1080 -> 661, 6850
+// 2913 -> 1870 (206 TFLOP/s); 24 heads, d = 64, M = 6450 1012 -> 721.
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
 template <int D, int NKG>
@@ -277,61 +278,50 @@ struct SplitCfg {
   static constexpr int NW = 8, RG = NW / NKG, BQ = 32 * RG;   // waves, row groups, rows per workgroup
   static constexpr int BK = 32, BKT = BK * NKG;               // keys per wave and per workgroup in a step
   static constexpr int ROWB = D * 2;                          // bytes of a row in a plane
-  static constexpr int PLANE = BKT * ROWB, BUF = 4 * PLANE;   // K high, K low, V high, V low
-  static constexpr int SCALES = 2 * BUF;                      // [buffer][key group][K, V][half-wave][4] factors that undo the scales
-  static constexpr int FLAGS = SCALES + 2 * NKG * 16 * 4;     // [buffer] the tile needs float32 products
-  static constexpr int QROWS = NKG == 1 ? 2 * BUF + 1024 : BUF;  // the query rows on their way to registers: not where the first tile goes
-  static constexpr int MERGE = 64 * (D / 2 + 4) * 4;          // one wave's outputs, maxima, sums and units
+  static constexpr int PLANE = BKT * ROWB;                    // three planes of K, then three of V
+  static constexpr int VAT = 3 * PLANE, Q3 = 6 * PLANE;       // the query rows' third terms: [row group][fragment][lane]
+  static constexpr int FLAGS = Q3 + RG * 32 * ROWB;           // [step parity] a step's numbers need float32 products
+  // the query rows on their way to registers, eight of each wave: where its third terms will be, or V's first planes
+  static constexpr int QTURN = NKG == 1 ? Q3 : VAT, QTURN_WAVE = NKG == 1 ? 32 * ROWB : 8 * D * 4;
+  static constexpr int MERGE = 64 * (D / 2 + 2) * 4;          // one wave's outputs, maxima and sums
   static constexpr int TURN = (NKG == 1 ? 8 : 32) * (D * 4 + 16);
   static constexpr int END = NKG == 1 ? NW * TURN : RG * (MERGE > TURN ? MERGE : TURN);
   static constexpr int TILES = FLAGS + 16 > END ? FLAGS + 16 : END, PLAIN = 2 * F32Cfg<D>::LDS_BYTES;
   static constexpr int LDS_BYTES = TILES > PLAIN ? TILES : PLAIN;
-  static_assert(QROWS + NW * 16 * D * 4 <= (NKG == 1 ? LDS_BYTES : SCALES), "room for 16 query rows of each wave");
+  static_assert(QTURN_WAVE >= 8 * D * 4 && NW * QTURN_WAVE <= (NKG == 1 ? FLAGS - Q3 : Q3 - VAT), "room for the query rows");
   // staging: lanes per row, rows per load, rows and loads per wave
   static constexpr int LPR = D / 4, RPI = 64 / LPR, RW = BKT / NW, NI = RW / RPI;
   static __device__ __forceinline__ int kswz(int row) { return D == 128 ? row & 15 : (row >> 1) & 7; }
   static __device__ __forceinline__ int vswz(int row) { return D == 128 ? 4 * (row & 3) : 4 * ((row >> 1) & 1); }
 };
 
-// x0 s and x1 s, s a power of two, as the sum of two half-precision terms each
-__device__ __forceinline__ void split2(float x0, float x1, float s, uint32_t* hi, uint32_t* lo) {
-  const f16x2 h = {(_Float16)(x0 * s), (_Float16)(x1 * s)};
-  uint32_t hw = __builtin_bit_cast(uint32_t, h);
-  asm("" : "+v"(hw));  // one packed conversion, whose halves the next line reads
-  const f16x2 g = __builtin_bit_cast(f16x2, hw);
-  const f16x2 l = {(_Float16)fmaf(x0, s, -(float)g[0]), (_Float16)fmaf(x1, s, -(float)g[1])};
-  *hi = hw;
-  *lo = __builtin_bit_cast(uint32_t, l);
+// x0 and x1 as the sums of three bf16 terms each, a pair of terms per word
+__device__ __forceinline__ void split3(float x0, float x1, uint32_t (&w)[3]) {
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    const bf16x2 b = {(__bf16)x0, (__bf16)x1};
+    w[i] = __builtin_bit_cast(uint32_t, b);
+    asm("" : "+v"(w[i]));  // one packed conversion, whose halves the next lines read
+    if (i < 2) {
+      x0 -= bf16_lo(w[i]);
+      x1 -= bf16_hi(w[i]);
+    }
+  }
 }
 
-template <int CTRL>
-__device__ __forceinline__ uint32_t dpp_max(uint32_t v) {
-  return max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, true));
-}
-__device__ __forceinline__ uint32_t wave_max(uint32_t v) {
-  v = dpp_max<0xB1>(v);
-  v = dpp_max<0x4E>(v);
-  v = dpp_max<0x141>(v);
-  v = dpp_max<0x140>(v);
-  const auto a = __builtin_amdgcn_permlane16_swap(v, v, false, false);
-  v = max(a[0], a[1]);
-  const auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-  return __builtin_amdgcn_readfirstlane(max(b[0], b[1]));
-}
-__device__ __forceinline__ float abs_max(const f32x4& x) {  // NaN wins
-  const float m = __builtin_elementwise_maximum(__builtin_fabsf(x[0]), __builtin_fabsf(x[1]));
-  return __builtin_fabsf(__builtin_elementwise_maximum(__builtin_elementwise_maximum(m, __builtin_fabsf(x[2])), __builtin_fabsf(x[3])));
-}
-
-// Numbers whose largest magnitude has the biased exponent e are multiplied by 2^(kExpScale - 127 - e), which puts that
-// magnitude into [2^12, 2^13); a later one may be up to 2^kExpRoom times as large.
-constexpr uint32_t kExpScale = 266, kExpUnscale = 12, kExpLow = 13, kExpHigh = 127 + 60, kExpRoom = 3, kExpSpan = 12;
-constexpr float kUnitSpan = 0x1p-8f;  // see above: fours of V rows and `unit`
+constexpr float kTermsEnd = 0x1p60f, kTermsEndV = 0x1p48f, kTermScale = 0x1p24f;  // see above
 constexpr int kHoldLds = 0x47F;  // LDS accesses may not be moved across such a scheduling barrier
-// whether the largest magnitude m of some numbers that are scaled by e is too large, or so small that they lose bits
-__device__ __forceinline__ bool outside(float m, uint32_t e) {
-  const uint32_t u = __float_as_uint(m);
-  return u - 1u < ((e - kExpSpan) << 23) - 1u || u >= min(e + kExpRoom, 255u) << 23;
+__device__ __forceinline__ float abs_max(float m, const f32x4& x) {  // NaN wins
+#pragma unroll
+  for (int e = 0; e < 4; ++e) m = __builtin_elementwise_maximum(m, __builtin_fabsf(x[e]));
+  return m;
+}
+
+// x, with what is computed from it computed anew: kept across steps, the addresses of all fragments would not fit the registers.
+template <class T>
+__device__ __forceinline__ T fresh(T x) {
+  asm volatile("" : "+v"(x));
+  return x;
 }
 
 template <int D, int NKG, bool CAUSAL>
@@ -368,174 +358,110 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs a, int bx, int by
   // ---- staging
   f32x4 rk[NI], rv[NI];
   const int srow = wave * C::RW + lane / C::LPR, scol = lane % C::LPR;
-  auto load_tile = [&](int j) {
-    const int k0 = j * BKT;
-    const char* kt = kbase + (size_t)k0 * (D * 4);
-    const char* vt = vbase + (size_t)k0 * (D * 4);
-    const int last = a.m - 1 - kv_begin - k0;
-    if (last >= BKT - 1) {
+  // (steps and rows past the last are read as that one; without a branch, which would wait for the loads to merge registers)
+  const int last_row = a.m - 1 - kv_begin;
+  auto load_rows = [&](const char* base, int j, f32x4 (&x)[NI]) {
+    const int row = min(j, n_tiles - 1) * BKT + srow;
 #pragma unroll
-      for (int i = 0; i < NI; ++i) {
-        const uint32_t off = (uint32_t)((srow + i * C::RPI) * (D * 4) + scol * 16);
-        rk[i] = *reinterpret_cast<const f32x4*>(kt + off);
-        rv[i] = *reinterpret_cast<const f32x4*>(vt + off);
-      }
-    } else {
-#pragma unroll
-      for (int i = 0; i < NI; ++i) {
-        const uint32_t off = (uint32_t)(min(srow + i * C::RPI, last) * (D * 4) + scol * 16);
-        rk[i] = *reinterpret_cast<const f32x4*>(kt + off);
-        rv[i] = *reinterpret_cast<const f32x4*>(vt + off);
-      }
-    }
+    for (int i = 0; i < NI; ++i)
+      x[i] = *reinterpret_cast<const f32x4*>(base + (uint32_t)(min(row + i * C::RPI, last_row) * (D * 4) + scol * 16));
   };
   // where the first of its numbers go; the swizzle of the others' rows enters by XOR, as their row bits are its own
   const uint32_t kst = (uint32_t)(srow * ROWB + (((scol >> 1) ^ C::kswz(srow)) * 16) + 8 * (scol & 1));
-  const uint32_t vst = (uint32_t)(srow * ROWB + (((scol >> 1) ^ C::vswz(srow)) * 16) + 8 * (scol & 1));
-  float* scales = reinterpret_cast<float*>(smem + C::SCALES);
+  const uint32_t vst = (uint32_t)(C::VAT + srow * ROWB + (((scol >> 1) ^ C::vswz(srow)) * 16) + 8 * (scol & 1));
   int* flags = reinterpret_cast<int*>(smem + C::FLAGS);
-  uint32_t ek = kExpLow, ev = kExpLow;  // the biased exponents by which this wave scales its rows of K and of V
-  bool odd_rows = false;
-  float sk, sv;
-  auto check_tile = [&]() {
-    float mk[NI], mv[NI];
+  // whether numbers are too large for the terms
+  auto check = [&](const f32x4 (&x)[NI], float end) {
+    float most = 0.f;
 #pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      mk[i] = abs_max(rk[i]);
-      mv[i] = abs_max(rv[i]);
-    }
-    bool off = false;
-#pragma unroll
-    for (int i = 0; i < NI; ++i) off = off | outside(mk[i], ek) | outside(mv[i], ev);
-    odd_rows = false;
-    if (__any(off)) {
-      uint32_t tk = 0, tv = 0;
-#pragma unroll
-      for (int i = 0; i < NI; ++i) {
-        tk = max(tk, __float_as_uint(mk[i]));
-        tv = max(tv, __float_as_uint(mv[i]));
-      }
-      tk = wave_max(tk);
-      tv = wave_max(tv);
-      if (tk != 0) ek = max(tk >> 23, (uint32_t)kExpLow);
-      if (tv != 0) ev = max(tv >> 23, (uint32_t)kExpLow);
-      off = false;
-#pragma unroll
-      for (int i = 0; i < NI; ++i) off = off | outside(mk[i], ek) | outside(mv[i], ev);
-      odd_rows = __any(off) || ek >= kExpHigh || ev == 255;
-    }
-    sk = __uint_as_float((kExpScale - ek) << 23);
-    sv = __uint_as_float((kExpScale - ev) << 23);
+    for (int i = 0; i < NI; ++i) most = abs_max(most, x[i]);
+    return !(most < end);
   };
-  // converts and stores the tile in 4 NI pieces of two numbers
-  uint2 hi2, lo2;
-  auto put_piece = [&](int j, int pc) {
-    const int n = pc / 4;
-    if (pc % 4 == 0) split2(rk[n][0], rk[n][1], sk, &hi2.x, &lo2.x);
-    if (pc % 4 == 1) {
-      split2(rk[n][2], rk[n][3], sk, &hi2.y, &lo2.y);
-      char* at = smem + ((kst ^ (uint32_t)(C::kswz(n * C::RPI) * 16)) + (j & 1) * C::BUF) + n * C::RPI * ROWB;
-      *reinterpret_cast<uint2*>(at) = hi2;
-      *reinterpret_cast<uint2*>(at + C::PLANE) = lo2;
-    }
-    if (pc % 4 == 2) split2(rv[n][0], rv[n][1], sv, &hi2.x, &lo2.x);
-    if (pc % 4 == 3) {
-      split2(rv[n][2], rv[n][3], sv, &hi2.y, &lo2.y);
-      char* at = smem + ((vst ^ (uint32_t)(C::vswz(n * C::RPI) * 16)) + (j & 1) * C::BUF) + n * C::RPI * ROWB;
-      *reinterpret_cast<uint2*>(at + 2 * C::PLANE) = hi2;
-      *reinterpret_cast<uint2*>(at + 3 * C::PLANE) = lo2;
+  // converts and stores K or V in 2 NI pieces of two numbers
+  uint32_t w0[3], w1[3];
+  auto put = [&](const f32x4& x, float scale, bool second, char* at) {
+    if (!second) {
+      split3(x[0] * scale, x[1] * scale, w0);
+    } else {
+      split3(x[2] * scale, x[3] * scale, w1);
+#pragma unroll
+      for (int i = 0; i < 3; ++i) *reinterpret_cast<uint2*>(at + i * C::PLANE) = make_uint2(w0[i], w1[i]);
     }
   };
-  auto put_scales = [&](int j) {
-    if (lane == 0) {
-#pragma unroll
-      for (int gi = 0; gi < C::RW / 4; ++gi) {
-        const int g8 = wave * (C::RW / 4) + gi, grp = g8 >> 3, gg = g8 & 7;  // group of four rows: key group, place in it
-        float* p = scales + (((j & 1) * NKG + grp) * 2) * 8 + (gg & 1) * 4 + (gg >> 1);
-        p[0] = __uint_as_float((ek - kExpUnscale) << 23);
-        p[8] = __uint_as_float((ev - kExpUnscale) << 23);
-      }
-      if (odd_rows) flags[j & 1] = 1;
-    }
+  auto put_k = [&](int pc) {
+    const int n = pc / 2;
+    put(rk[n], 1.f, pc % 2, smem + (fresh(kst) ^ (uint32_t)(C::kswz(n * C::RPI) * 16)) + n * C::RPI * ROWB);
   };
-  auto store_tile = [&](int j) {
-    check_tile();
-#pragma unroll
-    for (int pc = 0; pc < 4 * NI; ++pc) put_piece(j, pc);
-    put_scales(j);
+  auto put_v = [&](int pc) {
+    const int n = pc / 2;
+    put(rv[n], kTermScale, pc % 2, smem + (fresh(vst) ^ (uint32_t)(C::vswz(n * C::RPI) * 16)) + n * C::RPI * ROWB);
   };
 
-  load_tile(0);
+  load_rows(kbase, 0, rk);
   if (t < 2) flags[t] = 0;
 
-  // ---- query rows, requested behind the first tile, which is staged and followed by the next while they come
-  f16x8 qhi[ND], qlo[ND];
-  float cq;
-  bool q_slow;
+  // ---- query rows, requested behind the first keys, which are staged and followed by the next while they come
+  bf16x8 q1[ND], q2[ND];
+  char* q3 = smem + C::Q3 + rg * 32 * ROWB + lane * 16;
+  bool q_odd;
   const float c2 = (float)((double)a.scale * 1.4426950408889634074);
   {
-    // They come as whole rows and are turned through LDS (16 rows at a time, swizzled by the row): a load in the layout of the
-    // fragments touches 32 lines, 16 of them per wave 4000 cycles ahead of the first tile (32 heads x 700 rows 39.2 -> 37.8 us,
-    // 64 x 300 24.2 -> 23.2).
-    constexpr int NQ = 16 / C::RPI;
-    f32x4 raw[2][NQ], x[ND][2];
+    // They come as whole rows and are turned through LDS (eight rows at a time, swizzled by the row): a load in the layout of
+    // the fragments touches 32 lines, 16 of them per wave 4000 cycles ahead of the first tile.
+    constexpr int NQ = 8 / C::RPI;
+    f32x4 raw[4][NQ], x[ND][2];
     const int ql = lane / C::LPR, qc = lane % C::LPR;
 #pragma unroll
-    for (int p = 0; p < 2; ++p)
+    for (int p = 0; p < 4; ++p)
 #pragma unroll
       for (int i = 0; i < NQ; ++i) {
-        const int row = max(0, min(wave_first + 16 * p + i * C::RPI + ql, a.rows - 1));
+        const int row = max(0, min(wave_first + 8 * p + i * C::RPI + ql, a.rows - 1));
         raw[p][i] = *reinterpret_cast<const f32x4*>(qbase + (size_t)row * (D * 4) + qc * 16);
       }
     __syncthreads();  // the flags are clear
-    store_tile(0);
-    if (n_tiles > 1) load_tile(1);
-    char* turn = smem + C::QROWS + wave * (16 * D * 4);
+    if (check(rk, kTermsEnd)) flags[1] = 1;
 #pragma unroll
-    for (int p = 0; p < 2; ++p) {
+    for (int pc = 0; pc < 2 * NI; ++pc) put_k(pc);
+    load_rows(vbase, 0, rv);  // (in the order of the steps, in which the waits for them count)
+    load_rows(kbase, 1, rk);
+    char* turn = smem + C::QTURN + wave * C::QTURN_WAVE;
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
 #pragma unroll
       for (int i = 0; i < NQ; ++i) {
         const int row = i * C::RPI + ql;
         *reinterpret_cast<f32x4*>(turn + row * (D * 4) + (qc ^ row) * 16) = raw[p][i];
       }
       __builtin_amdgcn_wave_barrier();
-      if (rw / 16 == p) {
+      if (rw / 8 == p) {
 #pragma unroll
         for (int dc = 0; dc < ND; ++dc)
 #pragma unroll
           for (int i = 0; i < 2; ++i)
-            x[dc][i] = *reinterpret_cast<const f32x4*>(turn + rw % 16 * (D * 4) + ((dc * 4 + h * 2 + i) ^ rw % 16) * 16);
+            x[dc][i] = *reinterpret_cast<const f32x4*>(turn + rw % 8 * (D * 4) + ((dc * 4 + h * 2 + i) ^ rw % 8) * 16);
       }
       __builtin_amdgcn_wave_barrier();
     }
-    float mq[ND], most = 0.f;
+    float most = 0.f;
 #pragma unroll
     for (int dc = 0; dc < ND; ++dc) {
-      mq[dc] = __builtin_elementwise_maximum(abs_max(x[dc][0]), abs_max(x[dc][1]));
-      most = __builtin_elementwise_maximum(most, mq[dc]);
-    }
-    const uint32_t mb = __float_as_uint(most) & 0x7FFFFFFFu;
-    const auto sw = __builtin_amdgcn_permlane32_swap(mb, mb, false, false);
-    const uint32_t eq = max(max(sw[0], sw[1]) >> 23, (uint32_t)kExpLow);
-    bool off = eq >= kExpHigh;
-#pragma unroll
-    for (int dc = 0; dc < ND; ++dc) off = off || outside(mq[dc], eq);
-    q_slow = __any(off);
-    const float sq = __uint_as_float((kExpScale - eq) << 23);
-    cq = c2 * __uint_as_float((eq - kExpUnscale) << 23);
-#pragma unroll
-    for (int dc = 0; dc < ND; ++dc) {
-      u32x4 hi, lo;
+      most = abs_max(abs_max(most, x[dc][0]), x[dc][1]);
+      u32x4 term[3];
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
-        uint32_t h0, h1, l0, l1;
-        split2(x[dc][i][0], x[dc][i][1], sq, &h0, &l0);
-        split2(x[dc][i][2], x[dc][i][3], sq, &h1, &l1);
-        hi[2 * i] = h0; hi[2 * i + 1] = h1; lo[2 * i] = l0; lo[2 * i + 1] = l1;
+        split3(x[dc][i][0], x[dc][i][1], w0);
+        split3(x[dc][i][2], x[dc][i][3], w1);
+#pragma unroll
+        for (int n = 0; n < 3; ++n) {
+          term[n][2 * i] = w0[n];
+          term[n][2 * i + 1] = w1[n];
+        }
       }
-      qhi[dc] = __builtin_bit_cast(f16x8, hi);
-      qlo[dc] = __builtin_bit_cast(f16x8, lo);
+      q1[dc] = __builtin_bit_cast(bf16x8, term[0]);
+      q2[dc] = __builtin_bit_cast(bf16x8, term[1]);
+      if (kg == 0) *reinterpret_cast<u32x4*>(q3 + dc * 1024) = term[2];  // (both key groups hold the same rows)
     }
+    q_odd = !(most < kTermsEnd);
   }
 
   // ---- read side
@@ -545,7 +471,7 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs a, int bx, int by
     kaddr = (uint32_t)((kg * BK + rw) * ROWB + ((h ^ C::kswz(rw)) * 16));
     const int i16 = lane & 15, q2 = (lane >> 4) & 1;
     const int vrow = 4 * h + (i16 >> 2), c = 2 * q2 + ((i16 & 3) >> 1);
-    vaddr = (uint32_t)(2 * C::PLANE + (kg * BK + vrow) * ROWB + ((c ^ C::vswz(vrow)) * 16) + 8 * (i16 & 1));
+    vaddr = (uint32_t)(C::VAT + (kg * BK + vrow) * ROWB + ((c ^ C::vswz(vrow)) * 16) + 8 * (i16 & 1));
   }
 
   f32x16 o[NV];
@@ -554,148 +480,166 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs a, int bx, int by
 #pragma unroll
     for (int j = 0; j < 16; ++j) o[i][j] = 0.f;
   float m_ref = -INFINITY, l_run = 0.f;
-  float unit = __uint_as_float(8u << 23);
 
   auto vfrag = [&](const char* vp) {
     const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(vp));
     const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(vp + 8 * ROWB));
-    union { struct { s16x4 lo, hi; } s; f16x8 v; } u;
+    union { struct { s16x4 lo, hi; } s; bf16x8 v; } u;
     u.s.lo = lo;
     u.s.hi = hi;
     return u.v;
   };
 
-  auto compute = [&](int tile, bool masked) {
-    const uint32_t kat = kaddr + (tile & 1) * C::BUF, vat = vaddr + (tile & 1) * C::BUF;
-    auto kread = [&](int dc, f16x8* hi, f16x8* lo) {
-      const char* at = smem + (kat ^ (uint32_t)(dc * 32));
-      *hi = *reinterpret_cast<const f16x8*>(at);
-      *lo = *reinterpret_cast<const f16x8*>(at + C::PLANE);
-    };
-    const float* sc = scales + (((tile & 1) * NKG + kg) * 2) * 8 + h * 4;
-    f32x4 fk = *reinterpret_cast<const f32x4*>(sc);
-    f32x4 fv = *reinterpret_cast<const f32x4*>(sc + 8);
-    const int key0 = kv_begin + tile * BKT + kg * BK;
-    f32x16 s, sl;
+  f32x16 s;
+  // the scores of a step, beside them V's planes
+  auto scores = [&]() {
+    f32x16 sl;
 #pragma unroll
     for (int j = 0; j < 16; ++j) { s[j] = 0.f; sl[j] = 0.f; }
-    f32x4 cg;
-    {
-      constexpr int KA = 3;  // fragments in registers
-      f16x8 kh[KA], kl[KA];
+    constexpr int KA = 2;  // fragments in registers
+    const uint32_t ka = fresh(kaddr);
+    bf16x8 k1[KA], k2[KA], k3[KA];
+    auto kread = [&](int dc) {
+      const char* at = smem + (ka ^ (uint32_t)(dc * 32));
+      k3[dc % KA] = *reinterpret_cast<const bf16x8*>(at + 2 * C::PLANE);
+      k2[dc % KA] = *reinterpret_cast<const bf16x8*>(at + C::PLANE);
+      k1[dc % KA] = *reinterpret_cast<const bf16x8*>(at);
+    };
+    kread(0);
 #pragma unroll
-      for (int dc = 0; dc + 1 < KA; ++dc) kread(dc, &kh[dc], &kl[dc]);
+    for (int dc = 0; dc < ND; ++dc) {
+      const bf16x8 x3 = *reinterpret_cast<const bf16x8*>(q3 + dc * 1024);
+      if (dc + 1 < ND) kread(dc + 1);
+      __builtin_amdgcn_sched_barrier(kHoldLds);
 #pragma unroll
-      for (int dc = 0; dc < ND; ++dc) {
-        if (dc + KA - 1 < ND) kread(dc + KA - 1, &kh[(dc + KA - 1) % KA], &kl[(dc + KA - 1) % KA]);
-        __builtin_amdgcn_sched_barrier(kHoldLds);
-#pragma unroll
-        for (int pc = 0; pc < 4 * NI / ND; ++pc) put_piece(tile + 1, dc * (4 * NI / ND) + pc);
-        s = __builtin_amdgcn_mfma_f32_32x32x16_f16(kl[dc % KA], qhi[dc], s, 0, 0, 0);
-        sl = __builtin_amdgcn_mfma_f32_32x32x16_f16(kh[dc % KA], qlo[dc], sl, 0, 0, 0);
-        f32x16& x = dc & 1 ? s : sl;
-        x = __builtin_amdgcn_mfma_f32_32x32x16_f16(kh[dc % KA], qhi[dc], x, 0, 0, 0);
-      }
-      put_scales(tile + 1);
-      if (tile + 2 < n_tiles) load_tile(tile + 2);
-#pragma unroll
-      for (int j = 0; j < 16; ++j) s[j] += sl[j];
-#pragma unroll
-      for (int g = 0; g < 4; ++g) cg[g] = fmaxf(cq * fk[g], 0x1p-126f);  // not 0, which would make NaN of a masked score
+      for (int pc = dc * 2 * NI / ND; pc < (dc + 1) * 2 * NI / ND; ++pc) put_v(pc);
+      const int n = dc % KA;
+      sl = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k3[n], q1[dc], sl, 0, 0, 0);
+      sl = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k2[n], q2[dc], sl, 0, 0, 0);
+      sl = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k2[n], q1[dc], sl, 0, 0, 0);
+      sl = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k1[n], q2[dc], sl, 0, 0, 0);
+      sl = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k1[n], x3, sl, 0, 0, 0);
+      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k1[n], q1[dc], s, 0, 0, 0);
     }
+#pragma unroll
+    for (int j = 0; j < 16; ++j) s[j] += sl[j];
+  };
+  auto weights = [&](int tile, bool masked) {
     if (masked) {
-      const int n_ok = (CAUSAL ? min(kv_end, r + 1) : kv_end) - key0 - 4 * h;
+      const int n_ok = (CAUSAL ? min(kv_end, r + 1) : kv_end) - (kv_begin + tile * BKT + kg * BK) - 4 * h;
 #pragma unroll
       for (int j = 0; j < 16; ++j)
         if (8 * (j >> 2) + (j & 3) >= n_ok) s[j] = -INFINITY;
     }
-    float mx = -INFINITY;
+    float mx = s[0];
 #pragma unroll
-    for (int g = 0; g < 4; ++g)
-      mx = fmaxf(mx, fmaxf(fmaxf(s[4 * g], s[4 * g + 1]), fmaxf(s[4 * g + 2], s[4 * g + 3])) * cg[g]);
-    mx = max_across_halves(mx);
-    const float v_most = fmaxf(fmaxf(fv[0], fv[1]), fmaxf(fv[2], fv[3])), v_least = fminf(fminf(fv[0], fv[1]), fminf(fv[2], fv[3]));
-    if (__any(mx > m_ref + TAU || v_most > unit || v_least < unit * kUnitSpan)) {
-      const float m_new = fmaxf(m_ref, mx), u_new = fmaxf(unit, max_across_halves(v_most));
-      const float al = __builtin_amdgcn_exp2f(m_ref - (m_new == -INFINITY ? 0.f : m_new)), alo = al * (unit / u_new);
+    for (int j = 1; j < 16; ++j) mx = fmaxf(mx, s[j]);
+    mx = max_across_halves(mx) * c2;
+    if (__any(mx > m_ref + TAU)) {
+      const float m_new = fmaxf(m_ref, mx);
+      const float al = __builtin_amdgcn_exp2f(m_ref - (m_new == -INFINITY ? 0.f : m_new));
       l_run *= al;
 #pragma unroll
       for (int i = 0; i < NV; ++i)
 #pragma unroll
-        for (int j = 0; j < 16; ++j) o[i][j] *= alo;
+        for (int j = 0; j < 16; ++j) o[i][j] *= al;
       m_ref = m_new;
-      unit = u_new;
-      if (__any(v_least < unit * kUnitSpan) && lane == 0) flags[(tile + 1) & 1] = 1;
     }
-    const float per_unit = __uint_as_float((261u << 23) - __float_as_uint(unit));
     const float m_use = m_ref == -INFINITY ? 0.f : m_ref;
-    float psum[4] = {0.f, 0.f, 0.f, 0.f};
+    float psum[4] = {0.f, 0.f, 0.f, 0.f};  // (a step's own sum, so that small weights beside a large one are not lost one by one)
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
-      s[j] = __builtin_amdgcn_exp2f(fmaf(s[j], cg[j >> 2], -m_use));
+      s[j] = __builtin_amdgcn_exp2f(fmaf(s[j], c2, -m_use));
       psum[j & 3] += s[j];
+      s[j] *= kTermScale;
     }
     l_run += (psum[0] + psum[1]) + (psum[2] + psum[3]);
-    {
-      f16x8 ph[2], pl[2];
-      auto split_weights = [&](int s2) {
-        u32x4 hi, lo;
+  };
+  // a step's share of the outputs, beside it K's next planes
+  // OWN: its products, 12 to an output, are summed on their own and then added, so that the outputs are rounded once a step.
+  // With two key groups the sums are half as long, and at d = 128 the registers are taken.
+  constexpr bool OWN = NKG == 1 || D == 64;
+  auto outputs = [&]() {
+    bf16x8 p[2][3];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          uint32_t hw, lw;
-          split2(s[8 * s2 + 2 * e], s[8 * s2 + 2 * e + 1], fv[2 * s2 + (e >> 1)] * per_unit, &hw, &lw);
-          hi[e] = hw; lo[e] = lw;
-        }
-        ph[s2] = __builtin_bit_cast(f16x8, hi);
-        pl[s2] = __builtin_bit_cast(f16x8, lo);
-      };
-      // two 32-channel blocks of 16 keys at a time, their fragments read one such group ahead
-      constexpr int NG = NV;
-      f16x8 vh[2][2], vl[2][2];
-      auto vread = [&](int g) {
+    for (int s2 = 0; s2 < 2; ++s2) {
+      u32x4 term[3];
 #pragma unroll
-        for (int b = 0; b < 2; ++b) {
-          const char* at = smem + (vat ^ (uint32_t)((g * 2 + b) % NV * 64)) + (g * 2 / NV) * 16 * ROWB;
-          vh[g & 1][b] = vfrag(at);
-          vl[g & 1][b] = vfrag(at + C::PLANE);
-        }
-      };
-      vread(0);
-      split_weights(0);
+      for (int e = 0; e < 4; ++e) {
+        uint32_t w[3];
+        split3(s[8 * s2 + 2 * e], s[8 * s2 + 2 * e + 1], w);
 #pragma unroll
-      for (int g = 0; g < NG; ++g) {
-        if (g + 1 < NG) vread(g + 1);
-        __builtin_amdgcn_sched_barrier(kHoldLds);
-        const int s2 = g * 2 / NV, b0 = g * 2 % NV;
-        if (g == 0) split_weights(1);
+        for (int n = 0; n < 3; ++n) term[n][e] = w[n];
+      }
 #pragma unroll
-        for (int b = 0; b < 2; ++b) o[b0 + b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vl[g & 1][b], ph[s2], o[b0 + b], 0, 0, 0);
+      for (int n = 0; n < 3; ++n) p[s2][n] = __builtin_bit_cast(bf16x8, term[n]);
+    }
+    constexpr int NG = 2 * NV;  // groups: 16 keys of 32 channels
+    bf16x8 v[2][3];
+    const uint32_t va = fresh(vaddr);
+    auto vread = [&](int g) {
+      const char* at = smem + (va ^ (uint32_t)(g / 2 * 64)) + g % 2 * 16 * ROWB;
 #pragma unroll
-        for (int b = 0; b < 2; ++b) o[b0 + b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vh[g & 1][b], pl[s2], o[b0 + b], 0, 0, 0);
+      for (int n = 0; n < 3; ++n) v[g & 1][n] = vfrag(at + n * C::PLANE);
+    };
+    vread(0);
+    f32x16 z;
 #pragma unroll
-        for (int b = 0; b < 2; ++b) o[b0 + b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(vh[g & 1][b], ph[s2], o[b0 + b], 0, 0, 0);
+    for (int g = 0; g < NG; ++g) {
+      if (g + 1 < NG) vread(g + 1);
+      __builtin_amdgcn_sched_barrier(kHoldLds);
+#pragma unroll
+      for (int pc = g * 2 * NI / NG; pc < (g + 1) * 2 * NI / NG; ++pc) put_k(pc);
+      const bf16x8 (&x)[3] = v[g & 1];
+      const bf16x8 (&w)[3] = p[g & 1];
+      f32x16& y = OWN ? z : o[g / 2];
+      if (OWN && g % 2 == 0) {
+#pragma unroll
+        for (int j = 0; j < 16; ++j) z[j] = 0.f;
+      }
+      y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[2], w[0], y, 0, 0, 0);
+      y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[0], w[2], y, 0, 0, 0);
+      y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[1], w[1], y, 0, 0, 0);
+      y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[1], w[0], y, 0, 0, 0);
+      y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[0], w[1], y, 0, 0, 0);
+      y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[0], w[0], y, 0, 0, 0);
+      if (OWN && g % 2 == 1) {
+#pragma unroll
+        for (int j = 0; j < 16; ++j) o[g / 2][j] += z[j];
+        __builtin_amdgcn_sched_barrier(0);  // (begun side by side, these sums would not fit the registers)
       }
     }
   };
 
-  if (q_slow) flags[0] = 1;
+  if (q_odd) flags[1] = 1;
   __syncthreads();
   bool plain = false;
   for (int tile = 0; tile < n_tiles; ++tile) {
-    const int odd = flags[tile & 1];
-    const bool more = tile + 1 < n_tiles, busy = tile < n_full || (tile == n_full && has_tail);
-    if (busy) {
-      check_tile();
-      compute(tile, tile == n_full);
-    } else if (more) {
-      store_tile(tile + 1);
-      if (tile + 2 < n_tiles) load_tile(tile + 2);
-    }
-    if (odd) {
+    // what step tile - 1 raised: its slot is written again in step tile + 1 only, behind barriers that follow this read
+    if (flags[(tile + 1) & 1]) {
       plain = true;
       break;
     }
-    __syncthreads();
+    const bool busy = tile < n_full || (tile == n_full && has_tail);
+    if (check(rv, kTermsEndV)) flags[tile & 1] = 1;
+    if (busy) {
+      scores();
+    } else {
+#pragma unroll
+      for (int pc = 0; pc < 2 * NI; ++pc) put_v(pc);
+    }
+    load_rows(vbase, tile + 1, rv);  // (one load for both cases: the wait for the other's would stand in either)
+    if (busy) weights(tile, tile == n_full);
+    __syncthreads();  // V(tile) is there, K(tile) has been read
+    if (check(rk, kTermsEnd)) flags[tile & 1] = 1;
+    if (busy) {
+      outputs();
+    } else {
+#pragma unroll
+      for (int pc = 0; pc < 2 * NI; ++pc) put_k(pc);
+    }
+    load_rows(kbase, tile + 2, rk);
+    __syncthreads();  // K(tile + 1) is there, V(tile) has been read
   }
   if (plain || flags[0] || flags[1]) {
     __syncthreads();
@@ -719,26 +663,23 @@ __device__ __forceinline__ void attn_split_body(const AttnArgs a, int bx, int by
         for (int j = 0; j < 16; ++j) mg[(i * 16 + j) * 64] = o[i][j];
       mg[(NV * 16) * 64] = m_ref;
       mg[(NV * 16 + 1) * 64] = l_run;
-      mg[(NV * 16 + 2) * 64] = unit;
     }
     __syncthreads();
     if (kg == 1) return;
-    const float m1 = mg[(NV * 16) * 64], l1 = mg[(NV * 16 + 1) * 64], unit1 = mg[(NV * 16 + 2) * 64];
-    const float m_new = fmaxf(m_ref, m1), u_new = fmaxf(unit, unit1);
+    const float m1 = mg[(NV * 16) * 64], l1 = mg[(NV * 16 + 1) * 64];
+    const float m_new = fmaxf(m_ref, m1);
     const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
     const float a0 = __builtin_amdgcn_exp2f(m_ref - m_use), a1 = __builtin_amdgcn_exp2f(m1 - m_use);
-    const float s0 = a0 * (unit / u_new), s1 = a1 * (unit1 / u_new);
 #pragma unroll
     for (int i = 0; i < NV; ++i)
 #pragma unroll
-      for (int j = 0; j < 16; ++j) o[i][j] = o[i][j] * s0 + mg[(i * 16 + j) * 64] * s1;
+      for (int j = 0; j < 16; ++j) o[i][j] = o[i][j] * a0 + mg[(i * 16 + j) * 64] * a1;
     l_run = l_run * a0 + l1 * a1;
     m_ref = m_new;
-    unit = u_new;
   }
   if (!has_rows) return;
   const float l_tot = sum_across_halves(l_run);
-  const float inv = unit * 0.0078125f / l_tot;
+  const float inv = 1.f / (l_tot * (kTermScale * kTermScale));
   const size_t row0 = (size_t)batch * a.rows + wave_first;
   float* op0;
   float* lp0;
@@ -780,7 +721,7 @@ hipError_t run_split_d(const AttnLaunch& l, hipStream_t s) {
 // Both attentions in one launch with the causal one on products of terms (NKG): the query attention's workgroups come first
 // and take the shape, the chunks and the order that its own launch would (QKG = 0: float32 products, two units of 32 rows per
 // workgroup), so the results are the same bits.  (Behind the causal ones they end last: 32 heads x 1540 rows and 32 tokens,
-// with the merge, 112 us in front, 115 behind.)
+// on half-precision terms, 112 us with the merge in front, 115 behind.)
 template <int D, int NKG, int QKG>
 __global__ __launch_bounds__(512, 2) void k_attn_f32_split_pair(AttnArgs ac, AttnArgs aq, PairGrid g) {
   const int bid = blockIdx.x;

@@ -152,30 +152,33 @@ inline AttnShape attn_bf16_shape(int causal, int n_batch, int batch_per_kv, int 
 }
 
 // Which float32 attention kernel serves a problem: kPlain, float32 products, 32 rows and four groups of keys per workgroup, two
-// workgroups per compute unit; kSplit and kSplitKeys2, products of half-precision terms, 256 rows or 128 rows whose keys two
-// groups of waves share, one workgroup per compute unit.  Device times of single calls in us, kPlain / kSplit / kSplitKeys2.
+// workgroups per compute unit; kSplit and kSplitKeys2, products of bf16 terms, 256 rows or 128 rows whose keys two groups of
+// waves share, one workgroup per compute unit.  Fitted to device times of single calls of all three over 329 causal shapes (1 to
+// 512 heads, 64 to 9000 rows) and 997 others (1 to 128 KV heads, 16 to 2048 rows, 150 to 60000 keys): on average 0.4 % and 0.5 %
+// behind the best of the three, by more than 5 % on 12 and 22 shapes; against kPlain throughout 21 and 16 % faster, and slower by
+// more than 2 % on 1 and 23.  Examples in us, kPlain / kSplit / kSplitKeys2.
 // Causal: kPlain has four times the workgroups and a shorter start, so it stays ahead until its workgroups fill the chip, the
-// sooner the longer the chain of the last row tile (d = 128: 8 heads x 1000 rows 41 / 81 / 51, x 1540 75 / 118 / 72; 16 x 500
-// 24 / 45 / 32; 64 x 200 18.9 / 24.9 / 20.6, x 300 32 / 33 / 25; 128 x 100 15.1 / 16.3 / 16.4, x 200 37 / 26 / 22; d = 64: 8 x
-// 1540 42 / 79 / 48, 16 x 1000 33 / 54 / 34, 32 x 500 19.6 / 30 / 21, x 700 32 / 39 / 26).  kSplit from 384 of its workgroups
-// on (d = 128: 32 x 2300 357 / 184 / 166, x 3100 631 / 267 / 277; 64 x 1540 345 / 139 / 158), and where heads of one row tile
-// fill the chip once with it and twice without (256 x 200 64 / 29 / 42).
-// Not causal: the same by work, as the keys are cut into chunks; problems of up to 32 rows per KV head keep kPlain, whose
-// workgroups hold no more (rows x keys x KV heads, d = 128: 64 x 4000 x 8 20.4 / 25.5 / 24.8, 96 x 4000 x 8 31 / 27 / 26, 200 x
-// 1540 x 8 31 / 34 / 27, 128 x 1540 x 8 19.6 / 26 / 26, 32 x 20000 x 8 39 / 43 / 40, 128 x 20000 x 8 101 / 52 / 52; d = 64: 256
-// x 600 x 16 15.5 / 23 / 18, 96 x 4000 x 8 19.4 / 19.6 / 17.2).  kSplit for long ones (d = 128: 512 x 20000 x 8 332 / 135 / 142)
-// and where it fills the chip once (1024 x 600 x 64 178 / 70 / 85), not with half-empty row tiles (96 x 7000 x 64 239 / 127 / 115).
+// later the more steps the longest row tile takes (d = 128: 8 heads x 3300 rows 226 / 424 / 241, x 6000 599 / 759 / 460; 32 x 700
+// 58 / 95 / 59, x 1540 192 / 212 / 137; 64 x 300 32 / 46 / 32, x 400 52 / 59 / 40; d = 64: 16 x 2000 90 / 158 / 93, x 2600 135 /
+// 208 / 125; 64 x 400 25 / 35 / 24, x 700 59 / 60 / 39).  kSplit once three rounds of its workgroups exist (d = 128: 64 x 1200
+// 228 / 179 / 162, x 2600 917 / 593 / 594, x 4100 2145 / 1316 / 1392; d = 64: 64 x 4100 1139 / 741 / 795), and where heads of one
+// row tile fill the chip (d = 128: 200 x 200 48 / 38 / 44).
+// Not causal: the same by work, as the keys are cut into chunks; up to 64 rows per KV head, and 256 in all, keep kPlain, whose
+// workgroups hold no more (rows x keys x KV heads, d = 128: 32 x 4000 x 128 112 / 175 / 149, 96 x 60000 x 1 47 / 93 / 81, 160 x
+// 4000 x 8 40 / 49 / 35).  kSplit for long ones or where it fills the chip (d = 128: 1024 x 4000 x 16 289 / 185 / 187; d = 64: 800
+// x 1500 x 32 111 / 78 / 84).
 enum class AttnF32Shape { kPlain, kSplit, kSplitKeys2 };
 inline AttnF32Shape attn_f32_shape(int causal, int n_batch, int rows, int m, int d) {
   const long long wg32 = (long long)n_batch * ((rows + 31) / 32), wg256 = (long long)n_batch * ((rows + 255) / 256);
+  if (rows <= 64) return AttnF32Shape::kPlain;
   if (causal) {
-    if (wg32 + m / 8 <= (d == 128 ? 530 : 660)) return AttnF32Shape::kPlain;
-    if (wg256 >= 384 || (rows > 128 && rows <= 256 && n_batch > 128)) return AttnF32Shape::kSplit;
+    if (wg32 <= (d == 128 ? 500 + (m < 1050 ? m / 3 : 350) : 560 + (m < 1200 ? m / 2 : 600))) return AttnF32Shape::kPlain;
+    if (wg256 >= 780 || (rows > 100 && rows <= 256 && n_batch > 128)) return AttnF32Shape::kSplit;
     return AttnF32Shape::kSplitKeys2;
   }
   const long long work = (long long)rows * m * n_batch;
-  if (rows <= 32 || work <= (d == 128 ? 2200000 : 2900000)) return AttnF32Shape::kPlain;
-  if (rows > 128 && (wg256 >= 256 || (m >= 3000 && work >= 30000000))) return AttnF32Shape::kSplit;
+  if ((long long)n_batch * rows <= 256 || work <= (d == 128 ? 3500000 : 4500000)) return AttnF32Shape::kPlain;
+  if (rows > 128 && (wg256 >= 160 || (m >= 3000 && work >= 40000000))) return AttnF32Shape::kSplit;
   return AttnF32Shape::kSplitKeys2;
 }
 

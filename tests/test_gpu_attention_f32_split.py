@@ -1,7 +1,7 @@
-"""Float32 attention on products of half-precision terms, at the edges of its kernels: eight waves of 32 query rows, as 256
+"""Float32 attention on products of bf16 terms, at the edges of its kernels: eight waves of 32 query rows, as 256
 rows of a workgroup (one stream of keys, 32 a step) or as 128 rows whose keys two groups of waves share (64 a step).  The
 sizes are beyond those that `attn_f32_shape` leaves to the float32 products.  The inputs that terms do not hold (infinities,
-NaN, magnitudes past 2^60, neighbours more than 2^12 apart) must come out as exactly as with float32 products."""
+NaN, magnitudes past 2^60, in V past 2^48) must come out as exactly as with float32 products, and so must all others."""
 import math
 
 import pytest
@@ -145,7 +145,7 @@ def _run(q, k, v, scale, causal):
 
 
 # heads, rows, keys of a problem on 128 and on 256 rows per workgroup, the last step and row tile ragged
-SHAPES = {"causal128": (72, 330, 330), "causal256": (136, 200, 200), "query128": (8, 33, 12001), "query256": (136, 300, 3001)}
+SHAPES = {"causal128": (72, 330, 330), "causal256": (136, 200, 200), "query128": (8, 45, 14001), "query256": (136, 300, 3001)}
 
 
 @pytest.mark.parametrize("shape", SHAPES)
@@ -194,3 +194,87 @@ def test_infinity_behind_a_large_value(value, d, shape):
     col = out[:, 150 if causal else 0:, 7]
     assert (torch.isnan(col) if math.isnan(value) else col == value).all()
     assert torch.isfinite(lse).all()
+
+
+SINKS = [f"sink {nats} nats, V x {v}" for nats in (8, 12, 16, 20, 40) for v in (0.0, 0.01)]
+CHANNELS = [f"channel of {x} x 2^-{e}" for x in ("V", "K") for e in (12, 20, 24)]
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("kind", ["normal", "channel scales", "leading zeros of V", "v x 2^-130"] + SINKS + CHANNELS)
+def test_precision_of_float32(kind, d, shape):
+    """No more error against float64 than float32 products make, which is what the same heads get in a call of their own, too
+    small for the terms: over all outputs and, as a channel far below the others shows in its own outputs only, over each
+    channel.  A sink is a key that takes nearly all of the weight and has little or no V, so that the outputs are sums of small
+    weights."""
+    import torch
+    hq, rows, m = SHAPES[shape]
+    gen = torch.Generator(device="cuda").manual_seed(13)
+    normal = lambda *s: torch.randn(s, device="cuda", generator=gen)
+    q, k, v = normal(hq, rows, d), normal(1, m, d), normal(1, m, d)
+    if kind == "channel scales":
+        scales = torch.exp2(2 * normal(d).clamp(-1, 1))
+        q, k, v = q * scales, k * scales, v * scales
+    if kind == "leading zeros of V":
+        v[0, :70] = 0.0
+    if kind == "v x 2^-130":
+        v *= 2.0 ** -130
+    if kind in SINKS:
+        nats, x = float(kind.split()[1]), float(kind.split()[-1])
+        q += 1.0                                              # the direction of the sink's key
+        k[0, 0] = nats * d ** -0.5
+        v[0, 0] *= x
+    if kind in CHANNELS:
+        e = int(kind.split("-")[1])
+        if "V" in kind:
+            v[..., 5] *= 2.0 ** -e
+        else:
+            k[..., ::8] *= 2.0 ** -e
+            q[..., ::8] *= 2.0 ** e
+    causal, scale = shape.startswith("causal"), d ** -0.5
+    out, lse = _run(q, k, v, scale, causal)
+    heads = [0, hq // 2, hq - 1]
+    ref, lse_ref = _reference(q[heads], k, v, scale, causal)
+    if causal:
+        plain, lse_plain = _run(q[heads], k, v, scale, True)
+    else:
+        parts = [_run(q[h:h + 1, n:n + 50].contiguous(), k, v, scale, False) for h in heads for n in range(0, rows, 50)]
+        plain = torch.cat([x[0] for x in parts], 1).view(3, rows, d)
+        lse_plain = torch.cat([x[1] for x in parts], 1).view(3, rows)
+    per = lambda x, r: (x.double() - r).flatten(0, 1).norm(dim=0)
+    ours, theirs = per(out[heads], ref), per(plain, ref)
+    # Half as much again, as the roundings of a sink's score move whole rows; and outputs that one key holds nearly alone are
+    # rounded once in each step of 32 keys, by 2^-25 of them, where a call of fewer keys has fewer steps.
+    own = 2.0 ** -25 * math.sqrt(m / 32) * ref.norm()
+    assert (ours.norm() <= 1.5 * theirs.norm() + own).item(), (ours.norm() / theirs.norm()).item()
+    if kind in CHANNELS:
+        assert (ours <= 2 * theirs).all(), (ours / theirs).max().item()
+    assert ((lse[heads].double() - lse_ref).norm() <= 1.5 * (lse_plain.double() - lse_ref).norm()).item()
+
+
+@pytest.mark.parametrize("d,hq,hkv,m", [
+    (128, 16, 16, 2300), (64, 40, 8, 1300),                           # few heads, 128 rows per workgroup
+    (128, 400, 8, 300), (64, 400, 8, 290), (128, 200, 8, 900),        # 256 rows, several row tiles
+])
+def test_recompute_long(d, hq, hkv, m):
+    E.test_recompute_attention_shapes("f32", d, hq, hkv, m)
+
+
+@pytest.mark.parametrize("d,hq,hkv,lq,m", [
+    (128, 8, 2, 50, 9001), (64, 8, 1, 33, 18001), (64, 64, 64, 129, 600),   # 128 rows, one chunk and several
+    (128, 16, 4, 50, 60001), (128, 256, 256, 150, 140), (64, 192, 24, 200, 130),  # 256 rows
+])
+def test_query_long(d, hq, hkv, lq, m):
+    E.test_query_attention_shapes("f32", d, hq, hkv, lq, m)
+
+
+@pytest.mark.parametrize("d,hq,hkv,lq,m", [
+    (128, 72, 8, 4, 341), (64, 72, 8, 7, 385),          # causal on 128 rows, the query on float32 products
+    (128, 64, 8, 128, 600), (64, 64, 8, 130, 700),      # 128 rows for both
+    (128, 192, 24, 250, 300),                           # the query on 256 rows
+    (128, 400, 8, 1, 300), (64, 400, 8, 1, 290),        # causal on 256 rows, the query on each
+    (128, 400, 8, 50, 300), (128, 408, 24, 110, 300), (64, 408, 24, 110, 290),
+])
+def test_both_in_one_call_shapes(d, hq, hkv, lq, m):
+    E.test_both_attentions_in_one_call("f32", d, hq, hkv, lq, m)
