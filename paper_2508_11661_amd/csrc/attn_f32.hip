@@ -808,7 +808,7 @@ hipError_t attn_f32_raise_limits() {
 hipError_t launch_attn_f32(const AttnLaunch& l, hipStream_t s) {
   const hipError_t e = attn_prepare_device();
   if (e != hipSuccess) return e;
-  switch (attn_f32_shape(l.causal, l.n_batch, l.rows, l.m, l.d)) {
+  switch (l.f32) {
     case AttnF32Shape::kSplit: return run_split_d<1>(l, s);
     case AttnF32Shape::kSplitKeys2: return run_split_d<2>(l, s);
     case AttnF32Shape::kPlain: break;
@@ -820,8 +820,7 @@ hipError_t launch_attn_f32(const AttnLaunch& l, hipStream_t s) {
 hipError_t launch_attn_f32_pair(const AttnLaunch& causal, const AttnLaunch& query, hipStream_t s) {
   const hipError_t e = attn_prepare_device();
   if (e != hipSuccess) return e;
-  const AttnF32Shape cs = attn_f32_shape(1, causal.n_batch, causal.rows, causal.m, causal.d);
-  const AttnF32Shape qs = attn_f32_shape(0, query.n_batch, query.rows, query.m, query.d);
+  const AttnF32Shape cs = causal.f32, qs = query.f32;
   if (cs == AttnF32Shape::kPlain) {
     if (qs != AttnF32Shape::kPlain) {  // few kept tokens, many query rows
       const hipError_t e2 = launch_attn_f32(causal, s);

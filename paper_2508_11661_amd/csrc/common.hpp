@@ -209,6 +209,7 @@ struct AttnLaunch {
   float* out;      // [n_batch][rows][d]
   float* lse;      // [n_batch][rows]
   float scale;
+  AttnF32Shape f32;    // the kernel of a float32 problem
   int n_split, chunk;  // keys are cut into n_split chunks of `chunk` keys (not causal only)
   float* part_o;       // [n_split][n_batch][rows][d]   workspace when n_split > 1
   float* part_lse;     // [n_split][n_batch][rows]

@@ -114,10 +114,10 @@ ScoreWs score_ws(int n_ctx, int hq, int hkv, int d) {
 }
 
 // Not-causal attention: cut the keys into chunks when the row tiles alone cannot fill the chip.
-struct SplitPlan { int n_split, chunk; size_t part_o, part_lse, bytes; };
-// `n_own` > 0: one more part, the query tokens' n_own own keys, follows; `own`: in the same launch (attn_self_in_kernel).
-SplitPlan plan_splits(int dtype, int n_batch, int rows, int m, int d, int n_own = 0, bool own = false) {
-  const AttnF32Shape f32 = attn_f32_shape(0, n_batch, rows, m, d);
+struct SplitPlan { int n_split, chunk; size_t part_o, part_lse, bytes; AttnF32Shape f32; };
+// f32: the kernel of a float32 problem.  `n_own` > 0: one more part, the query tokens' n_own own keys, follows; `own`: in the
+// same launch (attn_self_in_kernel).
+SplitPlan plan_splits(int dtype, int n_batch, int rows, int m, int d, AttnF32Shape f32, int n_own = 0, bool own = false) {
   const int bq = dtype != SAMKV_BF16 ? (f32 == AttnF32Shape::kPlain ? 32 : f32 == AttnF32Shape::kSplit ? 256 : 128)
                  : own || attn_bf16_shape(0, n_batch, 1, rows, m, d) != AttnShape::kDma ? 128 : 256;
   const int bk = dtype == SAMKV_BF16 ? 64 : 128;
@@ -138,6 +138,7 @@ SplitPlan plan_splits(int dtype, int n_batch, int rows, int m, int d, int n_own 
   int tiles_per = (int)((key_tiles + want - 1) / want);
   if (tiles_per * bk < 256) tiles_per = 256 / bk;  // a shorter chunk costs more in the merge than it gains
   SplitPlan p;
+  p.f32 = f32;
   p.chunk = tiles_per * bk;
   p.n_split = (m + p.chunk - 1) / p.chunk;
   p.part_o = 0;
@@ -166,17 +167,29 @@ VPrepWs vprep_ws(int dtype, int hkv, int m, int d) {
 
 // Workspace of one attention problem: the key-chunk partials (not causal only), then the V preparation.
 struct AttnWs { SplitPlan split; VPrepWs vp; size_t vp_at, bytes; };
-AttnWs attn_ws(int dtype, bool causal, int hkv, int rows_per_kv, int m, int d) {
+AttnWs attn_ws(int dtype, bool causal, int hkv, int rows_per_kv, int m, int d, AttnF32Shape f32) {
   AttnWs w;
   if (causal) {
-    w.split.n_split = 1; w.split.chunk = m; w.split.part_o = w.split.part_lse = w.split.bytes = 0;
+    w.split.n_split = 1; w.split.chunk = m; w.split.part_o = w.split.part_lse = w.split.bytes = 0; w.split.f32 = f32;
   } else {
-    w.split = plan_splits(dtype, hkv, rows_per_kv, m, d);
+    w.split = plan_splits(dtype, hkv, rows_per_kv, m, d, f32);
   }
   w.vp = vprep_ws(dtype, hkv, m, d);
   w.vp_at = w.split.bytes;
   w.bytes = w.vp_at + w.vp.bytes;
   return w;
+}
+bool enough(const void* ws, size_t ws_bytes, size_t bytes) {
+  return bytes == 0 || (ws != nullptr && ((uintptr_t)ws % kAlign) == 0 && ws_bytes >= bytes);
+}
+// The plan of a query attention that the workspace has room for.  The float32 kernels cut the keys into different numbers of
+// chunks: float32 products may do without chunks, and so without a workspace, where the terms do not, and serve then.
+int query_ws(int dtype, int hkv, int rows, int m, int d, const void* ws, size_t ws_bytes, AttnWs* w) {
+  for (AttnF32Shape f32 : {attn_f32_shape(0, hkv, rows, m, d), AttnF32Shape::kPlain}) {
+    *w = attn_ws(dtype, false, hkv, rows, m, d, f32);
+    if (enough(ws, ws_bytes, w->bytes)) return SAMKV_OK;
+  }
+  return SAMKV_EWORKSPACE;
 }
 
 // Runs the V preparation of a bf16 attention call into its workspace slice and points the launch at the copy.
@@ -195,12 +208,13 @@ hipError_t prepare_v(AttnLaunch* a, const VPrepWs& vp, char* at, int hkv, hipStr
 // keys, [n_split + 1][Hq*Lq][d] and [n_split + 1][Hq*Lq], then the prepared V of the cache or of the query tokens (one
 // after the other on the stream) where a kernel needs it.
 struct SelfWs { SplitPlan split; VPrepWs vp, vp_own; size_t part_o, part_lse, inner, bytes; };
-SelfWs self_ws(int hq, int hkv, int d, int n_q_tok, int m_total, int dtype) {
+SelfWs self_ws(int hq, int hkv, int d, int n_q_tok, int m_total, int dtype, bool plain = false) {
   SelfWs w;
   const size_t n_rows = (size_t)hq * n_q_tok;
   const int rows = (hq / hkv) * n_q_tok;
   const bool in_kernel = attn_self_in_kernel(dtype, hkv, rows, m_total, n_q_tok, d);
-  w.split = plan_splits(dtype, hkv, rows, m_total, d, n_q_tok, in_kernel);
+  w.split = plan_splits(dtype, hkv, rows, m_total, d, plain ? AttnF32Shape::kPlain : attn_f32_shape(0, hkv, rows, m_total, d),
+                        n_q_tok, in_kernel);
   const size_t parts = w.split.n_split + 1;
   w.part_o = 0;
   w.part_lse = align_up(parts * n_rows * d * 4);
@@ -247,10 +261,11 @@ size_t samkv_workspace_bytes(int32_t n_ctx, int32_t n_q_heads, int32_t n_kv_head
   if (n_ctx < 1 || n_q_heads < 1 || n_kv_heads < 1 || head_dim < 1 || n_q_tok < 1 || m_total < 1) return 0;
   const size_t a = score_ws(n_ctx, n_q_heads, n_kv_heads, head_dim).bytes;
   const int rows = (n_q_heads / n_kv_heads) * n_q_tok;
-  size_t b = attn_ws(SAMKV_BF16, false, n_kv_heads, rows, m_total, head_dim).bytes;
-  const size_t c = attn_ws(SAMKV_F32, false, n_kv_heads, rows, m_total, head_dim).bytes;
+  const AttnF32Shape f32 = attn_f32_shape(0, n_kv_heads, rows, m_total, head_dim);
+  size_t b = attn_ws(SAMKV_BF16, false, n_kv_heads, rows, m_total, head_dim, f32).bytes;
+  const size_t c = attn_ws(SAMKV_F32, false, n_kv_heads, rows, m_total, head_dim, f32).bytes;
   if (c > b) b = c;
-  const size_t r = attn_ws(SAMKV_BF16, true, n_kv_heads, 0, m_total, head_dim).bytes;
+  const size_t r = attn_ws(SAMKV_BF16, true, n_kv_heads, 0, m_total, head_dim, f32).bytes;
   if (r > b) b = r;
   const size_t e = self_ws(n_q_heads, n_kv_heads, head_dim, n_q_tok, m_total, SAMKV_BF16).bytes;
   const size_t f = self_ws(n_q_heads, n_kv_heads, head_dim, n_q_tok, m_total, SAMKV_F32).bytes;
@@ -769,6 +784,7 @@ static AttnLaunch recompute_launch(const void* q_rec, const void* k_c, const voi
   a.dtype = dtype; a.d = d; a.causal = 1;
   a.n_batch = hq; a.batch_per_kv = hq / hkv; a.rows = m_total; a.m = m_total;
   a.q = q_rec; a.k = k_c; a.v = v_c; a.out = out; a.lse = lse; a.scale = scale;
+  a.f32 = attn_f32_shape(1, hq, m_total, m_total, d);
   a.n_split = 1; a.chunk = m_total;
   return a;
 }
@@ -781,6 +797,7 @@ static AttnLaunch query_launch(const void* q_tok, int n_q_tok, const void* k_c, 
   a.dtype = dtype; a.d = d; a.causal = 0;
   a.n_batch = hkv; a.batch_per_kv = 1; a.rows = (hq / hkv) * n_q_tok; a.m = m_total;
   a.q = q_tok; a.k = k_c; a.v = v_c; a.out = out; a.lse = lse; a.scale = scale;
+  a.f32 = p.f32;
   a.n_split = p.n_split; a.chunk = p.chunk;
   if (p.n_split > 1) {
     a.part_o = reinterpret_cast<float*>(static_cast<char*>(ws) + p.part_o);
@@ -800,8 +817,8 @@ int samkv_recompute_attn(const void* q_rec, const void* k_c, const void* v_c, in
                          void* ws, size_t ws_bytes, void* stream) {
   int rc = check_attn(q_rec, k_c, v_c, m_total, m_total, n_q_heads, n_kv_heads, head_dim, dtype, scale, out, lse);
   if (rc != SAMKV_OK) return rc;
-  const AttnWs w = attn_ws(dtype, true, n_kv_heads, 0, m_total, head_dim);
-  if (w.bytes > 0 && (ws == nullptr || ((uintptr_t)ws % kAlign) != 0 || ws_bytes < w.bytes)) return SAMKV_EWORKSPACE;
+  const AttnWs w = attn_ws(dtype, true, n_kv_heads, 0, m_total, head_dim, AttnF32Shape::kPlain);
+  if (!enough(ws, ws_bytes, w.bytes)) return SAMKV_EWORKSPACE;
   AttnLaunch a = recompute_launch(q_rec, k_c, v_c, m_total, n_q_heads, n_kv_heads, head_dim, dtype, scale, out, lse);
   hipStream_t s = static_cast<hipStream_t>(stream);
   hipError_t e = prepare_v(&a, w.vp, static_cast<char*>(ws) + w.vp_at, n_kv_heads, s);
@@ -814,8 +831,9 @@ int samkv_query_attn(const void* q_tok, int32_t n_q_tok, const void* k_c, const 
                      float* lse, void* ws, size_t ws_bytes, void* stream) {
   int rc = check_attn(q_tok, k_c, v_c, n_q_tok, m_total, n_q_heads, n_kv_heads, head_dim, dtype, scale, out, lse);
   if (rc != SAMKV_OK) return rc;
-  const AttnWs w = attn_ws(dtype, false, n_kv_heads, (n_q_heads / n_kv_heads) * n_q_tok, m_total, head_dim);
-  if (w.bytes > 0 && (ws == nullptr || ((uintptr_t)ws % kAlign) != 0 || ws_bytes < w.bytes)) return SAMKV_EWORKSPACE;
+  AttnWs w;
+  rc = query_ws(dtype, n_kv_heads, (n_q_heads / n_kv_heads) * n_q_tok, m_total, head_dim, ws, ws_bytes, &w);
+  if (rc != SAMKV_OK) return rc;
   AttnLaunch a = query_launch(q_tok, n_q_tok, k_c, v_c, m_total, n_q_heads, n_kv_heads, head_dim, dtype, scale, out, lse,
                               w.split, ws);
   hipStream_t s = static_cast<hipStream_t>(stream);
@@ -838,8 +856,8 @@ static int pair_setup(const void* q_rec, const void* q_tok, int32_t n_q_tok, con
   if (rc != SAMKV_OK) return rc;
   // the workspace of the query attention holds the prepared V behind its key-chunk partials; the causal attention
   // needs nothing else, so one preparation serves both
-  x->w = attn_ws(dtype, false, n_kv_heads, (n_q_heads / n_kv_heads) * n_q_tok, m_total, head_dim);
-  if (x->w.bytes > 0 && (ws == nullptr || ((uintptr_t)ws % kAlign) != 0 || ws_bytes < x->w.bytes)) return SAMKV_EWORKSPACE;
+  rc = query_ws(dtype, n_kv_heads, (n_q_heads / n_kv_heads) * n_q_tok, m_total, head_dim, ws, ws_bytes, &x->w);
+  if (rc != SAMKV_OK) return rc;
   x->rec = recompute_launch(q_rec, k_c, v_c, m_total, n_q_heads, n_kv_heads, head_dim, dtype, scale, rec_out, rec_lse);
   x->qry = query_launch(q_tok, n_q_tok, k_c, v_c, m_total, n_q_heads, n_kv_heads, head_dim, dtype, scale, q_out, q_lse,
                         x->w.split, ws);
@@ -904,8 +922,9 @@ int samkv_query_attn_self(const void* q_tok, int32_t n_q_tok, const void* k_c, c
   int rc = check_attn(q_tok, k_c, v_c, n_q_tok, m_total, n_q_heads, n_kv_heads, head_dim, dtype, scale, out, lse);
   if (rc != SAMKV_OK) return rc;
   if (k_self == nullptr || v_self == nullptr || !aligned16(k_self) || !aligned16(v_self)) return SAMKV_EINVAL;
-  const SelfWs w = self_ws(n_q_heads, n_kv_heads, head_dim, n_q_tok, m_total, dtype);
-  if (ws == nullptr || ((uintptr_t)ws % kAlign) != 0 || ws_bytes < w.bytes) return SAMKV_EWORKSPACE;
+  SelfWs w = self_ws(n_q_heads, n_kv_heads, head_dim, n_q_tok, m_total, dtype);
+  if (!enough(ws, ws_bytes, w.bytes)) w = self_ws(n_q_heads, n_kv_heads, head_dim, n_q_tok, m_total, dtype, true);
+  if (!enough(ws, ws_bytes, w.bytes)) return SAMKV_EWORKSPACE;
   char* base = static_cast<char*>(ws);
   const size_t n_rows = (size_t)n_q_heads * n_q_tok;
   const int rows = (n_q_heads / n_kv_heads) * n_q_tok, n_cache = w.split.n_split;

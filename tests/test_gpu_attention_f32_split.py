@@ -278,3 +278,27 @@ def test_query_long(d, hq, hkv, lq, m):
 ])
 def test_both_in_one_call_shapes(d, hq, hkv, lq, m):
     E.test_both_attentions_in_one_call("f32", d, hq, hkv, lq, m)
+
+
+@pytest.mark.parametrize("d,hq,hkv,lq,m", [(128, 16, 16, 1024, 300), (64, 32, 16, 512, 600)])
+def test_no_workspace_where_float32_products_need_none(d, hq, hkv, lq, m):
+    """Problems whose row tiles fill the chip with float32 products take one chunk of keys and no workspace, as ever; the terms'
+    larger workgroups would cut the keys in two.  One byte less than those chunks take counts as no workspace, too."""
+    import torch
+    from paper_2508_11661_amd import samkv as S
+    gen = torch.Generator(device="cuda").manual_seed(17)
+    normal = lambda *s: torch.randn(s, device="cuda", generator=gen)
+    q, qt, k, v, scale = normal(hq, m, d), normal(hq, lq, d), normal(hkv, m, d), normal(hkv, m, d), d ** -0.5
+    ref, lse_ref = _reference(qt[:1], k[:1], v[:1], scale, False)
+    for ws in (None, torch.empty((hq * lq * (d + 1) * 8 - 1,), dtype=torch.uint8, device="cuda")):
+        for both in (False, True):
+            out, lse = torch.full_like(qt, math.nan), torch.full((hq, lq), math.nan, device="cuda")
+            if both:
+                rec, rec_lse = torch.empty_like(q), torch.empty((hq, m), device="cuda")
+                S.samkv_recompute_query_attn(q, qt, k, v, scale, rec, rec_lse, out, lse, ws)
+            else:
+                S.samkv_query_attn(qt, k, v, scale, out, lse, ws)
+            torch.cuda.synchronize()
+            assert ((out[:1].double() - ref).norm() <= 4e-6 * ref.norm()).item()
+            assert ((lse[:1].double() - lse_ref).abs().max() <= 4e-6).item()
+            assert torch.isfinite(out).all() and torch.isfinite(lse).all()
