@@ -272,7 +272,12 @@ int samkv_gather_q_v(const samkv_caches* caches, const void* const* q_cache, con
  * the half-precision matrix cores: the softmax weights are rounded to IEEE half precision (11-bit significand), and
  * V is first rewritten into the workspace as half precision, each KV head scaled by a power of two so that nothing
  * overflows and bf16 values down to 2^-32 of the head's largest magnitude stay exact (smaller ones lose at most
- * 2^-40 of that magnitude).  f32: float32 throughout.
+ * 2^-40 of that magnitude).  f32: float32 sums of products, scores and weights of float32 precision.  Smaller problems take
+ * float32 products.  Larger ones, by a rule on the sizes, take every operand and weight as the exact sum of three bf16 terms and
+ * a product as the six of its nine term products that are 2^-16 of it or more, what is left out being below 2^-24 of it; the
+ * rounding differs from that of float32 products, with errors against exact arithmetic that are no larger.  Workgroups that
+ * meet an infinity, a NaN or a magnitude of 2^60 (V: 2^48) or more start again with float32 products, so such inputs take
+ * longer than either.
  * ws: samkv_workspace_bytes(...) bytes, 256-byte aligned, for bf16 (SAMKV_EWORKSPACE otherwise); f32 needs none. */
 int samkv_recompute_attn(const void* q_rec, const void* k_c, const void* v_c, int32_t m_total,
                          int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim, int32_t dtype,
@@ -282,7 +287,8 @@ int samkv_recompute_attn(const void* q_rec, const void* k_c, const void* v_c, in
  * cached token precedes the query, so there is no mask):
  *   out[h][t][:] = sum_{j < M} softmax_j(scale * <q_tok[h][t], k_c[g][j]>) * v_c[g][j],  lse likewise.
  *   q_tok [Hq][n_q_tok][d]; out [Hq][n_q_tok][d], lse [Hq][n_q_tok] float32.
- * Arithmetic as in samkv_recompute_attn, with one difference for bf16 with fewer than 512 query rows per KV head
+ * Arithmetic as in samkv_recompute_attn (f32: which products serve follows this problem's own sizes, and float32 products
+ * where ws has no room for the chunks that the others take), with one difference for bf16 with fewer than 512 query rows per KV head
  * (G * n_q_tok < 512) or so few rows and keys that rewriting V would cost more than the products (G * n_q_tok * M * Hkv * d
  * up to 3e9 to 4e9): V is read as stored and every softmax weight enters the second product as the sum of two bf16 terms
  * (16 significant bits), on the bf16 matrix cores; no copy of V is made.  Long caches are cut into key chunks whose
