@@ -91,9 +91,10 @@ struct GatherLaunch {
   const int32_t* idx;
   void* k_c;
   void* v_c;
-  uint32_t* v_max;  // null, or [Hkv][gather_v_parts]: the largest magnitudes of the bf16 V rows that a wave copies, for launch_v_prep
+  uint32_t* v_max;  // null, or [Hkv][gather_v_parts]: the largest magnitudes of the bf16 V rows that its waves copy, for launch_v_prep
 };
-// Waves per KV head that write a v_max, by the kernel of launch_gather, or by launch_score_select's own (fused).
+// Words of v_max per KV head, by the kernel of launch_gather, or by launch_score_select's own (fused).  At most one per 16 kept
+// rows and eight per document.
 int gather_v_parts(const GatherLaunch& a, const IntTable& cu_k, bool fused);
 hipError_t launch_gather(const GatherLaunch& a, const PtrTable& k, const PtrTable& v, const IntTable& cu_len,
                          const IntTable& cu_k, hipStream_t s);

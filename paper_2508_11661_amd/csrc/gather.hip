@@ -36,6 +36,13 @@ int gather_steps(const GatherLaunch& a, const IntTable& cu_k, int heads) {
   return even ? kStepsMany : kStepsFew;
 }
 
+// Where a document's words of the largest V magnitudes start, in workgroups of `rows` rows: room for its workgroups that hold
+// rows, and for at most one more, from the prefix sums alone (floor(a / rows) + ceil(n / rows) <= floor((a + n) / rows) + 1).  A
+// word per workgroup of the grid would grow with the longest document times the number of documents, and every workgroup of
+// launch_v_prep reads a head's words (128 documents, one of 6000 kept rows, the others of 16, 32 heads, whole path: 48128
+// words a head 831 us, 1004 words 776, without them 780).
+__host__ __device__ __forceinline__ int v_max_begin(const IntTable& cu_k, int i, int rows) { return cu_k.v[i] / rows + i; }
+
 template <int ROW_BYTES, int STEPS>
 __global__ __launch_bounds__(256) void k_gather(PtrTable kt, PtrTable vt, IntTable cu_len, IntTable cu_k, int m_total,
                                                 const int32_t* idx, char* k_c, char* v_c, uint32_t* v_max) {
@@ -47,7 +54,15 @@ __global__ __launch_bounds__(256) void k_gather(PtrTable kt, PtrTable vt, IntTab
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int sub = lane % LPR, rg = lane / LPR;
   const int r0 = blockIdx.x * ROWS_PER_BLOCK + wave * (RPS * STEPS);
-  uint32_t* mx_at = v_max == nullptr ? nullptr : v_max + (((size_t)g * gridDim.y + i) * gridDim.x + blockIdx.x) * 4 + wave;
+  const int block0 = blockIdx.x * ROWS_PER_BLOCK;
+  if (block0 >= k_i && blockIdx.x > 0) return;
+  uint32_t* mx_at = nullptr;
+  if (v_max != nullptr) {
+    const int first = v_max_begin(cu_k, i, ROWS_PER_BLOCK), next = v_max_begin(cu_k, i + 1, ROWS_PER_BLOCK);
+    mx_at = v_max + ((size_t)g * v_max_begin(cu_k, gridDim.y, ROWS_PER_BLOCK) + first + blockIdx.x) * 4 + wave;
+    // the document's last workgroup clears the room that none has
+    if (block0 + ROWS_PER_BLOCK >= k_i && first + (int)blockIdx.x + 1 < next && lane == 0) mx_at[4] = 0;
+  }
   if (r0 >= k_i) {
     if (mx_at != nullptr && lane == 0) *mx_at = 0;
     return;
@@ -228,9 +243,8 @@ hipError_t run(const GatherLaunch& a, const PtrTable& k, const PtrTable& v, cons
 
 int gather_v_parts(const GatherLaunch& a, const IntTable& cu_k, bool fused) {
   if (fused) return a.n_ctx * kFusedWaves;
-  const dim3 grid = a.row_bytes == 128 ? gather_grid<128>(a, gather_steps<128>(a, cu_k, a.hkv), a.hkv)
-                                       : gather_grid<256>(a, gather_steps<256>(a, cu_k, a.hkv), a.hkv);
-  return (int)(grid.x * grid.y) * 4;
+  const int rows = a.row_bytes == 128 ? 32 * gather_steps<128>(a, cu_k, a.hkv) : 16 * gather_steps<256>(a, cu_k, a.hkv);
+  return v_max_begin(cu_k, a.n_ctx, rows) * 4;
 }
 
 hipError_t launch_gather(const GatherLaunch& a, const PtrTable& k, const PtrTable& v, const IntTable& cu_len,

@@ -67,3 +67,13 @@ def test_other_heads_take_the_two_calls():
     out, lse = torch.empty_like(b.rec_out), torch.empty_like(b.rec_lse)
     S.samkv_recompute_attn(q_rec, b.k_c, b.v_c, 0.125, out, lse, b.ws)
     assert torch.equal(out, b.rec_out) and torch.equal(lse, b.rec_lse)
+
+
+@pytest.mark.parametrize("d,lens,hkv,group,ratio", [
+    (128, [9001] + [20, 64, 128, 1] * 8, 4, 2, 0.5),          # one document much longer than the others
+    (128, [128] * 66, 32, 1, 0.5), (64, [256] * 66, 32, 1, 0.5),  # every document fills its workgroups
+    (128, [127, 129] * 33, 32, 1, 0.5), (64, [9000, 1], 2, 1, 1.0),
+])
+def test_one_call_of_uneven_documents(d, lens, hkv, group, ratio):
+    """The words of the V magnitudes lie one behind the other, by the documents' prefix sums: none is missed or left as it was."""
+    test_one_call("bf16", d, lens, hkv, group, 3, ratio, 0, 0)
