@@ -18,9 +18,8 @@ namespace {
 
 constexpr size_t kAlign = 256;
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
-// samkv_hot_path: the largest V magnitudes that the waves of its compaction find, behind everything else in its workspace: at
-// most a word per wave of the fused kernel, or per 16 kept rows of the longest document and document
-size_t v_max_bytes(int n_ctx, int hkv, int m_total) { return align_up((size_t)hkv * n_ctx * (m_total / 16 + kFusedWaves) * 4); }
+// samkv_hot_path: the largest V magnitudes that its compaction finds (gather_v_parts), behind everything else in its workspace
+size_t v_max_bytes(int n_ctx, int hkv, int m_total) { return align_up((size_t)hkv * (m_total / 16 + (size_t)n_ctx * kFusedWaves) * 4); }
 // every kernel moves tensor rows with 16-byte vector accesses
 bool aligned16(const void* p) { return ((uintptr_t)p % 16) == 0; }
 

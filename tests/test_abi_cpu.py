@@ -248,3 +248,11 @@ def test_hot_path_reports_both_steps_errors(S):
         assert call(**bad) == -2, bad
     for bad in (dict(ws=none), dict(ws_bytes=64), dict(ws=ctypes.c_void_p(0x1010))):
         assert call(**bad) == -3, bad
+
+
+def test_workspace_of_many_documents(S):
+    """What the compaction's V magnitudes take follows the kept rows and the documents, not their product: 256 stacked heads, 25000
+    kept rows, 128 documents instead of one ask for 8 words per head and document more, and for scores' scratch."""
+    size = lambda n_ctx, hq: S.samkv_workspace_bytes(n_ctx, hq, 256, 128, 1, 25000)
+    for hq in (256, 512):
+        assert 0 <= size(128, hq) - size(1, hq) <= 256 * 128 * 8 * 4 + 4096

@@ -45,7 +45,7 @@ def test_one_call(dtype, d, lens, hkv, group, lq, ratio, n_sink, n_local):
         for x in names:
             assert torch.equal(getattr(one, x), getattr(two, x)), (rep, x)
     # a workspace that holds the two calls' scratch and nothing behind it
-    need = S.samkv_workspace_bytes(len(lens), hq, hkv, d, lq, m) - (hkv * len(lens) * (m // 16 + 8) * 4 + 255) // 256 * 256 - 256
+    need = S.samkv_workspace_bytes(len(lens), hq, hkv, d, lq, m) - (hkv * (m // 16 + 8 * len(lens)) * 4 + 255) // 256 * 256 - 256
     small = S.alloc_layer_buffers(caches, lq, ratio)
     small.ws = small.ws[:need]
     S.hot_path(caches, q_tok, q_loc, q_rec, ratio, d ** -0.5, small, n_sink, n_local)
