@@ -140,9 +140,15 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     return t.data_ptr()
 
 
+# torch's own way to the current stream without a Stream object around it, which takes 4 us a call; not public
+_device = getattr(torch._C, "_cuda_getDevice", None)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream() -> int:
-    # the current stream of the current device without building a Stream object around it (4 us a call)
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    if _device is None or _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_device())
 
 
 def upload(a, dtype: str) -> torch.Tensor:

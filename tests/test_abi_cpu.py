@@ -1,6 +1,7 @@
 """CPU-side checks of the C ABI: the library loads, exports what the header declares, computes the
 kept counts like the oracle and rejects bad arguments before touching the device."""
 import ctypes
+import importlib
 import os
 import re
 
@@ -256,3 +257,17 @@ def test_workspace_of_many_documents(S):
     size = lambda n_ctx, hq: S.samkv_workspace_bytes(n_ctx, hq, 256, 128, 1, 25000)
     for hq in (256, 512):
         assert 0 <= size(128, hq) - size(1, hq) <= 256 * 128 * 8 * 4 + 4096
+
+
+@pytest.mark.parametrize("name", ["_cuda_getDevice", "_cuda_getCurrentRawStream"])
+def test_current_stream_by_the_public_call(name, monkeypatch):
+    """A torch without one of the functions that it does not promise: the public call serves."""
+    import types
+    import torch
+    from paper_2508_11661_amd import samkv as mod
+    with monkeypatch.context() as m:
+        m.delattr(torch._C, name)
+        m.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=77))
+        importlib.reload(mod)
+        assert mod._stream() == 77
+    importlib.reload(mod)
