@@ -298,6 +298,7 @@ class Workbench:
                                                                             None, b.idx, b.cu_k_dev, b.k_c, b.v_c, b.ws),
             "recompute_query_attn": lambda s, b: S.samkv_recompute_query_attn(s["q_rec"], s["q_tok"], b.k_c, b.v_c, scale,
                                                                               b.rec_out, b.rec_lse, b.q_out, b.q_lse, b.ws),
+            "hot_path": lambda s, b: S.hot_path(s["caches"], s["q_tok"], s["q_loc"], s["q_rec"], ratio, scale, b),
         }
         self.work = algorithmic_work(w, w.lens, m, w.n_q_tok)
 
@@ -344,11 +345,12 @@ class Workbench:
         torch.cuda.synchronize()
         ms_per_step = (time.perf_counter() - t0) / steps * 1e3
 
-        events = {name: [] for name in STEP + KERNELS + EXTRA}
+        events = {name: [] for name in STEP + KERNELS + EXTRA + ("hot_path",)}
         for i in range(min(steps, per_call_steps)):
             self.step(warmup + steps + i, events)
             self.step(warmup + steps + i, events, names=KERNELS)
             self.step(warmup + steps + i, events, names=EXTRA)
+            self.step(warmup + steps + i, events, names=("hot_path",))
         torch.cuda.synchronize()
         events[dom] = dom_events[dom]          # the dominant call's figure is the one from the timed region
         w, work = self.w, self.work
@@ -363,6 +365,8 @@ class Workbench:
         per_kernel["score+select"] = {"ms": round(ss_ms, 5), "GB/s": round(ss_gbs, 1), "frac_hbm": round(ss_gbs / HBM_PEAK_GBS, 4),
                                       "note": "the two separate calls as one K-streaming stage, for comparison with the "
                                               "fused calls (score_select, and score_select_gather that the timed step launches)"}
+        per_kernel["hot_path"] = {"ms": round(float(np.median([a.elapsed_time(b) for a, b in events["hot_path"]])), 5),
+                                  "note": "the whole path as one call of the library, scores written too; not part of the timed step"}
         return ms_per_step, dom, per_kernel
 
     def graph_ms(self, steps, warmup):
