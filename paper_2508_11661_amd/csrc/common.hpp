@@ -155,9 +155,9 @@ inline AttnShape attn_bf16_shape(int causal, int n_batch, int batch_per_kv, int 
 // Which float32 attention kernel serves a problem: kPlain, float32 products, 32 rows and four groups of keys per workgroup, two
 // workgroups per compute unit; kSplit and kSplitKeys2, products of bf16 terms, 256 rows or 128 rows whose keys two groups of
 // waves share, one workgroup per compute unit.  Fitted to device times of single calls of all three over 329 causal shapes (1 to
-// 512 heads, 64 to 9000 rows) and 997 others (1 to 128 KV heads, 16 to 2048 rows, 150 to 60000 keys): on average 0.4 % and 0.5 %
-// behind the best of the three, by more than 5 % on 12 and 22 shapes; against kPlain throughout 21 and 16 % faster, and slower by
-// more than 2 % on 1 and 23.  Examples in us, kPlain / kSplit / kSplitKeys2.
+// 512 heads, 64 to 9000 rows) and 997 others (1 to 128 KV heads, 16 to 2048 rows, 150 to 60000 keys): on average 0.4 % and 0.3 %
+// behind the best of the three, by more than 5 % on 12 and 15 shapes; against kPlain throughout 21 and 17 % faster, and slower by
+// more than 2 % on 1 and 14.  Examples in us, kPlain / kSplit / kSplitKeys2.
 // Causal: kPlain has four times the workgroups and a shorter start, so it stays ahead until its workgroups fill the chip, the
 // later the more steps the longest row tile takes (d = 128: 8 heads x 3300 rows 226 / 424 / 241, x 6000 599 / 759 / 460; 32 x 700
 // 58 / 95 / 59, x 1540 192 / 212 / 137; 64 x 300 32 / 46 / 32, x 400 52 / 59 / 40; d = 64: 16 x 2000 90 / 158 / 93, x 2600 135 /
@@ -166,8 +166,9 @@ inline AttnShape attn_bf16_shape(int causal, int n_batch, int batch_per_kv, int 
 // row tile fill the chip (d = 128: 200 x 200 48 / 38 / 44).
 // Not causal: the same by work, as the keys are cut into chunks; up to 64 rows per KV head, and 256 in all, keep kPlain, whose
 // workgroups hold no more (rows x keys x KV heads, d = 128: 32 x 4000 x 128 112 / 175 / 149, 96 x 60000 x 1 47 / 93 / 81, 160 x
-// 4000 x 8 40 / 49 / 35).  kSplit for long ones or where it fills the chip (d = 128: 1024 x 4000 x 16 289 / 185 / 187; d = 64: 800
-// x 1500 x 32 111 / 78 / 84).
+// 4000 x 8 40 / 49 / 35), and so do, for longer, problems whose row tiles of 32 fill the chip once without chunks (d = 128: 2048 x
+// 300 x 8 36 / 56 / 40; d = 64: 19 / 33 / 24).  kSplit for long ones or where it fills the chip (d = 128: 1024 x 4000 x 16 289 /
+// 185 / 187; d = 64: 800 x 1500 x 32 111 / 78 / 84).
 enum class AttnF32Shape { kPlain, kSplit, kSplitKeys2 };
 inline AttnF32Shape attn_f32_shape(int causal, int n_batch, int rows, int m, int d) {
   const long long wg32 = (long long)n_batch * ((rows + 31) / 32), wg256 = (long long)n_batch * ((rows + 255) / 256);
@@ -178,7 +179,9 @@ inline AttnF32Shape attn_f32_shape(int causal, int n_batch, int rows, int m, int
     return AttnF32Shape::kSplitKeys2;
   }
   const long long work = (long long)rows * m * n_batch;
-  if ((long long)n_batch * rows <= 256 || work <= (d == 128 ? 3500000 : 4500000)) return AttnF32Shape::kPlain;
+  const bool once = wg32 > 400 && wg32 <= 512;
+  if ((long long)n_batch * rows <= 256 || work <= (d == 128 ? (once ? 5000000 : 3500000) : once ? 6000000 : 4500000))
+    return AttnF32Shape::kPlain;
   if (rows > 128 && (wg256 >= 160 || (m >= 3000 && work >= 40000000))) return AttnF32Shape::kSplit;
   return AttnF32Shape::kSplitKeys2;
 }

@@ -280,7 +280,7 @@ def test_both_in_one_call_shapes(d, hq, hkv, lq, m):
     E.test_both_attentions_in_one_call("f32", d, hq, hkv, lq, m)
 
 
-@pytest.mark.parametrize("d,hq,hkv,lq,m", [(128, 16, 16, 1024, 300), (64, 32, 16, 512, 600)])
+@pytest.mark.parametrize("d,hq,hkv,lq,m", [(128, 16, 16, 1024, 600), (64, 32, 16, 512, 900)])
 def test_no_workspace_where_float32_products_need_none(d, hq, hkv, lq, m):
     """Problems whose row tiles fill the chip with float32 products take one chunk of keys and no workspace, as ever; the terms'
     larger workgroups would cut the keys in two.  One byte less than those chunks take counts as no workspace, too."""
