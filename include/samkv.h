@@ -274,8 +274,9 @@ int samkv_gather_q_v(const samkv_caches* caches, const void* const* q_cache, con
  * overflows and bf16 values down to 2^-32 of the head's largest magnitude stay exact (smaller ones lose at most
  * 2^-40 of that magnitude).  f32: float32 sums of products, scores and weights of float32 precision.  Smaller problems take
  * float32 products.  Larger ones, by a rule on the sizes, take every operand and weight as the exact sum of three bf16 terms and
- * a product as the six of its nine term products that are 2^-16 of it or more, what is left out being below 2^-24 of it; the
- * rounding differs from that of float32 products, with errors against exact arithmetic that are no larger.  Workgroups that
+ * a product as the six of its nine term products that can reach 2^-18 of it, what is left out being below 2^-25 of it; the
+ * rounding differs from that of float32 products, with errors against exact arithmetic that are no larger (but within the unit
+ * of rounding, where one key holds an output alone).  Workgroups that
  * meet an infinity, a NaN or a magnitude of 2^60 (V: 2^48) or more start again with float32 products, so such inputs take
  * longer than either.
  * ws: samkv_workspace_bytes(...) bytes, 256-byte aligned, for bf16 (SAMKV_EWORKSPACE otherwise); f32 needs none. */

@@ -251,15 +251,16 @@ hipError_t run_pair(const AttnLaunch& c, const AttnLaunch& q, hipStream_t s) {
 // The bf16 matrix instructions do sixteen times the work of the float32 ones.  A float32 number x is the sum of three bf16
 // terms, x = x1 + x2 + x3 with x1 = bf16(x), x2 = bf16(x - x1), x3 = bf16(x - x1 - x2): each holds eight more bits and bf16 has
 // float32's exponents, so the sum is x itself, whatever its neighbours are.  Of the nine products of two such numbers the six
-// whose size is 2^-16 or more are taken, small ones first and the largest in an accumulator of its own where scores are summed;
-// the others, x2 y3, x3 y2 and x3 y3, are below 2^-25 of the product.  The sums are float32, with fewer roundings than the
+// that can reach 2^-18 of x y are taken, small ones first and the largest in an accumulator of its own where scores are summed;
+// the others, x2 y3, x3 y2 and x3 y3, are below 2^-25 of it together.  The sums are float32, with fewer roundings than the
 // float32 instruction makes.  Weights and V are multiplied by 2^24 before they are split, so that the last bit of the smallest
 // one is still a bf16 number; a term of K or Q that is too small for one moves a score by less than 2^-126 x 2^60 x d.
 //   Against 64 bits the errors are below those of float32 products on the inputs tried (72 heads x 700 rows, error over the norm,
 // float32 products / these: Gaussian 3.1e-7 / 1.7e-7; channels scaled apart 1.2e-6 / 4.7e-7; a key without V that takes all but
 // e^-20 of the weight 2.6e-6 / 1.1e-6; a channel of V 2^-24 of the others, over its own norm, 4.4e-7 / 2.4e-7).  Two
 // half-precision terms and three products took 0.6 of the time, but the absolute end of their range showed in the last two:
-// 1.4e-3 and 1.9e-4.
+// 1.4e-3 and 1.9e-4.  An output that one key holds alone is a single product with its normalisation: 3.3e-8 / 5.3e-8, both
+// below the unit of rounding.
 //   The terms leave out infinities, NaN and magnitudes whose sums might pass float32's range, 2^60 in K and Q and 2^48 in V: the
 // wave that meets one raises a flag, and the whole workgroup starts again with float32 products (attn_f32_unit).
 //   Eight waves of 32 query rows.  NKG = 1: 256 rows, one stream of keys, 32 a step.  NKG = 2, for short problems: 128 rows,
@@ -270,7 +271,7 @@ hipError_t run_pair(const AttnLaunch& c, const AttnLaunch& q, hipStream_t s) {
 // fragments.  Planes and fragments are laid out and read as in attn.hip.
 //   What bounds it: the matrix unit and the device's power limit (1.2 PFLOP/s of bf16 products at M = 6850), for short problems
 // the chain of steps.  32 heads over 8 KV heads, d = 128, float32 products -> these: M = 1540 176 -> 127 us, 4120 1080 -> 661, 6850
-// 2913 -> 1870 (206 TFLOP/s); 24 heads, d = 64, M = 6450 1012 -> 721.
+// 2913 -> 1870 (206 TFLOP/s); 24 heads, d = 64, M = 6450 1012 -> 733.
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
 template <int D, int NKG>
