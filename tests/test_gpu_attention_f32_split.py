@@ -19,18 +19,18 @@ def test_recompute_keys2_edges(d, m):
 
 
 @pytest.mark.parametrize("d,hq,hkv,m", [
-    (128, 136, 8, 129), (64, 200, 8, 129), (128, 136, 17, 161), (128, 136, 8, 255), (128, 136, 8, 256),  # one row tile
-    (128, 400, 8, 65), (64, 400, 8, 96),                                                                # a quarter of one
-    (128, 200, 8, 257), (128, 192, 24, 289), (64, 256, 8, 321), (128, 128, 8, 513), (64, 96, 8, 1000),  # several
-    (128, 8, 8, 1700), (64, 6, 3, 2700),                                                                # few heads, keys2
+    (128, 136, 8, 129), (64, 200, 8, 129), (128, 136, 17, 161), (128, 136, 8, 255), (128, 136, 8, 256),  # one tile of 256
+    (128, 400, 8, 65), (64, 400, 8, 96),                                                                # 128 rows, not full
+    (128, 200, 8, 257), (128, 192, 24, 289), (64, 256, 8, 321), (128, 128, 8, 513), (64, 96, 8, 1000),  # 128 rows
+    (128, 8, 8, 1700), (64, 6, 3, 2700),                                                 # few heads: float32 products
 ])
 def test_recompute(d, hq, hkv, m):
     E.test_recompute_attention_shapes("f32", d, hq, hkv, m)
 
 
 @pytest.mark.parametrize("d,hq,hkv,lq,m", [
-    (128, 16, 2, 16, 8800), (128, 8, 2, 33, 9001), (64, 8, 1, 5, 75001), (64, 16, 4, 50, 4033),       # 128 rows
-    (128, 64, 16, 40, 3001), (64, 64, 16, 40, 3021), (128, 256, 256, 150, 70),                        # 256 rows
+    (128, 16, 2, 16, 8800), (128, 8, 2, 33, 9001), (64, 8, 1, 5, 75001), (64, 16, 4, 50, 4033),       # float32 products
+    (128, 64, 16, 40, 3001), (64, 64, 16, 40, 3021), (128, 256, 256, 150, 70),            # 128 rows, the last one as above
 ])
 def test_query(d, hq, hkv, lq, m):
     E.test_query_attention_shapes("f32", d, hq, hkv, lq, m)
@@ -38,8 +38,8 @@ def test_query(d, hq, hkv, lq, m):
 
 @pytest.mark.parametrize("d,hq,hkv,lq,m", [
     (128, 64, 8, 4, 321), (64, 72, 8, 7, 385),       # query on float32 products: an odd number of units, and an even one
-    (128, 64, 8, 64, 600), (64, 64, 8, 96, 700),     # 128 rows for both
-    (128, 128, 8, 8, 700), (64, 128, 8, 40, 1100),   # 256 rows, and the query on either
+    (128, 64, 8, 64, 600), (64, 64, 8, 96, 700),     # the same, of several row tiles
+    (128, 128, 8, 8, 700), (64, 128, 8, 40, 1100),   # the same, and 128 rows for both
 ])
 def test_both_in_one_call(d, hq, hkv, lq, m):
     E.test_both_attentions_in_one_call("f32", d, hq, hkv, lq, m)
